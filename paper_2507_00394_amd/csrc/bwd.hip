@@ -98,7 +98,7 @@ bwd_delta_head_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k
   constexpr int TILE_BYTES = BN * D * 2;
   extern __shared__ __align__(16) char smem[];   // K[2] then V[2]
 
-  const TileCoord tc = map_block(blockIdx.x, BH, T, true);
+  const TileCoord tc = map_block<CAUSAL>(blockIdx.x, BH, T, true);
   if (!tc.valid) return;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int half = lane >> 5, n = lane & 31;

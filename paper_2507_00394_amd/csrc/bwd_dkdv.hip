@@ -179,7 +179,7 @@ bwd_dkdv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, cons
   constexpr int BN = 128, BM = 64, KS = G::KS, DB = G::DB;
   extern __shared__ __align__(16) char smem[];
 
-  const TileCoord tc = map_block(blockIdx.x, BH, T, false);
+  const TileCoord tc = map_block<CAUSAL>(blockIdx.x, BH, T, false);
   if (!tc.valid) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);

@@ -527,7 +527,7 @@ bwd_dkdv_pair_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
                      const __bf16* __restrict__ dO, const float* __restrict__ lse2, const float* __restrict__ neg_delta,
                      __bf16* __restrict__ dk, __bf16* __restrict__ dv, BwdMaps maps, int BH, int H, int S, int T,
                      float scale) {
-  const TileCoord tc = map_block(blockIdx.x, BH, T, false);
+  const TileCoord tc = map_block<CAUSAL>(blockIdx.x, BH, T, false);
   if (!tc.valid) return;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (w < 4) pair_sweep<CAUSAL, 0>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, tc, H, S, scale);

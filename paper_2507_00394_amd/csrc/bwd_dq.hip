@@ -120,7 +120,7 @@ bwd_dq_pipe_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, c
   constexpr int STAGE = 2 * TILE;   // [K tile][V tile]; tile j lives in stage j % 4
   extern __shared__ __align__(16) char smem[];
 
-  const TileCoord tc = map_block(blockIdx.x, BH, T, true);
+  const TileCoord tc = map_block<CAUSAL>(blockIdx.x, BH, T, true);
   if (!tc.valid) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);

@@ -260,12 +260,21 @@ __device__ __forceinline__ bf16x8 pack_half(const f32x16& acc, int t) {
 }
 
 // Map a linear workgroup id to (batch*head slice, tile).  Workgroup id mod 8 selects the XCD, and
-// each XCD sweeps whole "virtual heads", heaviest tiles first (`heavy_is_high`: the heaviest
+// each XCD sweeps "virtual heads", heaviest tiles first (`heavy_is_high`: the heaviest
 // tiles are those with the highest index (forward, dQ), else the lowest (dK/dV)).  A virtual
 // head is one of P interleaved parts of a head (tiles congruent mod P), with P the smallest
 // power of two that makes BH * P a multiple of 8: with 32 heads a virtual head is a head, with
 // the 4 or 5 heads of one GPU's share of a tensor-parallel layer (Section 2.2) a head is
 // spread over 2 or 8 XCDs so that none of them idles.
+//
+// Causal tiles differ in length, so an XCD that takes its virtual heads one after the other starts
+// the longest tiles of the last one when hardly anything is left to fill the other compute units.
+// The last virtual heads therefore go side by side, all of their heaviest tiles first: as many as
+// hold about four rounds of workgroups for the 32 compute units of an XCD, two at least.  More of
+// them only cost L2 hits (4 instead of 2 at 32 heads x 32k tokens: dK/dV 4 % slower), fewer leave the
+// imbalance.  One head after the other -> this rule, forward / dQ, us: 4 x 16 heads x 2k tokens 99 -> 77 /
+// 132 -> 101; 5 x 32k 1472 -> 1249 / 1997 -> 1733; 24 x 4k 131 -> 108 / 174 -> 147; 32 x 32k 7552 -> 7441 /
+// 10272 -> 10128.  Without a mask all tiles are equal and heads stay one after the other.
 struct TileCoord { int bh; int tile; bool valid; };
 __host__ __device__ inline int head_parts(int BH) { return (BH & 1) ? 8 : (BH & 2) ? 4 : (BH & 4) ? 2 : 1; }
 // Number of workgroups to launch for BH slices of T tiles.
@@ -273,12 +282,22 @@ __host__ __device__ inline long long grid_blocks(int BH, int T) {
   const int P = head_parts(BH);
   return (long long)BH * P * ((T + P - 1) / P);
 }
+template <bool CAUSAL>
 __device__ __forceinline__ TileCoord map_block(int n, int BH, int T, bool heavy_is_high) {
   TileCoord c;
   const int P = head_parts(BH), TP = (T + P - 1) / P;
   const int xcd = n & 7, s = n >> 3;
-  const int vh = xcd + 8 * (s / TP);
-  const int k = (s % TP) * P + (vh & (P - 1));   // rank of the tile inside its head, heaviest first
+  int v = s / TP, r = s - v * TP;                // virtual head of this XCD and position among its tiles
+  if (CAUSAL) {
+    const int V = (int)((long long)BH * P / 8), wanted = TP >= 64 ? 2 : 128 / TP;
+    const int side = V < wanted ? V : wanted, s2 = s - (V - side) * TP;
+    if (s2 >= 0) {
+      r = s2 / side;
+      v = V - side + s2 - r * side;
+    }
+  }
+  const int vh = xcd + 8 * v;
+  const int k = r * P + (vh & (P - 1));          // rank of the tile inside its head, heaviest first
   c.bh = vh / P;
   c.tile = heavy_is_high ? (T - 1 - k) : k;
   c.valid = c.bh < BH && k < T;
