@@ -1,6 +1,7 @@
 // dK / dV pass of the attention backward for gfx950 (Table 1, Attention column, "Backward B"),
-// one wave per SIMD.  The launcher at the end uses it for head dimension 64; head dimension 128
-// goes to the two-waves-per-SIMD kernel in bwd_dkdv_pair.hip (same arithmetic).
+// a wave for every 32 keys.  The launcher at the end uses it for head dimension 64; head dimension
+// 128 goes to the kernel in bwd_dkdv_pair.hip that splits the work of 32 keys over two waves (same
+// arithmetic).
 //
 // Work split: a workgroup of 4 waves owns 128 keys of one (batch, head) slice, 32 keys per
 // wave, and sweeps the 64-row query tiles that see them.  Per 32-row query block b a wave
@@ -13,8 +14,11 @@
 // K and V fragments of the wave's keys stay in registers (B operands of S and dP); bf16(P),
 // bf16(dS) in accumulator layout are the B operands of the last two products; Q, dO come
 // from LDS as A operands, row-major for S / dP and through the transposing LDS read for
-// dV / dK.  One wave per SIMD (up to 512 registers) so that both fp32 accumulators
-// (32 keys x D x 2) and the K, V fragments fit.
+// dV / dK.  At head dimension 64 both fp32 accumulators (32 keys x D x 2), the K, V fragments and
+// the pipeline's S, dP of two blocks take 220-239 registers and the four stages 72 KB of LDS, so TWO
+// workgroups share a compute unit.  A single wave per SIMD is bound by instruction issue (about
+// one instruction per four cycles, eight of them per MFMA); the second one issues under the
+// first one's MFMAs: 16 heads x 16k tokens 1234 -> 960 us (891 -> 1145 TFLOP/s).
 //
 // Schedule.  A second MFMA queued behind a running one stalls the vector-ALU port of the
 // SIMD, so matrix and vector work only overlap when they alternate in one instruction
@@ -170,7 +174,7 @@ __device__ __forceinline__ void dkdv_step(const f32x16& sp_cur, const f32x16& dp
 }  // namespace
 
 template <int D, bool CAUSAL>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 bwd_dkdv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
                 const __bf16* __restrict__ dO, const float* __restrict__ lse2, const float* __restrict__ neg_delta,
                 __bf16* __restrict__ dk, __bf16* __restrict__ dv, BwdMaps maps, int BH, int H, int S, int T,
