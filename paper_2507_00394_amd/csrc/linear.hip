@@ -8,16 +8,22 @@
 //   backward input   da[M][K]  = dqkv[M][N] * w[K][N]^T    X stored [i][r],  Y stored [r][j] after a transposing copy of w
 //   backward weight  dw[K][N]  = a[M][K]^T  * dqkv[M][N]   X stored [r][i],  Y stored [r][j]
 //
-// A workgroup of 4 waves (one per SIMD) owns a 256 x 256 tile of C; wave (wi, wj) owns 128 rows i
-// by 128 columns j as 4 x 4 accumulator blocks of the 32x32x16 MFMA (256 accumulator registers:
-// with 2.5 instructions per MFMA one wave keeps the matrix unit busy), computed transposed
-// (the MFMA's row index is j) so that a lane owns one row i of C and stores 4 consecutive j
-// at a time.  The contraction runs in stages of 32: each stage's X and Y tiles (16 KB each)
-// are copied global -> LDS asynchronously four stages ahead into five buffers (the scheme of the
-// attention kernels, one buffer deeper because a stage is only 16 MFMAs per wave long).  An operand whose contraction index is contiguous in memory sits in LDS
-// as [256][32] and is read with ds_read_b128; one whose contraction index is the row of the
-// stored matrix sits as two [32][128] tiles and is read with the transposing LDS read.  Eight
-// operand reads feed sixteen MFMAs; they are issued one sub-step (16 of the 32) ahead.
+// A workgroup of 4 waves owns a 256 x 256, 128 x 128 or 64 x 64 tile of C (pick_tile says which: a
+// large tile reads less per MFMA, a small one fills the chip when C is small); wave (wi, wj) owns a quarter of
+// it as accumulator blocks of the 32x32x16 MFMA (256 accumulator registers and one wave per SIMD for the large
+// tile), computed transposed (the MFMA's row index is j) so that a lane owns one row i of C and stores
+// consecutive j.  The contraction runs in stages of 32 or 64: each stage's X and Y tiles are copied
+// global -> LDS asynchronously AHEAD stages before their use (the scheme of the attention kernels, deeper
+// because a stage is shorter).  An operand whose contraction index is contiguous in memory sits in LDS
+// as [outer][STEP] and is read with ds_read_b128; one whose contraction index is the row of the
+// stored matrix sits as [STEP][128] tiles and is read with the transposing LDS read.  Operand reads are issued
+// one sub-step (16 contraction indices) ahead.
+//
+// What bounds it: at one GPU's share of a 7B layer (131072 x 4096 x 1536) the power limit, as in the attention
+// kernels; with few tokens the latency of the copies and barriers.  The copies are spread behind the MFMAs, each one
+// instruction with running scalar pointers; in front of the stage (as address arithmetic, an edge test and
+// eight copies in a row, with no MFMA in flight) they cost 14 %: forward 1571 -> 1365 us (1050 -> 1208 TFLOP/s),
+// da 1853 -> 1570, dw 1785 -> 1578.
 #include "helix_common.hpp"
 #include "kernels.hpp"
 #include <type_traits>
@@ -25,184 +31,278 @@
 namespace helix {
 namespace {
 
-constexpr int kTile = 256;                    // rows i and columns j of C per workgroup
-constexpr int kStep = 32;                     // contraction indices per stage
-constexpr int kOperandTile = kTile * kStep * 2;   // bytes of one operand's stage tile (either layout)
-constexpr int kStage = 2 * kOperandTile;
-constexpr int kWaves = 4;                     // 2 x 2 waves, one per SIMD, each 128 x 128 of the tile
-constexpr int kBlk = 4;                       // 32-wide blocks per wave in i and in j
-constexpr int kStages = 5;                    // 5 x 32 KB: all of the 160 KB of LDS
-constexpr int kAhead = kStages - 1;           // a stage's copy is issued this many iterations before its use
+constexpr int kWaves = 4;                     // 2 x 2 waves
+
+// Geometry of a workgroup tile: TI x TJ elements of C, contraction in stages of STEP, NST stage buffers.
+// A wave owns TI/2 x TJ/2 elements.
+template <int TI_, int TJ_, int STEP_, int NST_>
+struct Tile {
+  static constexpr int TI = TI_, TJ = TJ_, STEP = STEP_, NST = NST_;
+  static constexpr int BI = TI / 64, BJ = TJ / 64;   // 32-wide blocks per wave in i and in j
+  static constexpr int XBYTES = TI * STEP * 2, YBYTES = TJ * STEP * 2;
+  static constexpr int STAGE = XBYTES + YBYTES;
+  static constexpr int AHEAD = NST - 1;              // a stage's copy is issued this many iterations before its use
+  static constexpr int LDS = NST * STAGE;
+};
+using Tile256 = Tile<256, 256, 32, 5>;        // 160 KB of LDS: one workgroup per compute unit
+using Tile128 = Tile<128, 128, 32, 5>;        // 80 KB: two
+using Tile64ShortStages = Tile<64, 64, 32, 8>;
+using Tile64 = Tile<64, 64, 64, 5>;           // 80 KB: two
+
+__device__ __forceinline__ void copy_16_bytes_per_lane(uint32_t lane_byte_off, const __bf16* base, uint32_t lds_dst) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" :: "v"(lane_byte_off), "s"(base), "s"(lds_dst) : "memory");
+}
 
 // Operand whose stored rows are the outer index (i or j) and whose contraction index is
-// contiguous: LDS tile [256][32], 64-byte rows.
+// contiguous: LDS tile [OUTER][STEP].  Rows past the edge of the matrix are clamped to its last row once,
+// here, because the outer index of a workgroup never changes: a stage's copy is nothing but its copy instructions.
+template <int OUTER, int STEP>
 struct ContiguousOperand {
-  static constexpr int DMA = TileLoader<32, kTile, kWaves>::N;       // copy instructions per wave and stage
-  TileLoader<32, kTile, kWaves> loader;
-  const __bf16* base;   // element (outer0, 0)
-  int outer0, outer_n;
-  __device__ __forceinline__ ContiguousOperand(const __bf16* p, long long ld, int outer0_, int outer_n_, int lane, int wave)
-      : loader(lane, wave, (int)ld), base(p), outer0(outer0_), outer_n(outer_n_) {}
-  __device__ __forceinline__ void copy(int r0, uint32_t lds) const { loader.issue(base + r0, outer0, outer_n, lds); }
-  // lane addresses of the operand of 32-row block `blk` (rows blk0 + 32*blk + lane%32), sub-steps 0 and 1
-  __device__ __forceinline__ static void addresses(int lane, int blk0, int blk, uint32_t (&a)[2]) {
-    const int row = blk0 + 32 * blk + (lane & 31), half = lane >> 5;
-    a[0] = lds_chunk_off<32>(row, half);
-    a[1] = lds_chunk_off<32>(row, 2 + half);
+  using Loader = TileLoader<STEP, OUTER, kWaves>;
+  static constexpr int DMA = Loader::N;              // copy instructions per wave and stage
+  uint32_t off[DMA];
+  const __bf16* ptr;                                 // element (outer0, first contraction index of the next stage to copy)
+  uint32_t piece0;                                   // this wave's first 1 KB piece of the LDS tile
+  __device__ __forceinline__ ContiguousOperand(const __bf16* p, long long ld, int outer0, int outer_n, int r0, int lane, int wave)
+      : piece0((uint32_t)wave * 1024) {
+    const Loader loader(lane, wave, (int)ld);
+    const int last = outer_n - 1 - outer0;
+#pragma unroll
+    for (int i = 0; i < DMA; i++) {
+      const int row = (wave + kWaves * i) * Loader::ROWS_PER_KB + loader.lane_row;
+      off[i] = loader.off[i] - (uint32_t)(row > last ? row - last : 0) * loader.row_bytes;
+    }
+    ptr = uniform_ptr(p + (size_t)outer0 * ld + r0);
   }
-  __device__ __forceinline__ static bf16x8 read(const uint32_t (&a)[2], int ks) { return lds_b128(a[ks], 0); }
+  // Copy instruction i of the next stage; `next` after the last one.
+  __device__ __forceinline__ void copy(int i, uint32_t lds) const { copy_16_bytes_per_lane(off[i], ptr, lds + piece0 + i * kWaves * 1024); }
+  __device__ __forceinline__ void next() { ptr += STEP; }
+  // lane addresses of the operand of a 32-row block starting at tile row blk0, one per sub-step of 16
+  static constexpr int NADDR = STEP / 16;
+  __device__ __forceinline__ static void addresses(int lane, int blk0, uint32_t (&a)[NADDR]) {
+    const int row = blk0 + (lane & 31), half = lane >> 5;
+#pragma unroll
+    for (int ks = 0; ks < NADDR; ks++) a[ks] = lds_chunk_off<STEP>(row, 2 * ks + half);
+  }
+  __device__ __forceinline__ static bf16x8 read(const uint32_t (&a)[NADDR], int ks) { return lds_b128(a[ks], 0); }
 };
 
-// Operand whose stored rows are the contraction index: LDS holds two [32][128] tiles (outer
-// indices 0..127 and 128..255 of the workgroup tile), read with the transposing LDS read so
-// that contraction slot e of lane half h is row 8h + e.
+// Operand whose stored rows are the contraction index: LDS holds [STEP][W] tiles side by side (W = 128, or 64
+// for 64 outer indices), read with the transposing LDS read so that contraction slot e of lane half h is row 8h + e.
+template <int OUTER, int STEP>
 struct TransposedOperand {
-  static constexpr int DMA = 2 * TileLoader<128, kStep, kWaves>::N;
-  TileLoader<128, kStep, kWaves> loader;
-  const __bf16* col[2];   // element (0, outer0) and (0, outer0 + 128); the second falls back to the first past the edge
-  int r_n;
-  __device__ __forceinline__ TransposedOperand(const __bf16* p, long long ld, int outer0, int outer_n, int r_n_, int lane, int wave)
-      : loader(lane, wave, (int)ld), r_n(r_n_) {
-    col[0] = p + outer0;
-    col[1] = p + (outer0 + 128 < outer_n ? outer0 + 128 : outer0);
+  static constexpr int W = OUTER < 128 ? OUTER : 128, SUBS = OUTER / W;
+  using Loader = TileLoader<W, STEP, kWaves>;
+  static constexpr int DMA = SUBS * Loader::N;
+  uint32_t off[Loader::N];
+  const __bf16* ptr[SUBS];   // element (first contraction index of the next stage, first outer index of the sub-tile)
+  uint32_t piece0;
+  long long stage_elems;
+  __device__ __forceinline__ TransposedOperand(const __bf16* p, long long ld, int outer0, int outer_n, int r0, int lane, int wave)
+      : piece0((uint32_t)wave * 1024), stage_elems(STEP * ld) {
+    const Loader loader(lane, wave, (int)ld);
+#pragma unroll
+    for (int i = 0; i < Loader::N; i++) off[i] = loader.off[i];
+#pragma unroll
+    for (int b = 0; b < SUBS; b++)   // a sub-tile past the edge falls back to the first one; its results are not stored
+      ptr[b] = uniform_ptr(p + (size_t)r0 * ld + (outer0 + b * W < outer_n ? outer0 + b * W : outer0));
   }
-  __device__ __forceinline__ void copy(int r0, uint32_t lds) const {
-    loader.issue(col[0], r0, r_n, lds);
-    loader.issue(col[1], r0, r_n, lds + kOperandTile / 2);
+  __device__ __forceinline__ void copy(int i, uint32_t lds) const {
+    const int sub = i / Loader::N, piece = i % Loader::N;
+    copy_16_bytes_per_lane(off[piece], ptr[sub], lds + sub * (W * STEP * 2) + piece0 + piece * kWaves * 1024);
   }
-  __device__ __forceinline__ static void addresses(int lane, int blk0, int blk, uint32_t (&a)[2]) {
-    const int o = blk0 + 32 * blk;                 // first outer index of the block inside the workgroup tile
+  __device__ __forceinline__ void next() {
+#pragma unroll
+    for (int b = 0; b < SUBS; b++) ptr[b] += stage_elems;
+  }
+  static constexpr int NADDR = 2;
+  __device__ __forceinline__ static void addresses(int lane, int blk0, uint32_t (&a)[NADDR]) {
     const int i = lane & 15;
-    const int c = (o & 127) + ((lane >> 4) & 1) * 16 + (i & 3) * 4;
+    const int c = (blk0 & (W - 1)) + ((lane >> 4) & 1) * 16 + (i & 3) * 4;
     const int r = (lane >> 5) * 8 + (i >> 2);
-    const int sub = (o >> 7) * (kOperandTile / 2);
-    a[0] = sub + lds_chunk_off<128>(r, c >> 3) + (c & 7) * 2;
-    a[1] = sub + lds_chunk_off<128>(r + 4, c >> 3) + (c & 7) * 2;
+    const int sub = (blk0 / W) * (W * STEP * 2);
+    a[0] = sub + lds_chunk_off<W>(r, c >> 3) + (c & 7) * 2;
+    a[1] = sub + lds_chunk_off<W>(r + 4, c >> 3) + (c & 7) * 2;
   }
   // rows 16*ks + ...: the swizzle has period 16 in the row, so the sub-step is an immediate
-  __device__ __forceinline__ static bf16x8 read(const uint32_t (&a)[2], int ks) { return lds_tr_pair(a[0], a[1], ks * 16 * 256); }
+  __device__ __forceinline__ static bf16x8 read(const uint32_t (&a)[NADDR], int ks) { return lds_tr_pair(a[0], a[1], ks * 16 * W * 2); }
 };
 
-template <typename T> struct StoreFour;
-template <> struct StoreFour<__bf16> {
-  __device__ __forceinline__ static void put(__bf16* p, f32x4 x) { *reinterpret_cast<bf16x4*>(p) = __builtin_convertvector(x, bf16x4); }
-};
-template <> struct StoreFour<float> {
-  __device__ __forceinline__ static void put(float* p, f32x4 x) { *reinterpret_cast<f32x4*>(p) = x; }
-};
+// Stores one 32 x 32 accumulator block: the lane owns a row, its registers 4g..4g+3 are the columns
+// 8g + 4*half .. +3 (half = lane / 32).
+__device__ __forceinline__ void store_block(float* row, int half, const f32x16& acc) {
+#pragma unroll
+  for (int g = 0; g < 4; g++) {
+    const f32x4 x = {acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]};
+    *reinterpret_cast<f32x4*>(row + 8 * g + 4 * half) = x;
+  }
+}
+// bf16: the two lanes of a row exchange halves of two groups, so that each stores 16 consecutive bytes.
+__device__ __forceinline__ void store_block(__bf16* row, int half, const f32x16& acc) {
+#pragma unroll
+  for (int g = 0; g < 4; g += 2) {
+    const auto lo = __builtin_amdgcn_permlane32_swap(pack_bf16_pair(acc[4 * g], acc[4 * g + 1]),
+                                                     pack_bf16_pair(acc[4 * g + 4], acc[4 * g + 5]), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(pack_bf16_pair(acc[4 * g + 2], acc[4 * g + 3]),
+                                                     pack_bf16_pair(acc[4 * g + 6], acc[4 * g + 7]), false, false);
+    const u32x4 x = {lo[0], hi[0], lo[1], hi[1]};
+    *reinterpret_cast<u32x4*>(row + 8 * (g + half)) = x;
+  }
+}
+
+// All but the N newest vector memory operations of this wave are done, and every wave of the workgroup has got here.
+// LDS reads may stay in flight across it: the reads of a stage are consumed by MFMAs of that stage's own iteration.
+template <int N>
+__device__ __forceinline__ void stage_barrier() {
+  wait_tile_loads_except<N>();
+  asm volatile("s_barrier" ::: "memory");
+}
 
 }  // namespace
 
-template <bool X_ROWS_ARE_R, bool Y_ROWS_ARE_R, typename OutT>
-__global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(1, 1)))
+template <typename G, bool X_ROWS_ARE_R, bool Y_ROWS_ARE_R, typename OutT>
+__global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(G::LDS > 80 * 1024 ? 1 : 2, G::LDS > 80 * 1024 ? 1 : 2)))
 gemm_kernel(const __bf16* __restrict__ X, long long ldx, const __bf16* __restrict__ Y, long long ldy,
             OutT* __restrict__ C, long long ldc, int I, int J, int R, int tiles_i, int tiles_j,
             int r_per_part, long long part_stride) {
-  using XOp = typename std::conditional<X_ROWS_ARE_R, TransposedOperand, ContiguousOperand>::type;
-  using YOp = typename std::conditional<Y_ROWS_ARE_R, TransposedOperand, ContiguousOperand>::type;
+  using XOp = typename std::conditional<X_ROWS_ARE_R, TransposedOperand<G::TI, G::STEP>, ContiguousOperand<G::TI, G::STEP>>::type;
+  using YOp = typename std::conditional<Y_ROWS_ARE_R, TransposedOperand<G::TJ, G::STEP>, ContiguousOperand<G::TJ, G::STEP>>::type;
+  constexpr int BI = G::BI, BJ = G::BJ, NS = G::STEP / 16, AHEAD = G::AHEAD, NST = G::NST, STAGE = G::STAGE;
   extern __shared__ __align__(16) char smem[];
 
-  // workgroup id mod 8 is the XCD: all column tiles of a row tile run on one XCD, so the X panel
-  // is fetched into one L2 only
-  const int xcd = blockIdx.x & 7, s = blockIdx.x >> 3;
-  const int tj = s % tiles_j, ti = (s / tiles_j) * 8 + xcd;
-  if (ti >= tiles_i) return;
+  // workgroup id mod 8 is the XCD: each XCD takes a contiguous run of tiles, all column tiles of a row tile
+  // one after the other, so an X panel reaches one L2 only
+  const int total = tiles_i * tiles_j, share = (total + 7) >> 3;
+  const int t = (blockIdx.x & 7) * share + (blockIdx.x >> 3);
+  if (t >= total) return;
+  const int ti = t / tiles_j, tj = t - ti * tiles_j;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wi = w & 1, wj = w >> 1;
-  const int i0 = ti * kTile, j0 = tj * kTile;
+  const int i0 = ti * G::TI, j0 = tj * G::TJ;
   const uint32_t base = lds_base(smem);
 
-  XOp xop_src = [&]() {
-    if constexpr (X_ROWS_ARE_R) return TransposedOperand(X, ldx, i0, I, R, lane, w);
-    else return ContiguousOperand(X, ldx, i0, I, lane, w);
-  }();
-  YOp yop_src = [&]() {
-    if constexpr (Y_ROWS_ARE_R) return TransposedOperand(Y, ldy, j0, J, R, lane, w);
-    else return ContiguousOperand(Y, ldy, j0, J, lane, w);
-  }();
-  constexpr int NDMA = XOp::DMA + YOp::DMA;
   // blockIdx.y selects a part of the contraction range; its partial result goes to C + y * part_stride
   const int r_begin = blockIdx.y * r_per_part;
-  const int nk = ((R - r_begin < r_per_part ? R - r_begin : r_per_part)) / kStep;
+  const int nk = ((R - r_begin < r_per_part ? R - r_begin : r_per_part)) / G::STEP;
   C += (size_t)blockIdx.y * part_stride;
-  auto copy_stage = [&](int k, int buf) __attribute__((always_inline)) {
-    xop_src.copy(r_begin + k * kStep, base + buf * kStage);
-    yop_src.copy(r_begin + k * kStep, base + buf * kStage + kOperandTile);
+  XOp xsrc(X, ldx, i0, I, r_begin, lane, w);
+  YOp ysrc(Y, ldy, j0, J, r_begin, lane, w);
+  constexpr int NDMA = XOp::DMA + YOp::DMA;
+  auto copy = [&](int n, uint32_t lds) __attribute__((always_inline)) {   // copy instruction n of the next stage
+    if (n < XOp::DMA) xsrc.copy(n, lds);
+    else ysrc.copy(n - XOp::DMA, lds + G::XBYTES);
   };
 #pragma unroll
-  for (int k = 0; k < kAhead; k++)
-    if (k < nk) copy_stage(k, k);
+  for (int k = 0; k < AHEAD; k++)
+    if (k < nk) {
+#pragma unroll
+      for (int n = 0; n < NDMA; n++) copy(n, base + k * STAGE);
+      xsrc.next();
+      ysrc.next();
+    }
   // iteration k reads stages k and k+1: the first two must be complete, the others may still fly
-  if (nk >= kAhead) wait_tile_loads_except<(kAhead - 2) * NDMA>();   // all kAhead copies are out: the newest two may fly
-  else wait_tile_loads();
-  __syncthreads();
+  if (nk >= AHEAD) stage_barrier<(AHEAD - 2) * NDMA>();   // all AHEAD copies are out: the newest may fly
+  else stage_barrier<0>();
 
-  uint32_t xa[kBlk][2], ya[kBlk][2];
+  uint32_t xa[BI][XOp::NADDR], ya[BJ][YOp::NADDR];
 #pragma unroll
-  for (int b = 0; b < kBlk; b++) { XOp::addresses(lane, 32 * kBlk * wi, b, xa[b]); xa[b][0] += base; xa[b][1] += base; }
+  for (int b = 0; b < BI; b++) {
+    XOp::addresses(lane, 32 * (BI * wi + b), xa[b]);
 #pragma unroll
-  for (int b = 0; b < kBlk; b++) { YOp::addresses(lane, 32 * kBlk * wj, b, ya[b]); ya[b][0] += base + kOperandTile; ya[b][1] += base + kOperandTile; }
+    for (int e = 0; e < XOp::NADDR; e++) xa[b][e] += base;
+  }
+#pragma unroll
+  for (int b = 0; b < BJ; b++) {
+    YOp::addresses(lane, 32 * (BJ * wj + b), ya[b]);
+#pragma unroll
+    for (int e = 0; e < YOp::NADDR; e++) ya[b][e] += base + G::XBYTES;
+  }
 
-  f32x16 acc[kBlk][kBlk];
+  f32x16 acc[BJ][BI];
 #pragma unroll
-  for (int jb = 0; jb < kBlk; jb++)
+  for (int jb = 0; jb < BJ; jb++)
 #pragma unroll
-    for (int ib = 0; ib < kBlk; ib++)
+    for (int ib = 0; ib < BI; ib++)
 #pragma unroll
       for (int e = 0; e < 16; e++) acc[jb][ib][e] = 0.f;
 
-  bf16x8 xo[2][kBlk], yo[2][kBlk];   // [sub-step parity][block]
+  bf16x8 xo[2][BI], yo[2][BJ];   // [sub-step parity][block]
 #pragma unroll
-  for (int b = 0; b < kBlk; b++) xo[0][b] = XOp::read(xa[b], 0);
+  for (int b = 0; b < BI; b++) xo[0][b] = XOp::read(xa[b], 0);
 #pragma unroll
-  for (int b = 0; b < kBlk; b++) yo[0][b] = YOp::read(ya[b], 0);
+  for (int b = 0; b < BJ; b++) yo[0][b] = YOp::read(ya[b], 0);
 
+  // One stage: NS sub-steps of BI * BJ MFMAs; behind each MFMA its share of the operand reads of the next
+  // sub-step ((k, ks+1), in the last one (k+1, 0) from the next buffer) and of the copies of stage k + AHEAD,
+  // which replaces stage k - 1.
   int buf = 0;
-  for (int k = 0; k < nk; k++) {
-    if (k + kAhead < nk) copy_stage(k + kAhead, buf == 0 ? kStages - 1 : buf - 1);   // replaces stage k-1
-    const int step = (buf == kStages - 1) ? -(kStages - 1) * kStage : kStage;
+  auto stage = [&](auto copying) __attribute__((always_inline)) {
+    constexpr bool COPY = decltype(copying)::value;
+    constexpr int MM = BI * BJ, SLOTS = NS * MM, READS = BI + BJ;
+    const int step = (buf == NST - 1) ? -(NST - 1) * STAGE : STAGE;
+    const uint32_t dst = base + (buf == 0 ? NST - 1 : buf - 1) * STAGE;
 #pragma unroll
-    for (int ks = 0; ks < 2; ks++) {
-      // operands of the next sub-step: (k, 1) while (k, 0) is multiplied, then (k+1, 0) from the next buffer
-      if (ks == 1) {
+    for (int ks = 0; ks < NS; ks++) {
+      if (ks == NS - 1) {
 #pragma unroll
-        for (int b = 0; b < kBlk; b++) { xa[b][0] += step; xa[b][1] += step; ya[b][0] += step; ya[b][1] += step; }
+        for (int b = 0; b < BI; b++)
+#pragma unroll
+          for (int e = 0; e < XOp::NADDR; e++) xa[b][e] += step;
+#pragma unroll
+        for (int b = 0; b < BJ; b++)
+#pragma unroll
+          for (int e = 0; e < YOp::NADDR; e++) ya[b][e] += step;
       }
 #pragma unroll
-      for (int m = 0; m < kBlk * kBlk; m++) {
-        const int jb = m / kBlk, ib = m % kBlk;
-        acc[jb][ib] = mfma32(yo[ks][jb], xo[ks][ib], acc[jb][ib]);
-        if (m < kBlk) xo[ks ^ 1][m] = XOp::read(xa[m], ks ^ 1);
-        else if (m < 2 * kBlk) yo[ks ^ 1][m - kBlk] = YOp::read(ya[m - kBlk], ks ^ 1);
+      for (int m = 0; m < MM; m++) {
+        const int jb = m / BI, ib = m % BI;
+        acc[jb][ib] = mfma32(yo[ks & 1][jb], xo[ks & 1][ib], acc[jb][ib]);
+        // reads go behind the first MFMAs of a sub-step, one each where there are enough of them
+#pragma unroll
+        for (int q = 0; q < READS; q++) {
+          if ((MM >= READS ? q : q * MM / READS) != m) continue;
+          if (q < BI) xo[(ks & 1) ^ 1][q] = XOp::read(xa[q], (ks + 1) % NS);
+          else yo[(ks & 1) ^ 1][q - BI] = YOp::read(ya[q - BI], (ks + 1) % NS);
+        }
+        if constexpr (COPY) {
+#pragma unroll
+          for (int n = 0; n < NDMA; n++)
+            if (n * SLOTS / NDMA == ks * MM + m) copy(n, dst);
+        }
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    // stages up to k+2 must have landed before the next iteration starts (it reads k+1 and k+2);
-    // the copies of stages k+3 .. k+kAhead may stay in flight.  Near the end fewer copies are
-    // outstanding than that, so waiting for "all but (kAhead-2) stages" is still sufficient.
-    if (k + kAhead < nk) wait_tile_loads_except<(kAhead - 2) * NDMA>();
-    else wait_tile_loads();
-    __syncthreads();
-    buf = (buf == kStages - 1) ? 0 : buf + 1;
+    if constexpr (COPY) {
+      xsrc.next();
+      ysrc.next();
+    }
+    buf = (buf == NST - 1) ? 0 : buf + 1;
+  };
+  int k = 0;
+  // stages up to k+2 must have landed before the next iteration starts (it reads k+1 and k+2);
+  // the copies of stages k+3 .. k+AHEAD may stay in flight
+  for (; k + AHEAD < nk; k++) {
+    stage(std::true_type{});
+    stage_barrier<(AHEAD - 2) * NDMA>();
+  }
+  for (; k < nk; k++) {
+    stage(std::false_type{});
+    stage_barrier<0>();
   }
 
-  // lane owns row i of C; accumulator registers 4g..4g+3 of block (jb, ib) are 4 consecutive columns
+  // lane owns row i of C
   const int half = lane >> 5, n = lane & 31;
 #pragma unroll
-  for (int ib = 0; ib < kBlk; ib++) {
-    const int i = i0 + 32 * kBlk * wi + 32 * ib + n;
+  for (int ib = 0; ib < BI; ib++) {
+    const int i = i0 + 32 * (BI * wi + ib) + n;
     if (i >= I) continue;
     OutT* row = C + (size_t)i * ldc;
 #pragma unroll
-    for (int jb = 0; jb < kBlk; jb++)
-#pragma unroll
-      for (int g = 0; g < 4; g++) {
-        const int j = j0 + 32 * kBlk * wj + 32 * jb + 8 * g + 4 * half;
-        if (j >= J) continue;
-        const f32x4 x = {acc[jb][ib][4 * g], acc[jb][ib][4 * g + 1], acc[jb][ib][4 * g + 2], acc[jb][ib][4 * g + 3]};
-        StoreFour<OutT>::put(row + j, x);
-      }
+    for (int jb = 0; jb < BJ; jb++) {
+      const int j = j0 + 32 * (BJ * wj + jb);
+      if (j < J) store_block(row + j, half, acc[jb][ib]);   // J is a multiple of 128
+    }
   }
 }
 
@@ -219,13 +319,13 @@ __global__ void __launch_bounds__(256) sum_parts_kernel(const float* __restrict_
   *reinterpret_cast<f32x4*>(dst + (size_t)r * ld_dst + c) = acc;
 }
 
-template <bool XR, bool YR, typename OutT>
-static hipError_t launch_gemm(const void* X, long long ldx, const void* Y, long long ldy, void* C, long long ldc,
+template <typename G, bool XR, bool YR, typename OutT>
+static hipError_t launch_gemm_tile(const void* X, long long ldx, const void* Y, long long ldy, void* C, long long ldc,
                               int I, int J, int R, int parts, int r_per_part, long long part_stride, hipStream_t stream) {
-  const int tiles_i = (I + kTile - 1) / kTile, tiles_j = (J + kTile - 1) / kTile;
-  const unsigned grid = 8u * ((tiles_i + 7) / 8) * tiles_j;
-  const size_t lds = (size_t)kStages * kStage;
-  auto kern = gemm_kernel<XR, YR, OutT>;
+  const int tiles_i = (I + G::TI - 1) / G::TI, tiles_j = (J + G::TJ - 1) / G::TJ;
+  const unsigned grid = 8u * (unsigned)(((long long)tiles_i * tiles_j + 7) / 8);
+  const size_t lds = G::LDS;
+  auto kern = gemm_kernel<G, XR, YR, OutT>;
   static unsigned long long configured = 0;   // one static per template instantiation
   hipError_t e = allow_dynamic_lds(kern, lds, configured);
   if (e != hipSuccess) return e;
@@ -234,9 +334,41 @@ static hipError_t launch_gemm(const void* X, long long ldx, const void* Y, long 
   return hipGetLastError();
 }
 
+// The tile that takes the least time by a model of four figures per tile, fitted to 38 shapes (64 to 131072
+// tokens, K 640 to 4096, N 384 to 2304), which it meets within 20 %.  A round of workgroups takes between `sparse`
+// (few of them on the chip: latency of the copies and barriers) and `full` nanoseconds per contraction index, plus
+// `fixed` for first copies and stores.  Measured, 256 / 128 / 64, us: forward of 64 tokens x 2048 x 768
+// 39 / 14.5 / 10.2; 2080 x 2048 x 768 45 / 18.6 / 14.7; 2080 x 4096 x 1536 82 / 38 / 60; 8192 x 2048 x 768
+// 48 / 35 / 43; 16384 x 4096 x 1536 207 / 224 / 489; 131072 x 4096 x 1536 1396 / 1862 / 3873.
+// `extra_256`: microseconds that only the large tile's path spends.
+enum class TileKind { k256, k128, k64 };
+static TileKind pick_tile(int I, int J, int R, int parts, double extra_256 = 0.) {
+  auto microseconds = [&](int edge, int slots, double sparse, double full, double fixed) {
+    const long long n = (long long)((I + edge - 1) / edge) * ((J + edge - 1) / edge) * parts;
+    const long long rounds = n / slots, rest = n % slots;
+    const double per_index = rounds * full + (rest ? sparse + (full - sparse) * rest / slots : 0.);
+    return per_index * R * 1e-3 + (rounds + (rest ? 1 : 0)) * fixed;
+  };
+  const double t256 = microseconds(256, 256, 17., 28., 11.) + extra_256;
+  const double t128 = microseconds(128, 512, 6.5, 18.5, 4.4);
+  const double t64 = microseconds(64, 512, 2.5, 9.5, 2.);
+  return t256 <= t128 && t256 <= t64 ? TileKind::k256 : t128 <= t64 ? TileKind::k128 : TileKind::k64;
+}
+
+template <bool XR, bool YR, typename OutT>
+static hipError_t launch_gemm(TileKind kind, const void* X, long long ldx, const void* Y, long long ldy, void* C, long long ldc,
+                              int I, int J, int R, int parts, int r_per_part, long long part_stride, hipStream_t stream) {
+  using Small = typename std::conditional<XR, Tile64ShortStages, Tile64>::type;
+  switch (kind) {
+    case TileKind::k256: return launch_gemm_tile<Tile256, XR, YR, OutT>(X, ldx, Y, ldy, C, ldc, I, J, R, parts, r_per_part, part_stride, stream);
+    case TileKind::k128: return launch_gemm_tile<Tile128, XR, YR, OutT>(X, ldx, Y, ldy, C, ldc, I, J, R, parts, r_per_part, part_stride, stream);
+    default: return launch_gemm_tile<Small, XR, YR, OutT>(X, ldx, Y, ldy, C, ldc, I, J, R, parts, r_per_part, part_stride, stream);
+  }
+}
+
 hipError_t launch_linear_fwd(const void* a, long long lda, const void* w, long long ldw, void* out, long long ldo,
                              int M, int K, int N, hipStream_t stream) {
-  return launch_gemm<false, true, __bf16>(a, lda, w, ldw, out, ldo, M, N, K, 1, K, 0, stream);
+  return launch_gemm<false, true, __bf16>(pick_tile(M, N, K, 1), a, lda, w, ldw, out, ldo, M, N, K, 1, K, 0, stream);
 }
 // out[c][r] = in[r][c] for a [rows][cols] bf16 matrix (both extents multiples of 64).
 __global__ void __launch_bounds__(256) transpose_kernel(const __bf16* __restrict__ in, long long ld_in,
@@ -257,18 +389,20 @@ __global__ void __launch_bounds__(256) transpose_kernel(const __bf16* __restrict
 // (w^T [N][K], in the workspace) turns it into the forward's operand combination.
 hipError_t launch_linear_bwd_input(const void* dout, long long ldd, const void* w, long long ldw, void* da, long long lda,
                                    void* wt, int M, int K, int N, hipStream_t stream) {
+  const TileKind kind = pick_tile(M, K, N, 1, 6.);   // the transposing copy
+  if (kind != TileKind::k256) return launch_gemm<false, false, __bf16>(kind, dout, ldd, w, ldw, da, lda, M, K, N, 1, N, 0, stream);
   hipLaunchKernelGGL(transpose_kernel, dim3((unsigned)(N / 64), (unsigned)(K / 64)), dim3(256), 0, stream,
                      (const __bf16*)w, ldw, (__bf16*)wt, (long long)K);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return launch_gemm<false, true, __bf16>(dout, ldd, wt, K, da, lda, M, K, N, 1, N, 0, stream);
+  return launch_gemm<false, true, __bf16>(kind, dout, ldd, wt, K, da, lda, M, K, N, 1, N, 0, stream);
 }
 
 // The weight gradient has few output tiles and a long contraction (over all M tokens), so the
 // contraction is cut into parts until the grid fills the chip about twice; the parts' fp32
 // results go to the workspace and are summed in a fixed order (no atomics).
 int linear_bwd_weight_parts(int M, int K, int N) {
-  const long long tiles = (long long)((K + kTile - 1) / kTile) * ((N + kTile - 1) / kTile);
+  const long long tiles = (long long)((K + 255) / 256) * ((N + 255) / 256);
   long long parts = (512 + tiles - 1) / tiles;
   const long long most = M / 2048 > 0 ? M / 2048 : 1;      // at least 2048 tokens per part
   if (parts > most) parts = most;
@@ -284,9 +418,10 @@ size_t linear_bwd_workspace_bytes(int M, int K, int N) {
 hipError_t launch_linear_bwd_weight(const void* a, long long lda, const void* dout, long long ldd, float* dw, long long ldw,
                                     float* workspace, int M, int K, int N, hipStream_t stream) {
   const int parts = linear_bwd_weight_parts(M, K, N);
-  if (parts == 1) return launch_gemm<true, true, float>(a, lda, dout, ldd, dw, ldw, K, N, M, 1, M, 0, stream);
-  const int per = ((M / kStep + parts - 1) / parts) * kStep;    // tokens per part, a multiple of the stage length
-  hipError_t e = launch_gemm<true, true, float>(a, lda, dout, ldd, workspace, N, K, N, M, parts, per, (long long)K * N, stream);
+  const TileKind kind = pick_tile(K, N, (M + parts - 1) / parts, parts);
+  if (parts == 1) return launch_gemm<true, true, float>(kind, a, lda, dout, ldd, dw, ldw, K, N, M, 1, M, 0, stream);
+  const int per = ((M / 32 + parts - 1) / parts) * 32;    // tokens per part, a multiple of the stage length
+  hipError_t e = launch_gemm<true, true, float>(kind, a, lda, dout, ldd, workspace, N, K, N, M, parts, per, (long long)K * N, stream);
   if (e != hipSuccess) return e;
   const long long quads = (long long)K * N / 4;
   hipLaunchKernelGGL(sum_parts_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream, workspace, dw, ldw, K, N, parts);
