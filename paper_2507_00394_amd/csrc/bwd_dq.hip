@@ -31,20 +31,20 @@ namespace {
 
 constexpr int kRing = 4;   // A operands in flight
 
-// One pipelined half step.  B_HALF: h is the second half of its tile, so the block ahead
-// (h+1) lives in the next tile: the lane addresses move on by stage_step as soon as their
+// One pipelined half step.  CUR: byte offset of h inside its tile; B_HALF: the block ahead
+// (h+1) starts the next tile, so the lane addresses move on by stage_step as soon as their
 // last read of the current tile is out.  On entry s_cur = S^T(h) with entries 0..7 already
 // exponentiated and ring = first four V(h) operands; on exit the same holds for s_next.
-template <int D, bool B_HALF, typename Copy>
+template <int D, bool B_HALF, int CUR, typename Copy>
 __device__ __forceinline__ void dq_half_step(const Copy& copy_tile, f32x16& s_cur, f32x16& s_next, bf16x8 (&ring)[kRing],
                                              const bf16x8 (&qf)[D / 16], const bf16x8 (&gf)[D / 16],
                                              f32x16 (&dqacc)[D / 32], uint32_t (&ab)[D / 16], uint32_t (&at)[D / 32][2],
                                              int stage_step, float c, float lse2, const f32x16& nd) {
   constexpr int KS = D / 16, DB = D / 32, NS = 3 * KS, R = kRing;
   constexpr int TILE = 64 * D * 2, HALF = 32 * D * 2;
-  constexpr int V_CUR = TILE + (B_HALF ? HALF : 0);      // V rows of h, stage layout [K tile][V tile]
+  constexpr int V_CUR = TILE + CUR;                      // V rows of h, stage layout [K tile][V tile]
   constexpr int K_NEXT = B_HALF ? 0 : HALF;              // K rows of h+1 (after the move when B_HALF)
-  constexpr int K_CUR_T = B_HALF ? HALF : 0;             // K rows of h for the transposing reads
+  constexpr int K_CUR_T = CUR;                           // K rows of h for the transposing reads
   constexpr int V_NEXT = TILE + (B_HALF ? 0 : HALF);     // V rows of h+1
   constexpr int EV = 8 / KS > 0 ? 8 / KS : 1;            // exponentials per slot in the first / last group
   constexpr int ED = 16 / KS;                            // dS elements per slot in the middle group
@@ -233,8 +233,8 @@ bwd_dq_pipe_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, c
       }
     };
     const int stage_step = (st == 3) ? -3 * STAGE : STAGE;
-    dq_half_step<D, false>(copy_whole, sa, sb, ring, qf, gf, dqacc, ab, at, stage_step, c, lse2, nd);
-    dq_half_step<D, true>(no_copy, sb, sa, ring, qf, gf, dqacc, ab, at, stage_step, c, lse2, nd);
+    dq_half_step<D, false, 0>(copy_whole, sa, sb, ring, qf, gf, dqacc, ab, at, stage_step, c, lse2, nd);
+    dq_half_step<D, true, HALF>(no_copy, sb, sa, ring, qf, gf, dqacc, ab, at, stage_step, c, lse2, nd);
     finish_tile();
   }
 
@@ -299,17 +299,208 @@ bwd_dq_pipe_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, c
   }
 }
 
+// The dQ pass for grids that 256-row tiles cannot fill (split_rows in helix_common.hpp): 128 query rows per
+// workgroup, wave (rg, kg) on 32 rows and half kg of every 64-key tile, the two partial sums of a row added in LDS at
+// the end (see fwd_split_kernel).  12 heads x 1500 tokens 49.1 -> 31.5 us, 2 heads x 32k 904 -> 693.
+template <int D>
+struct DqSplit {
+  static constexpr int NST = 5, AHEAD = NST - 1;
+  static constexpr int TILE = 64 * D * 2, STAGE = 2 * TILE;
+  static constexpr int LDS = NST * STAGE;
+};
+
+template <int D, bool CAUSAL>
+__global__ void __launch_bounds__(512, 1)
+bwd_dq_split_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
+                    const __bf16* __restrict__ dO, const float* __restrict__ lse2_all, const float* __restrict__ neg_delta,
+                    __bf16* __restrict__ dq, BwdMaps maps, int BH, int H, int S, int T, float scale) {
+  using G = DqSplit<D>;
+  constexpr int BM = 128, BN = 64, KS = D / 16, DB = D / 32;
+  constexpr int TILE = G::TILE, HALF = 32 * D * 2, STAGE = G::STAGE, NST = G::NST, AHEAD = G::AHEAD;
+  extern __shared__ __align__(16) char smem[];   // tile j (K, V) in stage j % NST
+
+  const TileCoord tc = map_block<CAUSAL>(blockIdx.x, BH, T, true);
+  if (!tc.valid) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rg = w & 3, kg = w >> 2;
+  const int half = lane >> 5, n = lane & 31;
+  const int q0 = tc.tile * BM;
+  const int wave_qmin = q0 + 32 * rg, my_q = wave_qmin + n;
+  const __bf16* qh = q + head_offset(maps.q, tc.bh, H);
+  const __bf16* gh = dO + head_offset(maps.dO, tc.bh, H);
+  const __bf16* kh = k + head_offset(maps.k, tc.bh, H);
+  const __bf16* vh = v + head_offset(maps.v, tc.bh, H);
+  const float c = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, scale * kLog2e)));
+  const uint32_t base = lds_base(smem);
+
+  bf16x8 qf[KS], gf[KS];
+  float lse2;
+  f32x16 nd;     // -delta of this lane's query in every accumulator register
+  {
+    const int row = my_q < S ? my_q : S - 1;
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) {
+      qf[ks] = *reinterpret_cast<const bf16x8*>(qh + (size_t)row * maps.q.row + 16 * ks + 8 * half);
+      gf[ks] = *reinterpret_cast<const bf16x8*>(gh + (size_t)row * maps.dO.row + 16 * ks + 8 * half);
+    }
+    lse2 = lse2_all[(size_t)tc.bh * S + row];
+    const float dl = neg_delta[(size_t)tc.bh * S + row];
+#pragma unroll
+    for (int e = 0; e < 16; e++) nd[e] = dl;
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) { pin(qf[ks]); pin(gf[ks]); }
+    pin(lse2); pin(nd);
+  }
+  f32x16 dqacc[DB];
+#pragma unroll
+  for (int db = 0; db < DB; db++)
+#pragma unroll
+    for (int e = 0; e < 16; e++) dqacc[db][e] = 0.f;
+
+  const int q_end = (q0 + BM < S ? q0 + BM : S);
+  const int n_tiles = CAUSAL ? (q_end + BN - 1) / BN : (S + BN - 1) / BN;
+  // Key blocks of this wave and how many of them need no mask, as in fwd_split_kernel.
+  const int k_end = CAUSAL ? (wave_qmin + 32 < S ? wave_qmin + 32 : S) : S;
+  const int k_all = CAUSAL ? wave_qmin + 1 : S;
+  const int n_w = wave_qmin < S ? (k_end - 32 * kg + BN - 1) / BN : 0;
+  const int n_full = (k_all + 32 - 32 * kg) / BN;
+
+  const TileLoader<D, BN, 8> kload(lane, w, maps.k.row), vload(lane, w, maps.v.row);
+  constexpr int NDMA = decltype(kload)::N + decltype(vload)::N;
+  int j = 0, st = 0;   // tile and its stage (j % NST)
+  auto plus = [&](int d) __attribute__((always_inline)) { return st + d >= NST ? st + d - NST : st + d; };
+  auto copy_tile = [&](int jj, int stage) __attribute__((always_inline)) {
+    kload.issue(kh, jj * BN, S, base + stage * STAGE);
+    vload.issue(vh, jj * BN, S, base + stage * STAGE + TILE);
+  };
+  auto copy_ahead = [&]() __attribute__((always_inline)) {
+    if (j + AHEAD < n_tiles) copy_tile(j + AHEAD, plus(AHEAD));   // replaces tile j-1
+  };
+  auto finish_tile = [&]() __attribute__((always_inline)) {
+    // tiles up to j+2 have landed before the next iteration (which reads j+1 and j+2) starts
+    if (j + AHEAD < n_tiles) wait_tile_loads_except<(AHEAD - 2) * NDMA>();
+    else wait_tile_loads();
+    __syncthreads();
+    st = plus(1);
+  };
+#pragma unroll
+  for (int jj = 0; jj < AHEAD; jj++)
+    if (jj < n_tiles) copy_tile(jj, jj);
+  wait_tile_loads();
+  __syncthreads();
+
+  const uint32_t kbase = base + kg * HALF;
+  uint32_t ab[KS], at[DB][2];
+#pragma unroll
+  for (int ks = 0; ks < KS; ks++) ab[ks] = kbase + lds_chunk_off<D>(n, 2 * ks + half);
+#pragma unroll
+  for (int db = 0; db < DB; db++) {
+    int o0, o1;
+    tr_pair_offsets<D>(lane, db, o0, o1);
+    at[db][0] = kbase + o0;
+    at[db][1] = kbase + o1;
+  }
+  f32x16 sa, sb;
+  bf16x8 ring[kRing];
+  if (n_w > 0) {
+    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    sa = zero;
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) sa = mfma32(lds_b128(ab[ks], 0), qf[ks], sa);
+#pragma unroll
+    for (int e = 0; e < 8; e++) sa[e] = __builtin_amdgcn_exp2f(fmaf(sa[e], c, -lse2));
+#pragma unroll
+    for (int i = 0; i < kRing; i++) ring[i] = lds_b128(ab[i], TILE);
+  }
+
+  auto step = [&](f32x16& s_cur, f32x16& s_next) __attribute__((always_inline)) {
+    const bool whole = j + AHEAD < n_tiles && (j + AHEAD + 1) * BN <= S;
+    if (!whole) copy_ahead();
+    const __bf16* kt = kload.tile_ptr(kh, (j + AHEAD) * BN);
+    const __bf16* vt = vload.tile_ptr(vh, (j + AHEAD) * BN);
+    const uint32_t dst = base + plus(AHEAD) * STAGE;
+    const auto copy_whole = [&]() __attribute__((always_inline)) {
+      if (whole) {
+        kload.issue_whole(kt, dst);
+        vload.issue_whole(vt, dst + TILE);
+      }
+    };
+    const int stage_step = (st == NST - 1) ? -(NST - 1) * STAGE : STAGE;
+    dq_half_step<D, true, 0>(copy_whole, s_cur, s_next, ring, qf, gf, dqacc, ab, at, stage_step, c, lse2, nd);
+    finish_tile();
+    j++;
+  };
+  while (j + 1 < n_w - 1) {
+    step(sa, sb);
+    step(sb, sa);
+  }
+  if (j < n_w - 1) {
+    step(sa, sb);
+    sa = sb;
+  }
+  for (; j < n_tiles; j++) {
+    copy_ahead();
+    if (j == n_w - 1) {
+#pragma unroll
+      for (int e = 8; e < 16; e++) sa[e] = __builtin_amdgcn_exp2f(fmaf(sa[e], c, -lse2));
+      f32x16 pacc = nd;
+#pragma unroll
+      for (int ks = 0; ks < KS; ks++) pacc = mfma32(lds_b128(ab[ks], TILE), gf[ks], pacc);
+      const bool masked = j >= n_full;
+#pragma unroll
+      for (int e = 0; e < 16; e++) {
+        float p = sa[e];
+        if (masked) {
+          const int key = j * BN + 32 * kg + 8 * (e >> 2) + 4 * half + (e & 3);
+          p = (CAUSAL ? key <= my_q : key < S) ? p : 0.f;
+        }
+        pacc[e] = p * pacc[e];
+      }
+#pragma unroll
+      for (int t = 0; t < 2; t++) {
+        const bf16x8 sbk = pack_half(pacc, t);
+#pragma unroll
+        for (int db = 0; db < DB; db++)
+          dqacc[db] = mfma32(lds_tr_pair(at[db][0], at[db][1], 16 * t * D * 2), sbk, dqacc[db]);
+      }
+    }
+    finish_tile();
+  }
+
+  // wave kg finishes half of the head dimension and hands the other half over
+  constexpr int HB = DB / 2;
+#pragma unroll
+  for (int b = 0; b < HB; b++) {
+    const f32x16 give = kg == 0 ? dqacc[HB + b] : dqacc[b];
+    lds_put_block(smem + ((kg * 4 + rg) * HB + b) * 4096, lane, give);
+  }
+  __syncthreads();
+  if (my_q < S) {
+    __bf16* row = dq + head_offset(maps.dq, tc.bh, H) + (size_t)my_q * maps.dq.row + 32 * HB * kg;
+#pragma unroll
+    for (int b = 0; b < HB; b++) {
+      f32x16 x = kg == 0 ? dqacc[b] : dqacc[HB + b];
+      const f32x16 got = lds_get_block(smem + (((kg ^ 1) * 4 + rg) * HB + b) * 4096, lane);
+#pragma unroll
+      for (int e = 0; e < 16; e++) x[e] = (x[e] + got[e]) * scale;
+      store_block(row + 32 * b, half, x);
+    }
+  }
+}
+
 template <int D, bool CAUSAL>
 static hipError_t launch_dq_pipe_t(const void* q, const void* k, const void* v, const void* dO,
                                    const float* lse2, const float* neg_delta, void* dq, const BwdMaps& maps,
                                    int B, int H, int S, float scale, hipStream_t stream) {
-  constexpr int BM = 256, BN = 64;
-  const int T = (S + BM - 1) / BM, BH = B * H;
+  const int BH = B * H;
+  const bool split = split_rows(BH, S, CAUSAL);
+  const int BM = split ? 128 : 256, T = (S + BM - 1) / BM;
   const unsigned grid = (unsigned)grid_blocks(BH, T);
-  const size_t lds = 4 * 2 * BN * D * 2;
-  auto kern = bwd_dq_pipe_kernel<D, CAUSAL>;
-  static unsigned long long configured = 0;   // one static per template instantiation
-  hipError_t e = allow_dynamic_lds(kern, lds, configured);
+  const size_t lds = split ? DqSplit<D>::LDS : 4 * 2 * 64 * D * 2;
+  auto kern = split ? bwd_dq_split_kernel<D, CAUSAL> : bwd_dq_pipe_kernel<D, CAUSAL>;
+  static unsigned long long configured[2] = {};   // per template instantiation and kernel
+  hipError_t e = allow_dynamic_lds(kern, lds, configured[split]);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(512), lds, stream, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v,
                      (const __bf16*)dO, lse2, neg_delta, (__bf16*)dq, maps, BH, H, S, T, scale);

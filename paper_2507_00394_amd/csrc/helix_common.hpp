@@ -219,6 +219,40 @@ __device__ __forceinline__ uint32_t pack_bf16_pair(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2));
 }
 
+// Stores one 32 x 32 accumulator block as bf16: the lane owns a row, its registers 4g..4g+3 are the columns
+// 8g + 4*half .. +3 (half = lane / 32).  The two lanes of a row exchange halves of two groups, so that each
+// stores 16 consecutive bytes.
+__device__ __forceinline__ void store_block(__bf16* row, int half, const f32x16& acc) {
+#pragma unroll
+  for (int g = 0; g < 4; g += 2) {
+    const auto lo = __builtin_amdgcn_permlane32_swap(pack_bf16_pair(acc[4 * g], acc[4 * g + 1]),
+                                                     pack_bf16_pair(acc[4 * g + 4], acc[4 * g + 5]), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(pack_bf16_pair(acc[4 * g + 2], acc[4 * g + 3]),
+                                                     pack_bf16_pair(acc[4 * g + 6], acc[4 * g + 7]), false, false);
+    const u32x4 x = {lo[0], hi[0], lo[1], hi[1]};
+    *reinterpret_cast<u32x4*>(row + 8 * (g + half)) = x;
+  }
+}
+
+// One accumulator block through LDS between two waves of a workgroup (16 bytes per lane and access; 4 KB).
+__device__ __forceinline__ void lds_put_block(char* p, int lane, const f32x16& x) {
+#pragma unroll
+  for (int g = 0; g < 4; g++) {
+    const f32x4 y = {x[4 * g], x[4 * g + 1], x[4 * g + 2], x[4 * g + 3]};
+    *reinterpret_cast<f32x4*>(p + 1024 * g + 16 * lane) = y;
+  }
+}
+__device__ __forceinline__ f32x16 lds_get_block(const char* p, int lane) {
+  f32x16 x;
+#pragma unroll
+  for (int g = 0; g < 4; g++) {
+    const f32x4 y = *reinterpret_cast<const f32x4*>(p + 1024 * g + 16 * lane);
+#pragma unroll
+    for (int e = 0; e < 4; e++) x[4 * g + e] = y[e];
+  }
+  return x;
+}
+
 // Forces a value loaded from global memory to be complete at this point of the program.
 // Without it the compiler sinks such loads below the asynchronous tile copies and then
 // waits for both together in the middle of the main loop.
@@ -302,6 +336,23 @@ __device__ __forceinline__ TileCoord map_block(int n, int BH, int T, bool heavy_
   c.tile = heavy_is_high ? (T - 1 - k) : k;
   c.valid = c.bh < BH && k < T;
   return c;
+}
+
+// Whether the forward and dQ passes take 128-row tiles with the keys split over two groups of waves instead
+// of 256-row tiles.  A split workgroup needs 0.55-0.65 of the time of a whole one for the same keys, and there
+// are twice as many: it pays where whole tiles leave compute units idle.  One workgroup per compute unit (256) is
+// a round.
+//   causal: tiles differ in length, so with up to one round the longest one sets the time.  Measured at head
+//     dimension 128, whole -> split, forward / dQ, us: 12 heads x 1500 (72 tiles) 39.7 -> 25.9 / 49 -> 31.5;
+//     2 x 32k (256) 710 -> 531 / 904 -> 693; 64 x 1024 (256) 33.5 -> 30.5 / 42 -> 39.5; just beyond,
+//     40 x 2048 (320) 58 -> 61 / 75 -> 79; 16 x 8192 (512) 255 -> 282 / 339 -> 364.
+//   no mask: all tiles are equal, so whole rounds are compared.  32 x 1024 (128) 31.8 -> 23.4 / 39 -> 30; 12 x 8192
+//     (384: 2 rounds or 3) 412 -> 399 / 533 -> 522; 32 x 1500 (192: 1 or 2) 45.6 -> 54.5 / 58 -> 68.
+// Head dimension 64 behaves alike (the sweep covered 1 to 64 heads, 200 to 32k tokens, both dimensions).
+inline bool split_rows(int BH, int S, bool causal) {
+  const long long whole = (long long)BH * ((S + 255) / 256), split = (long long)BH * ((S + 127) / 128);
+  if (causal) return whole <= 256;
+  return ((split + 255) / 256) * 5 < ((whole + 255) / 256) * 9;
 }
 
 // Element offset of row 0 of slice bh = b * H + h.

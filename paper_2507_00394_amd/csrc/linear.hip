@@ -128,8 +128,7 @@ struct TransposedOperand {
   __device__ __forceinline__ static bf16x8 read(const uint32_t (&a)[NADDR], int ks) { return lds_tr_pair(a[0], a[1], ks * 16 * W * 2); }
 };
 
-// Stores one 32 x 32 accumulator block: the lane owns a row, its registers 4g..4g+3 are the columns
-// 8g + 4*half .. +3 (half = lane / 32).
+// The fp32 counterpart of store_block in helix_common.hpp.
 __device__ __forceinline__ void store_block(float* row, int half, const f32x16& acc) {
 #pragma unroll
   for (int g = 0; g < 4; g++) {
@@ -137,19 +136,6 @@ __device__ __forceinline__ void store_block(float* row, int half, const f32x16& 
     *reinterpret_cast<f32x4*>(row + 8 * g + 4 * half) = x;
   }
 }
-// bf16: the two lanes of a row exchange halves of two groups, so that each stores 16 consecutive bytes.
-__device__ __forceinline__ void store_block(__bf16* row, int half, const f32x16& acc) {
-#pragma unroll
-  for (int g = 0; g < 4; g += 2) {
-    const auto lo = __builtin_amdgcn_permlane32_swap(pack_bf16_pair(acc[4 * g], acc[4 * g + 1]),
-                                                     pack_bf16_pair(acc[4 * g + 4], acc[4 * g + 5]), false, false);
-    const auto hi = __builtin_amdgcn_permlane32_swap(pack_bf16_pair(acc[4 * g + 2], acc[4 * g + 3]),
-                                                     pack_bf16_pair(acc[4 * g + 6], acc[4 * g + 7]), false, false);
-    const u32x4 x = {lo[0], hi[0], lo[1], hi[1]};
-    *reinterpret_cast<u32x4*>(row + 8 * (g + half)) = x;
-  }
-}
-
 // All but the N newest vector memory operations of this wave are done, and every wave of the workgroup has got here.
 // LDS reads may stay in flight across it: the reads of a stage are consumed by MFMAs of that stage's own iteration.
 template <int N>

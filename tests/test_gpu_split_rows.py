@@ -1,0 +1,32 @@
+"""Forward and dQ on both sides of the rule that splits the keys of small grids over two groups of waves: lengths at
+the edges of the 32-key halves, of the 64-key tiles and of the 128- and 256-row workgroup tiles, few heads (split)
+and more than a round of tiles (whole)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import attention_ref as A
+from paper_2507_00394_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+SPLIT = [(3, S) for S in (1, 31, 32, 33, 64, 65, 96, 97, 128, 129, 255, 257, 321, 449, 640)]
+WHOLE = [(260, 65), (258, 255), (130, 257), (90, 641)]
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("H,S", SPLIT + WHOLE)
+def test_both_sides(H, S, causal, D):
+    from tests import gpu_util as G
+
+    cfg, bits = I.random_case_bits(4100 + S + H, 1, H, S, D)
+    out = G.run_fwd_bwd(bits, cfg.scale, causal)
+    for n in ("o", "lse", "dq"):
+        assert bool(torch.isfinite(out[n].float()).all()), n
+    heads = list(range(H)) if H < 10 else [0, 7, H // 2, H - 1]
+    x = {t: I.bf16_bits_to_float(bits[t][:, heads]) for t in bits}
+    ref = A.attn_bwd_ref(x["q"], x["k"], x["v"], x["dO"], cfg.scale, causal)
+    for n in ("o", "dq", "dk", "dv"):
+        G.check(n, G.to_f64(out[n][:, heads].contiguous()), ref[n])
+    assert np.abs(G.to_f64(out["lse"][:, heads]) - ref["lse"]).max() <= G.TOL_LSE
