@@ -175,7 +175,7 @@ int helix_attn_bwd_preprocess(const void* o, const void* dO, const float* lse, v
   HELIX_TRY(check_stats(stats));
   HELIX_TRY(check_shape(B, H, S, D));
   return launched(helix::launch_bwd_preprocess(o, dO, lse, neg_delta_plane(stats), lse2_plane(stats, B, H, S),
-                                               contiguous_bwd(H, S, D), B, H, S, D, (hipStream_t)stream));
+                                               contiguous_bwd(H, S, D), B, H, S, D, 0, (hipStream_t)stream));
 }
 
 int helix_attn_bwd_delta_head(const void* q, const void* k, const void* v, const void* dO,
@@ -187,7 +187,7 @@ int helix_attn_bwd_delta_head(const void* q, const void* k, const void* v, const
   HELIX_TRY(check_shape(B, H, S, D));
   HELIX_TRY(check_scale(scale));
   if (rows < 0) return HELIX_ERR_BAD_SHAPE;
-  return launched(helix::launch_bwd_delta_head(q, k, v, dO, lse, neg_delta_plane(stats), contiguous_bwd(H, S, D), B, H, S, D, rows, scale, causal != 0, (hipStream_t)stream));
+  return launched(helix::launch_bwd_delta_head(q, k, v, dO, lse, neg_delta_plane(stats), nullptr, contiguous_bwd(H, S, D), B, H, S, D, rows, scale, causal != 0, (hipStream_t)stream));
 }
 
 int helix_attn_bwd_dkdv(const void* q, const void* k, const void* v, const void* dO,
@@ -348,8 +348,10 @@ int run_bwd(const void* q, const void* k, const void* v, const void* o, const fl
             int B, int H, int S, int D, float scale, int causal, hipStream_t st) {
   float* nd = neg_delta_plane(stats);
   float* l2 = lse2_plane(stats, B, H, S);
-  HELIX_TRY(launched(helix::launch_bwd_preprocess(o, dO, lse, nd, l2, maps, B, H, S, D, st)));
-  if (causal) HELIX_TRY(launched(helix::launch_bwd_delta_head(q, k, v, dO, lse, nd, maps, B, H, S, D, HELIX_DELTA_HEAD_ROWS, scale, true, st)));
+  // causal: the first rows get both statistics from delta_head, the streaming pass starts behind them (and is not
+  // launched at all up to HELIX_DELTA_HEAD_ROWS tokens)
+  HELIX_TRY(launched(helix::launch_bwd_preprocess(o, dO, lse, nd, l2, maps, B, H, S, D, causal ? HELIX_DELTA_HEAD_ROWS : 0, st)));
+  if (causal) HELIX_TRY(launched(helix::launch_bwd_delta_head(q, k, v, dO, lse, nd, l2, maps, B, H, S, D, HELIX_DELTA_HEAD_ROWS, scale, true, st)));
   HELIX_TRY(launched(helix::launch_bwd_dkdv(q, k, v, dO, l2, nd, dk, dv, maps, B, H, S, D, scale, causal != 0, st)));
   return launched(helix::launch_bwd_dq(q, k, v, dO, l2, nd, dq, maps, B, H, S, D, scale, causal != 0, st));
 }

@@ -9,8 +9,8 @@
 //                dK^T += Q^T dS
 //   dq         : (bwd_dq.hip) a workgroup owns 256 queries and sweeps the visible key tiles:
 //                S^T = K Q^T, dP^T = V dO^T, dS^T = P^T o (dP^T - delta), dQ^T += K^T dS^T
-//   delta_head : the unpipelined variant of the dQ sweep kept in this file; it only produces
-//                delta_i = sum_j p_ij dp_ij for the first rows of every head
+//   delta_head : a sweep in the dQ layout that only produces delta_i = sum_j p_ij dp_ij for the first
+//                rows of every head
 // Between the kernels the row statistics travel as neg_delta = -delta and lse2 = LSE * log2(e).
 //
 // Every output element is produced by exactly one lane, so there are no atomics and the
@@ -33,14 +33,14 @@ template <int D>
 __global__ void __launch_bounds__(256)
 bwd_preprocess_kernel(const __bf16* __restrict__ o, const __bf16* __restrict__ dO, const float* __restrict__ lse,
                       float* __restrict__ neg_delta, float* __restrict__ lse2, TensorMap mo, TensorMap mdo,
-                      int H, int S, int blocks_per_head) {
+                      int H, int S, int first_row, int blocks_per_head) {
   constexpr int LPR = D / 8;            // lanes per row
   constexpr int RPB = 256 / LPR;        // rows per workgroup pass
   constexpr int PASSES = kPreprocessPasses;
   const int tid = threadIdx.x;
   const int sub = tid % LPR;
   const int bh = blockIdx.x / blocks_per_head;
-  const int row0 = (blockIdx.x - bh * blocks_per_head) * (RPB * PASSES) + tid / LPR;
+  const int row0 = first_row + (blockIdx.x - bh * blocks_per_head) * (RPB * PASSES) + tid / LPR;
   const __bf16* oh = o + head_offset(mo, bh, H);
   const __bf16* gh = dO + head_offset(mdo, bh, H);
   bf16x8 a[PASSES], b[PASSES];
@@ -70,45 +70,64 @@ bwd_preprocess_kernel(const __bf16* __restrict__ o, const __bf16* __restrict__ d
 }
 
 hipError_t launch_bwd_preprocess(const void* o, const void* dO, const float* lse, float* neg_delta, float* lse2,
-                                 const BwdMaps& maps, int B, int H, int S, int D, hipStream_t stream) {
+                                 const BwdMaps& maps, int B, int H, int S, int D, int first_row, hipStream_t stream) {
+  if (first_row >= S) return hipSuccess;
   const int per = (256 / (D / 8)) * kPreprocessPasses;
-  const int bph = (S + per - 1) / per;
+  const int bph = (S - first_row + per - 1) / per;
   const unsigned grid = (unsigned)((long long)bph * B * H);
   if (D == 128)
     hipLaunchKernelGGL(bwd_preprocess_kernel<128>, dim3(grid), dim3(256), 0, stream, (const __bf16*)o, (const __bf16*)dO, lse,
-                       neg_delta, lse2, maps.o, maps.dO, H, S, bph);
+                       neg_delta, lse2, maps.o, maps.dO, H, S, first_row, bph);
   else
     hipLaunchKernelGGL(bwd_preprocess_kernel<64>, dim3(grid), dim3(256), 0, stream, (const __bf16*)o, (const __bf16*)dO, lse,
-                       neg_delta, lse2, maps.o, maps.dO, H, S, bph);
+                       neg_delta, lse2, maps.o, maps.dO, H, S, first_row, bph);
   return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ delta of the first rows
-// An unpipelined sweep in the dQ layout (a lane owns a query) that evaluates
-// delta_i = sum_j p_ij dp_ij from its definition.  It runs on the first rows of every head,
-// where attention is concentrated on few keys and the bf16 rounding of O would otherwise
-// dominate delta.
+// A sweep in the dQ layout (a lane owns a query) that evaluates delta_i = sum_j p_ij dp_ij from its definition.
+// It runs on the first rows of every head, where attention is concentrated on few keys and the bf16 rounding of O
+// would otherwise dominate delta.
+//
+// The tiles are short (at most 2048 keys for causal attention) and few, so what counts is the length of one
+// workgroup's chain: it owns 128 rows, wave (rg, kg) sweeps half kg of every 64-key tile for 32 of them (as in the split
+// forward), one block of 2*D/16 hand-ordered slots per tile:
+//     slots 0.. 7   dP^T(j)   = V(j) dO^T   | P^T(j) = exp2(S^T(j)*c - lse2)
+//     slots 8..15   S^T(j+1)  = K(j+1) Q^T  | sum += P^T(j) o dP^T(j)
+// with the tile copies asynchronous and four tiles ahead.  Against an unpipelined sweep of 256-row tiles through staging
+// registers: 2 heads x 32k tokens 71 -> 32 us, 5 x 32k 72 -> 33, 16 x 16k at head dimension 64 56 -> 28, 4 x 16 x 2k
+// (1024 workgroups; the time of the two products at full rate is 70) 107 -> 95.
+template <int D>
+struct DeltaHead {
+  static constexpr int NST = 5, AHEAD = NST - 1;
+  static constexpr int TILE = 64 * D * 2, STAGE = 2 * TILE;
+  static constexpr int LDS = NST * STAGE;
+};
+
 template <int D, bool CAUSAL>
 __global__ void __launch_bounds__(512, 1)
 bwd_delta_head_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
                       const __bf16* __restrict__ dO, const float* __restrict__ lse, float* __restrict__ neg_delta_out,
-                      BwdMaps maps, int BH, int H, int S, int T, float scale) {
-  constexpr int BM = 256, BN = 64, NT = 512;
-  constexpr int KS = D / 16;
-  constexpr int TILE_BYTES = BN * D * 2;
-  extern __shared__ __align__(16) char smem[];   // K[2] then V[2]
+                      float* __restrict__ lse2_out, BwdMaps maps, int BH, int H, int S, int T, float scale) {
+  using G = DeltaHead<D>;
+  constexpr int BM = 128, BN = 64, KS = D / 16, R = 4;   // R: operands in flight
+  constexpr int TILE = G::TILE, HALF = 32 * D * 2, STAGE = G::STAGE, NST = G::NST, AHEAD = G::AHEAD;
+  extern __shared__ __align__(16) char smem[];   // tile j (K, V) in stage j % NST
 
   const TileCoord tc = map_block<CAUSAL>(blockIdx.x, BH, T, true);
   if (!tc.valid) return;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rg = w & 3, kg = w >> 2;
   const int half = lane >> 5, n = lane & 31;
   const int q0 = tc.tile * BM;
-  const int my_q = q0 + 32 * w + n;
+  const int wave_qmin = q0 + 32 * rg, my_q = wave_qmin + n;
   const __bf16* qh = q + head_offset(maps.q, tc.bh, H);
   const __bf16* gh = dO + head_offset(maps.dO, tc.bh, H);
   const __bf16* kh = k + head_offset(maps.k, tc.bh, H);
   const __bf16* vh = v + head_offset(maps.v, tc.bh, H);
-  const float c = scale * kLog2e;
+  const float c = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, scale * kLog2e)));
+  const uint32_t base = lds_base(smem);
 
   bf16x8 qf[KS], gf[KS];
   float lse2;
@@ -120,89 +139,159 @@ bwd_delta_head_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k
       gf[ks] = *reinterpret_cast<const bf16x8*>(gh + (size_t)row * maps.dO.row + 16 * ks + 8 * half);
     }
     lse2 = lse[(size_t)tc.bh * S + row] * kLog2e;
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) { pin(qf[ks]); pin(gf[ks]); }
+    pin(lse2);
   }
-  float dsum = 0.f;   // this lane's share of sum_j p_ij dp_ij
+  float dsum[2] = {0.f, 0.f};   // this lane's share of sum_j p_ij dp_ij
 
   const int q_end = (q0 + BM < S ? q0 + BM : S);
   const int n_tiles = CAUSAL ? (q_end + BN - 1) / BN : (S + BN - 1) / BN;
-  const int wave_qmin = q0 + 32 * w, wave_qmax = wave_qmin + 31;
+  // Key blocks of this wave and how many of them need no mask, as in fwd_split_kernel.
+  const int k_end = CAUSAL ? (wave_qmin + 32 < S ? wave_qmin + 32 : S) : S;
+  const int k_all = CAUSAL ? wave_qmin + 1 : S;
+  const int n_w = wave_qmin < S ? (k_end - 32 * kg + BN - 1) / BN : 0;
+  const int n_full = (k_all + 32 - 32 * kg) / BN;
 
-  TileStage<D, BN, NT> sk, sv;
-  sk.fetch(kh, maps.k.row, 0, S, tid);
-  sv.fetch(vh, maps.v.row, 0, S, tid);
-  sk.commit(smem, tid);
-  sv.commit(smem + 2 * TILE_BYTES, tid);
+  const TileLoader<D, BN, 8> kload(lane, w, maps.k.row), vload(lane, w, maps.v.row);
+  constexpr int NDMA = decltype(kload)::N + decltype(vload)::N;
+  int j = 0, st = 0;   // tile and its stage (j % NST)
+  auto plus = [&](int d) __attribute__((always_inline)) { return st + d >= NST ? st + d - NST : st + d; };
+  auto copy_tile = [&](int jj, int stage) __attribute__((always_inline)) {
+    kload.issue(kh, jj * BN, S, base + stage * STAGE);
+    vload.issue(vh, jj * BN, S, base + stage * STAGE + TILE);
+  };
+  auto copy_ahead = [&]() __attribute__((always_inline)) {
+    if (j + AHEAD < n_tiles) copy_tile(j + AHEAD, plus(AHEAD));   // replaces tile j-1
+  };
+  auto finish_tile = [&]() __attribute__((always_inline)) {
+    // tiles up to j+2 have landed before the next iteration (which reads j+1 and j+2) starts
+    if (j + AHEAD < n_tiles) wait_tile_loads_except<(AHEAD - 2) * NDMA>();
+    else wait_tile_loads();
+    __syncthreads();
+    st = plus(1);
+  };
+#pragma unroll
+  for (int jj = 0; jj < AHEAD; jj++)
+    if (jj < n_tiles) copy_tile(jj, jj);
+  wait_tile_loads();
   __syncthreads();
 
-  for (int j = 0; j < n_tiles; j++) {
-    const char* kt = smem + (j & 1) * TILE_BYTES;
-    const char* vt = smem + (2 + (j & 1)) * TILE_BYTES;
-    const int k0 = j * BN;
-    const bool more = j + 1 < n_tiles;
-    if (more) {
-      sk.fetch(kh, maps.k.row, k0 + BN, S, tid);
-      sv.fetch(vh, maps.v.row, k0 + BN, S, tid);
-    }
-    if (!CAUSAL || k0 <= wave_qmax) {
+  uint32_t ab[KS];   // row n, contraction step ks of the K half tile (the V tile is TILE bytes further)
 #pragma unroll
-      for (int kb = 0; kb < 2; kb++) {
-        if (CAUSAL && k0 + 32 * kb > wave_qmax) continue;
-        f32x16 sacc, pacc;
+  for (int ks = 0; ks < KS; ks++) ab[ks] = base + kg * HALF + lds_chunk_off<D>(n, 2 * ks + half);
+  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  f32x16 sa, sb;
+  bf16x8 ring[R];
+  if (n_w > 0) {
+    sa = zero;
 #pragma unroll
-        for (int e = 0; e < 16; e++) { sacc[e] = 0.f; pacc[e] = 0.f; }
+    for (int ks = 0; ks < KS; ks++) sa = mfma32(lds_b128(ab[ks], 0), qf[ks], sa);
 #pragma unroll
-        for (int ks = 0; ks < KS; ks++) sacc = mfma32(lds_operand<D>(kt, 32 * kb + n, ks, half), qf[ks], sacc);
-#pragma unroll
-        for (int ks = 0; ks < KS; ks++) pacc = mfma32(lds_operand<D>(vt, 32 * kb + n, ks, half), gf[ks], pacc);
-        const bool need_mask = CAUSAL ? (k0 + 32 * kb + 31 > wave_qmin) : (k0 + 32 * kb + 32 > S);
-#pragma unroll
-        for (int e = 0; e < 16; e++) {
-          float p = __builtin_amdgcn_exp2f(fmaf(sacc[e], c, -lse2));
-          if (need_mask) {
-            const int key = k0 + 32 * kb + 8 * (e >> 2) + 4 * half + (e & 3);
-            p = (CAUSAL ? key <= my_q : key < S) ? p : 0.f;
-          }
-          dsum = fmaf(p, pacc[e], dsum);
-        }
-      }
-    }
-    if (more) {
-      sk.commit(smem + ((j + 1) & 1) * TILE_BYTES, tid);
-      sv.commit(smem + (2 + ((j + 1) & 1)) * TILE_BYTES, tid);
-    }
-    __syncthreads();
+    for (int i = 0; i < R; i++) ring[i] = lds_b128(ab[i], TILE);
   }
 
-  dsum = half_sum(dsum);
-  if (my_q < S && half == 0) neg_delta_out[(size_t)tc.bh * S + my_q] = -dsum;
+  // Block j: on entry s_cur = S^T(j) and ring = the first V operands of tile j; on exit the same for j + 1.
+  auto step = [&](f32x16& s_cur, f32x16& s_next) __attribute__((always_inline)) {
+    const bool whole = j + AHEAD < n_tiles && (j + AHEAD + 1) * BN <= S;
+    if (!whole) copy_ahead();
+    const __bf16* kt = kload.tile_ptr(kh, (j + AHEAD) * BN);
+    const __bf16* vt = vload.tile_ptr(vh, (j + AHEAD) * BN);
+    const uint32_t dst = base + plus(AHEAD) * STAGE;
+    const int stage_step = (st == NST - 1) ? -(NST - 1) * STAGE : STAGE;
+    f32x16 dp;
+#pragma unroll
+    for (int s = 0; s < 2 * KS; s++) {
+      if (s < KS) dp = mfma32(ring[s % R], gf[s], s == 0 ? zero : dp);
+      else s_next = mfma32(ring[s % R], qf[s - KS], s == KS ? zero : s_next);
+      if (s == 1 && whole) {
+        kload.issue_whole(kt, dst);
+        vload.issue_whole(vt, dst + TILE);
+      }
+      if (s == KS - R) {   // the last read of this tile is out
+#pragma unroll
+        for (int ks = 0; ks < KS; ks++) ab[ks] += stage_step;
+      }
+      const int u = s + R;
+      if (u < KS) ring[s % R] = lds_b128(ab[u], TILE);
+      else if (u < 2 * KS) ring[s % R] = lds_b128(ab[u - KS], 0);
+      else ring[s % R] = lds_b128(ab[u - 2 * KS], TILE);
+#pragma unroll
+      for (int e = 0; e < 16; e++) {
+        if (e * KS / 16 == s) s_cur[e] = __builtin_amdgcn_exp2f(fmaf(s_cur[e], c, -lse2));
+        if (KS + e * KS / 16 == s) dsum[e & 1] = fmaf(s_cur[e], dp[e], dsum[e & 1]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    finish_tile();
+    j++;
+  };
+  while (j + 1 < n_w - 1) {
+    step(sa, sb);
+    step(sb, sa);
+  }
+  if (j < n_w - 1) {
+    step(sa, sb);
+    sa = sb;
+  }
+  for (; j < n_tiles; j++) {
+    copy_ahead();
+    if (j == n_w - 1) {
+      const bool masked = j >= n_full;
+      f32x16 dp = zero;
+#pragma unroll
+      for (int ks = 0; ks < KS; ks++) dp = mfma32(lds_b128(ab[ks], TILE), gf[ks], dp);
+#pragma unroll
+      for (int e = 0; e < 16; e++) {
+        float p = __builtin_amdgcn_exp2f(fmaf(sa[e], c, -lse2));
+        if (masked) {
+          const int key = j * BN + 32 * kg + 8 * (e >> 2) + 4 * half + (e & 3);
+          p = (CAUSAL ? key <= my_q : key < S) ? p : 0.f;
+        }
+        dsum[e & 1] = fmaf(p, dp[e], dsum[e & 1]);
+      }
+    }
+    finish_tile();
+  }
+
+  // the two key halves of a row meet in LDS (free by now)
+  const float mine = half_sum(dsum[0] + dsum[1]);
+  float* sums = reinterpret_cast<float*>(smem);
+  if (kg == 1 && half == 0) sums[32 * rg + n] = mine;
+  __syncthreads();
+  if (kg == 0 && half == 0 && my_q < S) {
+    neg_delta_out[(size_t)tc.bh * S + my_q] = -(mine + sums[32 * rg + n]);
+    if (lse2_out) lse2_out[(size_t)tc.bh * S + my_q] = lse2;
+  }
 }
 
 template <int D, bool CAUSAL>
 static hipError_t launch_delta_head_t(const void* q, const void* k, const void* v, const void* dO, const float* lse,
-                                      float* delta_out, const BwdMaps& maps, int B, int H, int S, int rows,
+                                      float* delta_out, float* lse2_out, const BwdMaps& maps, int B, int H, int S, int rows,
                                       float scale, hipStream_t stream) {
-  constexpr int BM = 256, BN = 64;
-  const int T = (rows + BM - 1) / BM, BH = B * H;   // query tiles 0..T-1 of every head
+  const int T = (rows + 127) / 128, BH = B * H;   // query tiles 0..T-1 of every head
   const unsigned grid = (unsigned)grid_blocks(BH, T);
-  const size_t lds = 4 * BN * D * 2;
+  const size_t lds = DeltaHead<D>::LDS;
   auto kern = bwd_delta_head_kernel<D, CAUSAL>;
   static unsigned long long configured = 0;   // one static per template instantiation
   hipError_t e = allow_dynamic_lds(kern, lds, configured);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(512), lds, stream, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v,
-                     (const __bf16*)dO, lse, delta_out, maps, BH, H, S, T, scale);
+                     (const __bf16*)dO, lse, delta_out, lse2_out, maps, BH, H, S, T, scale);
   return hipGetLastError();
 }
 
 hipError_t launch_bwd_delta_head(const void* q, const void* k, const void* v, const void* dO,
-                                 const float* lse, float* delta, const BwdMaps& maps, int B, int H, int S, int D,
+                                 const float* lse, float* delta, float* lse2, const BwdMaps& maps, int B, int H, int S, int D,
                                  int rows, float scale, bool causal, hipStream_t stream) {
   if (rows <= 0) return hipSuccess;
   if (rows > S) rows = S;
-  if (D == 128) return causal ? launch_delta_head_t<128, true>(q, k, v, dO, lse, delta, maps, B, H, S, rows, scale, stream)
-                              : launch_delta_head_t<128, false>(q, k, v, dO, lse, delta, maps, B, H, S, rows, scale, stream);
-  return causal ? launch_delta_head_t<64, true>(q, k, v, dO, lse, delta, maps, B, H, S, rows, scale, stream)
-                : launch_delta_head_t<64, false>(q, k, v, dO, lse, delta, maps, B, H, S, rows, scale, stream);
+  rows = (rows + 255) / 256 * 256;   // whole groups of 256 rows
+  if (rows > S) rows = S;
+  if (D == 128) return causal ? launch_delta_head_t<128, true>(q, k, v, dO, lse, delta, lse2, maps, B, H, S, rows, scale, stream)
+                              : launch_delta_head_t<128, false>(q, k, v, dO, lse, delta, lse2, maps, B, H, S, rows, scale, stream);
+  return causal ? launch_delta_head_t<64, true>(q, k, v, dO, lse, delta, lse2, maps, B, H, S, rows, scale, stream)
+                : launch_delta_head_t<64, false>(q, k, v, dO, lse, delta, lse2, maps, B, H, S, rows, scale, stream);
 }
 
 }  // namespace helix

@@ -57,38 +57,6 @@ __device__ __forceinline__ int lds_chunk_off(int row, int chunk) {
   return row * (D * 2) + ((chunk ^ swizzle<D>(row)) << 4);
 }
 
-// One 16-byte chunk from global memory, zero when the row is past the end.
-__device__ __forceinline__ u32x4 load_chunk(const __bf16* base, int row, int nrows, int row_stride, int col) {
-  u32x4 z = {0u, 0u, 0u, 0u};
-  if (row < nrows) z = *reinterpret_cast<const u32x4*>(base + (size_t)row * row_stride + col);
-  return z;
-}
-
-// Register-staged copy of a [ROWS][D] bf16 tile: `fetch` issues the global loads, `commit`
-// writes them to LDS (swizzled).  NT threads cooperate; chunk id = tid + NT*i.
-template <int D, int ROWS, int NT>
-struct TileStage {
-  static constexpr int CH = D / 8;                 // 16-byte chunks per row
-  static constexpr int N = (ROWS * CH + NT - 1) / NT;
-  u32x4 r[N];
-  __device__ __forceinline__ void fetch(const __bf16* head_base, int row_stride, int row0, int nrows, int tid) {
-#pragma unroll
-    for (int i = 0; i < N; i++) {
-      int id = tid + NT * i;
-      int row = id / CH, c = id % CH;
-      if (ROWS * CH % NT == 0 || id < ROWS * CH) r[i] = load_chunk(head_base, row0 + row, nrows, row_stride, c * 8);
-    }
-  }
-  __device__ __forceinline__ void commit(char* lds, int tid) const {
-#pragma unroll
-    for (int i = 0; i < N; i++) {
-      int id = tid + NT * i;
-      int row = id / CH, c = id % CH;
-      if (ROWS * CH % NT == 0 || id < ROWS * CH) *reinterpret_cast<u32x4*>(lds + lds_chunk_off<D>(row, c)) = r[i];
-    }
-  }
-};
-
 // Asynchronous global -> LDS copy of a [ROWS][D] bf16 tile without staging registers
 // (global_load_lds_dwordx4: lane i of a wave deposits its 16 bytes at lds_base + 16*i).
 // A wave copies 1 KB per instruction; the swizzle is applied by choosing WHICH global chunk

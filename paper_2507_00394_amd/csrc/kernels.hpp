@@ -37,10 +37,11 @@ struct BwdMaps { TensorMap q, k, v, o, dO, dq, dk, dv; };
 hipError_t launch_fwd(const void* q, const void* k, const void* v, void* o, float* lse, const FwdMaps& maps,
                       int B, int H, int S, int D, float scale, bool causal, hipStream_t stream);
 hipError_t launch_bwd_preprocess(const void* o, const void* dO, const float* lse, float* neg_delta, float* lse2,
-                                 const BwdMaps& maps, int B, int H, int S, int D, hipStream_t stream);
-// neg_delta_i = -sum_j p_ij dp_ij for query rows 0..rows-1 of every head, overwriting neg_delta there.
+                                 const BwdMaps& maps, int B, int H, int S, int D, int first_row, hipStream_t stream);
+// neg_delta_i = -sum_j p_ij dp_ij for query rows 0..rows-1 (rounded up to a multiple of 256) of every head, overwriting
+// neg_delta there; lse2, unless null, is written for the same rows.
 hipError_t launch_bwd_delta_head(const void* q, const void* k, const void* v, const void* dO,
-                                 const float* lse, float* neg_delta, const BwdMaps& maps, int B, int H, int S, int D,
+                                 const float* lse, float* neg_delta, float* lse2, const BwdMaps& maps, int B, int H, int S, int D,
                                  int rows, float scale, bool causal, hipStream_t stream);
 hipError_t launch_bwd_dkdv(const void* q, const void* k, const void* v, const void* dO,
                            const float* lse2, const float* neg_delta, void* dk, void* dv, const BwdMaps& maps,
