@@ -173,8 +173,10 @@ __device__ __forceinline__ void dkdv_step(const f32x16& sp_cur, const f32x16& dp
 
 }  // namespace
 
-template <int D, bool CAUSAL>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
+// GROUPS = 2 (see split_queries): two groups of four waves own the same 128 keys and sweep one half of the query
+// tiles each, with stages of their own; at the end they swap partial sums through LDS and each stores one result.
+template <int D, bool CAUSAL, int GROUPS>
+__global__ void __launch_bounds__(256 * GROUPS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 bwd_dkdv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
                 const __bf16* __restrict__ dO, const float* __restrict__ lse2, const float* __restrict__ neg_delta,
                 __bf16* __restrict__ dk, __bf16* __restrict__ dv, BwdMaps maps, int BH, int H, int S, int T,
@@ -186,7 +188,8 @@ bwd_dkdv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, cons
   const TileCoord tc = map_block<CAUSAL>(blockIdx.x, BH, T, false);
   if (!tc.valid) return;
   const int tid = threadIdx.x, lane = tid & 63;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6) & 3;       // wave of its group
+  const int group = GROUPS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 8);
   const int half = lane >> 5, n = lane & 31;
   const int n0 = tc.tile * BN;
   const int wave_kmin = n0 + 32 * w;
@@ -198,7 +201,8 @@ bwd_dkdv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, cons
   const float* lse_h = lse2 + (size_t)tc.bh * S;
   const float* delta_h = neg_delta + (size_t)tc.bh * S;
   const float c = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, scale * kLog2e)));
-  const uint32_t base = lds_base(smem);
+  const char* const stages = smem + group * (G::NSTAGE * G::STAGE);
+  const uint32_t base = lds_base(stages);
 
   // K^T and V^T operand fragments of this lane's key (columns of S and dP).
   bf16x8 kf[KS], vf[KS];
@@ -218,12 +222,16 @@ bwd_dkdv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, cons
 #pragma unroll
     for (int e = 0; e < 16; e++) { dkacc[db][e] = 0.f; dvacc[db][e] = 0.f; }
 
-  const int m_start = CAUSAL ? n0 : 0;                       // first query row that sees a key of this tile
-  const int nt = (S - m_start + BM - 1) / BM;                // query tiles to sweep
+  const int m_first = CAUSAL ? n0 : 0;                       // first query row that sees a key of this tile
+  const int nt_all = (S - m_first + BM - 1) / BM;            // query tiles to sweep
+  const int nt_first = (nt_all + GROUPS - 1) / GROUPS;       // of which the first group takes these
+  const int nt = group == 0 ? nt_first : nt_all - nt_first;
+  const int m_start = m_first + group * nt_first * BM;
   // Plain (masked) path: the tiles the causal diagonal crosses and a ragged last tile.
-  int t_lo = CAUSAL ? 2 : 0;
+  int t_lo = CAUSAL ? 2 - group * nt_first : 0;
+  if (t_lo < 0) t_lo = 0;
   if (t_lo > nt) t_lo = nt;
-  int t_hi = ((S - m_start) % BM != 0) ? nt - 1 : nt;
+  int t_hi = (m_start + nt * BM > S) ? nt - 1 : nt;
   if (t_hi < t_lo) t_hi = t_lo;
 
   const TileLoader<D, BM, 4> qload(lane, w, maps.q.row), gload(lane, w, maps.dO.row);
@@ -252,7 +260,7 @@ bwd_dkdv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, cons
     __syncthreads();
     st = (st + 1) & 3;
   };
-  copy_tile(0, 0);
+  if (GROUPS == 1 || nt > 0) copy_tile(0, 0);
   if (nt > 1) copy_tile(1, 1);
   if (nt > 2) copy_tile(2, 2);
   wait_tile_loads();
@@ -261,7 +269,7 @@ bwd_dkdv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, cons
   // One 32-row block through the plain path: everything in program order, masks applied.
   auto plain_block = [&](int blk) __attribute__((always_inline)) {
     const int r0 = m_start + t * BM + 32 * blk;   // global row of the block's first query
-    const char* qt = smem + st * G::STAGE;
+    const char* qt = stages + st * G::STAGE;
     const char* gt = qt + G::TILE;
     const float* lse_t = reinterpret_cast<const float*>(qt + G::STATS + w * 512);
     const float* dlt_t = lse_t + 64;
@@ -353,6 +361,30 @@ bwd_dkdv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, cons
 
   for (; t < nt; t++) { copy_ahead(); plain_tile(); finish_tile(); }
 
+  if constexpr (GROUPS == 2) {
+    for (; t < nt_first; t++) __syncthreads();   // the second group has one tile fewer at times; all stages are free after this
+    char* const give = smem + (group * 4 + w) * (DB * 4096);
+    const char* const take = smem + ((group ^ 1) * 4 + w) * (DB * 4096);
+#pragma unroll
+    for (int db = 0; db < DB; db++) lds_put_block(give + db * 4096, lane, group == 0 ? dkacc[db] : dvacc[db]);
+    __syncthreads();
+    if (my_key < S) {
+      const TensorMap& m = group == 0 ? maps.dv : maps.dk;
+      __bf16* row = (group == 0 ? dv : dk) + head_offset(m, tc.bh, H) + (size_t)my_key * m.row;
+      const float f = group == 0 ? 1.f : scale;
+#pragma unroll
+      for (int db = 0; db < DB; db++) {
+        const f32x16 x = lds_get_block(take + db * 4096, lane) + (group == 0 ? dvacc[db] : dkacc[db]);
+#pragma unroll
+        for (int g = 0; g < 4; g++) {
+          const f32x4 y = {x[4 * g] * f, x[4 * g + 1] * f, x[4 * g + 2] * f, x[4 * g + 3] * f};
+          *reinterpret_cast<bf16x4*>(row + 32 * db + 8 * g + 4 * half) = __builtin_convertvector(y, bf16x4);
+        }
+      }
+    }
+    return;
+  }
+
   if (my_key < S) {
     __bf16* dkrow = dk + head_offset(maps.dk, tc.bh, H) + (size_t)my_key * maps.dk.row;
     __bf16* dvrow = dv + head_offset(maps.dv, tc.bh, H) + (size_t)my_key * maps.dv.row;
@@ -369,21 +401,34 @@ bwd_dkdv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, cons
   }
 }
 
-template <int D, bool CAUSAL>
+template <int D, bool CAUSAL, int GROUPS>
 static hipError_t launch_dkdv_t(const void* q, const void* k, const void* v, const void* dO,
                                 const float* lse2, const float* neg_delta, void* dk, void* dv, const BwdMaps& maps,
                                 int B, int H, int S, float scale, hipStream_t stream) {
   constexpr int BN = 128;
   const int T = (S + BN - 1) / BN, BH = B * H;
   const unsigned grid = (unsigned)grid_blocks(BH, T);
-  const size_t lds = Geometry<D>::NSTAGE * Geometry<D>::STAGE;
-  auto kern = bwd_dkdv_kernel<D, CAUSAL>;
+  const size_t lds = GROUPS * Geometry<D>::NSTAGE * Geometry<D>::STAGE;
+  auto kern = bwd_dkdv_kernel<D, CAUSAL, GROUPS>;
   static unsigned long long configured = 0;   // one static per template instantiation
   hipError_t e = allow_dynamic_lds(kern, lds, configured);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, stream, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v,
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(256 * GROUPS), lds, stream, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v,
                      (const __bf16*)dO, lse2, neg_delta, (__bf16*)dk, (__bf16*)dv, maps, BH, H, S, T, scale);
   return hipGetLastError();
+}
+
+// Whether two groups of waves share a workgroup's query tiles.  A workgroup of one group leaves a SIMD with one wave, which
+// is bound by instruction issue, unless a second workgroup finds room beside it; with two groups the sweep is
+// half as long, the swap of partial sums costs about 1 us.  Measured, one -> two groups, us:
+//   causal (the first key tiles are the longest, so what counts is the length of one sweep): 12 heads x 1500 (144 key tiles)
+//     30.8 -> 27.5; 2 x 16k (256) 239 -> 203; 3 x 16k (384) 277 -> 235; 4 x 16k (512) 310 -> 266; 32 x 1800 (480)
+//     42.0 -> 42.1; beyond two workgroups per compute unit 40 x 2048 (640) 53 -> 64.
+//   no mask: 12 x 1500 (144) 28.9 -> 26.6; 2 x 16k (256) 284 -> 260; short sweeps gain nothing, 27 x 777 (189) 21.2 -> 21.6;
+//     beyond one workgroup per compute unit 24 x 1500 (288) 45 -> 55, 3 x 16k (384) 417 -> 436.
+static bool split_queries(int BH, int S, bool causal) {
+  const long long tiles = (long long)BH * ((S + 127) / 128);
+  return causal ? tiles <= 512 : tiles <= 256 && S >= 1024;
 }
 
 hipError_t launch_bwd_dkdv(const void* q, const void* k, const void* v, const void* dO,
@@ -391,8 +436,11 @@ hipError_t launch_bwd_dkdv(const void* q, const void* k, const void* v, const vo
                            int B, int H, int S, int D, float scale, bool causal, hipStream_t stream) {
   // Head dimension 128 has its own kernel with two waves per SIMD; this one serves head dimension 64.
   if (D == 128) return launch_bwd_dkdv_pair(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B, H, S, scale, causal, stream);
-  return causal ? launch_dkdv_t<64, true>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B, H, S, scale, stream)
-                : launch_dkdv_t<64, false>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B, H, S, scale, stream);
+  if (split_queries(B * H, S, causal))
+    return causal ? launch_dkdv_t<64, true, 2>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B, H, S, scale, stream)
+                  : launch_dkdv_t<64, false, 2>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B, H, S, scale, stream);
+  return causal ? launch_dkdv_t<64, true, 1>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B, H, S, scale, stream)
+                : launch_dkdv_t<64, false, 1>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B, H, S, scale, stream);
 }
 
 }  // namespace helix
