@@ -352,8 +352,7 @@ int run_bwd(const void* q, const void* k, const void* v, const void* o, const fl
   // launched at all up to HELIX_DELTA_HEAD_ROWS tokens)
   HELIX_TRY(launched(helix::launch_bwd_preprocess(o, dO, lse, nd, l2, maps, B, H, S, D, causal ? HELIX_DELTA_HEAD_ROWS : 0, st)));
   if (causal) HELIX_TRY(launched(helix::launch_bwd_delta_head(q, k, v, dO, lse, nd, l2, maps, B, H, S, D, HELIX_DELTA_HEAD_ROWS, scale, true, st)));
-  HELIX_TRY(launched(helix::launch_bwd_dkdv(q, k, v, dO, l2, nd, dk, dv, maps, B, H, S, D, scale, causal != 0, st)));
-  return launched(helix::launch_bwd_dq(q, k, v, dO, l2, nd, dq, maps, B, H, S, D, scale, causal != 0, st));
+  return launched(helix::launch_bwd_dkdv_dq(q, k, v, dO, l2, nd, dq, dk, dv, maps, B, H, S, D, scale, causal != 0, st));
 }
 
 }  // namespace

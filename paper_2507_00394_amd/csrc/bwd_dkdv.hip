@@ -37,6 +37,8 @@
 // masked path.  No atomics: every dK / dV element is produced by exactly one lane.
 #include "helix_common.hpp"
 #include "kernels.hpp"
+#include "bwd_dq.hpp"
+#include <algorithm>
 
 namespace helix {
 
@@ -176,16 +178,15 @@ __device__ __forceinline__ void dkdv_step(const f32x16& sp_cur, const f32x16& dp
 // GROUPS = 2 (see split_queries): two groups of four waves own the same 128 keys and sweep one half of the query
 // tiles each, with stages of their own; at the end they swap partial sums through LDS and each stores one result.
 template <int D, bool CAUSAL, int GROUPS>
-__global__ void __launch_bounds__(256 * GROUPS) __attribute__((amdgpu_waves_per_eu(2, 2)))
-bwd_dkdv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
-                const __bf16* __restrict__ dO, const float* __restrict__ lse2, const float* __restrict__ neg_delta,
-                __bf16* __restrict__ dk, __bf16* __restrict__ dv, BwdMaps maps, int BH, int H, int S, int T,
-                float scale) {
+__device__ __forceinline__ void dkdv_keys(int block, const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
+                                          const __bf16* __restrict__ dO, const float* __restrict__ lse2, const float* __restrict__ neg_delta,
+                                          __bf16* __restrict__ dk, __bf16* __restrict__ dv, BwdMaps maps, int BH, int H, int S, int T,
+                                          float scale) {
   using G = Geometry<D>;
   constexpr int BN = 128, BM = 64, KS = G::KS, DB = G::DB;
   extern __shared__ __align__(16) char smem[];
 
-  const TileCoord tc = map_block<CAUSAL>(blockIdx.x, BH, T, false);
+  const TileCoord tc = map_block<CAUSAL>(block, BH, T, false);
   if (!tc.valid) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6) & 3;       // wave of its group
@@ -402,6 +403,28 @@ bwd_dkdv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, cons
 }
 
 template <int D, bool CAUSAL, int GROUPS>
+__global__ void __launch_bounds__(256 * GROUPS) __attribute__((amdgpu_waves_per_eu(2, 2)))
+bwd_dkdv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
+                const __bf16* __restrict__ dO, const float* __restrict__ lse2, const float* __restrict__ neg_delta,
+                __bf16* __restrict__ dk, __bf16* __restrict__ dv, BwdMaps maps, int BH, int H, int S, int T,
+                float scale) {
+  dkdv_keys<D, CAUSAL, GROUPS>(blockIdx.x, q, k, v, dO, lse2, neg_delta, dk, dv, maps, BH, H, S, T, scale);
+}
+
+// The dK/dV and the dQ pass in one launch (see launch_bwd_dkdv_dq): the first `key_blocks` workgroups take key tiles, the others
+// 128-row query tiles.
+template <int D, bool CAUSAL>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+bwd_dkdv_dq_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
+                   const __bf16* __restrict__ dO, const float* __restrict__ lse2, const float* __restrict__ neg_delta,
+                   __bf16* __restrict__ dq, __bf16* __restrict__ dk, __bf16* __restrict__ dv, BwdMaps maps, int BH, int H, int S,
+                   int key_tiles, int key_blocks, int query_tiles, float scale) {
+  const int block = (int)blockIdx.x;
+  if (block < key_blocks) dkdv_keys<D, CAUSAL, 2>(block, q, k, v, dO, lse2, neg_delta, dk, dv, maps, BH, H, S, key_tiles, scale);
+  else dq_split_rows<D, CAUSAL>(block - key_blocks, q, k, v, dO, lse2, neg_delta, dq, maps, BH, H, S, query_tiles, scale);
+}
+
+template <int D, bool CAUSAL, int GROUPS>
 static hipError_t launch_dkdv_t(const void* q, const void* k, const void* v, const void* dO,
                                 const float* lse2, const float* neg_delta, void* dk, void* dv, const BwdMaps& maps,
                                 int B, int H, int S, float scale, hipStream_t stream) {
@@ -441,6 +464,45 @@ hipError_t launch_bwd_dkdv(const void* q, const void* k, const void* v, const vo
                   : launch_dkdv_t<64, false, 2>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B, H, S, scale, stream);
   return causal ? launch_dkdv_t<64, true, 1>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B, H, S, scale, stream)
                 : launch_dkdv_t<64, false, 1>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B, H, S, scale, stream);
+}
+
+template <int D, bool CAUSAL>
+static hipError_t launch_dkdv_dq_t(const void* q, const void* k, const void* v, const void* dO, const float* lse2,
+                                   const float* neg_delta, void* dq, void* dk, void* dv, const BwdMaps& maps, int B, int H, int S,
+                                   float scale, hipStream_t stream) {
+  const int BH = B * H, TK = (S + 127) / 128, TQ = dq_tiles(S, true);
+  const long long key_blocks = grid_blocks(BH, TK);
+  const size_t lds = std::max(2 * Geometry<D>::NSTAGE * Geometry<D>::STAGE, DqSplit<D>::LDS);
+  auto kern = bwd_dkdv_dq_kernel<D, CAUSAL>;
+  static unsigned long long configured = 0;   // one static per template instantiation
+  hipError_t e = allow_dynamic_lds(kern, lds, configured);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(key_blocks + grid_blocks(BH, TQ))), dim3(512), lds, stream, (const __bf16*)q,
+                     (const __bf16*)k, (const __bf16*)v, (const __bf16*)dO, lse2, neg_delta, (__bf16*)dq, (__bf16*)dk, (__bf16*)dv, maps,
+                     BH, H, S, TK, (int)key_blocks, TQ, scale);
+  return hipGetLastError();
+}
+
+// Both passes need the row statistics and nothing of each other, and a workgroup of either fills a compute unit (LDS at head
+// dimension 128, registers at 64), so one launch with the key tiles first fills the compute units that a small grid or its
+// last, uneven round leaves idle, and pays for one start instead of two.  Backward, two launches -> one, us, at head dimension
+// 128 / 64, causal: 2 heads x 512 58.8 -> 43.2 / 34.2 -> 23.4; 12 x 1500 101 -> 72 / 64 -> 45; 16 x 2048 133 -> 105 /
+// 80 -> 63; 5 x 8192 383 -> 336; 64 x 2048 (1024 key tiles) 381 -> 375; with more rounds there is little left to
+// fill and the change from one pass to the other costs L2 hits: 5 x 32k (1280) 4190 -> 4276, 16 x 16k (2048) 3164 -> 3159,
+// 80 x 8000 (5040) 4139 -> 4165.
+// No mask: 2 x 512 43.8 -> 27.4 / 26.7 -> 15.9; 27 x 777 68 -> 63 / 43 -> 39; 16 x 8192 1558 -> 1542.
+// At head dimension 64 the launch needs workgroups of eight waves on either side: the two-group dK/dV and the split dQ.
+hipError_t launch_bwd_dkdv_dq(const void* q, const void* k, const void* v, const void* dO, const float* lse2, const float* neg_delta,
+                              void* dq, void* dk, void* dv, const BwdMaps& maps, int B, int H, int S, int D, float scale, bool causal,
+                              hipStream_t stream) {
+  const long long key_tiles = (long long)B * H * ((S + 127) / 128);
+  if (D == 128 && key_tiles <= 1024)
+    return launch_bwd_dkdv_dq_pair(q, k, v, dO, lse2, neg_delta, dq, dk, dv, maps, B, H, S, scale, causal, stream);
+  if (D == 64 && split_rows(B * H, S, causal))
+    return causal ? launch_dkdv_dq_t<64, true>(q, k, v, dO, lse2, neg_delta, dq, dk, dv, maps, B, H, S, scale, stream)
+                  : launch_dkdv_dq_t<64, false>(q, k, v, dO, lse2, neg_delta, dq, dk, dv, maps, B, H, S, scale, stream);
+  hipError_t e = launch_bwd_dkdv(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B, H, S, D, scale, causal, stream);
+  return e != hipSuccess ? e : launch_bwd_dq(q, k, v, dO, lse2, neg_delta, dq, maps, B, H, S, D, scale, causal, stream);
 }
 
 }  // namespace helix

@@ -26,7 +26,9 @@
 // remains at the end run through a plain path (A, barrier, B, barrier).
 #include "helix_common.hpp"
 #include "kernels.hpp"
+#include "bwd_dq.hpp"
 
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -522,16 +524,63 @@ __device__ __forceinline__ void pair_sweep(const __bf16* __restrict__ q, const _
 }
 
 template <bool CAUSAL>
+__device__ __forceinline__ void pair_keys(int block, const __bf16* __restrict__ q, const __bf16* __restrict__ k,
+                                          const __bf16* __restrict__ v, const __bf16* __restrict__ dO, const float* __restrict__ lse2,
+                                          const float* __restrict__ neg_delta, __bf16* __restrict__ dk, __bf16* __restrict__ dv,
+                                          const BwdMaps& maps, int BH, int H, int S, int T, float scale) {
+  const TileCoord tc = map_block<CAUSAL>(block, BH, T, false);
+  if (!tc.valid) return;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (w < 4) pair_sweep<CAUSAL, 0>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, tc, H, S, scale);
+  else pair_sweep<CAUSAL, 1>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, tc, H, S, scale);
+}
+
+template <bool CAUSAL>
 __global__ void __launch_bounds__(512, 1)
 bwd_dkdv_pair_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
                      const __bf16* __restrict__ dO, const float* __restrict__ lse2, const float* __restrict__ neg_delta,
                      __bf16* __restrict__ dk, __bf16* __restrict__ dv, BwdMaps maps, int BH, int H, int S, int T,
                      float scale) {
-  const TileCoord tc = map_block<CAUSAL>(blockIdx.x, BH, T, false);
-  if (!tc.valid) return;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (w < 4) pair_sweep<CAUSAL, 0>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, tc, H, S, scale);
-  else pair_sweep<CAUSAL, 1>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, tc, H, S, scale);
+  pair_keys<CAUSAL>(blockIdx.x, q, k, v, dO, lse2, neg_delta, dk, dv, maps, BH, H, S, T, scale);
+}
+
+// The dK/dV and the dQ pass in one launch (see launch_bwd_dkdv_dq): the first `key_blocks` workgroups take key tiles, the others
+// query tiles.
+template <bool CAUSAL, bool SPLIT>
+__global__ void __launch_bounds__(512, 1)
+bwd_dkdv_dq_pair_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
+                        const __bf16* __restrict__ dO, const float* __restrict__ lse2, const float* __restrict__ neg_delta,
+                        __bf16* __restrict__ dq, __bf16* __restrict__ dk, __bf16* __restrict__ dv, BwdMaps maps, int BH, int H,
+                        int S, int key_tiles, int key_blocks, int query_tiles, float scale) {
+  const int block = (int)blockIdx.x;
+  if (block < key_blocks) pair_keys<CAUSAL>(block, q, k, v, dO, lse2, neg_delta, dk, dv, maps, BH, H, S, key_tiles, scale);
+  else if constexpr (SPLIT) dq_split_rows<128, CAUSAL>(block - key_blocks, q, k, v, dO, lse2, neg_delta, dq, maps, BH, H, S, query_tiles, scale);
+  else dq_whole_rows<128, CAUSAL>(block - key_blocks, q, k, v, dO, lse2, neg_delta, dq, maps, BH, H, S, query_tiles, scale);
+}
+
+template <bool CAUSAL>
+static hipError_t launch_dkdv_dq_pair_t(const void* q, const void* k, const void* v, const void* dO, const float* lse2,
+                                        const float* neg_delta, void* dq, void* dk, void* dv, const BwdMaps& maps, int B, int H, int S,
+                                        float scale, hipStream_t stream) {
+  const int BH = B * H;
+  const bool split = split_rows(BH, S, CAUSAL);
+  const int TK = (S + PG::BN - 1) / PG::BN, TQ = dq_tiles(S, split);
+  const long long key_blocks = grid_blocks(BH, TK);
+  const size_t lds = std::max(PG::LDS, split ? DqSplit<128>::LDS : kDqWholeLds<128>);
+  auto kern = split ? bwd_dkdv_dq_pair_kernel<CAUSAL, true> : bwd_dkdv_dq_pair_kernel<CAUSAL, false>;
+  static unsigned long long configured[2] = {};   // per template instantiation and kernel
+  hipError_t e = allow_dynamic_lds(kern, lds, configured[split]);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(key_blocks + grid_blocks(BH, TQ))), dim3(512), lds, stream, (const __bf16*)q,
+                     (const __bf16*)k, (const __bf16*)v, (const __bf16*)dO, lse2, neg_delta, (__bf16*)dq, (__bf16*)dk, (__bf16*)dv, maps,
+                     BH, H, S, TK, (int)key_blocks, TQ, scale);
+  return hipGetLastError();
+}
+hipError_t launch_bwd_dkdv_dq_pair(const void* q, const void* k, const void* v, const void* dO, const float* lse2,
+                                   const float* neg_delta, void* dq, void* dk, void* dv, const BwdMaps& maps, int B, int H, int S,
+                                   float scale, bool causal, hipStream_t stream) {
+  return causal ? launch_dkdv_dq_pair_t<true>(q, k, v, dO, lse2, neg_delta, dq, dk, dv, maps, B, H, S, scale, stream)
+                : launch_dkdv_dq_pair_t<false>(q, k, v, dO, lse2, neg_delta, dq, dk, dv, maps, B, H, S, scale, stream);
 }
 
 hipError_t launch_bwd_dkdv_pair(const void* q, const void* k, const void* v, const void* dO, const float* lse2,
