@@ -22,8 +22,13 @@
 // issued) plus small rings for lse2 / -delta.  The block loop is unrolled seven times, so the
 // stage of every LDS access is a compile-time immediate added to the lane's address register
 // (a whole ring is within the 64 KB reach of an LDS instruction's offset field): the loop
-// contains no address arithmetic at all.  Blocks cut by the causal diagonal and whatever
-// remains at the end run through a plain path (A, barrier, B, barrier).
+// contains no address arithmetic at all.
+//
+// All complete blocks are pipelined: those the causal diagonal cuts with the mask in the step, the last ones with a
+// copy that checks the end of the sequence in front of the step.  Through the plain path that a ragged last block still takes
+// (A, barrier, B, barrier: the two waves of a SIMD take turns), the first four and the last six to twelve blocks cost
+// a key tile about 6 us, which short sweeps feel most: backward of 4 x 16 heads x 2k 378 -> 351 us, forward + backward of
+// 2 x 40 x 8000 5.41 -> 5.30 ms, 16 x 16k 4.08 -> 4.01, 5 x 32k 5.57 -> 5.54, the same bits.
 #include "helix_common.hpp"
 #include "kernels.hpp"
 #include "bwd_dq.hpp"
@@ -136,9 +141,10 @@ __device__ __forceinline__ f32x4 (&l2ref(f32x4 (&st)[4]))[2] { return reinterpre
 // ------------------------------------------------------------------ wave A: one pipelined block
 // Block i at stage K.  On entry s_cur = S(i) with entries 0..7 already exponentiated, l2 =
 // lse2 of block i, ring = the first four Q row operands of block i+1.  On exit the same for i+1.
-template <int K>
+// COPY: copies block i + AHEAD.  MASK: rows 8g + r of this lane's half count from first_row on (block i; 32 less for i+1).
+template <int K, bool COPY, bool MASK>
 __device__ __forceinline__ void step_a(f32x16& s_cur, f32x16& s_next, bf16x8 (&ring)[4], f32x4 (&l2)[2], Lane& ln,
-                                       const bf16x8 (&kf)[PG::KS], f32x16 (&dvacc)[PG::DB], float c, Copier& cp) {
+                                       const bf16x8 (&kf)[PG::KS], f32x16 (&dvacc)[PG::DB], float c, Copier& cp, int first_row) {
   using G = PG;
   constexpr int KS = G::KS, DB = G::DB;
   constexpr int KN = wrap(K + 1), KP = wrap(K + 2);
@@ -175,15 +181,17 @@ __device__ __forceinline__ void step_a(f32x16& s_cur, f32x16& s_next, bf16x8 (&r
       // second half of P(i); packs of the first half
       constexpr int e = 8 + s;
       s_cur[e] = __builtin_amdgcn_exp2f(fmaf(s_cur[e], c, -l2[(s / 4) & 1][e % 4]));
+      if constexpr (MASK) s_cur[e] = 8 * (e / 4) + e % 4 >= first_row ? s_cur[e] : 0.f;
       if constexpr (s < 4) pk[s] = pack_bf16_pair(s_cur[2 * s], s_cur[2 * s + 1]);
       if constexpr (e & 1) pk[e / 2] = pack_bf16_pair(s_cur[e - 1], s_cur[e]);
     } else {
       // first half of P(i+1)
       constexpr int e = s - KS;
       s_next[e] = __builtin_amdgcn_exp2f(fmaf(s_next[e], c, -l2[(s / 4) & 1][e % 4]));
+      if constexpr (MASK) s_next[e] = PG::RB + 8 * (e / 4) + e % 4 >= first_row ? s_next[e] : 0.f;
     }
     // ---- copy of block i + AHEAD into the stage block i - 2 has left
-    if constexpr (s == 2) copy_whole_block<wrap(K + G::AHEAD)>(cp);
+    if constexpr (COPY && s == 2) copy_whole_block<wrap(K + G::AHEAD)>(cp);
     // ---- P(i) to wave B
     if constexpr (s == 0) { lds_store_f32x4(ln.pbuf, 0, quarter(s_cur, 0)); lds_store_f32x4(ln.pbuf, 1024, quarter(s_cur, 1)); }
     if constexpr (s == KS) { lds_store_f32x4(ln.pbuf, 2048, quarter(s_cur, 2)); lds_store_f32x4(ln.pbuf, 3072, quarter(s_cur, 3)); }
@@ -198,7 +206,7 @@ __device__ __forceinline__ void step_a(f32x16& s_cur, f32x16& s_next, bf16x8 (&r
 // ------------------------------------------------------------------ wave B: one pipelined iteration
 // Iteration i (A's block, stage K): finishes block j = i-1 (dS, dK) unless SKIP and computes
 // dP(i).  On entry dp_cur = dP(j), nd = -delta(i), ring = the first four dO row operands of block i.
-template <int K, bool SKIP>
+template <int K, bool COPY, bool SKIP>
 __device__ __forceinline__ void step_b(f32x16& dp_cur, f32x16& dp_next, bf16x8 (&ring)[4], f32x4 (&nd)[4], Lane& ln,
                                        const bf16x8 (&vf)[PG::KS], f32x16 (&dkacc)[PG::DB], Copier& cp) {
   using G = PG;
@@ -233,7 +241,7 @@ __device__ __forceinline__ void step_b(f32x16& dp_cur, f32x16& dp_next, bf16x8 (
       } else ring[s % 4] = lds_b128(ln.aq[u - 2 * KS], stage_imm(KN));
     }
     // ---- copy of block i + AHEAD into the stage block i - 2 has left
-    if constexpr (s == 2) copy_whole_block<wrap(K + G::AHEAD)>(cp);
+    if constexpr (COPY && s == 2) copy_whole_block<wrap(K + G::AHEAD)>(cp);
     // ---- -delta of block i+1 (the registers are free once the dP product has started)
     if constexpr (s >= 12) nd[s - 12] = lds_f32x4(ln.astat, KN * G::STAT_STAGE + 8 * (s - 12) * 4);
     // ---- vector work: dS(j) = P(j) o dP(j), two elements per slot in slots 4..7 (first half, P was
@@ -317,16 +325,11 @@ __device__ __forceinline__ void pair_sweep(const __bf16* __restrict__ q, const _
   const int m_start = CAUSAL ? n0 : 0;                       // first query row that sees a key of this tile
   const int nb = (S - m_start + RB - 1) / RB;                // blocks to sweep
   const int nfull = (S - m_start) / RB;                      // of which complete
-  // pipelined blocks [i0, i1): after the blocks the causal diagonal cuts, starting at stage 0, 1 + 7 g of them
-  const int i0 = CAUSAL ? G::BN / RB : 0;
-  // Block i lives in stage (i + kStageShift) % NSTAGE: the first pipelined block sits in stage 0, where the
-  // unrolled loop starts, without padding the plain prefix to a multiple of seven.
-  constexpr int kStageShift = CAUSAL ? NST - G::BN / RB : 0;
-  auto stage_of = [&](int i) __attribute__((always_inline)) { return (i + kStageShift) % NST; };
-  int i1 = i0;
-  // (every copy they issue, up to block i1 - 1 + AHEAD, and the 64 statistics rows it reads are whole)
-  const int navail = nfull - (G::AHEAD + 1) - i0;
-  if (navail >= 1 + NST) i1 = i0 + 1 + ((navail - 1) / NST) * NST;
+  // Block i lives in stage i % NSTAGE.  The complete blocks are pipelined: the first kStart of them (with a causal mask
+  // those the diagonal cuts) and the last ones with the general copy in front of the step, those between, seven at a time,
+  // with the copy inside it.  A ragged last block, and sweeps shorter than kStart, take the plain path.
+  constexpr int kStart = CAUSAL ? G::BN / RB : 1;
+  auto stage_of = [](int i) __attribute__((always_inline)) { return i % NST; };
 
   const TileLoader<D, RB, 8> qload(lane, w, maps.q.row), gload(lane, w, maps.dO.row);
   static_assert(decltype(qload)::N + decltype(gload)::N + 1 == G::NDMA, "copy instructions per wave and block");
@@ -410,16 +413,15 @@ __device__ __forceinline__ void pair_sweep(const __bf16* __restrict__ q, const _
   };
 
   int i = 0;
-  for (; i < i0 && i < nb; i++) plain_block(i);
-
-  if (i1 > i0) {
+  if (nfull >= kStart) {
     ln.pbuf = pbuf0;
     ln.pstep = G::PBYTES;
     bf16x8 ring[4];
     f32x16 xa, xb;            // S (A) or dP (B) of the current and of the next block
     f32x4 st[4];              // A: two groups of lse2 (st[0], st[1]); B: -delta of the block whose dP product starts next
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    // ---- prime at block i0 (stage 0)
+    int first_row = my_key - m_start - 4 * half;   // causal: first row of the block, less this half's 4, that sees this lane's key
+    // ---- prime at block 0
     xa = zero;
     xb = zero;
     if constexpr (role == 0) {
@@ -429,7 +431,10 @@ __device__ __forceinline__ void pair_sweep(const __bf16* __restrict__ q, const _
       for (int g = 0; g < 2; g++) {
         const f32x4 l4 = lds_f32x4(ln.astat, 8 * g * 4);
 #pragma unroll
-        for (int e4 = 0; e4 < 4; e4++) xa[4 * g + e4] = __builtin_amdgcn_exp2f(fmaf(xa[4 * g + e4], c, -l4[e4]));
+        for (int e4 = 0; e4 < 4; e4++) {
+          const float p = __builtin_amdgcn_exp2f(fmaf(xa[4 * g + e4], c, -l4[e4]));
+          xa[4 * g + e4] = !CAUSAL || 8 * g + e4 >= first_row ? p : 0.f;
+        }
       }
       st[0] = lds_f32x4(ln.astat, 8 * 2 * 4);
 #pragma unroll
@@ -441,8 +446,32 @@ __device__ __forceinline__ void pair_sweep(const __bf16* __restrict__ q, const _
       for (int r = 0; r < 4; r++) ring[r] = lds_b128(ln.aq[r], 0);
     }
     Copier cp;
-    {
-      const int row0 = m_start + (i0 + G::AHEAD) * RB;
+    // One block of this wave's role at stage K with the general copy in front of it.
+    auto careful = [&](auto stage, auto masked, auto skip, f32x16& cur, f32x16& next) __attribute__((always_inline)) {
+      constexpr int K = decltype(stage)::value;
+      copy_ahead(i);
+      if constexpr (role == 0) step_a<K, false, decltype(masked)::value>(cur, next, ring, l2ref(st), ln, frag, acc, c, cp, first_row);
+      else step_b<K, false, decltype(skip)::value>(cur, next, ring, st, ln, frag, acc, cp);
+      if (i + G::AHEAD < nb) block_barrier<2 * G::NDMA>();
+      else block_barrier<0>();
+      first_row -= RB;
+      i++;
+    };
+    // ---- the first blocks; B has no finished block in the first one
+    const auto whole = std::integral_constant<bool, false>{};
+    const auto diagonal = std::integral_constant<bool, CAUSAL>{};
+    careful(std::integral_constant<int, 0>{}, diagonal, std::true_type{}, xa, xb);
+    if constexpr (CAUSAL) {
+      careful(std::integral_constant<int, 1>{}, diagonal, std::false_type{}, xb, xa);
+      careful(std::integral_constant<int, 2>{}, diagonal, std::false_type{}, xa, xb);
+      careful(std::integral_constant<int, 3>{}, diagonal, std::false_type{}, xb, xa);
+    } else {
+      xa = xb;
+    }
+    // ---- seven blocks per trip, stages kStart, kStart + 1, ...; S / dP alternate between xa and xb.  Every copy a
+    // trip issues, up to that of its last block + AHEAD, and the 64 statistics rows it reads are whole.
+    if (i + NST + G::AHEAD < nfull) {
+      const int row0 = m_start + (i + G::AHEAD) * RB;
       cp.qstep = RB * qload.row_bytes;
       cp.gstep = RB * gload.row_bytes;
       cp.qptr = uniform_ptr(reinterpret_cast<const __bf16*>(reinterpret_cast<const char*>(qh) + (size_t)row0 * qload.row_bytes));
@@ -453,46 +482,37 @@ __device__ __forceinline__ void pair_sweep(const __bf16* __restrict__ q, const _
       cp.soff = (uint32_t)(row0 + lane) * 4;
       cp.dst = __builtin_amdgcn_readfirstlane(base + w * 1024);
       cp.sdst = __builtin_amdgcn_readfirstlane(base + G::STATS + role * 256);
-    }
-    // ---- first iteration: B has no finished block yet
-    if constexpr (role == 0) step_a<0>(xa, xb, ring, l2ref(st), ln, frag, acc, c, cp);
-    else step_b<0, true>(xa, xb, ring, st, ln, frag, acc, cp);
-    block_barrier<2 * G::NDMA>();
-    i++;
-    // ---- seven blocks per trip: stages 1, 2, ..., 6, 0; S / dP alternate between xb and xa
-    if constexpr (role == 0) {
-      for (; i < i1; i += NST) {
-        step_a<1>(xb, xa, ring, l2ref(st), ln, frag, acc, c, cp); block_barrier<2 * G::NDMA>();
-        step_a<2>(xa, xb, ring, l2ref(st), ln, frag, acc, c, cp); block_barrier<2 * G::NDMA>();
-        step_a<3>(xb, xa, ring, l2ref(st), ln, frag, acc, c, cp); block_barrier<2 * G::NDMA>();
-        step_a<4>(xa, xb, ring, l2ref(st), ln, frag, acc, c, cp); block_barrier<2 * G::NDMA>();
-        step_a<5>(xb, xa, ring, l2ref(st), ln, frag, acc, c, cp); block_barrier<2 * G::NDMA>();
-        step_a<6>(xa, xb, ring, l2ref(st), ln, frag, acc, c, cp); block_barrier<2 * G::NDMA>();
-        step_a<0>(xb, xa, ring, l2ref(st), ln, frag, acc, c, cp); block_barrier<2 * G::NDMA>();
-        // seven steps swap the roles of xa and xb once more: swap them back so that the trip starts as before
-        const f32x16 t = xa; xa = xb; xb = t;
-      }
-    } else {
-      for (; i < i1; i += NST) {
-        step_b<1, false>(xb, xa, ring, st, ln, frag, acc, cp); block_barrier<2 * G::NDMA>();
-        step_b<2, false>(xa, xb, ring, st, ln, frag, acc, cp); block_barrier<2 * G::NDMA>();
-        step_b<3, false>(xb, xa, ring, st, ln, frag, acc, cp); block_barrier<2 * G::NDMA>();
-        step_b<4, false>(xa, xb, ring, st, ln, frag, acc, cp); block_barrier<2 * G::NDMA>();
-        step_b<5, false>(xb, xa, ring, st, ln, frag, acc, cp); block_barrier<2 * G::NDMA>();
-        step_b<6, false>(xa, xb, ring, st, ln, frag, acc, cp); block_barrier<2 * G::NDMA>();
-        step_b<0, false>(xb, xa, ring, st, ln, frag, acc, cp); block_barrier<2 * G::NDMA>();
+      for (; i + NST + G::AHEAD < nfull; i += NST) {
+        for_each_slot<0>([&](auto x) __attribute__((always_inline)) {
+          constexpr int X = decltype(x)::value, K = wrap(kStart + X);
+          f32x16& cur = X % 2 == 0 ? xa : xb;
+          f32x16& next = X % 2 == 0 ? xb : xa;
+          if constexpr (role == 0) step_a<K, true, false>(cur, next, ring, l2ref(st), ln, frag, acc, c, cp, 0);
+          else step_b<K, true, false>(cur, next, ring, st, ln, frag, acc, cp);
+          block_barrier<2 * G::NDMA>();
+        }, std::make_integer_sequence<int, NST>{});
+        // seven steps leave the state in xb: swap so that the trip starts as before
         const f32x16 t = xa; xa = xb; xb = t;
       }
     }
-    // ---- drain: B finishes block i1 - 1 (its dP is in xb, its P in the buffer A wrote last)
+    // ---- the last complete blocks
+    while (i < nfull) {
+      const int before = i;
+      for_each_slot<0>([&](auto x) __attribute__((always_inline)) {
+        constexpr int X = decltype(x)::value;
+        if (i < nfull) careful(std::integral_constant<int, wrap(kStart + X)>{}, whole, std::false_type{}, X % 2 == 0 ? xa : xb, X % 2 == 0 ? xb : xa);
+      }, std::make_integer_sequence<int, NST>{});
+      if ((i - before) & 1) xa = xb;
+    }
+    // ---- drain: B finishes block nfull - 1 (its dP is in xa, its P in the buffer A wrote last)
     if constexpr (role == 1) {
-      const int so = stage_of(i1 - 1) * G::BLOCK;
+      const int so = stage_of(nfull - 1) * G::BLOCK;
       f32x16 ds;
 #pragma unroll
       for (int g = 0; g < 4; g++) {
         const f32x4 p4 = lds_f32x4(ln.pbuf, 1024 * g);
 #pragma unroll
-        for (int e4 = 0; e4 < 4; e4++) ds[4 * g + e4] = p4[e4] * xb[4 * g + e4];
+        for (int e4 = 0; e4 < 4; e4++) ds[4 * g + e4] = p4[e4] * xa[4 * g + e4];
       }
 #pragma unroll
       for (int tt = 0; tt < 2; tt++) {
