@@ -18,6 +18,8 @@
 #include "helix_common.hpp"
 #include "kernels.hpp"
 
+#include <type_traits>
+
 namespace helix {
 
 constexpr int kPreprocessPasses = 4;   // rows in flight per lane group
@@ -96,7 +98,7 @@ hipError_t launch_bwd_preprocess(const void* o, const void* dO, const float* lse
 //     slots 8..15   S^T(j+1)  = K(j+1) Q^T  | sum += P^T(j) o dP^T(j)
 // with the tile copies asynchronous and four tiles ahead.  Against an unpipelined sweep of 256-row tiles through staging
 // registers: 2 heads x 32k tokens 71 -> 32 us, 5 x 32k 72 -> 33, 16 x 16k at head dimension 64 56 -> 28, 4 x 16 x 2k
-// (1024 workgroups; the time of the two products at full rate is 70) 107 -> 95.
+// (the time of the two products at full rate is 70) 107 -> 95, and about 82 with whole tiles (below).
 template <int D>
 struct DeltaHead {
   static constexpr int NST = 5, AHEAD = NST - 1;
@@ -104,13 +106,17 @@ struct DeltaHead {
   static constexpr int LDS = NST * STAGE;
 };
 
-template <int D, bool CAUSAL>
+// KG = 2: 128 rows per workgroup, key halves in two groups of waves, as above.  KG = 1, for the grids that fill the chip with
+// 256-row tiles (split_rows): every wave takes both halves of a tile for 32 rows of its own, one after the other, so an operand
+// copied to LDS serves twice the rows; the halves keep sums of their own, and delta has the same bits.  Whole backward of 4 x 16
+// heads x 2k tokens (512 tiles of 256 rows) with KG = 2 -> 1: 350.5 -> 336.7 us; 2 x 40 x 8000 forward + backward unchanged.
+template <int D, bool CAUSAL, int KG>
 __global__ void __launch_bounds__(512, 1)
 bwd_delta_head_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
                       const __bf16* __restrict__ dO, const float* __restrict__ lse, float* __restrict__ neg_delta_out,
                       float* __restrict__ lse2_out, BwdMaps maps, int BH, int H, int S, int T, float scale) {
   using G = DeltaHead<D>;
-  constexpr int BM = 128, BN = 64, KS = D / 16, R = 4;   // R: operands in flight
+  constexpr int BM = 256 / KG, BN = 64, KS = D / 16, R = 4;   // R: operands in flight
   constexpr int TILE = G::TILE, HALF = 32 * D * 2, STAGE = G::STAGE, NST = G::NST, AHEAD = G::AHEAD;
   extern __shared__ __align__(16) char smem[];   // tile j (K, V) in stage j % NST
 
@@ -118,7 +124,7 @@ bwd_delta_head_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k
   if (!tc.valid) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int rg = w & 3, kg = w >> 2;
+  const int rg = KG == 2 ? w & 3 : w, kg = KG == 2 ? w >> 2 : 0;
   const int half = lane >> 5, n = lane & 31;
   const int q0 = tc.tile * BM;
   const int wave_qmin = q0 + 32 * rg, my_q = wave_qmin + n;
@@ -143,7 +149,7 @@ bwd_delta_head_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k
     for (int ks = 0; ks < KS; ks++) { pin(qf[ks]); pin(gf[ks]); }
     pin(lse2);
   }
-  float dsum[2] = {0.f, 0.f};   // this lane's share of sum_j p_ij dp_ij
+  float dsum[3 - KG][2] = {};   // this lane's share of sum_j p_ij dp_ij, by key half
 
   const int q_end = (q0 + BM < S ? q0 + BM : S);
   const int n_tiles = CAUSAL ? (q_end + BN - 1) / BN : (S + BN - 1) / BN;
@@ -151,7 +157,7 @@ bwd_delta_head_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k
   const int k_end = CAUSAL ? (wave_qmin + 32 < S ? wave_qmin + 32 : S) : S;
   const int k_all = CAUSAL ? wave_qmin + 1 : S;
   const int n_w = wave_qmin < S ? (k_end - 32 * kg + BN - 1) / BN : 0;
-  const int n_full = (k_all + 32 - 32 * kg) / BN;
+  const int n_full = KG == 2 ? (k_all + 32 - 32 * kg) / BN : k_all / BN;
 
   const TileLoader<D, BN, 8> kload(lane, w, maps.k.row), vload(lane, w, maps.v.row);
   constexpr int NDMA = decltype(kload)::N + decltype(vload)::N;
@@ -192,9 +198,13 @@ bwd_delta_head_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k
   }
 
   // Block j: on entry s_cur = S^T(j) and ring = the first V operands of tile j; on exit the same for j + 1.
-  auto step = [&](f32x16& s_cur, f32x16& s_next) __attribute__((always_inline)) {
-    const bool whole = j + AHEAD < n_tiles && (j + AHEAD + 1) * BN <= S;
-    if (!whole) copy_ahead();
+  // KG = 1: the first half of tile j ahead of the second, or the second half ahead of tile j + 1.
+  auto step = [&](auto second, f32x16& s_cur, f32x16& s_next) __attribute__((always_inline)) {
+    constexpr int H2 = decltype(second)::value;
+    constexpr bool MOVES = KG == 2 || H2 == 1, COPIES = H2 == 0;
+    constexpr int CUR = H2 * HALF, NEXT = MOVES ? 0 : HALF;
+    const bool whole = COPIES && j + AHEAD < n_tiles && (j + AHEAD + 1) * BN <= S;
+    if (COPIES && !whole) copy_ahead();
     const __bf16* kt = kload.tile_ptr(kh, (j + AHEAD) * BN);
     const __bf16* vt = vload.tile_ptr(vh, (j + AHEAD) * BN);
     const uint32_t dst = base + plus(AHEAD) * STAGE;
@@ -208,54 +218,80 @@ bwd_delta_head_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k
         kload.issue_whole(kt, dst);
         vload.issue_whole(vt, dst + TILE);
       }
-      if (s == KS - R) {   // the last read of this tile is out
+      if (MOVES && s == KS - R) {   // the last read of this tile is out
 #pragma unroll
         for (int ks = 0; ks < KS; ks++) ab[ks] += stage_step;
       }
       const int u = s + R;
-      if (u < KS) ring[s % R] = lds_b128(ab[u], TILE);
-      else if (u < 2 * KS) ring[s % R] = lds_b128(ab[u - KS], 0);
-      else ring[s % R] = lds_b128(ab[u - 2 * KS], TILE);
+      if (u < KS) ring[s % R] = lds_b128(ab[u], TILE + CUR);
+      else if (u < 2 * KS) ring[s % R] = lds_b128(ab[u - KS], NEXT);
+      else ring[s % R] = lds_b128(ab[u - 2 * KS], TILE + NEXT);
 #pragma unroll
       for (int e = 0; e < 16; e++) {
         if (e * KS / 16 == s) s_cur[e] = __builtin_amdgcn_exp2f(fmaf(s_cur[e], c, -lse2));
-        if (KS + e * KS / 16 == s) dsum[e & 1] = fmaf(s_cur[e], dp[e], dsum[e & 1]);
+        if (KS + e * KS / 16 == s) dsum[H2][e & 1] = fmaf(s_cur[e], dp[e], dsum[H2][e & 1]);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    finish_tile();
-    j++;
+    if constexpr (MOVES) {
+      finish_tile();
+      j++;
+    }
   };
-  while (j + 1 < n_w - 1) {
-    step(sa, sb);
-    step(sb, sa);
-  }
-  if (j < n_w - 1) {
-    step(sa, sb);
-    sa = sb;
+  const std::integral_constant<int, 0> first_half{};
+  if constexpr (KG == 2) {
+    while (j + 1 < n_w - 1) {
+      step(first_half, sa, sb);
+      step(first_half, sb, sa);
+    }
+    if (j < n_w - 1) {
+      step(first_half, sa, sb);
+      sa = sb;
+    }
+  } else {
+    while (j < n_w - 1) {
+      step(first_half, sa, sb);
+      step(std::integral_constant<int, 1>{}, sb, sa);
+    }
   }
   for (; j < n_tiles; j++) {
     copy_ahead();
     if (j == n_w - 1) {
       const bool masked = j >= n_full;
-      f32x16 dp = zero;
 #pragma unroll
-      for (int ks = 0; ks < KS; ks++) dp = mfma32(lds_b128(ab[ks], TILE), gf[ks], dp);
+      for (int h = 0; h < 3 - KG; h++) {
+        if (h == 1) {
+          sa = zero;
 #pragma unroll
-      for (int e = 0; e < 16; e++) {
-        float p = __builtin_amdgcn_exp2f(fmaf(sa[e], c, -lse2));
-        if (masked) {
-          const int key = j * BN + 32 * kg + 8 * (e >> 2) + 4 * half + (e & 3);
-          p = (CAUSAL ? key <= my_q : key < S) ? p : 0.f;
+          for (int ks = 0; ks < KS; ks++) sa = mfma32(lds_b128(ab[ks], HALF), qf[ks], sa);
         }
-        dsum[e & 1] = fmaf(p, dp[e], dsum[e & 1]);
+        f32x16 dp = zero;
+#pragma unroll
+        for (int ks = 0; ks < KS; ks++) dp = mfma32(lds_b128(ab[ks], TILE + h * HALF), gf[ks], dp);
+#pragma unroll
+        for (int e = 0; e < 16; e++) {
+          float p = __builtin_amdgcn_exp2f(fmaf(sa[e], c, -lse2));
+          if (masked) {
+            const int key = j * BN + 32 * (kg + h) + 8 * (e >> 2) + 4 * half + (e & 3);
+            p = (CAUSAL ? key <= my_q : key < S) ? p : 0.f;
+          }
+          dsum[h][e & 1] = fmaf(p, dp[e], dsum[h][e & 1]);
+        }
       }
     }
     finish_tile();
   }
 
+  const float mine = half_sum(dsum[0][0] + dsum[0][1]);
+  if constexpr (KG == 1) {
+    const float other = half_sum(dsum[1][0] + dsum[1][1]);
+    if (half == 0 && my_q < S) {
+      neg_delta_out[(size_t)tc.bh * S + my_q] = -(mine + other);
+      if (lse2_out) lse2_out[(size_t)tc.bh * S + my_q] = lse2;
+    }
+    return;
+  }
   // the two key halves of a row meet in LDS (free by now)
-  const float mine = half_sum(dsum[0] + dsum[1]);
   float* sums = reinterpret_cast<float*>(smem);
   if (kg == 1 && half == 0) sums[32 * rg + n] = mine;
   __syncthreads();
@@ -269,12 +305,14 @@ template <int D, bool CAUSAL>
 static hipError_t launch_delta_head_t(const void* q, const void* k, const void* v, const void* dO, const float* lse,
                                       float* delta_out, float* lse2_out, const BwdMaps& maps, int B, int H, int S, int rows,
                                       float scale, hipStream_t stream) {
-  const int T = (rows + 127) / 128, BH = B * H;   // query tiles 0..T-1 of every head
+  const int BH = B * H;
+  const bool split = split_rows(BH, rows, CAUSAL);
+  const int T = split ? (rows + 127) / 128 : (rows + 255) / 256;   // query tiles 0..T-1 of every head
   const unsigned grid = (unsigned)grid_blocks(BH, T);
   const size_t lds = DeltaHead<D>::LDS;
-  auto kern = bwd_delta_head_kernel<D, CAUSAL>;
-  static unsigned long long configured = 0;   // one static per template instantiation
-  hipError_t e = allow_dynamic_lds(kern, lds, configured);
+  auto kern = split ? bwd_delta_head_kernel<D, CAUSAL, 2> : bwd_delta_head_kernel<D, CAUSAL, 1>;
+  static unsigned long long configured[2] = {};   // per template instantiation and kernel
+  hipError_t e = allow_dynamic_lds(kern, lds, configured[split]);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(512), lds, stream, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v,
                      (const __bf16*)dO, lse, delta_out, lse2_out, maps, BH, H, S, T, scale);
