@@ -26,6 +26,8 @@
 #include "helix_common.hpp"
 #include "kernels.hpp"
 
+#include <cfloat>
+
 namespace helix {
 
 // The running reference maximum may lag the true row maximum by up to 2^kSlack before the
@@ -435,6 +437,9 @@ fwd_split_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, con
 #pragma unroll
     for (int e = 0; e < 16; e++) oacc[db][e] = 0.f;
   SoftmaxState st;
+  // A row need not see a key of the second half, nor one with a score above -inf: its reference starts at the lowest finite value
+  // instead of -inf, where a score of -inf weighs 0 and NaN stays NaN.  Key 0 is in the first half, which starts as in fwd_kernel.
+  if (kg == 1) st.mref_c = -FLT_MAX;
 
   // Key blocks (half kg of tiles 0, 1, ...) this wave works on and how many of them need no mask (n_full >= n_w - 1).
   const int k_end = CAUSAL ? (wave_qmin + 32 < S ? wave_qmin + 32 : S) : S;        // keys [0, k_end) are visible to some row,
@@ -530,7 +535,8 @@ fwd_split_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, con
   }
 
   // merge: O = a0 O0 + a1 O1 with a = 2^(own reference - common reference); wave kg finishes half of the head
-  // dimension and hands the other half over.  A half without any visible key has reference -inf and counts nothing.
+  // dimension and hands the other half over.  The second half counts for the rows that see its first key, 32; which rows these
+  // are is a matter of the indexes and not of the reference, which a NaN score does not move.
   constexpr int HB = DB / 2;
   const float l_own = half_sum(st.lsum[0] + st.lsum[1]);
   float* stats = reinterpret_cast<float*>(smem + G::ROW_STATS);
@@ -545,7 +551,8 @@ fwd_split_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, con
   if (my_q < S) {
     const float m_other = stats[((w ^ 4) * 64 + lane) * 2], l_other = stats[((w ^ 4) * 64 + lane) * 2 + 1];
     const float m = fmaxf(st.mref_c, m_other);
-    const bool own = st.mref_c != -INFINITY, other = m_other != -INFINITY;
+    const bool second = (CAUSAL ? my_q : S - 1) >= 32;
+    const bool own = kg == 0 || second, other = kg == 1 || second;
     const float a_own = own ? __builtin_amdgcn_exp2f(st.mref_c - m) : 0.f;
     const float a_other = other ? __builtin_amdgcn_exp2f(m_other - m) : 0.f;
     const float ltot = (own ? l_own * a_own : 0.f) + (other ? l_other * a_other : 0.f);
