@@ -261,6 +261,7 @@ bwd_delta_head_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k
 #pragma unroll
       for (int h = 0; h < 3 - KG; h++) {
         if (h == 1) {
+          if (CAUSAL && j * BN + 32 > wave_qmin + 31) continue;   // above the diagonal: 0 * dP would be NaN for an infinite V there
           sa = zero;
 #pragma unroll
           for (int ks = 0; ks < KS; ks++) sa = mfma32(lds_b128(ab[ks], HALF), qf[ks], sa);
