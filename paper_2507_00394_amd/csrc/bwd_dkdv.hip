@@ -175,7 +175,7 @@ __device__ __forceinline__ void dkdv_step(const f32x16& sp_cur, const f32x16& dp
 
 }  // namespace
 
-// GROUPS = 2 (see split_queries): two groups of four waves own the same 128 keys and sweep one half of the query
+// GROUPS = 2 (see two_query_groups): two groups of four waves own the same 128 keys and sweep one half of the query
 // tiles each, with stages of their own; at the end they swap partial sums through LDS and each stores one result.
 template <int D, bool CAUSAL, int GROUPS>
 __device__ __forceinline__ void dkdv_keys(int block, const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
@@ -441,25 +441,12 @@ static hipError_t launch_dkdv_t(const void* q, const void* k, const void* v, con
   return hipGetLastError();
 }
 
-// Whether two groups of waves share a workgroup's query tiles.  A workgroup of one group leaves a SIMD with one wave, which
-// is bound by instruction issue, unless a second workgroup finds room beside it; with two groups the sweep is
-// half as long, the swap of partial sums costs about 1 us.  Measured, one -> two groups, us:
-//   causal (the first key tiles are the longest, so what counts is the length of one sweep): 12 heads x 1500 (144 key tiles)
-//     30.8 -> 27.5; 2 x 16k (256) 239 -> 203; 3 x 16k (384) 277 -> 235; 4 x 16k (512) 310 -> 266; 32 x 1800 (480)
-//     42.0 -> 42.1; beyond two workgroups per compute unit 40 x 2048 (640) 53 -> 64.
-//   no mask: 12 x 1500 (144) 28.9 -> 26.6; 2 x 16k (256) 284 -> 260; short sweeps gain nothing, 27 x 777 (189) 21.2 -> 21.6;
-//     beyond one workgroup per compute unit 24 x 1500 (288) 45 -> 55, 3 x 16k (384) 417 -> 436.
-static bool split_queries(int BH, int S, bool causal) {
-  const long long tiles = (long long)BH * ((S + 127) / 128);
-  return causal ? tiles <= 512 : tiles <= 256 && S >= 1024;
-}
-
 hipError_t launch_bwd_dkdv(const void* q, const void* k, const void* v, const void* dO,
                            const float* lse2, const float* neg_delta, void* dk, void* dv, const BwdMaps& maps,
                            int B, int H, int S, int D, float scale, bool causal, hipStream_t stream) {
   // Head dimension 128 has its own kernel with two waves per SIMD; this one serves head dimension 64.
   if (D == 128) return launch_bwd_dkdv_pair(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B, H, S, scale, causal, stream);
-  if (split_queries(B * H, S, causal))
+  if (two_query_groups(B * H, S, causal))
     return causal ? launch_dkdv_t<64, true, 2>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B, H, S, scale, stream)
                   : launch_dkdv_t<64, false, 2>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B, H, S, scale, stream);
   return causal ? launch_dkdv_t<64, true, 1>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B, H, S, scale, stream)
@@ -485,20 +472,20 @@ static hipError_t launch_dkdv_dq_t(const void* q, const void* k, const void* v, 
 
 // Both passes need the row statistics and nothing of each other, and a workgroup of either fills a compute unit (LDS at head
 // dimension 128, registers at 64), so one launch with the key tiles first fills the compute units that a small grid or its
-// last, uneven round leaves idle, and pays for one start instead of two.  Backward, two launches -> one, us, at head dimension
-// 128 / 64, causal: 2 heads x 512 58.8 -> 43.2 / 34.2 -> 23.4; 12 x 1500 101 -> 72 / 64 -> 45; 16 x 2048 133 -> 105 /
-// 80 -> 63; 5 x 8192 383 -> 336; 64 x 2048 (1024 key tiles) 381 -> 375; with more rounds there is little left to
-// fill and the change from one pass to the other costs L2 hits: 5 x 32k (1280) 4190 -> 4276, 16 x 16k (2048) 3164 -> 3159,
-// 80 x 8000 (5040) 4139 -> 4165.
-// No mask: 2 x 512 43.8 -> 27.4 / 26.7 -> 15.9; 27 x 777 68 -> 63 / 43 -> 39; 16 x 8192 1558 -> 1542.
-// At head dimension 64 the launch needs workgroups of eight waves on either side: the two-group dK/dV and the split dQ.
+// last, uneven round leaves idle, and pays for one start instead of two.  The work of a workgroup is that of the separate passes, bit for bit.
+// Head dimension 128, two launches -> one, backward, us, key tiles in brackets: causal 2 heads x 512 [8] 51 -> 34; 12 x 1500 [144] 94 -> 65;
+// 16 x 2048 [256] 124 -> 99; 5 x 8192 383 -> 336; 16 x 8192 [1024] 848 -> 841; 36 x 4096 [1152] 568 -> 548; 80 x 2048 [1280] 411 -> 405;
+// with more rounds there is little left to fill and the change from one pass to the other costs L2 hits: 5 x 32k [1280] 4190 -> 4276,
+// 16 x 16k [2048] 3164 -> 3159, 80 x 8000 [5040] 4139 -> 4165.  No mask: 2 x 512 39 -> 23; 16 x 7168 [896] 1259 -> 1288; 16 x 8192 [1024]
+// 1548 -> 1536; 36 x 4096 [1152] 995 -> 943; 5 x 30000 [1175] 6871 -> 6998.  The line at 1024 gives away up to 4 % between 1024 and 1280.
+// Head dimension 64: two_query_groups in dispatch.hpp.
 hipError_t launch_bwd_dkdv_dq(const void* q, const void* k, const void* v, const void* dO, const float* lse2, const float* neg_delta,
                               void* dq, void* dk, void* dv, const BwdMaps& maps, int B, int H, int S, int D, float scale, bool causal,
                               hipStream_t stream) {
   const long long key_tiles = (long long)B * H * ((S + 127) / 128);
   if (D == 128 && key_tiles <= 1024)
     return launch_bwd_dkdv_dq_pair(q, k, v, dO, lse2, neg_delta, dq, dk, dv, maps, B, H, S, scale, causal, stream);
-  if (D == 64 && split_rows(B * H, S, causal))
+  if (D == 64 && two_query_groups(B * H, S, causal))
     return causal ? launch_dkdv_dq_t<64, true>(q, k, v, dO, lse2, neg_delta, dq, dk, dv, maps, B, H, S, scale, stream)
                   : launch_dkdv_dq_t<64, false>(q, k, v, dO, lse2, neg_delta, dq, dk, dv, maps, B, H, S, scale, stream);
   hipError_t e = launch_bwd_dkdv(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B, H, S, D, scale, causal, stream);

@@ -583,7 +583,7 @@ static hipError_t launch_dkdv_dq_pair_t(const void* q, const void* k, const void
                                         const float* neg_delta, void* dq, void* dk, void* dv, const BwdMaps& maps, int B, int H, int S,
                                         float scale, hipStream_t stream) {
   const int BH = B * H;
-  const bool split = split_rows(BH, S, CAUSAL);
+  const bool split = split_dq(PG::D, BH, S, CAUSAL);
   const int TK = (S + PG::BN - 1) / PG::BN, TQ = dq_tiles(S, split);
   const long long key_blocks = grid_blocks(BH, TK);
   const size_t lds = std::max(PG::LDS, split ? DqSplit<128>::LDS : kDqWholeLds<128>);

@@ -17,7 +17,7 @@ static hipError_t launch_dq_pipe_t(const void* q, const void* k, const void* v, 
                                    const float* lse2, const float* neg_delta, void* dq, const BwdMaps& maps,
                                    int B, int H, int S, float scale, hipStream_t stream) {
   const int BH = B * H;
-  const bool split = split_rows(BH, S, CAUSAL);
+  const bool split = split_dq(D, BH, S, CAUSAL);
   const int T = dq_tiles(S, split);
   const unsigned grid = (unsigned)grid_blocks(BH, T);
   const size_t lds = split ? DqSplit<D>::LDS : kDqWholeLds<D>;

@@ -371,7 +371,7 @@ fwd_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __b
   }
 }
 
-// The forward for grids that 256-row tiles cannot fill (split_rows in helix_common.hpp says which): a workgroup owns
+// The forward for grids that 256-row tiles cannot fill (split_rows in dispatch.hpp says which): a workgroup owns
 // 128 query rows and its two groups of four waves share the keys.  Wave (rg, kg) works on 32 query rows and on
 // half kg of every 64-key tile, through the same half steps as above, one per tile; at the end the two partial
 // results of a row are merged in LDS.  Twice the workgroups, each of half the length, at two waves per SIMD;

@@ -3,6 +3,7 @@
 // transposing LDS read and the cross-half lane exchange.
 #pragma once
 #include <hip/hip_runtime.h>
+#include "dispatch.hpp"
 #include "kernels.hpp"
 #include <stdint.h>
 
@@ -278,12 +279,6 @@ __device__ __forceinline__ bf16x8 pack_half(const f32x16& acc, int t) {
 // 132 -> 101; 5 x 32k 1472 -> 1249 / 1997 -> 1733; 24 x 4k 131 -> 108 / 174 -> 147; 32 x 32k 7552 -> 7441 /
 // 10272 -> 10128.  Without a mask all tiles are equal and heads stay one after the other.
 struct TileCoord { int bh; int tile; bool valid; };
-__host__ __device__ inline int head_parts(int BH) { return (BH & 1) ? 8 : (BH & 2) ? 4 : (BH & 4) ? 2 : 1; }
-// Number of workgroups to launch for BH slices of T tiles.
-__host__ __device__ inline long long grid_blocks(int BH, int T) {
-  const int P = head_parts(BH);
-  return (long long)BH * P * ((T + P - 1) / P);
-}
 template <bool CAUSAL>
 __device__ __forceinline__ TileCoord map_block(int n, int BH, int T, bool heavy_is_high) {
   TileCoord c;
@@ -304,23 +299,6 @@ __device__ __forceinline__ TileCoord map_block(int n, int BH, int T, bool heavy_
   c.tile = heavy_is_high ? (T - 1 - k) : k;
   c.valid = c.bh < BH && k < T;
   return c;
-}
-
-// Whether the forward and dQ passes take 128-row tiles with the keys split over two groups of waves instead
-// of 256-row tiles.  A split workgroup needs 0.55-0.65 of the time of a whole one for the same keys, and there
-// are twice as many: it pays where whole tiles leave compute units idle.  One workgroup per compute unit (256) is
-// a round.
-//   causal: tiles differ in length, so with up to one round the longest one sets the time.  Measured at head
-//     dimension 128, whole -> split, forward / dQ, us: 12 heads x 1500 (72 tiles) 39.7 -> 25.9 / 49 -> 31.5;
-//     2 x 32k (256) 710 -> 531 / 904 -> 693; 64 x 1024 (256) 33.5 -> 30.5 / 42 -> 39.5; just beyond,
-//     40 x 2048 (320) 58 -> 61 / 75 -> 79; 16 x 8192 (512) 255 -> 282 / 339 -> 364.
-//   no mask: all tiles are equal, so whole rounds are compared.  32 x 1024 (128) 31.8 -> 23.4 / 39 -> 30; 12 x 8192
-//     (384: 2 rounds or 3) 412 -> 399 / 533 -> 522; 32 x 1500 (192: 1 or 2) 45.6 -> 54.5 / 58 -> 68.
-// Head dimension 64 behaves alike (the sweep covered 1 to 64 heads, 200 to 32k tokens, both dimensions).
-inline bool split_rows(int BH, int S, bool causal) {
-  const long long whole = (long long)BH * ((S + 255) / 256), split = (long long)BH * ((S + 127) / 128);
-  if (causal) return whole <= 256;
-  return ((split + 255) / 256) * 5 < ((whole + 255) / 256) * 9;
 }
 
 // Element offset of row 0 of slice bh = b * H + h.

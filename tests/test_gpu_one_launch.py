@@ -1,7 +1,7 @@
-"""The backward's dK/dV and dQ passes in one launch: head dimension 64 and 128, one short tile, ragged ends, the split and
-the whole query tiles, and the grids on both sides of the line (1024 key tiles; 256 query tiles at head dimension
-64).  Causal results and all of head dimension 128 equal those of the passes launched one by one, bit for bit, for the work
-of a workgroup is the same; without a mask head dimension 64 is held against the oracle."""
+"""The backward's dK/dV and dQ passes in one launch or in two: one short tile, ragged ends, the split and the whole query tiles, and
+the grids on both sides of the lines (1024 key tiles at head dimension 128; at 64 256 and 512 key tiles causal, 256, 512 and 640
+without a mask).  Either way the results equal those of the passes launched one by one, bit for bit, for the work of a workgroup is the
+same; and, as beyond the lines both are the same kernels, some heads are held against the oracle."""
 import pytest
 import torch
 
@@ -15,19 +15,20 @@ pytestmark = pytest.mark.gpu
     (1, 1, 64, True), (1, 1, 128, False), (3, 129, 64, True), (3, 129, 64, False), (3, 385, 128, True), (2, 640, 128, False),
     (11, 1500, 128, True), (64, 1030, 128, True), (27, 777, 64, False), (128, 511, 64, True), (129, 511, 64, True),
     (512, 129, 128, True), (513, 129, 128, True), (256, 100, 64, False), (257, 100, 64, False),
+    # head dimension 64: within each line and beyond it, far beyond the last
+    (56, 1030, 64, True), (64, 1030, 64, True), (80, 640, 64, False), (24, 1500, 64, False), (56, 1280, 64, False), (72, 1100, 64, False),
+    (300, 300, 64, False), (160, 1024, 64, False), (1024, 100, 64, False),
 ])
 def test_equals_separate_passes(H, S, D, causal):
     from tests import gpu_util as G
 
     cfg, bits = I.random_case_bits(7300 + S + H, 1, H, S, D)
     one = G.run_fwd_bwd(bits, cfg.scale, causal)
-    if causal or D == 128:
-        two = G.run_fwd_bwd(bits, cfg.scale, causal, fused_bwd=False)
-        for n in ("dq", "dk", "dv"):
-            assert bool(one[n].isfinite().all()), n
-            assert torch.equal(one[n], two[n]), n
-        return
-    heads = [0, H // 2, H - 1]
+    two = G.run_fwd_bwd(bits, cfg.scale, causal, fused_bwd=False)
+    for n in ("dq", "dk", "dv"):
+        assert bool(one[n].isfinite().all()), n
+        assert torch.equal(one[n], two[n]), n
+    heads = sorted({0, H // 2, H - 1})
     x = {t: I.bf16_bits_to_float(bits[t][:, heads]) for t in bits}
     ref = A.attn_bwd_ref(x["q"], x["k"], x["v"], x["dO"], cfg.scale, causal)
     for n in ("dq", "dk", "dv"):
