@@ -371,7 +371,7 @@ fwd_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __b
   }
 }
 
-// The forward for grids that 256-row tiles cannot fill (split_rows in dispatch.hpp says which): a workgroup owns
+// The forward for grids that 256-row tiles cannot fill (split_forward in dispatch.hpp says which): a workgroup owns
 // 128 query rows and its two groups of four waves share the keys.  Wave (rg, kg) works on 32 query rows and on
 // half kg of every 64-key tile, through the same half steps as above, one per tile; at the end the two partial
 // results of a row are merged in LDS.  Twice the workgroups, each of half the length, at two waves per SIMD;
@@ -575,11 +575,14 @@ template <int D, bool CAUSAL>
 static hipError_t launch_fwd_t(const void* q, const void* k, const void* v, void* o, float* lse,
                                const FwdMaps& maps, int B, int H, int S, float scale, hipStream_t stream) {
   const int BH = B * H;
-  const bool split = split_rows(BH, S, CAUSAL);
+  const bool split = split_forward(D, BH, S, CAUSAL);
   const int BM = split ? 128 : 256, T = (S + BM - 1) / BM;
   const unsigned grid = (unsigned)grid_blocks(BH, T);
   const size_t lds = split ? FwdSplit<D>::LDS : 8 * 64 * D * 2;
-  auto kern = split ? fwd_split_kernel<D, CAUSAL> : fwd_kernel<D, CAUSAL>;
+  auto kern = fwd_split_kernel<D, CAUSAL>;
+  if constexpr (!kForwardSplitsAlways(D)) {
+    if (!split) kern = fwd_kernel<D, CAUSAL>;
+  }
   static unsigned long long configured[2] = {};   // per template instantiation and kernel
   hipError_t e = allow_dynamic_lds(kern, lds, configured[split]);
   if (e != hipSuccess) return e;

@@ -12,7 +12,8 @@ PROGRAM = """
 int main() {
   int BH, S, causal;
   while (scanf("%d %d %d", &BH, &S, &causal) == 3)
-    printf("%d %d %d\\n", helix::two_query_groups(BH, S, causal), helix::split_dq(64, BH, S, causal), helix::split_dq(128, BH, S, causal));
+    printf("%d %d %d %d %d\\n", helix::two_query_groups(BH, S, causal), helix::split_dq(64, BH, S, causal), helix::split_dq(128, BH, S, causal),
+           helix::split_forward(64, BH, S, causal), helix::split_forward(128, BH, S, causal));
 }
 """
 
@@ -43,6 +44,27 @@ ONE_LAUNCH_FULL = """2 512 26.7 16.2; 27 777 40.5 38.9; 12 1500 50.2 48.1; 2 163
 160 1024 173.1 187.0; 40 4096 570.3 580.6; 27 8192 1498.2 1535.9; 80 6528 2756.0 2846.5; 512 300 101.8 120.6; 256 600 121.2 139.4; 1024 100 54.7 62.9"""
 
 
+# head dimension 128, us: 256-row tiles, 128-row tiles with the keys split; the forward, and the backward in separate passes with dQ either way
+FORWARD_CAUSAL = """1 32768 661.9 413.2; 2 32768 708.3 526.6; 4 16384 356.7 265.8; 7 9000 203.2 164.9; 16 2048 50.0 33.0; 12 1500 39.0 24.9
+32 1500 40.1 29.0; 32 2048 53.7 43.3; 36 1700 44.4 42.6; 64 1024 32.4 29.7; 85 640 62.5 49.1; 500 200 59.4 40.8; 512 777 186.1 179.5
+1024 100 34.9 33.8; 36 3500 124.8 132.6; 64 8192 986.5 1091.9; 120 900 47.5 54.6; 128 512 21.9 24.0; 128 300 15.1 18.3; 232 210 16.2 18.6
+256 256 19.4 23.4; 256 512 44.7 53.2; 512 1024 241.1 252.1; 1024 512 176.3 226.5; 16 32768 3699.5 4095.1; 78 52 10.4 11.8
+252 761 94.5 85.6; 169 282 93.6 67.5; 21 6398 284.4 265.2; 11 16034 731.3 820.3; 49 10018 1320.7 1461.5; 194 2314 364.6 394.8"""
+FORWARD_FULL = """1 32768 665.8 512.7; 4 8192 174.7 133.8; 7 9000 445.5 285.6; 12 1500 40.4 26.3; 16 2048 50.7 38.0; 32 1024 30.3 22.3; 36 1700 94.2 64.0
+85 640 71.8 51.3; 500 200 60.5 45.4; 2 32768 917.0 1019.5; 4 16384 464.0 514.5; 21 1216 38.5 45.9; 32 1500 43.9 53.8; 64 1024 38.7 42.6
+120 900 65.8 74.5; 120 3637 775.3 847.7; 128 300 16.9 21.4; 256 512 47.2 54.6; 512 777 228.8 245.1; 512 1024 300.5 342.1; 1024 512 200.7 239.2
+1241 19 150.4 173.5; 624 17 12.5 14.5; 64 8192 1856.9 2076.7
+275 987 340.6 229.3; 55 629 49.0 35.7; 87 4995 1316.8 1261.0; 36 16568 4585.3 5195.8"""
+DQ_CAUSAL = """2 512 57.5 50.9; 7 9000 584.9 535.6; 12 1500 110.9 93.9; 16 4096 291.4 265.3; 32 1500 126.4 113.8; 85 640 197.6 180.6; 500 200 180.7 158.9
+120 900 188.9 197.3; 128 512 86.7 88.8; 256 256 78.0 82.7; 256 1500 793.9 855.0; 512 256 142.8 152.3; 16 32768 12166.3 12571.9"""
+DQ_FULL = """2 512 46.6 39.4; 4 8192 453.0 412.4; 7 9000 1086.7 880.8; 32 1024 80.9 72.3; 36 1700 238.0 200.4; 85 640 174.5 147.9; 500 200 150.0 131.9
+32 1500 151.9 162.0; 64 1024 132.5 139.8; 120 900 228.8 238.2; 256 2048 1688.6 1762.1; 512 256 129.7 137.7; 2 32768 3024.7 3115.3"""
+# dQ at head dimension 64 on grids that two_query_groups leaves to it
+DQ_64_CAUSAL = "16 32768 6567.6 6826.7; 60 900 68.5 69.9; 128 300 38.0 40.5; 200 200 36.7 38.8; 256 2048 730.1 766.5; 1024 512 363.6 403.3; 85 640 116.6 106.8"
+DQ_64_FULL = """85 777 119.6 97.6; 48 1900 179.9 175.0; 28 2304 174.6 142.0; 32 1500 85.1 93.3; 64 1024 71.8 75.9; 80 640 48.6 53.9; 512 1024 507.8 556.1
+2048 128 109.9 116.3; 22 4096 348.3 332.2; 250 300 92.1 79.3"""
+
+
 def _table(text):
     for entry in text.replace("\n", ";").split(";"):
         bh, s, a, b = entry.split()
@@ -67,5 +89,28 @@ def test_one_launch_takes_split_tiles(rules):
     """The common launch at head dimension 64 has split dQ workgroups only: wherever it is taken, the pass by itself splits too."""
     shapes = [(bh, s, c) for bh in (1, 2, 3, 5, 8, 27, 64, 100, 255, 256, 257, 640, 5000) for s in (1, 17, 64, 65, 128, 129, 500, 1023, 1024, 5000, 40000)
               for c in (True, False)]
-    for two, split64, _ in rules(shapes):
+    for two, split64, *_ in rules(shapes):
         assert split64 or not two
+
+
+@pytest.mark.parametrize("column,causal,text", [(4, True, FORWARD_CAUSAL), (4, False, FORWARD_FULL), (2, True, DQ_CAUSAL), (2, False, DQ_FULL),
+                                                (1, True, DQ_64_CAUSAL), (1, False, DQ_64_FULL)])
+def test_split_tiles(rules, column, causal, text):
+    table = list(_table(text))
+    picks = [r[column] for r in rules((bh, s, causal) for bh, s, _, _ in table)]
+    regret = _regret(picks, table)
+    assert 0 < sum(picks) < len(picks)
+    assert max(regret.values()) <= 1.11, regret          # the most that is given away: forward of 252 x 761, causal
+    assert sum(regret.values()) / len(regret) <= 1.01
+
+
+def test_forward_at_head_dimension_64_does_not_depend_on_the_other_heads(rules):
+    for s in (1, 20, 64, 65, 128, 129, 777, 4096, 131072):
+        for causal in (True, False):
+            assert len({r[3] for r in rules((bh, s, causal) for bh in (1, 2, 5, 8, 40, 300, 2048))}) == 1
+
+
+def test_far_ends_of_the_shape_limits(rules):
+    """Sixteen million tokens, a quarter of a billion heads: the arithmetic neither overflows nor loops."""
+    for r in rules([(1, 1 << 24, True), (1, 1 << 24, False), (3355443, 1, True), (3355443, 1, False), (8, 1 << 24, True)]):
+        assert set(r) <= {0, 1}
