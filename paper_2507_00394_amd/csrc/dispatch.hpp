@@ -65,20 +65,27 @@ inline bool split_forward(int D, int BH, int S, bool causal) { return kForwardSp
 // Head dimension 64: whether two groups of waves share the query tiles of a key tile in the dK/dV pass, and that pass its launch with
 // the dQ pass on split tiles (a launch of its own is what the stage calls make of it).  With one group a SIMD has one wave, which
 // is bound by instruction issue, unless a second workgroup finds room beside it; two groups halve the sweep, and the common launch fills
-// the compute units that a small grid or its last round leaves idle.  Where the chip is full both only cost: the swap of partial sums,
-// and one workgroup in the place of two.  The backward in separate passes (the faster way) -> in one launch, us; key tiles in brackets:
+// the compute units that a small grid or its last round leaves idle and saves a start.  Where the chip is full both only cost: the swap of
+// partial sums, and one workgroup in the place of two.  The times of both ways, fitted to the whole backward at 282 shapes (2 to 2048
+// heads, 20 to 32k tokens): the rule costs 0.4 % against the best of all variants, 6 % at worst.
+// Separate passes (the faster way) -> one launch, us, key tiles in brackets:
 //   causal: 2 heads x 512 [8] 33.7 -> 23.1; 12 x 1500 [144] 64 -> 44; 32 x 1024 [256] 51 -> 41; 32 x 1500 [384] 72.5 -> 70.5; 4 x 16k [512]
-//     486 -> 484 (533 with one group); 2 x 32k [512] 937 -> 931 (1033).  Short sweeps of more than 256 key tiles: 60 x 900 [480] 69 -> 73;
-//     128 x 512 [512] 51 -> 55; 256 x 256 [512] 43 -> 48.  Beyond 512: one -> two groups, dK/dV alone, 40 x 2048 [640] 53 -> 64.
-//   no mask, up to 256: 2 x 512 [8] 26.7 -> 16.2; 27 x 777 [189] 40.5 -> 39; 2 x 16k [256] 446 -> 443.  Up to 512 the separate passes do
-//     with one round: 40 x 1500 [480] 94 -> 102; 64 x 1024 [512] 72 -> 79.  Just beyond they start a second one: 24 x 3000 [576] 248 -> 214;
-//     10 x 8192 [640] 626 -> 563.  From there on 11 x 8192 [704] 634 -> 649; 12 x 8192 [768] 670 -> 671; 160 x 1024 [1280] 173 -> 187;
-//     512 x 300 [1536] 102 -> 120; 80 x 6528 [4080] 2756 -> 2841.
-// (Key tiles as launched: a head whose tiles the XCDs cannot share evenly counts for its fullest XCD.)
+//     486 -> 484 (533 with one group); 60 x 900 [480] 69 -> 73; 128 x 512 [512] 51 -> 55; 256 x 256 [512] 43 -> 48; 256 x 2048 [4096] 730 -> 811.
+//   no mask: 2 x 512 [8] 26.7 -> 16.2; 27 x 777 [189] 40.5 -> 39; 2 x 16k [256] 446 -> 443; 24 x 1500 [288] 80.5 -> 74; 40 x 1500 [480]
+//     94 -> 102; 64 x 1024 [512] 72 -> 79; 24 x 3000 [576] 248 -> 214; 10 x 8192 [640] 626 -> 563; 11 x 8192 [704] 634 -> 649; 190 x 400 [760]
+//     74 -> 81; 8 x 17920 [1120] 2244 -> 2128; 160 x 1024 [1280] 173 -> 187; 512 x 300 [1536] 102 -> 120; 80 x 6528 [4080] 2756 -> 2841.
 inline bool two_query_groups(int BH, int S, bool causal) {
-  const long long tiles = grid_blocks(BH, (S + 127) / 128);
-  if (tiles <= 256) return true;
-  return causal ? tiles <= 512 && S >= 1024 : tiles > 512 && tiles <= 640;
+  const Share k = share(BH, S, causal, 128, true), q = share(BH, S, causal, 128, false);
+  // one group: two workgroups beside one another on a compute unit, 1.6 a step; one alone takes 0.7 of that
+  const double rest = std::fmod(k.blocks, 64.);
+  double one = std::floor(k.blocks / 64) * (1.6 * k.longest + 6.) + (rest == 0. ? 0. : (rest <= 32. ? 0.7 : 1.) * 1.6 * k.longest + 6.);
+  if (causal) one = 1.6 * std::max(0.7 * k.longest, k.steps / 64) + 6. * std::ceil(k.blocks / 64);
+  const double separate = one + std::min(split_rows_time(BH, S, causal), whole_rows_time(BH, S, causal)) + 6.;   // a second launch
+  // together: key tiles, 0.85 a step, then query tiles, 0.55; no mask: rounded up to a whole query tile
+  const double query = 0.55 * q.longest + 4.5;
+  const double work = 0.85 * k.steps + 8. * k.blocks + 0.55 * q.steps + 4.5 * q.blocks;
+  const double together = causal ? std::max(0.85 * k.longest + 8., work / 32) : query * std::ceil(work / 32 / query);
+  return together < separate;
 }
 inline bool split_dq(int D, int BH, int S, bool causal) {
   return (D == 64 && two_query_groups(BH, S, causal)) || split_rows(BH, S, causal);

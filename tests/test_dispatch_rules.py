@@ -32,17 +32,20 @@ def rules(tmp_path_factory):
     return ask
 
 
-# head dimension 64, the whole backward in us: dK/dV (the faster grouping) and dQ (the faster tiles) in separate passes, both in one launch
-ONE_LAUNCH_CAUSAL = """2 512 33.7 23.2; 32 1024 51.0 40.4; 12 1500 64.2 44.8; 32 1500 72.5 70.2; 40 1500 86.3 84.4; 32 2048 104.2 102.3; 8 8192 268.9 266.5
-4 16384 486.3 484.8; 2 32768 937.2 934.0; 64 1024 68.4 68.6; 256 128 24.6 22.5; 128 256 28.4 24.8; 256 256 42.7 48.3; 128 512 50.7 54.3
-85 640 106.8 112.1; 60 900 68.5 73.1; 200 200 36.7 38.5; 250 100 65.7 74.6; 7 9000 312.1 301.0; 1024 512 363.6 472.1; 512 1024 491.1 578.1
-256 2048 730.1 810.6; 64 8192 1788.6 1935.1; 16 32768 6567.6 7054.7"""
-ONE_LAUNCH_FULL = """2 512 26.7 16.2; 27 777 40.5 38.9; 12 1500 50.2 48.1; 2 16384 446.7 442.8; 24 1500 80.5 74.4; 3 16384 708.3 673.2; 40 1500 93.9 102.4
-64 1024 71.8 78.7; 32 2048 123.3 131.2; 16 4096 226.1 237.6; 128 300 34.1 35.4; 400 100 28.0 30.6; 80 640 48.6 54.8; 24 3000 247.6 214.2
-18 4096 328.5 282.3; 48 1500 143.1 125.4; 64 1280 124.9 114.5; 10 8192 625.8 564.4; 5 16384 1220.2 1099.4; 300 256 58.9 56.9; 100 700 82.9 76.8
-11 8192 633.6 649.0; 48 1900 175.0 180.7; 250 300 79.3 89.6; 190 400 74.4 81.1; 700 128 74.4 88.9; 48 2048 189.0 192.7; 12 8192 669.8 671.1
-160 1024 173.1 187.0; 40 4096 570.3 580.6; 27 8192 1498.2 1535.9; 80 6528 2756.0 2846.5; 512 300 101.8 120.6; 256 600 121.2 139.4; 1024 100 54.7 62.9"""
-
+# head dimension 64, the whole backward in us: one group of waves and dQ on whole tiles, the same with dQ on split tiles, two groups and split
+# tiles in one launch
+BACKWARD_64_CAUSAL = """2 50 19.7 20.5 16.8; 2 512 39.0 34.4 23.2; 8 4109 164.7 138.8 98.5; 9 6873 284.6 261.6 250.5; 16 2048 99.0 85.5 62.6
+2 32768 1184.1 1032.8 934.0; 4 16384 607.6 533.4 484.8; 32 512 39.8 35.5 24.6; 32 1500 84.1 75.1 70.2; 37 181 42.5 37.7 33.3; 40 1500 90.7 86.3 84.4
+43 113 33.8 34.1 32.3; 90 254 53.4 47.3 45.2; 128 300 38.0 40.5 37.8; 18 7882 529.6 546.4 561.7; 60 900 68.5 69.9 73.1; 83 1552 275.1 270.0 280.6
+64 8192 1788.6 1860.6 1935.1; 85 640 116.6 106.8 112.1; 97 425 120.2 105.6 107.9; 99 43 39.1 40.5 44.7; 128 512 50.7 51.8 54.3; 149 770 246.3 213.1 223.3
+155 488 187.8 163.8 184.0; 179 20 49.6 50.7 63.3; 216 191 33.4 36.3 39.3; 250 100 65.7 66.5 74.6; 256 256 42.7 45.5 48.3; 256 1500 424.6 455.4 495.2
+352 244 65.5 63.6 66.2; 1845 38 503.4 533.7 686.0; 2048 256 305.9 336.4 375.8"""
+BACKWARD_64_FULL = """2 16384 538.6 464.2 442.8; 12 1500 63.3 52.8 48.1; 16 512 31.5 27.5 17.0; 27 777 47.8 40.5 38.9; 29 26 20.4 20.9 17.5; 33 636 64.2 54.5 46.7; 8 17920 2312.9 2264.8 2150.4
+24 1500 80.5 90.2 74.4; 3 16384 708.3 768.3 673.2; 20 4096 346.4 329.1 296.6; 36 1800 168.0 160.8 139.6; 24 3000 260.5 247.6 214.2; 100 700 82.9 84.5 76.8
+65 2914 637.3 580.0 561.3; 124 23 20.0 20.3 15.9; 150 200 60.7 53.8 50.1; 2 32768 1659.5 1719.8 1732.5; 28 2304 174.6 142.0 143.3; 51 95 25.2 26.0 27.8
+64 1024 71.8 75.9 78.7; 40 1500 93.9 99.0 102.4; 85 777 119.6 97.6 102.3; 93 48 25.3 27.0 31.6; 120 756 95.0 94.3 103.0; 129 115 60.2 63.3 68.0
+22 4096 348.3 332.2 341.2; 250 300 92.1 79.3 89.6; 190 400 85.9 74.4 81.1; 160 1024 173.1 175.4 187.0; 256 600 121.2 126.8 139.4; 512 300 101.8 104.4 120.6
+512 1024 507.8 556.1 613.9; 1024 100 54.7 56.6 62.9; 80 6528 2756.0 2772.5 2846.5; 1845 38 340.0 368.9 512.1; 200 300 55.6 55.9 52.7"""
 
 # head dimension 128, us: 256-row tiles, 128-row tiles with the keys split; the forward, and the backward in separate passes with dQ either way
 FORWARD_CAUSAL = """1 32768 661.9 413.2; 2 32768 708.3 526.6; 4 16384 356.7 265.8; 7 9000 203.2 164.9; 16 2048 50.0 33.0; 12 1500 39.0 24.9
@@ -59,30 +62,26 @@ DQ_CAUSAL = """2 512 57.5 50.9; 7 9000 584.9 535.6; 12 1500 110.9 93.9; 16 4096 
 120 900 188.9 197.3; 128 512 86.7 88.8; 256 256 78.0 82.7; 256 1500 793.9 855.0; 512 256 142.8 152.3; 16 32768 12166.3 12571.9"""
 DQ_FULL = """2 512 46.6 39.4; 4 8192 453.0 412.4; 7 9000 1086.7 880.8; 32 1024 80.9 72.3; 36 1700 238.0 200.4; 85 640 174.5 147.9; 500 200 150.0 131.9
 32 1500 151.9 162.0; 64 1024 132.5 139.8; 120 900 228.8 238.2; 256 2048 1688.6 1762.1; 512 256 129.7 137.7; 2 32768 3024.7 3115.3"""
-# dQ at head dimension 64 on grids that two_query_groups leaves to it
-DQ_64_CAUSAL = "16 32768 6567.6 6826.7; 60 900 68.5 69.9; 128 300 38.0 40.5; 200 200 36.7 38.8; 256 2048 730.1 766.5; 1024 512 363.6 403.3; 85 640 116.6 106.8"
-DQ_64_FULL = """85 777 119.6 97.6; 48 1900 179.9 175.0; 28 2304 174.6 142.0; 32 1500 85.1 93.3; 64 1024 71.8 75.9; 80 640 48.6 53.9; 512 1024 507.8 556.1
-2048 128 109.9 116.3; 22 4096 348.3 332.2; 250 300 92.1 79.3"""
 
 
 def _table(text):
     for entry in text.replace("\n", ";").split(";"):
-        bh, s, a, b = entry.split()
-        yield int(bh), int(s), float(a), float(b)
+        bh, s, *us = entry.split()
+        yield int(bh), int(s), [float(x) for x in us]
 
 
-def _regret(choices, table):
-    return {(bh, s): (b if c else a) / min(a, b) for c, (bh, s, a, b) in zip(choices, table)}
+def _check(table, variants, worst, mean=1.01):
+    """The chosen variants (an index into the times of each shape) against the best of each."""
+    regret = {(bh, s): us[v] / min(us) for v, (bh, s, us) in zip(variants, table)}
+    assert len(set(variants)) > 1
+    assert max(regret.values()) <= worst, regret
+    assert sum(regret.values()) / len(regret) <= mean
 
 
-@pytest.mark.parametrize("causal,text", [(True, ONE_LAUNCH_CAUSAL), (False, ONE_LAUNCH_FULL)])
-def test_one_launch_at_head_dimension_64(rules, causal, text):
+@pytest.mark.parametrize("causal,text", [(True, BACKWARD_64_CAUSAL), (False, BACKWARD_64_FULL)])
+def test_backward_at_head_dimension_64(rules, causal, text):
     table = list(_table(text))
-    picks = [r[0] for r in rules((bh, s, causal) for bh, s, _, _ in table)]
-    regret = _regret(picks, table)
-    assert 0 < sum(picks) < len(picks)
-    assert max(regret.values()) <= 1.09, regret          # the most that is given away: 24 x 1500 without a mask
-    assert sum(regret.values()) / len(regret) <= 1.01
+    _check(table, [2 if r[0] else r[1] for r in rules((bh, s, causal) for bh, s, _ in table)], 1.06)   # 200 x 300 without a mask
 
 
 def test_one_launch_takes_split_tiles(rules):
@@ -93,15 +92,10 @@ def test_one_launch_takes_split_tiles(rules):
         assert split64 or not two
 
 
-@pytest.mark.parametrize("column,causal,text", [(4, True, FORWARD_CAUSAL), (4, False, FORWARD_FULL), (2, True, DQ_CAUSAL), (2, False, DQ_FULL),
-                                                (1, True, DQ_64_CAUSAL), (1, False, DQ_64_FULL)])
+@pytest.mark.parametrize("column,causal,text", [(4, True, FORWARD_CAUSAL), (4, False, FORWARD_FULL), (2, True, DQ_CAUSAL), (2, False, DQ_FULL)])
 def test_split_tiles(rules, column, causal, text):
     table = list(_table(text))
-    picks = [r[column] for r in rules((bh, s, causal) for bh, s, _, _ in table)]
-    regret = _regret(picks, table)
-    assert 0 < sum(picks) < len(picks)
-    assert max(regret.values()) <= 1.11, regret          # the most that is given away: forward of 252 x 761, causal
-    assert sum(regret.values()) / len(regret) <= 1.01
+    _check(table, [r[column] for r in rules((bh, s, causal) for bh, s, _ in table)], 1.11)   # forward of 252 x 761, causal
 
 
 def test_forward_at_head_dimension_64_does_not_depend_on_the_other_heads(rules):
