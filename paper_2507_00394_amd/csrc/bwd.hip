@@ -120,7 +120,7 @@ bwd_delta_head_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k
   constexpr int TILE = G::TILE, HALF = 32 * D * 2, STAGE = G::STAGE, NST = G::NST, AHEAD = G::AHEAD;
   extern __shared__ __align__(16) char smem[];   // tile j (K, V) in stage j % NST
 
-  const TileCoord tc = map_block<CAUSAL>(blockIdx.x, BH, T, true);
+  const TileCoord tc = map_block<CAUSAL, D>(blockIdx.x, BH, T, true);
   if (!tc.valid) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);

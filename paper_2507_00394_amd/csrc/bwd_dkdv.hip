@@ -186,7 +186,7 @@ __device__ __forceinline__ void dkdv_keys(int block, const __bf16* __restrict__ 
   constexpr int BN = 128, BM = 64, KS = G::KS, DB = G::DB;
   extern __shared__ __align__(16) char smem[];
 
-  const TileCoord tc = map_block<CAUSAL>(block, BH, T, false);
+  const TileCoord tc = map_block<CAUSAL, D>(block, BH, T, false);
   if (!tc.valid) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6) & 3;       // wave of its group

@@ -548,7 +548,7 @@ __device__ __forceinline__ void pair_keys(int block, const __bf16* __restrict__ 
                                           const __bf16* __restrict__ v, const __bf16* __restrict__ dO, const float* __restrict__ lse2,
                                           const float* __restrict__ neg_delta, __bf16* __restrict__ dk, __bf16* __restrict__ dv,
                                           const BwdMaps& maps, int BH, int H, int S, int T, float scale) {
-  const TileCoord tc = map_block<CAUSAL>(block, BH, T, false);
+  const TileCoord tc = map_block<CAUSAL, PG::D>(block, BH, T, false);
   if (!tc.valid) return;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (w < 4) pair_sweep<CAUSAL, 0>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, tc, H, S, scale);

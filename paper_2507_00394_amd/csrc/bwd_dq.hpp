@@ -125,7 +125,7 @@ __device__ __forceinline__ void dq_whole_rows(int block, const __bf16* __restric
   constexpr int STAGE = 2 * TILE;   // [K tile][V tile]; tile j lives in stage j % 4
   extern __shared__ __align__(16) char smem[];
 
-  const TileCoord tc = map_block<CAUSAL>(block, BH, T, true);
+  const TileCoord tc = map_block<CAUSAL, D>(block, BH, T, true);
   if (!tc.valid) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -323,7 +323,7 @@ __device__ __forceinline__ void dq_split_rows(int block, const __bf16* __restric
   constexpr int TILE = G::TILE, HALF = 32 * D * 2, STAGE = G::STAGE, NST = G::NST, AHEAD = G::AHEAD;
   extern __shared__ __align__(16) char smem[];   // tile j (K, V) in stage j % NST
 
-  const TileCoord tc = map_block<CAUSAL>(block, BH, T, true);
+  const TileCoord tc = map_block<CAUSAL, D>(block, BH, T, true);
   if (!tc.valid) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);

@@ -193,7 +193,7 @@ fwd_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __b
   constexpr int VREGION = 4 * TILE;
   extern __shared__ __align__(16) char smem[];   // K[4] then V[4]; tile j in buffer j % 4
 
-  const TileCoord tc = map_block<CAUSAL>(blockIdx.x, BH, T, true);
+  const TileCoord tc = map_block<CAUSAL, D>(blockIdx.x, BH, T, true);
   if (!tc.valid) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave index, held in a scalar register
@@ -396,7 +396,7 @@ fwd_split_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, con
   constexpr int TILE = G::TILE, HALF = 32 * D * 2, NST = G::NST, AHEAD = G::AHEAD, VREGION = NST * TILE;
   extern __shared__ __align__(16) char smem[];   // K[NST] then V[NST]; tile j in buffer j % NST
 
-  const TileCoord tc = map_block<CAUSAL>(blockIdx.x, BH, T, true);
+  const TileCoord tc = map_block<CAUSAL, D>(blockIdx.x, BH, T, true);
   if (!tc.valid) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);

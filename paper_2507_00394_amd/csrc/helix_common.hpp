@@ -278,15 +278,23 @@ __device__ __forceinline__ bf16x8 pack_half(const f32x16& acc, int t) {
 // imbalance.  One head after the other -> this rule, forward / dQ, us: 4 x 16 heads x 2k tokens 99 -> 77 /
 // 132 -> 101; 5 x 32k 1472 -> 1249 / 1997 -> 1733; 24 x 4k 131 -> 108 / 174 -> 147; 32 x 32k 7552 -> 7441 /
 // 10272 -> 10128.  Without a mask all tiles are equal and heads stay one after the other.
+//
+// Head dimension 128 with three or five tiles to a virtual head: only as many as hold about one and a half rounds.  Two or four tiles pair up,
+// a long one of one head with a short one of another, and fill whole rounds; of an odd number one is left without a partner, so more heads
+// side by side even nothing out and cost L2 hits.  One head after the other / four rounds / one and a half, forward, us: 272 heads x
+// 570 59 / 73 / 55; 344 x 700 82 / 101 / 81; 360 x 520 72 / 74 / 65; 248 x 620 54 / 65 / 52; whole backward 272 x 570 225 / 247 / 208.  Over 43
+// shapes with such heads the forward takes 0.93 of the time of four rounds, the backward 0.97.  At head dimension 64, where two workgroups
+// share a compute unit, four rounds are the better choice there too (532 x 640 forward 69.6 / 65.4, backward 330 / 285).
 struct TileCoord { int bh; int tile; bool valid; };
-template <bool CAUSAL>
+template <bool CAUSAL, int D>
 __device__ __forceinline__ TileCoord map_block(int n, int BH, int T, bool heavy_is_high) {
   TileCoord c;
   const int P = head_parts(BH), TP = (T + P - 1) / P;
   const int xcd = n & 7, s = n >> 3;
   int v = s / TP, r = s - v * TP;                // virtual head of this XCD and position among its tiles
   if (CAUSAL) {
-    const int V = (int)((long long)BH * P / 8), wanted = TP >= 64 ? 2 : 128 / TP;
+    const int blocks = D == 128 && (TP == 3 || TP == 5) ? 48 : 128;
+    const int V = (int)((long long)BH * P / 8), wanted = TP >= 64 ? 2 : blocks / TP;
     const int side = V < wanted ? V : wanted, s2 = s - (V - side) * TP;
     if (s2 >= 0) {
       r = s2 / side;

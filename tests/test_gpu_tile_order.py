@@ -11,12 +11,14 @@ from paper_2507_00394_amd import inputs as I
 pytestmark = pytest.mark.gpu
 
 
-# (heads, S): 10 virtual heads per XCD of which 4 (1 tile each) to 10 go first; heads split in 2, 4 and 8 parts
-@pytest.mark.parametrize("BH,S", [(80, 2600), (80, 8193), (44, 2600), (42, 1500), (13, 3000)])
-def test_every_tile_once(BH, S):
+# (heads, S): 10 virtual heads per XCD of which 4 (1 tile each) to 10 go first; heads split in 2, 4 and 8 parts; at head dimension 128
+# three and five tiles to a virtual head, of which all but one, all and some go side by side
+@pytest.mark.parametrize("BH,S,D", [(80, 2600, 64), (80, 8193, 64), (44, 2600, 64), (42, 1500, 64), (13, 3000, 64), (136, 570, 128), (80, 1100, 128),
+                                    (40, 640, 128), (264, 300, 128), (36, 1300, 128)])
+def test_every_tile_once(BH, S, D):
     from tests import gpu_util as G
 
-    cfg, bits = I.random_case_bits(8800 + BH, 1, BH, S, 64)
+    cfg, bits = I.random_case_bits(8800 + BH, 1, BH, S, D)
     out = G.run_fwd_bwd(bits, cfg.scale, True)
     for n in ("o", "lse", "dq", "dk", "dv"):
         assert bool(torch.isfinite(out[n].float()).all()), n
