@@ -23,6 +23,13 @@
  *     as the launches are queued.
  *   - Outputs are overwritten in full; inputs are never written; an output must not
  *     alias any other argument.
+ *   - Repeating a call reproduces every bit (no atomics), and the values in one (batch, head) slice
+ *     never reach the results of another.  How many slices share a call may: B*H and S decide which
+ *     tiles a pass takes, and with them the order of its sums.  One call with B = 2 then agrees with
+ *     two calls with B = 1 (or the heads of one call with those of two) within rounding only, where
+ *     the smaller grid takes other tiles; where both take the same, bit for bit.  It concerns, given
+ *     the same inputs, O and LSE at D = 128, dQ, and dK and dV at D = 64; O and LSE at D = 64 and
+ *     dK and dV at D = 128 depend on nothing but their slice.
  *   - Arguments are validated on the host before the first HIP call.  The return value
  *     is a helix_status; anything but HELIX_OK means nothing (or, for HELIX_ERR_LAUNCH,
  *     only part of the work) was enqueued.

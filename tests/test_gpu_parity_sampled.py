@@ -75,7 +75,9 @@ def test_config_sampled(cfg_id):
 
 def test_two_micro_batches_equal_two_calls_and_runs_repeat():
     """B = 2 in one call is bit-identical to two B = 1 calls (the two micro batches a stage
-    holds are independent), and repeating a call reproduces every bit (no atomics)."""
+    holds are independent) where both calls take the same tiles, as here and at all sizes of the
+    workload table (test_gpu_batch_rounding.py has the others), and repeating a call reproduces
+    every bit (no atomics)."""
     from tests import gpu_util as G
 
     cfg, bits = I.random_case_bits(501, 2, 5, 2304, 128, k_mult=2.0)
