@@ -83,9 +83,10 @@ int helix_attn_fwd(const void* q, const void* k, const void* v, void* o, float* 
 
 /* Backward (Table 1, "Backward B": gradients wrt the inputs only; attention has no
  * "Backward W").  Runs its kernels in order on `stream`: the row sums
- * delta_i = sum_d dO_id * O_id, for causal attention a refinement of delta on the first
- * HELIX_DELTA_HEAD_ROWS rows of every head (see helix_attn_bwd_delta_head), the dK/dV
- * pass and the dQ pass.
+ * delta_i = sum_d dO_id * O_id -- for causal attention only of the rows from
+ * HELIX_DELTA_HEAD_ROWS on, the first ones of every head get delta as
+ * helix_attn_bwd_delta_head computes it -- then the dK/dV and the dQ pass, in one launch or
+ * two.  Results are those of the separate stage calls below, bit for bit.
  *   q, k, v, o, lse : in, as given to / produced by helix_attn_fwd
  *   dO              : in,  bf16 [B, H, S, D]
  *   dq, dk, dv      : out, bf16 [B, H, S, D]

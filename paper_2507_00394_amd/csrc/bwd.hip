@@ -1,17 +1,17 @@
 // Backward attention for gfx950 (Table 1, Attention column, "Backward B"; attention has no
 // parameters, so there is no "Backward W").  Works from q, k, v, o, lse only -- the
-// activations the paper calls "saved by flash attention" (Section 4.4) -- in three kernels:
+// activations the paper calls "saved by flash attention" (Section 4.4) -- in these passes:
 //
 //   preprocess : delta_i = sum_d dO_id * O_id                         (streams 2 tensors, HBM bound)
+//   delta_head : causal attention only, the first rows of every head, which the preprocess pass then leaves out: a sweep
+//                in the dQ layout that only produces delta_i = sum_j p_ij dp_ij
 //   dkdv       : (bwd_dkdv_pair.hip for head dimension 128, bwd_dkdv.hip for 64) a workgroup owns
 //                128 keys and sweeps the query blocks that see them: S = Q K^T,
 //                P = exp(scale*S - LSE), dV^T += dO^T P, dP = dO V^T, dS = P o (dP - delta),
 //                dK^T += Q^T dS
-//   dq         : (bwd_dq.hip) a workgroup owns 256 queries and sweeps the visible key tiles:
+//   dq         : (bwd_dq.hpp) a workgroup owns 256 or 128 queries and sweeps the visible key tiles:
 //                S^T = K Q^T, dP^T = V dO^T, dS^T = P^T o (dP^T - delta), dQ^T += K^T dS^T
-//   delta_head : a sweep in the dQ layout that only produces delta_i = sum_j p_ij dp_ij for the first
-//                rows of every head
-// Between the kernels the row statistics travel as neg_delta = -delta and lse2 = LSE * log2(e).
+// dkdv and dq share a launch on all but the largest grids (launch_bwd_dkdv_dq).  Between the kernels the row statistics travel as neg_delta = -delta and lse2 = LSE * log2(e).
 //
 // Every output element is produced by exactly one lane, so there are no atomics and the
 // result is bit-reproducible.
@@ -98,7 +98,7 @@ hipError_t launch_bwd_preprocess(const void* o, const void* dO, const float* lse
 //     slots 8..15   S^T(j+1)  = K(j+1) Q^T  | sum += P^T(j) o dP^T(j)
 // with the tile copies asynchronous and four tiles ahead.  Against an unpipelined sweep of 256-row tiles through staging
 // registers: 2 heads x 32k tokens 71 -> 32 us, 5 x 32k 72 -> 33, 16 x 16k at head dimension 64 56 -> 28, 4 x 16 x 2k
-// (the time of the two products at full rate is 70) 107 -> 95, and about 82 with whole tiles (below).
+// (the time of the two products at 1230 TFLOP/s is 56) 107 -> 95, and about 82 with whole tiles (below).
 template <int D>
 struct DeltaHead {
   static constexpr int NST = 5, AHEAD = NST - 1;

@@ -15,7 +15,7 @@
 // bf16(dS) in accumulator layout are the B operands of the last two products; Q, dO come
 // from LDS as A operands, row-major for S / dP and through the transposing LDS read for
 // dV / dK.  At head dimension 64 both fp32 accumulators (32 keys x D x 2), the K, V fragments and
-// the pipeline's S, dP of two blocks take 220-239 registers and the four stages 72 KB of LDS, so TWO
+// the pipeline's S, dP of two blocks take 218-230 registers and the four stages 72 KB of LDS, so TWO
 // workgroups share a compute unit.  A single wave per SIMD is bound by instruction issue (about
 // one instruction per four cycles, eight of them per MFMA); the second one issues under the
 // first one's MFMAs: 16 heads x 16k tokens 1234 -> 960 us (891 -> 1145 TFLOP/s).

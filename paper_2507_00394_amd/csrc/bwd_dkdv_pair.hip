@@ -13,7 +13,7 @@
 //     wave B (waves 4..7):  dP = dO V^T - delta,  dS = P o dP,  dK^T += Q^T bf16(dS)
 // A hands P (fp32, register for register: both accumulators have the same lane layout)
 // to B through LDS; B works one 32-row block behind A, and one workgroup barrier per block
-// orders the hand-over.  Each wave needs 216-233 registers, so two fit on a SIMD and the
+// orders the hand-over.  Each wave needs 212 registers (240-242 in the launch shared with dQ), so two fit on a SIMD and the
 // instructions of one issue under the MFMAs of the other; per MFMA a wave issues about two
 // vector-ALU and two LDS instructions.
 //

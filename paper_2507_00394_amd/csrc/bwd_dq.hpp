@@ -1,7 +1,8 @@
 // dQ pass of the attention backward for gfx950 (Table 1, Attention column, "Backward B"): the work of one workgroup,
 // for the kernel that is nothing else (bwd_dq.hip) and for the ones that share a launch with the dK/dV pass.
 //
-// Work split: a workgroup of 8 waves owns 256 query rows of one (batch, head) slice, 32 per
+// Work split (dq_whole_rows; dq_split_rows, for small grids, differs as its comment says): a workgroup of 8 waves owns
+// 256 query rows of one (batch, head) slice, 32 per
 // wave, and sweeps the 64-key tiles the causal mask leaves visible.  Everything is kept
 // transposed so that a lane owns ONE query (column l%32): its LSE and delta are plain
 // per-lane scalars.  Per 32-key half tile h a wave evaluates with the 32x32x16 bf16 MFMA

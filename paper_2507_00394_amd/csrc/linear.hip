@@ -320,10 +320,13 @@ static hipError_t launch_gemm_tile(const void* X, long long ldx, const void* Y, 
   return hipGetLastError();
 }
 
-// The tile that takes the least time by a model of four figures per tile, fitted to 38 shapes (64 to 131072
-// tokens, K 640 to 4096, N 384 to 2304), which it meets within 20 %.  A round of workgroups takes between `sparse`
+// The tile that takes the least time by a model of four figures per tile.  A round of workgroups takes between `sparse`
 // (few of them on the chip: latency of the copies and barriers) and `full` nanoseconds per contraction index, plus
-// `fixed` for first copies and stores.  Measured, 256 / 128 / 64, us: forward of 64 tokens x 2048 x 768
+// `fixed` for first copies and stores.  The times themselves are rough (a third too low to a half too high: 8192 x 2048 x 768 on 64 tiles
+// 64 for 43 us); what counts is the choice.  Over 110 random shapes (32 to 131072 tokens, K to 5120, N to 3072) it is the fastest tile or
+// within 3 % of it for 99 forward products, 103 input and 98 weight gradients, 1.4, 0.6 and 1.1 % off on average; at worst, with a short
+// contraction or few columns, 47776 x 256 x 1024 forward 47.9 for 36.8 us, 5888 x 1920 x 1920 da + dw 118 for 108, 37024 x 896 x 512 121 for 105.
+// Measured, 256 / 128 / 64, us: forward of 64 tokens x 2048 x 768
 // 39 / 14.5 / 10.2; 2080 x 2048 x 768 45 / 18.6 / 14.7; 2080 x 4096 x 1536 82 / 38 / 60; 8192 x 2048 x 768
 // 48 / 35 / 43; 16384 x 4096 x 1536 207 / 224 / 489; 131072 x 4096 x 1536 1396 / 1862 / 3873.
 // `extra_256`: microseconds that only the large tile's path spends.
@@ -346,7 +349,9 @@ static hipError_t launch_gemm(TileKind kind, const void* X, long long ldx, const
                               int I, int J, int R, int parts, int r_per_part, long long part_stride, hipStream_t stream) {
   using Small = typename std::conditional<XR, Tile64ShortStages, Tile64>::type;
   switch (kind) {
-    case TileKind::k256: return launch_gemm_tile<Tile256, XR, YR, OutT>(X, ldx, Y, ldy, C, ldc, I, J, R, parts, r_per_part, part_stride, stream);
+    case TileKind::k256:
+      if constexpr (XR || YR) return launch_gemm_tile<Tile256, XR, YR, OutT>(X, ldx, Y, ldy, C, ldc, I, J, R, parts, r_per_part, part_stride, stream);
+      return hipErrorInvalidValue;   // two contiguous operands: launch_linear_bwd_input transposes w for this tile
     case TileKind::k128: return launch_gemm_tile<Tile128, XR, YR, OutT>(X, ldx, Y, ldy, C, ldc, I, J, R, parts, r_per_part, part_stride, stream);
     default: return launch_gemm_tile<Small, XR, YR, OutT>(X, ldx, Y, ldy, C, ldc, I, J, R, parts, r_per_part, part_stride, stream);
   }
