@@ -17,35 +17,47 @@ constexpr long long grid_blocks(int BH, int T) {
   return (long long)BH * P * ((T + P - 1) / P);
 }
 
-// The workgroups of a launch on the fullest XCD (32 compute units): how many, the 64-row (64-key) steps of the longest, and of all of them.
-// `keys`: tiles of the dK/dV pass, which sweep the query rows from their first key on; else of query rows, which sweep the keys up
-// to their last row.
-struct Share { double blocks, longest, steps; };
-inline Share share(int BH, int S, bool causal, int rows, bool keys) {
-  const int P = head_parts(BH), T = (S + rows - 1) / rows;
-  const double heads = (double)BH * P / 8, own = (T + P - 1) / P;   // virtual heads of an XCD and their tiles: the longest, then every P-th
-  const double n = (S + 63) / 64, per_tile = rows / 64;
-  double head = own * n;
-  if (causal && keys) head -= per_tile * P * own * (own - 1) / 2;
-  else if (causal) head = n + per_tile * ((own - 1) * T - P * own * (own - 1) / 2);
-  return Share{own * heads, n, head * heads};
+// The workgroups of a launch on the fullest XCD (32 compute units): `heads` virtual heads with `own` tiles each, the longest of every
+// head, the second longest of every head, ...  `keys`: tiles of the dK/dV pass, which sweep the query rows from their first key on;
+// else of query rows, which sweep the keys up to their last row.  Lengths in steps of 64 rows or keys.
+struct Share {
+  bool causal, keys;
+  int P, T, per_tile;          // parts of a head, tiles of a head, steps by which neighbouring tiles differ
+  double heads, own, longest;
+  Share(int BH, int S, bool causal_, int rows, bool keys_)
+      : causal(causal_), keys(keys_), P(head_parts(BH)), T((S + rows - 1) / rows), per_tile(rows / 64), heads((double)BH * P / 8),
+        own((T + P - 1) / P), longest((S + 63) / 64) {}
+  double blocks() const { return own * heads; }
+  double length(double i) const {   // of the i-th longest tile of a head
+    if (!causal || i == 0.) return longest;
+    return keys ? longest - per_tile * P * i : per_tile * (T - P * i);
+  }
+  double steps() const {
+    if (!causal) return blocks() * longest;
+    return heads * (keys ? own * longest - per_tile * P * own * (own - 1) / 2 : longest + per_tile * ((own - 1) * T - P * own * (own - 1) / 2));
+  }
+};
+// Time of a pass whose workgroups go `slots` at a time, `per_step` for a step and `start` for a workgroup's first loads, its last tile and its
+// results, the longest first: the average of a slot or, if that is more, what the longest ones take where k of them cannot help
+// sharing a slot.  Without a mask all are equal, and that is whole rounds.  The unit is a step of a 256-row workgroup.
+inline double pass_time(const Share& w, int slots, double per_step, double start) {
+  const double rounds = std::ceil(w.blocks() / slots);
+  double t = (per_step * w.steps() + start * w.blocks()) / slots;
+  if (!w.causal) return std::max(t, rounds * (per_step * w.longest + start));
+  for (int k = 0; k < 3 && k < rounds; k++) t = std::max(t, (k + 1) * (per_step * w.length(std::floor(k * slots / w.heads)) + start));
+  return t;
 }
-// Time of a pass whose workgroups go `slots` at a time per XCD, `per_step` for a step and `start` for a workgroup's first loads, its last
-// tile and its results.  No mask: whole rounds of equal workgroups.  Causal: the longest workgroup, or the average of a slot if that
-// is more (the longest go first).  The unit is a step of a 256-row workgroup.
-inline double pass_time(const Share& w, bool causal, int slots, double per_step, double start) {
-  const double rounds = std::ceil(w.blocks / slots);
-  return per_step * (causal ? std::max(w.longest, w.steps / slots) : rounds * w.longest) + start * rounds;
-}
-inline double whole_rows_time(int BH, int S, bool causal) { return pass_time(share(BH, S, causal, 256, false), causal, 32, 1., 4.); }
-inline double split_rows_time(int BH, int S, bool causal) { return pass_time(share(BH, S, causal, 128, false), causal, 32, 0.55, 4.5); }
+inline double whole_rows_time(int BH, int S, bool causal) { return pass_time(Share(BH, S, causal, 256, false), 32, 1., 3.5); }
+inline double split_rows_time(int BH, int S, bool causal) { return pass_time(Share(BH, S, causal, 128, false), 32, 0.58, 4.5); }
 
 // Whether a pass takes 128-row tiles with the keys split over two groups of waves instead of 256-row tiles.  A split workgroup needs little
 // more than half of a whole one's time per key tile, a little more for its start and end, and there are twice as many: it pays where
-// whole tiles leave compute units idle, or where they fill a round or an XCD badly.  Over 174 shapes (1 to 2048 heads, 65 to 32k tokens; forward
-// at head dimension 128, dQ at both) the rule costs 0.2-0.3 % against the faster variant of each, 10 % at worst (252 x 761 causal).
+// whole tiles leave compute units idle, or where they fill a round or an XCD badly.  Over 467 shapes (1 to 2048 heads, 65 to 32k tokens; forward
+// at head dimension 128, dQ at both) the rule costs 0.4 and 0.2 % against the faster variant of each, more than 10 % at four forward ones:
+// 416 x 304 without a mask 64 for 52 us; causal 472 x 381 67 for 60, 252 x 761 95 for 86, 66 x 2521 166 for 151.
 // Whole -> split, us, forward / dQ (or the whole backward, b) at head dimension 128:
 //   causal: 12 heads x 1500 39.0 -> 24.9 / 49 -> 31.5; 2 x 32k 708 -> 527 / 904 -> 693; 64 x 1024 32.4 -> 29.7; 500 x 200 59 -> 41 / b 182 -> 157;
+//     78 x 589 39.9 -> 32.7; 66 x 768 53 -> 41;
 //     128 x 512 21.9 -> 24.0; 256 x 256 19.4 -> 23.4 / b 77.7 -> 81.0; 16 x 8192 255 -> 282 / 339 -> 364; 256 x 2048 316 -> 367 / b 1353 -> 1394.
 //   no mask: 32 x 1024 30.3 -> 22.3; 7 x 9000 446 -> 286 / b 1079 -> 875; 36 x 1700 94 -> 64; 12 x 8192 412 -> 399 / 533 -> 522;
 //     275 x 987 341 -> 229 / b 824 -> 658;
@@ -66,8 +78,8 @@ inline bool split_forward(int D, int BH, int S, bool causal) { return kForwardSp
 // the dQ pass on split tiles (a launch of its own is what the stage calls make of it).  With one group a SIMD has one wave, which
 // is bound by instruction issue, unless a second workgroup finds room beside it; two groups halve the sweep, and the common launch fills
 // the compute units that a small grid or its last round leaves idle and saves a start.  Where the chip is full both only cost: the swap of
-// partial sums, and one workgroup in the place of two.  The times of both ways, fitted to the whole backward at 282 shapes (2 to 2048
-// heads, 20 to 32k tokens): the rule costs 0.4 % against the best of all variants, 6 % at worst.
+// partial sums, and one workgroup in the place of two.  The times of both ways, fitted to the whole backward at 465 shapes (1 to 2048
+// heads, 20 to 32k tokens): the rule costs 0.3 % against the best of all variants, 10 % at worst.
 // Separate passes (the faster way) -> one launch, us, key tiles in brackets:
 //   causal: 2 heads x 512 [8] 33.7 -> 23.1; 12 x 1500 [144] 64 -> 44; 32 x 1024 [256] 51 -> 41; 32 x 1500 [384] 72.5 -> 70.5; 4 x 16k [512]
 //     486 -> 484 (533 with one group); 60 x 900 [480] 69 -> 73; 128 x 512 [512] 51 -> 55; 256 x 256 [512] 43 -> 48; 256 x 2048 [4096] 730 -> 811.
@@ -75,16 +87,16 @@ inline bool split_forward(int D, int BH, int S, bool causal) { return kForwardSp
 //     94 -> 102; 64 x 1024 [512] 72 -> 79; 24 x 3000 [576] 248 -> 214; 10 x 8192 [640] 626 -> 563; 11 x 8192 [704] 634 -> 649; 190 x 400 [760]
 //     74 -> 81; 8 x 17920 [1120] 2244 -> 2128; 160 x 1024 [1280] 173 -> 187; 512 x 300 [1536] 102 -> 120; 80 x 6528 [4080] 2756 -> 2841.
 inline bool two_query_groups(int BH, int S, bool causal) {
-  const Share k = share(BH, S, causal, 128, true), q = share(BH, S, causal, 128, false);
+  const Share k(BH, S, causal, 128, true), q(BH, S, causal, 128, false);
   // one group: two workgroups beside one another on a compute unit, 1.6 a step; one alone takes 0.7 of that
-  const double rest = std::fmod(k.blocks, 64.);
-  double one = std::floor(k.blocks / 64) * (1.6 * k.longest + 6.) + (rest == 0. ? 0. : (rest <= 32. ? 0.7 : 1.) * 1.6 * k.longest + 6.);
-  if (causal) one = 1.6 * std::max(0.7 * k.longest, k.steps / 64) + 6. * std::ceil(k.blocks / 64);
-  const double separate = one + std::min(split_rows_time(BH, S, causal), whole_rows_time(BH, S, causal)) + 6.;   // a second launch
-  // together: key tiles, 0.85 a step, then query tiles, 0.55; no mask: rounded up to a whole query tile
-  const double query = 0.55 * q.longest + 4.5;
-  const double work = 0.85 * k.steps + 8. * k.blocks + 0.55 * q.steps + 4.5 * q.blocks;
-  const double together = causal ? std::max(0.85 * k.longest + 8., work / 32) : query * std::ceil(work / 32 / query);
+  const double beside = 1.6 * k.longest + 7., alone = 0.7 * 1.6 * k.longest + 7., rest = std::fmod(k.blocks(), 64.);
+  const double one = causal ? std::max((1.6 * k.steps() + 7. * k.blocks()) / 64, alone)
+                            : std::floor(k.blocks() / 64) * beside + (rest == 0. ? 0. : rest <= 32. ? alone : beside);
+  const double separate = one + std::min(split_rows_time(BH, S, causal), whole_rows_time(BH, S, causal)) + 7.;   // a second launch
+  // together: key tiles, 0.8 a step, then query tiles, 0.55; no mask: rounded up to a whole query tile
+  const double query = 0.55 * q.longest + 5.2;
+  const double work = (0.8 * k.steps() + 10. * k.blocks() + 0.55 * q.steps() + 5.2 * q.blocks()) / 32;
+  const double together = causal ? std::max(work, pass_time(k, 32, 0.8, 10.)) : query * std::ceil(work / query);
   return together < separate;
 }
 inline bool split_dq(int D, int BH, int S, bool causal) {
