@@ -10,7 +10,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("H,S,D", [(257, 1, 64), (257, 33, 128), (260, 65, 64), (260, 256, 128), (130, 257, 128), (100, 600, 64), (43, 1537, 128),
-                                   (33, 2049, 128), (33, 2304, 64)])
+                                   (33, 2049, 128), (33, 2304, 64),
+                                   (192, 256, 128), (128, 257, 128), (96, 600, 64), (48, 1537, 128), (40, 2049, 128), (40, 2304, 64)])
 @pytest.mark.parametrize("causal", [True, False])
 def test_same_bits_as_small_grid(H, S, D, causal):
     from paper_2507_00394_amd import binding as hx

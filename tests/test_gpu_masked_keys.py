@@ -8,7 +8,7 @@ from paper_2507_00394_amd import inputs as I
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("H,S,D", [(3, 64, 64), (3, 200, 128), (300, 64, 64), (300, 64, 128), (300, 200, 128)])
+@pytest.mark.parametrize("H,S,D", [(3, 64, 64), (3, 200, 128), (300, 64, 64), (300, 64, 128), (300, 200, 128), (192, 200, 128)])
 def test_delta_of_rows_that_do_not_see_an_infinite_value(H, S, D):
     from paper_2507_00394_amd import binding as hx
     from tests import gpu_util as G

@@ -1,6 +1,6 @@
 """dK/dV at head dimension 64 with the query tiles of a key tile split over two groups of waves: one, two and three
-tiles (the second group has none, or fewer than the first), the diagonal in one or both groups, ragged ends, and the
-grids on both sides of the rule's lines (512 key tiles causal; 256 and 1024 tokens without a mask)."""
+tiles (the second group has none, or fewer than the first), the diagonal in one or both groups, ragged ends, and
+grids on both sides of the rule."""
 import pytest
 
 from oracle import attention_ref as A
@@ -12,6 +12,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("H,S,causal", [
     (1, 1, True), (2, 64, True), (1, 65, True), (2, 129, True), (1, 192, True), (2, 200, True), (3, 320, True), (1, 1000, True),
     (171, 321, True), (170, 321, True), (4, 1023, False), (4, 1024, False), (1, 1089, False), (28, 1100, False), (29, 1100, False),
+    (48, 1030, True), (32, 2100, True),
 ])
 def test_dkdv(H, S, causal):
     from tests import gpu_util as G
