@@ -10,7 +10,7 @@ namespace helix {
 // Heads are dealt to the 8 XCDs as "virtual heads", P interleaved parts each (see map_block in helix_common.hpp): the smallest power
 // of two that makes BH * P a multiple of 8.
 constexpr int head_parts(int BH) { return (BH & 1) ? 8 : (BH & 2) ? 4 : (BH & 4) ? 2 : 1; }
-// Number of workgroups to launch for BH slices of T tiles.  An eighth of them is the share of the fullest XCD, which has the
+// Number of workgroups to launch for BH slices of T tiles.  An eighth of them is the share of the fullest XCD, which has one
 // tile more where T is not a multiple of P.
 constexpr long long grid_blocks(int BH, int T) {
   const int P = head_parts(BH);
