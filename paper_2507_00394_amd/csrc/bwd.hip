@@ -135,20 +135,6 @@ bwd_delta_head_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k
   const float c = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, scale * kLog2e)));
   const uint32_t base = lds_base(smem);
 
-  bf16x8 qf[KS], gf[KS];
-  float lse2;
-  {
-    const int row = my_q < S ? my_q : S - 1;
-#pragma unroll
-    for (int ks = 0; ks < KS; ks++) {
-      qf[ks] = *reinterpret_cast<const bf16x8*>(qh + (size_t)row * maps.q.row + 16 * ks + 8 * half);
-      gf[ks] = *reinterpret_cast<const bf16x8*>(gh + (size_t)row * maps.dO.row + 16 * ks + 8 * half);
-    }
-    lse2 = lse[(size_t)tc.bh * S + row] * kLog2e;
-#pragma unroll
-    for (int ks = 0; ks < KS; ks++) { pin(qf[ks]); pin(gf[ks]); }
-    pin(lse2);
-  }
   float dsum[3 - KG][2] = {};   // this lane's share of sum_j p_ij dp_ij, by key half
 
   const int q_end = (q0 + BM < S ? q0 + BM : S);
@@ -177,11 +163,28 @@ bwd_delta_head_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k
     __syncthreads();
     st = plus(1);
   };
+  // The Q and dO rows pass through the last stages: two of them for 128 rows, copied by one wave of a row group each, four for 256.
+  // The tiles those stages are for follow when every wave has its fragments.
+  constexpr int FIRST = KG == 2 ? 3 : 1;
+  const uint32_t frag = base + FIRST * STAGE + rg * 2 * HALF;
+  if (KG == 1 || kg == 0) issue_fragments<D>(qh, maps.q.row, wave_qmin, S, lane, 0, frag);
+  if (KG == 1 || kg == 1) issue_fragments<D>(gh, maps.dO.row, wave_qmin, S, lane, 0, frag + HALF);
 #pragma unroll
-  for (int jj = 0; jj < AHEAD; jj++)
+  for (int jj = 0; jj < FIRST; jj++)
     if (jj < n_tiles) copy_tile(jj, jj);
+  float lse2 = lse[(size_t)tc.bh * S + (my_q < S ? my_q : S - 1)] * kLog2e;
+  pin(lse2);
+  if (n_tiles >= FIRST) wait_tile_loads_except<FIRST * NDMA>();
+  else wait_tile_loads();
+  if (KG == 2) __syncthreads();
+  bf16x8 qf[KS], gf[KS];
+  read_fragments<D>(frag, lane, qf);
+  read_fragments<D>(frag + HALF, lane, gf);
   wait_tile_loads();
   __syncthreads();
+#pragma unroll
+  for (int jj = FIRST; jj < AHEAD; jj++)
+    if (jj < n_tiles) copy_tile(jj, jj);
 
   uint32_t ab[KS];   // row n, contraction step ks of the K half tile (the V tile is TILE bytes further)
 #pragma unroll
@@ -195,6 +198,11 @@ bwd_delta_head_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k
     for (int ks = 0; ks < KS; ks++) sa = mfma32(lds_b128(ab[ks], 0), qf[ks], sa);
 #pragma unroll
     for (int i = 0; i < R; i++) ring[i] = lds_b128(ab[i], TILE);
+  }
+  if (KG == 1) {   // tile 1 has landed
+    if (n_tiles >= AHEAD) wait_tile_loads_except<(AHEAD - 2) * NDMA>();
+    else wait_tile_loads();
+    __syncthreads();
   }
 
   // Block j: on entry s_cur = S^T(j) and ring = the first V operands of tile j; on exit the same for j + 1.

@@ -205,18 +205,12 @@ __device__ __forceinline__ void dkdv_keys(int block, const __bf16* __restrict__ 
   const char* const stages = smem + group * (G::NSTAGE * G::STAGE);
   const uint32_t base = lds_base(stages);
 
-  // K^T and V^T operand fragments of this lane's key (columns of S and dP).
-  bf16x8 kf[KS], vf[KS];
-  {
-    const int row = my_key < S ? my_key : S - 1;
-#pragma unroll
-    for (int ks = 0; ks < KS; ks++) {
-      kf[ks] = *reinterpret_cast<const bf16x8*>(kh + (size_t)row * maps.k.row + 16 * ks + 8 * half);
-      vf[ks] = *reinterpret_cast<const bf16x8*>(vh + (size_t)row * maps.v.row + 16 * ks + 8 * half);
-    }
-#pragma unroll
-    for (int ks = 0; ks < KS; ks++) { pin(kf[ks]); pin(vf[ks]); }
-  }
+  // K^T and V^T operand fragments of this lane's key (columns of S and dP): through stages 2 and 3, so tile 2 follows
+  // when every wave has them.
+  const uint32_t frag = base + 2 * G::STAGE + w * 2 * G::ROWS32;
+  static_assert(4 * 2 * G::ROWS32 <= 2 * G::STAGE, "the fragments of four waves fit two stages");
+  issue_fragments<D>(kh, maps.k.row, wave_kmin, S, lane, 0, frag);
+  issue_fragments<D>(vh, maps.v.row, wave_kmin, S, lane, 0, frag + G::ROWS32);
   f32x16 dkacc[DB], dvacc[DB];
 #pragma unroll
   for (int db = 0; db < DB; db++)
@@ -263,9 +257,14 @@ __device__ __forceinline__ void dkdv_keys(int block, const __bf16* __restrict__ 
   };
   if (GROUPS == 1 || nt > 0) copy_tile(0, 0);
   if (nt > 1) copy_tile(1, 1);
-  if (nt > 2) copy_tile(2, 2);
+  if (nt > 1) wait_tile_loads_except<2 * NDMA>();
+  else wait_tile_loads();
+  bf16x8 kf[KS], vf[KS];
+  read_fragments<D>(frag, lane, kf);
+  read_fragments<D>(frag + G::ROWS32, lane, vf);
   wait_tile_loads();
   __syncthreads();
+  if (nt > 2) copy_tile(2, 2);
 
   // One 32-row block through the plain path: everything in program order, masks applied.
   auto plain_block = [&](int blk) __attribute__((always_inline)) {
@@ -365,41 +364,34 @@ __device__ __forceinline__ void dkdv_keys(int block, const __bf16* __restrict__ 
   if constexpr (GROUPS == 2) {
     for (; t < nt_first; t++) __syncthreads();   // the second group has one tile fewer at times; all stages are free after this
     char* const give = smem + (group * 4 + w) * (DB * 4096);
-    const char* const take = smem + ((group ^ 1) * 4 + w) * (DB * 4096);
+    char* const take = smem + ((group ^ 1) * 4 + w) * (DB * 4096);   // the results pass through it too
 #pragma unroll
     for (int db = 0; db < DB; db++) lds_put_block(give + db * 4096, lane, group == 0 ? dkacc[db] : dvacc[db]);
     __syncthreads();
-    if (my_key < S) {
-      const TensorMap& m = group == 0 ? maps.dv : maps.dk;
-      __bf16* row = (group == 0 ? dv : dk) + head_offset(m, tc.bh, H) + (size_t)my_key * m.row;
-      const float f = group == 0 ? 1.f : scale;
+    const TensorMap& m = group == 0 ? maps.dv : maps.dk;
+    const float f = group == 0 ? 1.f : scale;
 #pragma unroll
-      for (int db = 0; db < DB; db++) {
-        const f32x16 x = lds_get_block(take + db * 4096, lane) + (group == 0 ? dvacc[db] : dkacc[db]);
+    for (int db = 0; db < DB; db++) {
+      f32x16 x = lds_get_block(take + db * 4096, lane) + (group == 0 ? dvacc[db] : dkacc[db]);
 #pragma unroll
-        for (int g = 0; g < 4; g++) {
-          const f32x4 y = {x[4 * g] * f, x[4 * g + 1] * f, x[4 * g + 2] * f, x[4 * g + 3] * f};
-          *reinterpret_cast<bf16x4*>(row + 32 * db + 8 * g + 4 * half) = __builtin_convertvector(y, bf16x4);
-        }
-      }
+      for (int e = 0; e < 16; e++) x[e] *= f;
+      put_rows<D>(take, lane, db, x);   // inside the blocks already taken
     }
+    store_rows<D>(take, lane, (group == 0 ? dv : dk) + head_offset(m, tc.bh, H) + (size_t)wave_kmin * m.row, m.row, S - wave_kmin);
     return;
   }
 
-  if (my_key < S) {
-    __bf16* dkrow = dk + head_offset(maps.dk, tc.bh, H) + (size_t)my_key * maps.dk.row;
-    __bf16* dvrow = dv + head_offset(maps.dv, tc.bh, H) + (size_t)my_key * maps.dv.row;
+  char* const out = smem + w * 2 * G::ROWS32;   // free since the last barrier
 #pragma unroll
-    for (int db = 0; db < DB; db++)
+  for (int db = 0; db < DB; db++) {
+    f32x16 x;
 #pragma unroll
-      for (int g = 0; g < 4; g++) {
-        f32x4 x, y;
-#pragma unroll
-        for (int e = 0; e < 4; e++) { x[e] = dkacc[db][4 * g + e] * scale; y[e] = dvacc[db][4 * g + e]; }
-        *reinterpret_cast<bf16x4*>(dkrow + 32 * db + 8 * g + 4 * half) = __builtin_convertvector(x, bf16x4);
-        *reinterpret_cast<bf16x4*>(dvrow + 32 * db + 8 * g + 4 * half) = __builtin_convertvector(y, bf16x4);
-      }
+    for (int e = 0; e < 16; e++) x[e] = dkacc[db][e] * scale;
+    put_rows<D>(out, lane, db, x);
+    put_rows<D>(out + G::ROWS32, lane, db, dvacc[db]);
   }
+  store_rows<D>(out, lane, dk + head_offset(maps.dk, tc.bh, H) + (size_t)wave_kmin * maps.dk.row, maps.dk.row, S - wave_kmin);
+  store_rows<D>(out + G::ROWS32, lane, dv + head_offset(maps.dv, tc.bh, H) + (size_t)wave_kmin * maps.dv.row, maps.dv.row, S - wave_kmin);
 }
 
 template <int D, bool CAUSAL, int GROUPS>

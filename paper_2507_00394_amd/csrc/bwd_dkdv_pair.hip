@@ -56,6 +56,7 @@ struct PG {
   static constexpr int NDMA = 3;                          // copy instructions per wave and block: Q piece, dO piece, one statistics row
 };
 static_assert(PG::LDS <= 160 * 1024, "LDS budget of a compute unit");
+static_assert(PG::AHEAD + 2 <= PG::NSTAGE && 4 * PG::BLOCK <= 2 * PG::PBYTES, "room for the fragments on their way to registers");
 static_assert(PG::NSTAGE * PG::BLOCK <= 65536, "a whole ring is within reach of the 16-bit offset field of an LDS instruction");
 
 // LDS byte offset of stage k inside a ring.
@@ -290,16 +291,12 @@ __device__ __forceinline__ void pair_sweep(const __bf16* __restrict__ q, const _
   const float c = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, scale * kLog2e)));
   const uint32_t base = lds_base(smem);
 
-  // B operand of this wave's first product: K fragments for A (S = Q K^T), V fragments for B (dP = dO V^T)
-  bf16x8 frag[KS];
-  {
-    const int row = my_key < S ? my_key : S - 1;
-    const __bf16* src = role == 0 ? kh + (size_t)row * maps.k.row : vh + (size_t)row * maps.v.row;
-#pragma unroll
-    for (int ks = 0; ks < KS; ks++) frag[ks] = *reinterpret_cast<const bf16x8*>(src + 16 * ks + 8 * half);
-#pragma unroll
-    for (int ks = 0; ks < KS; ks++) pin(frag[ks]);
-  }
+  // B operand of this wave's first product: K fragments for A (S = Q K^T), V fragments for B (dP = dO V^T).  They pass through the
+  // P buffers (A) and the last two stages of either ring (B), which the blocks copied first leave free.
+  const uint32_t frag_lds = base + (role == 0 ? G::PBUF + pair * G::BLOCK
+                                              : (pair < 2 ? G::QRING : G::GRING) + (G::AHEAD + (pair & 1)) * G::BLOCK);
+  if constexpr (role == 0) issue_fragments<D>(kh, maps.k.row, n0 + 32 * pair, S, lane, 0, frag_lds);
+  else issue_fragments<D>(vh, maps.v.row, n0 + 32 * pair, S, lane, 0, frag_lds);
   f32x16 acc[DB];   // dV^T (A) or dK^T (B) of this wave's 32 keys
 #pragma unroll
   for (int db = 0; db < DB; db++)
@@ -348,6 +345,10 @@ __device__ __forceinline__ void pair_sweep(const __bf16* __restrict__ q, const _
 #pragma unroll
   for (int i = 0; i < G::AHEAD; i++)
     if (i < nb) copy_block(i, stage_of(i));
+  if (nb >= G::AHEAD) wait_tile_loads_except<G::AHEAD * G::NDMA>();
+  else wait_tile_loads();
+  bf16x8 frag[KS];
+  read_fragments<D>(frag_lds, lane, frag);
   wait_tile_loads();
   __syncthreads();
 
@@ -527,20 +528,18 @@ __device__ __forceinline__ void pair_sweep(const __bf16* __restrict__ q, const _
 
   for (; i < nb; i++) plain_block(i);
 
-  if (my_key < S) {
-    const float m = role == 0 ? 1.f : scale;
-    __bf16* row = role == 0 ? dv + head_offset(maps.dv, tc.bh, H) + (size_t)my_key * maps.dv.row
-                            : dk + head_offset(maps.dk, tc.bh, H) + (size_t)my_key * maps.dk.row;
+  const float m = role == 0 ? 1.f : scale;
+  const TensorMap& map = role == 0 ? maps.dv : maps.dk;
+  const int key0 = n0 + 32 * pair;
+  char* const out = smem + w * G::BLOCK;   // free since the last barrier
 #pragma unroll
-    for (int db = 0; db < DB; db++)
+  for (int db = 0; db < DB; db++) {
+    f32x16 x;
 #pragma unroll
-      for (int g = 0; g < 4; g++) {
-        f32x4 x;
-#pragma unroll
-        for (int e = 0; e < 4; e++) x[e] = acc[db][4 * g + e] * m;
-        *reinterpret_cast<bf16x4*>(row + 32 * db + 8 * g + 4 * half) = __builtin_convertvector(x, bf16x4);
-      }
+    for (int e = 0; e < 16; e++) x[e] = acc[db][e] * m;
+    put_rows<D>(out, lane, db, x);
   }
+  store_rows<D>(out, lane, (role == 0 ? dv : dk) + head_offset(map, tc.bh, H) + (size_t)key0 * map.row, map.row, S - key0);
 }
 
 template <bool CAUSAL>

@@ -113,7 +113,7 @@ __device__ __forceinline__ void dq_half_step(const Copy& copy_tile, f32x16& s_cu
 }  // namespace
 
 template <int D>
-constexpr int kDqWholeLds = 4 * 2 * 64 * D * 2;
+constexpr int kDqWholeLds = 5 * 2 * 64 * D * 2;   // four stages; the Q and dO rows of a workgroup take one more
 inline int dq_tiles(int S, bool split) { return split ? (S + 127) / 128 : (S + 255) / 256; }
 
 template <int D, bool CAUSAL>
@@ -140,24 +140,6 @@ __device__ __forceinline__ void dq_whole_rows(int block, const __bf16* __restric
   const float c = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, scale * kLog2e)));
   const uint32_t base = lds_base(smem);
 
-  bf16x8 qf[KS], gf[KS];
-  float lse2;
-  f32x16 nd;     // -delta of this lane's query in every accumulator register
-  {
-    const int row = my_q < S ? my_q : S - 1;
-#pragma unroll
-    for (int ks = 0; ks < KS; ks++) {
-      qf[ks] = *reinterpret_cast<const bf16x8*>(qh + (size_t)row * maps.q.row + 16 * ks + 8 * half);
-      gf[ks] = *reinterpret_cast<const bf16x8*>(gh + (size_t)row * maps.dO.row + 16 * ks + 8 * half);
-    }
-    lse2 = lse2_all[(size_t)tc.bh * S + row];
-    const float dl = neg_delta[(size_t)tc.bh * S + row];
-#pragma unroll
-    for (int e = 0; e < 16; e++) nd[e] = dl;
-#pragma unroll
-    for (int ks = 0; ks < KS; ks++) { pin(qf[ks]); pin(gf[ks]); }
-    pin(lse2); pin(nd);
-  }
   f32x16 dqacc[DB];
 #pragma unroll
   for (int db = 0; db < DB; db++)
@@ -190,11 +172,28 @@ __device__ __forceinline__ void dq_whole_rows(int block, const __bf16* __restric
     __syncthreads();
     st = (st + 1) & 3;
   };
+  // the Q and dO rows of this wave pass through the stages behind the first; tiles 1 and 2 follow when every wave has them
+  const uint32_t frag = base + STAGE + w * 2 * HALF;
+  issue_fragments<D>(qh, maps.q.row, wave_qmin, S, lane, 0, frag);
+  issue_fragments<D>(gh, maps.dO.row, wave_qmin, S, lane, 0, frag + HALF);
   copy_tile(0, 0);
+  float lse2;
+  f32x16 nd;     // -delta of this lane's query in every accumulator register
+  {
+    const int row = my_q < S ? my_q : S - 1;
+    lse2 = lse2_all[(size_t)tc.bh * S + row];
+    const float dl = neg_delta[(size_t)tc.bh * S + row];
+#pragma unroll
+    for (int e = 0; e < 16; e++) nd[e] = dl;
+    pin(lse2); pin(nd);
+  }
+  wait_tile_loads();
+  bf16x8 qf[KS], gf[KS];
+  read_fragments<D>(frag, lane, qf);
+  read_fragments<D>(frag + HALF, lane, gf);
+  __syncthreads();
   if (n_tiles > 1) copy_tile(1, 1);
   if (n_tiles > 2) copy_tile(2, 2);
-  wait_tile_loads();
-  __syncthreads();
 
   // Lane addresses in stage 0: ab = row n, contraction step ks (K tile; the V tile is TILE
   // bytes further); at = transposing reads of the K tile.
@@ -222,6 +221,9 @@ __device__ __forceinline__ void dq_whole_rows(int block, const __bf16* __restric
 #pragma unroll
     for (int i = 0; i < kDqRing; i++) ring[i] = lds_b128(ab[i], TILE);
   }
+  if (n_tiles > 2) wait_tile_loads_except<NDMA>();   // tile 1 has landed
+  else wait_tile_loads();
+  __syncthreads();
 
   const auto no_copy = []() {};
   for (; j < n_w - 1; j++) {
@@ -291,18 +293,15 @@ __device__ __forceinline__ void dq_whole_rows(int block, const __bf16* __restric
     finish_tile();
   }
 
-  if (my_q < S) {
-    __bf16* row = dq + head_offset(maps.dq, tc.bh, H) + (size_t)my_q * maps.dq.row;
+  char* const out = smem + w * HALF;
 #pragma unroll
-    for (int db = 0; db < DB; db++)
+  for (int db = 0; db < DB; db++) {
+    f32x16 x;
 #pragma unroll
-      for (int g = 0; g < 4; g++) {
-        f32x4 x;
-#pragma unroll
-        for (int e = 0; e < 4; e++) x[e] = dqacc[db][4 * g + e] * scale;
-        *reinterpret_cast<bf16x4*>(row + 32 * db + 8 * g + 4 * half) = __builtin_convertvector(x, bf16x4);
-      }
+    for (int e = 0; e < 16; e++) x[e] = dqacc[db][e] * scale;
+    put_rows<D>(out, lane, db, x);
   }
+  store_rows<D>(out, lane, dq + head_offset(maps.dq, tc.bh, H) + (size_t)wave_qmin * maps.dq.row, maps.dq.row, S - wave_qmin);
 }
 
 // The dQ pass for grids that 256-row tiles cannot fill (split_rows in dispatch.hpp): 128 query rows per
@@ -339,24 +338,6 @@ __device__ __forceinline__ void dq_split_rows(int block, const __bf16* __restric
   const float c = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, scale * kLog2e)));
   const uint32_t base = lds_base(smem);
 
-  bf16x8 qf[KS], gf[KS];
-  float lse2;
-  f32x16 nd;     // -delta of this lane's query in every accumulator register
-  {
-    const int row = my_q < S ? my_q : S - 1;
-#pragma unroll
-    for (int ks = 0; ks < KS; ks++) {
-      qf[ks] = *reinterpret_cast<const bf16x8*>(qh + (size_t)row * maps.q.row + 16 * ks + 8 * half);
-      gf[ks] = *reinterpret_cast<const bf16x8*>(gh + (size_t)row * maps.dO.row + 16 * ks + 8 * half);
-    }
-    lse2 = lse2_all[(size_t)tc.bh * S + row];
-    const float dl = neg_delta[(size_t)tc.bh * S + row];
-#pragma unroll
-    for (int e = 0; e < 16; e++) nd[e] = dl;
-#pragma unroll
-    for (int ks = 0; ks < KS; ks++) { pin(qf[ks]); pin(gf[ks]); }
-    pin(lse2); pin(nd);
-  }
   f32x16 dqacc[DB];
 #pragma unroll
   for (int db = 0; db < DB; db++)
@@ -389,11 +370,33 @@ __device__ __forceinline__ void dq_split_rows(int block, const __bf16* __restric
     __syncthreads();
     st = plus(1);
   };
+  // the Q and dO rows pass through the last two stages, copied by one wave of a row group each; tile 3 follows when every
+  // wave has them
+  const uint32_t frag = base + 3 * STAGE + rg * 2 * HALF;
+  if (kg == 0) issue_fragments<D>(qh, maps.q.row, wave_qmin, S, lane, 0, frag);
+  else issue_fragments<D>(gh, maps.dO.row, wave_qmin, S, lane, 0, frag + HALF);
 #pragma unroll
-  for (int jj = 0; jj < AHEAD; jj++)
+  for (int jj = 0; jj < 3; jj++)
     if (jj < n_tiles) copy_tile(jj, jj);
+  float lse2;
+  f32x16 nd;     // -delta of this lane's query in every accumulator register
+  {
+    const int row = my_q < S ? my_q : S - 1;
+    lse2 = lse2_all[(size_t)tc.bh * S + row];
+    const float dl = neg_delta[(size_t)tc.bh * S + row];
+#pragma unroll
+    for (int e = 0; e < 16; e++) nd[e] = dl;
+    pin(lse2); pin(nd);
+  }
+  if (n_tiles > 2) wait_tile_loads_except<3 * NDMA>();
+  else wait_tile_loads();
+  __syncthreads();
+  bf16x8 qf[KS], gf[KS];
+  read_fragments<D>(frag, lane, qf);
+  read_fragments<D>(frag + HALF, lane, gf);
   wait_tile_loads();
   __syncthreads();
+  if (n_tiles > 3) copy_tile(3, 3);
 
   const uint32_t kbase = base + kg * HALF;
   uint32_t ab[KS], at[DB][2];
@@ -481,17 +484,16 @@ __device__ __forceinline__ void dq_split_rows(int block, const __bf16* __restric
     lds_put_block(smem + ((kg * 4 + rg) * HB + b) * 4096, lane, give);
   }
   __syncthreads();
-  if (my_q < S) {
-    __bf16* row = dq + head_offset(maps.dq, tc.bh, H) + (size_t)my_q * maps.dq.row + 32 * HB * kg;
+  char* const in = smem + ((kg ^ 1) * 4 + rg) * HB * 4096;   // what the other wave handed over; the results pass through it too
 #pragma unroll
-    for (int b = 0; b < HB; b++) {
-      f32x16 x = kg == 0 ? dqacc[b] : dqacc[HB + b];
-      const f32x16 got = lds_get_block(smem + (((kg ^ 1) * 4 + rg) * HB + b) * 4096, lane);
+  for (int b = 0; b < HB; b++) {
+    f32x16 x = kg == 0 ? dqacc[b] : dqacc[HB + b];
+    const f32x16 got = lds_get_block(in + b * 4096, lane);
 #pragma unroll
-      for (int e = 0; e < 16; e++) x[e] = (x[e] + got[e]) * scale;
-      store_block(row + 32 * b, half, x);
-    }
+    for (int e = 0; e < 16; e++) x[e] = (x[e] + got[e]) * scale;
+    put_rows<32 * HB>(in, lane, b, x);   // inside the blocks already taken
   }
+  store_rows<32 * HB>(in, lane, dq + head_offset(maps.dq, tc.bh, H) + (size_t)wave_qmin * maps.dq.row + 32 * HB * kg, maps.dq.row, S - wave_qmin);
 }
 
 }  // namespace helix

@@ -207,16 +207,6 @@ fwd_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __b
   const float c = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, scale * kLog2e)));
   const uint32_t base = lds_base(smem);
 
-  bf16x8 qf[KS];
-  {
-    const int row = my_q < S ? my_q : S - 1;
-#pragma unroll
-    for (int ks = 0; ks < KS; ks++)
-      qf[ks] = *reinterpret_cast<const bf16x8*>(qh + (size_t)row * maps.q.row + 16 * ks + 8 * half);
-#pragma unroll
-    for (int ks = 0; ks < KS; ks++) pin(qf[ks]);
-  }
-
   f32x16 oacc[DB];
 #pragma unroll
   for (int db = 0; db < DB; db++)
@@ -236,12 +226,19 @@ fwd_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __b
 
   const TileLoader<D, BN, 8> kload(lane, w, maps.k.row), vload(lane, w, maps.v.row);
   constexpr int NDMA = decltype(kload)::N + decltype(vload)::N;   // copy instructions per wave and tile: what copy_ahead() issues
+  // the Q rows of this wave pass through the last two K or V buffers; tile 2 follows when every wave has them
+  const uint32_t frag = base + (w < 4 ? 0 : VREGION) + 2 * TILE + (w & 3) * HALF;
+  issue_fragments<D>(qh, maps.q.row, wave_qmin, S, lane, 0, frag);
   kload.issue(kh, 0, S, base);
   vload.issue(vh, 0, S, base + VREGION);
   if (n_tiles > 1) { kload.issue(kh, BN, S, base + TILE); vload.issue(vh, BN, S, base + VREGION + TILE); }
-  if (n_tiles > 2) { kload.issue(kh, 2 * BN, S, base + 2 * TILE); vload.issue(vh, 2 * BN, S, base + VREGION + 2 * TILE); }
+  if (n_tiles > 1) wait_tile_loads_except<2 * NDMA>();
+  else wait_tile_loads();
+  bf16x8 qf[KS];
+  read_fragments<D>(frag, lane, qf);
   wait_tile_loads();
   __syncthreads();
+  if (n_tiles > 2) { kload.issue(kh, 2 * BN, S, base + 2 * TILE); vload.issue(vh, 2 * BN, S, base + VREGION + 2 * TILE); }
 
   const FwdLaneAddr<D> la(lane);
   // Lane addresses: klo = contraction steps 0..KS/2-1 of the K tile the NEXT block comes from,
@@ -357,19 +354,16 @@ fwd_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __b
   // epilogue: normalise, store O (bf16) and LSE (natural log, scale included)
   const float ltot = half_sum(st.lsum[0] + st.lsum[1]);
   const float inv = 1.f / ltot;
-  if (my_q < S) {
-    __bf16* orow = o + head_offset(maps.o, tc.bh, H) + (size_t)my_q * maps.o.row;
+  char* const out = smem + w * HALF;
 #pragma unroll
-    for (int db = 0; db < DB; db++)
+  for (int db = 0; db < DB; db++) {
+    f32x16 x;
 #pragma unroll
-      for (int g = 0; g < 4; g++) {
-        f32x4 x;
-#pragma unroll
-        for (int e = 0; e < 4; e++) x[e] = oacc[db][4 * g + e] * inv;
-        *reinterpret_cast<bf16x4*>(orow + 32 * db + 8 * g + 4 * half) = __builtin_convertvector(x, bf16x4);
-      }
-    if (half == 0) lse[(size_t)tc.bh * S + my_q] = st.mref_c * kLn2 + __logf(ltot);
+    for (int e = 0; e < 16; e++) x[e] = oacc[db][e] * inv;
+    put_rows<D>(out, lane, db, x);
   }
+  if (half == 0 && my_q < S) lse[(size_t)tc.bh * S + my_q] = st.mref_c * kLn2 + __logf(ltot);
+  store_rows<D>(out, lane, o + head_offset(maps.o, tc.bh, H) + (size_t)wave_qmin * maps.o.row, maps.o.row, S - wave_qmin);
 }
 
 // The forward for grids that 256-row tiles cannot fill (split_forward in dispatch.hpp says which): a workgroup owns
@@ -420,15 +414,9 @@ fwd_split_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, con
     vload.issue(vh, jj * BN, S, base + VREGION + buf * TILE);
   };
 
-  bf16x8 qf[KS];
-  {
-    const int row = my_q < S ? my_q : S - 1;
-#pragma unroll
-    for (int ks = 0; ks < KS; ks++)
-      qf[ks] = *reinterpret_cast<const bf16x8*>(qh + (size_t)row * maps.q.row + 16 * ks + 8 * half);
-#pragma unroll
-    for (int ks = 0; ks < KS; ks++) pin(qf[ks]);
-  }
+  // the Q rows pass through the last buffer, K first, then V; a row group's two waves copy one half each
+  const uint32_t frag = base + (rg < 2 ? 0 : VREGION) + AHEAD * TILE + (rg & 1) * HALF;
+  issue_fragments<D, 2>(qh, maps.q.row, wave_qmin, S, lane, kg, frag);
 #pragma unroll
   for (int jj = 0; jj < AHEAD; jj++)
     if (jj < n_tiles) copy_tile(jj, jj);
@@ -448,6 +436,11 @@ fwd_split_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, con
   const int n_w = wave_qmin < S ? (k_end - 32 * kg + BN - 1) / BN : 0;              // (numerators are >= 0: k_end >= 1, k_all >= 1)
   const int n_full = (k_all + 32 - 32 * kg) / BN;
 
+  if (n_tiles >= AHEAD) wait_tile_loads_except<AHEAD * NDMA>();
+  else wait_tile_loads();
+  __syncthreads();
+  bf16x8 qf[KS];
+  read_fragments<D>(frag, lane, qf);
   wait_tile_loads();
   __syncthreads();
 
@@ -549,7 +542,7 @@ fwd_split_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, con
   stats[(w * 64 + lane) * 2] = st.mref_c;
   stats[(w * 64 + lane) * 2 + 1] = l_own;
   __syncthreads();
-  if (my_q < S) {
+  {
     const float m_other = stats[((w ^ 4) * 64 + lane) * 2], l_other = stats[((w ^ 4) * 64 + lane) * 2 + 1];
     const float m = fmaxf(st.mref_c, m_other);
     const bool second = (CAUSAL ? my_q : S - 1) >= 32;
@@ -558,17 +551,18 @@ fwd_split_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, con
     const float a_other = other ? __builtin_amdgcn_exp2f(m_other - m) : 0.f;
     const float ltot = (own ? l_own * a_own : 0.f) + (other ? l_other * a_other : 0.f);
     const float inv = 1.f / ltot;
-    __bf16* orow = o + head_offset(maps.o, tc.bh, H) + (size_t)my_q * maps.o.row + 32 * HB * kg;
+    char* const in = smem + ((kg ^ 1) * 4 + rg) * HB * 4096;   // what the other wave handed over; the results pass through it too
 #pragma unroll
     for (int b = 0; b < HB; b++) {
       const f32x16 mine = kg == 0 ? oacc[b] : oacc[HB + b];
-      const f32x16 got = lds_get_block(smem + (((kg ^ 1) * 4 + rg) * HB + b) * 4096, lane);
+      const f32x16 got = lds_get_block(in + b * 4096, lane);
       f32x16 x;
 #pragma unroll
       for (int e = 0; e < 16; e++) x[e] = ((own ? mine[e] * a_own : 0.f) + (other ? got[e] * a_other : 0.f)) * inv;
-      store_block(orow + 32 * b, half, x);
+      put_rows<32 * HB>(in, lane, b, x);   // block b takes no more than the first b + 1 blocks
     }
-    if (half == 0 && kg == 0) lse[(size_t)tc.bh * S + my_q] = m * kLn2 + __logf(ltot);
+    if (half == 0 && kg == 0 && my_q < S) lse[(size_t)tc.bh * S + my_q] = m * kLn2 + __logf(ltot);
+    store_rows<32 * HB>(in, lane, o + head_offset(maps.o, tc.bh, H) + (size_t)wave_qmin * maps.o.row + 32 * HB * kg, maps.o.row, S - wave_qmin);
   }
 }
 

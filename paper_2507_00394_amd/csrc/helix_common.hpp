@@ -188,10 +188,17 @@ __device__ __forceinline__ uint32_t pack_bf16_pair(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2));
 }
 
-// Stores one 32 x 32 accumulator block as bf16: the lane owns a row, its registers 4g..4g+3 are the columns
-// 8g + 4*half .. +3 (half = lane / 32).  The two lanes of a row exchange halves of two groups, so that each
-// stores 16 consecutive bytes.
-__device__ __forceinline__ void store_block(__bf16* row, int half, const f32x16& acc) {
+// Forces a value loaded from global memory to be complete at this point of the program.
+// Without it the compiler sinks such loads below the asynchronous tile copies and then
+// waits for both together in the middle of the main loop.
+template <typename T>
+__device__ __forceinline__ void pin(T& x) { asm volatile("" : "+v"(x)); }
+
+// One 32 x 32 accumulator block as bf16: the lane owns a row, its registers 4g..4g+3 are the columns 8g + 4*half .. +3
+// (half = lane / 32).  The two lanes of a row exchange halves of two groups, so that each holds 16 consecutive bytes:
+// put(chunk, x) takes the 8 columns from 8*chunk on.
+template <typename Put>
+__device__ __forceinline__ void for_each_chunk(int half, const f32x16& acc, Put&& put) {
 #pragma unroll
   for (int g = 0; g < 4; g += 2) {
     const auto lo = __builtin_amdgcn_permlane32_swap(pack_bf16_pair(acc[4 * g], acc[4 * g + 1]),
@@ -199,7 +206,36 @@ __device__ __forceinline__ void store_block(__bf16* row, int half, const f32x16&
     const auto hi = __builtin_amdgcn_permlane32_swap(pack_bf16_pair(acc[4 * g + 2], acc[4 * g + 3]),
                                                      pack_bf16_pair(acc[4 * g + 6], acc[4 * g + 7]), false, false);
     const u32x4 x = {lo[0], hi[0], lo[1], hi[1]};
-    *reinterpret_cast<u32x4*>(row + 8 * (g + half)) = x;
+    put(g + half, x);
+  }
+}
+__device__ __forceinline__ void store_block(__bf16* row, int half, const f32x16& acc) {
+  for_each_chunk(half, acc, [&](int chunk, const u32x4& x) __attribute__((always_inline)) { *reinterpret_cast<u32x4*>(row + 8 * chunk) = x; });
+}
+
+// What a wave loads before its sweep and stores after it are 32 rows of a tensor with a lane to a row: read or written from
+// the lanes directly, an instruction touches 32 or 64 rows with 16 or 8 bytes each, and the address unit takes a cycle for each of
+// them - 64 to 128 of them a workgroup, 2 to 6 us in which the compute unit does nothing else.  Both go through LDS instead,
+// as whole rows in pieces of 1 KB.
+//
+// Results: the wave's own 32 x W tile of LDS (W bf16 columns), filled block by block and stored by store_rows.  `rows` of the 32
+// exist.  Only this wave touches the tile, and its LDS operations complete in order, so there is no barrier.  (The lane is pinned
+// so that the addresses are computed here: the compiler would keep those of the sweep's operands for them, 8 registers.)
+template <int W>
+__device__ __forceinline__ void put_rows(char* tile, int lane, int block, const f32x16& acc) {
+  pin(lane);
+  for_each_chunk(lane >> 5, acc, [&](int chunk, const u32x4& x) __attribute__((always_inline)) {
+    *reinterpret_cast<u32x4*>(tile + lds_chunk_off<W>(lane & 31, 4 * block + chunk)) = x;
+  });
+}
+template <int W>
+__device__ __forceinline__ void store_rows(const char* tile, int lane, __bf16* row0, int row_stride, int rows) {
+  constexpr int CH = W / 8, PER = 64 / CH;   // chunks of a row, rows of a piece
+#pragma unroll
+  for (int i = 0; i < 32 / PER; i++) {
+    const int r = i * PER + lane / CH, chunk = lane % CH;
+    const u32x4 x = *reinterpret_cast<const u32x4*>(tile + lds_chunk_off<W>(r, chunk));
+    if (r < rows) *reinterpret_cast<u32x4*>(row0 + (size_t)r * row_stride + 8 * chunk) = x;
   }
 }
 
@@ -222,11 +258,21 @@ __device__ __forceinline__ f32x16 lds_get_block(const char* p, int lane) {
   return x;
 }
 
-// Forces a value loaded from global memory to be complete at this point of the program.
-// Without it the compiler sinks such loads below the asynchronous tile copies and then
-// waits for both together in the middle of the main loop.
-template <typename T>
-__device__ __forceinline__ void pin(T& x) { asm volatile("" : "+v"(x)); }
+// Fragments of 32 rows (B operands kept in registers for the whole sweep), through 32 * D * 2 bytes of LDS: issue_fragments
+// copies the rows from row0 on asynchronously (SHARE waves, `part` of them this one, take the pieces in turn), read_fragments takes
+// them once they have landed.  Rows past the end are the last row, as in TileLoader.
+template <int D, int SHARE = 1>
+__device__ __forceinline__ void issue_fragments(const __bf16* head_base, int row_stride, int row0, int nrows, int lane, int part, uint32_t lds) {
+  const TileLoader<D, 32, SHARE> load(lane, part, row_stride);
+  load.issue(head_base, row0 < nrows ? row0 : nrows - 1, nrows, lds);
+}
+template <int D>
+__device__ __forceinline__ void read_fragments(uint32_t lds, int lane, bf16x8 (&f)[D / 16]) {
+#pragma unroll
+  for (int ks = 0; ks < D / 16; ks++) f[ks] = lds_b128(lds + lds_chunk_off<D>(lane & 31, 2 * ks + (lane >> 5)));
+#pragma unroll
+  for (int ks = 0; ks < D / 16; ks++) pin(f[ks]);   // all of them are in registers: the LDS is free for this wave
+}
 
 // MFMA operand whose 8 contraction slots are contiguous in memory: row `row`, elements
 // 16*ks + 8*half .. +7 of a swizzled LDS tile.
