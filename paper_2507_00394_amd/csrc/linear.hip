@@ -128,12 +128,37 @@ struct TransposedOperand {
   __device__ __forceinline__ static bf16x8 read(const uint32_t (&a)[NADDR], int ks) { return lds_tr_pair(a[0], a[1], ks * 16 * W * 2); }
 };
 
-// The fp32 counterpart of store_block in helix_common.hpp.
-__device__ __forceinline__ void store_block(float* row, int half, const f32x16& acc) {
+// The fp32 counterparts of put_rows and store_rows in helix_common.hpp: 32 rows of W floats in this wave's own LDS, 16-byte
+// chunks permuted by the row so that neither access has bank conflicts.
+template <int W>
+__device__ __forceinline__ int float_chunk_off(int row, int chunk) {
+  return row * (W * 4) + ((chunk ^ (W == 32 ? (row >> 1) & 7 : row & 15)) << 4);
+}
+template <int W>
+__device__ __forceinline__ void put_rows(char* tile, int lane, int block, const f32x16& acc, float) {
+  pin(lane);
 #pragma unroll
   for (int g = 0; g < 4; g++) {
     const f32x4 x = {acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]};
-    *reinterpret_cast<f32x4*>(row + 8 * g + 4 * half) = x;
+    *reinterpret_cast<f32x4*>(tile + float_chunk_off<W>(lane & 31, 8 * block + 2 * g + (lane >> 5))) = x;
+  }
+}
+template <int W>
+__device__ __forceinline__ void put_rows(char* tile, int lane, int block, const f32x16& acc, __bf16) { helix::put_rows<W>(tile, lane, block, acc); }
+// Stores the tile; `rows` of its rows and `cols` of its columns (a multiple of 32) exist.
+template <int W, typename T>
+__device__ __forceinline__ void store_rows(const char* tile, int lane, T* row0, long long row_stride, int rows, int cols) {
+  constexpr int PER_CHUNK = 16 / sizeof(T), CH = W / PER_CHUNK, PER = 64 / CH;   // elements of a chunk, chunks of a row, rows of a piece
+  pin(lane);
+  const int r0 = lane / CH, chunk = lane % CH;
+  const uint32_t lane_off = (uint32_t)(r0 * (int)row_stride + chunk * PER_CHUNK) * (uint32_t)sizeof(T);   // below 2^30: the row pitch is bounded
+#pragma unroll
+  for (int i = 0; i < 32 / PER; i++) {
+    const int r = i * PER + r0;
+    const int off = sizeof(T) == 4 ? float_chunk_off<W>(r, chunk) : lds_chunk_off<W>(r, chunk);
+    const u32x4 x = *reinterpret_cast<const u32x4*>(tile + off);
+    char* const rows_i = const_cast<char*>(uniform_ptr(reinterpret_cast<const char*>(row0 + (size_t)(i * PER) * row_stride)));
+    if (r < rows && chunk * PER_CHUNK < cols) *reinterpret_cast<u32x4*>(rows_i + lane_off) = x;
   }
 }
 // All but the N newest vector memory operations of this wave are done, and every wave of the workgroup has got here.
@@ -277,18 +302,27 @@ gemm_kernel(const __bf16* __restrict__ X, long long ldx, const __bf16* __restric
     stage_barrier<0>();
   }
 
-  // lane owns row i of C
-  const int half = lane >> 5, n = lane & 31;
+  // A lane owns row i of C: 32 rows at a time go through LDS (free since the last barrier), this wave's part of it, and leave as whole
+  // rows.  Stored from the lanes, 16 bytes of 32 or 64 rows an instruction, a 256 x 256 tile takes 4 to 5 us (fp32 7) in which the
+  // compute unit has nothing else to do, of 21 us for a contraction of 768.
+  if constexpr (BI * BJ == 16) {   // 256 sums stay in accumulator registers: moved to the others all at once, they push the lane's index out to memory
+#pragma unroll
+    for (int jb = 0; jb < BJ; jb++)
+#pragma unroll
+      for (int ib = 0; ib < BI; ib++) asm volatile("" : "+a"(acc[jb][ib]));
+  }
+  constexpr int W = 32 * BJ;
+  char* const out = smem + w * (32 * W * (int)sizeof(OutT));
+  const int i_wave = i0 + 32 * BI * wi, j_wave = j0 + W * wj;
 #pragma unroll
   for (int ib = 0; ib < BI; ib++) {
-    const int i = i0 + 32 * (BI * wi + ib) + n;
-    if (i >= I) continue;
-    OutT* row = C + (size_t)i * ldc;
 #pragma unroll
     for (int jb = 0; jb < BJ; jb++) {
-      const int j = j0 + 32 * (BJ * wj + jb);
-      if (j < J) store_block(row + j, half, acc[jb][ib]);   // J is a multiple of 128
+      put_rows<W>(out, lane, jb, acc[jb][ib], OutT());
+      __builtin_amdgcn_sched_barrier(0);   // keeps the registers of one block in flight, not of all
     }
+    store_rows<W>(out, lane, C + (size_t)(i_wave + 32 * ib) * ldc + j_wave, ldc, I - i_wave - 32 * ib, J - j_wave);
+    __builtin_amdgcn_sched_barrier(0);
   }
 }
 
