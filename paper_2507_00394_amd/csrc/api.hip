@@ -287,11 +287,7 @@ int helix_qkv_linear_bwd(const void* a, long long lda, const void* w, long long 
   if (!workspace) return HELIX_ERR_NULL_POINTER;
   if (!aligned(workspace, 256)) return HELIX_ERR_MISALIGNED;
   if (workspace_bytes < helix_qkv_linear_bwd_workspace_bytes(M, K, N)) return HELIX_ERR_WORKSPACE;
-  char* ws = static_cast<char*>(workspace);
-  HELIX_TRY(launched(helix::launch_linear_bwd_input(dqkv, lddqkv, w, ldw, da, ldda, ws, M, K, N, (hipStream_t)stream)));
-  return launched(helix::launch_linear_bwd_weight(a, lda, dqkv, lddqkv, dw, lddw,
-                                                  reinterpret_cast<float*>(ws + helix::linear_bwd_wt_bytes(K, N)), M, K, N,
-                                                  (hipStream_t)stream));
+  return launched(helix::launch_linear_bwd(a, lda, w, ldw, dqkv, lddqkv, da, ldda, dw, lddw, workspace, M, K, N, (hipStream_t)stream));
 }
 
 int helix_mfma_probe(float* sink, int workgroups, int iters, int random_operands, long long* flops, void* stream) {

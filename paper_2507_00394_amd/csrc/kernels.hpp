@@ -66,14 +66,10 @@ hipError_t launch_bwd_dkdv_dq_pair(const void* q, const void* k, const void* v, 
 // ld*: elements between consecutive rows.
 hipError_t launch_linear_fwd(const void* a, long long lda, const void* w, long long ldw, void* out, long long ldo,
                              int M, int K, int N, hipStream_t stream);
-// The backward's workspace (linear_bwd_workspace_bytes) holds w^T in its first linear_bwd_wt_bytes(K, N)
-// bytes and the partial weight gradients after them.
+// The backward's workspace (linear_bwd_workspace_bytes) holds w^T and after it the partial weight gradients.
 size_t linear_bwd_workspace_bytes(int M, int K, int N);
-size_t linear_bwd_wt_bytes(int K, int N);
-hipError_t launch_linear_bwd_input(const void* dout, long long ldd, const void* w, long long ldw, void* da, long long lda,
-                                   void* wt, int M, int K, int N, hipStream_t stream);
-hipError_t launch_linear_bwd_weight(const void* a, long long lda, const void* dout, long long ldd, float* dw, long long ldw,
-                                    float* workspace, int M, int K, int N, hipStream_t stream);
+hipError_t launch_linear_bwd(const void* a, long long lda, const void* w, long long ldw, const void* dout, long long ldd, void* da,
+                             long long ldda, float* dw, long long lddw, void* workspace, int M, int K, int N, hipStream_t stream);
 
 // Pure MFMA loop (mfma_probe.hip): `workgroups` x 8 waves x `iters` x 16 independent 32x32x16 bf16 MFMAs.
 long long mfma_probe_flops(int workgroups, int iters);

@@ -8,7 +8,7 @@
 //   backward input   da[M][K]  = dqkv[M][N] * w[K][N]^T    X stored [i][r],  Y stored [r][j] after a transposing copy of w
 //   backward weight  dw[K][N]  = a[M][K]^T  * dqkv[M][N]   X stored [r][i],  Y stored [r][j]
 //
-// A workgroup of 4 waves owns a 256 x 256, 128 x 128 or 64 x 64 tile of C (pick_tile says which: a
+// A workgroup of 4 waves owns a 256 x 256, 128 x 128 or 64 x 64 tile of C (pick_tile and pick_tiles say which: a
 // large tile reads less per MFMA, a small one fills the chip when C is small); wave (wi, wj) owns a quarter of
 // it as accumulator blocks of the 32x32x16 MFMA (256 accumulator registers and one wave per SIMD for the large
 // tile), computed transposed (the MFMA's row index is j) so that a lane owns one row i of C and stores
@@ -26,6 +26,8 @@
 // da 1853 -> 1570, dw 1785 -> 1578.
 #include "helix_common.hpp"
 #include "kernels.hpp"
+#include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 namespace helix {
@@ -43,6 +45,7 @@ struct Tile {
   static constexpr int STAGE = XBYTES + YBYTES;
   static constexpr int AHEAD = NST - 1;              // a stage's copy is issued this many iterations before its use
   static constexpr int LDS = NST * STAGE;
+  static constexpr int WORKGROUPS = LDS > 80 * 1024 ? 1 : 2;   // on a compute unit
 };
 using Tile256 = Tile<256, 256, 32, 5>;        // 160 KB of LDS: one workgroup per compute unit
 using Tile128 = Tile<128, 128, 32, 5>;        // 80 KB: two
@@ -162,7 +165,8 @@ __device__ __forceinline__ void store_rows(const char* tile, int lane, T* row0, 
   }
 }
 // All but the N newest vector memory operations of this wave are done, and every wave of the workgroup has got here.
-// LDS reads may stay in flight across it: the reads of a stage are consumed by MFMAs of that stage's own iteration.
+// LDS reads may stay in flight across it: the reads of a stage are consumed by MFMAs of that stage's own iteration, and
+// its buffer is not copied into before the one after.
 template <int N>
 __device__ __forceinline__ void stage_barrier() {
   wait_tile_loads_except<N>();
@@ -171,11 +175,20 @@ __device__ __forceinline__ void stage_barrier() {
 
 }  // namespace
 
+// One product C = X Y, with its tiles and the parts its contraction is cut into.
+template <typename OutT>
+struct Gemm {
+  const __bf16 *X, *Y;
+  OutT* C;
+  long long ldx, ldy, ldc, part_stride;   // a part's partial result goes to C + part * part_stride
+  int I, J, R, tiles_i, tiles_j, parts, r_per_part;
+  // Workgroups of a part: all tiles, rounded up so that the XCD of a workgroup is its number mod 8 in every part.
+  __host__ __device__ int blocks_per_part() const { return (tiles_i * tiles_j + 7) & ~7; }
+};
+
+// The tile of workgroup `block`.
 template <typename G, bool X_ROWS_ARE_R, bool Y_ROWS_ARE_R, typename OutT>
-__global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(G::LDS > 80 * 1024 ? 1 : 2, G::LDS > 80 * 1024 ? 1 : 2)))
-gemm_kernel(const __bf16* __restrict__ X, long long ldx, const __bf16* __restrict__ Y, long long ldy,
-            OutT* __restrict__ C, long long ldc, int I, int J, int R, int tiles_i, int tiles_j,
-            int r_per_part, long long part_stride) {
+__device__ __forceinline__ void gemm_block(int block, const Gemm<OutT>& g) {
   using XOp = typename std::conditional<X_ROWS_ARE_R, TransposedOperand<G::TI, G::STEP>, ContiguousOperand<G::TI, G::STEP>>::type;
   using YOp = typename std::conditional<Y_ROWS_ARE_R, TransposedOperand<G::TJ, G::STEP>, ContiguousOperand<G::TJ, G::STEP>>::type;
   constexpr int BI = G::BI, BJ = G::BJ, NS = G::STEP / 16, AHEAD = G::AHEAD, NST = G::NST, STAGE = G::STAGE;
@@ -183,22 +196,21 @@ gemm_kernel(const __bf16* __restrict__ X, long long ldx, const __bf16* __restric
 
   // workgroup id mod 8 is the XCD: each XCD takes a contiguous run of tiles, all column tiles of a row tile
   // one after the other, so an X panel reaches one L2 only
-  const int total = tiles_i * tiles_j, share = (total + 7) >> 3;
-  const int t = (blockIdx.x & 7) * share + (blockIdx.x >> 3);
-  if (t >= total) return;
-  const int ti = t / tiles_j, tj = t - ti * tiles_j;
+  const int per_part = g.blocks_per_part();
+  const int part = block / per_part, n = block - part * per_part;
+  const int t = (n & 7) * (per_part >> 3) + (n >> 3);
+  if (t >= g.tiles_i * g.tiles_j) return;
+  const int ti = t / g.tiles_j, tj = t - ti * g.tiles_j;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wi = w & 1, wj = w >> 1;
   const int i0 = ti * G::TI, j0 = tj * G::TJ;
   const uint32_t base = lds_base(smem);
 
-  // blockIdx.y selects a part of the contraction range; its partial result goes to C + y * part_stride
-  const int r_begin = blockIdx.y * r_per_part;
-  const int nk = ((R - r_begin < r_per_part ? R - r_begin : r_per_part)) / G::STEP;
-  C += (size_t)blockIdx.y * part_stride;
-  XOp xsrc(X, ldx, i0, I, r_begin, lane, w);
-  YOp ysrc(Y, ldy, j0, J, r_begin, lane, w);
+  const int r_begin = part * g.r_per_part;
+  const int nk = ((g.R - r_begin < g.r_per_part ? g.R - r_begin : g.r_per_part)) / G::STEP;
+  XOp xsrc(g.X, g.ldx, i0, g.I, r_begin, lane, w);
+  YOp ysrc(g.Y, g.ldy, j0, g.J, r_begin, lane, w);
   constexpr int NDMA = XOp::DMA + YOp::DMA;
   auto copy = [&](int n, uint32_t lds) __attribute__((always_inline)) {   // copy instruction n of the next stage
     if (n < XOp::DMA) xsrc.copy(n, lds);
@@ -238,15 +250,22 @@ gemm_kernel(const __bf16* __restrict__ X, long long ldx, const __bf16* __restric
 #pragma unroll
       for (int e = 0; e < 16; e++) acc[jb][ib][e] = 0.f;
 
-  bf16x8 xo[2][BI], yo[2][BJ];   // [sub-step parity][block]
+  // Operands are read a sub-step ahead into the other of two sets.  With a single MFMA to a sub-step (the 64 x 64 tile) that is not
+  // ahead enough: there a set for every sub-step is refilled behind its MFMA, a whole stage ahead (64 tokens x 2048 x 768 forward
+  // 8.8 -> 7.8 us; the larger tiles lose 5 to 10 % that way, by 14 registers more and reads in bursts).
+  constexpr bool STAGE_AHEAD = BI * BJ == 1;
+  constexpr int SETS = STAGE_AHEAD ? NS : 2;
+  bf16x8 xo[SETS][BI], yo[SETS][BJ];
 #pragma unroll
-  for (int b = 0; b < BI; b++) xo[0][b] = XOp::read(xa[b], 0);
+  for (int ks = 0; ks < (STAGE_AHEAD ? NS : 1); ks++) {
 #pragma unroll
-  for (int b = 0; b < BJ; b++) yo[0][b] = YOp::read(ya[b], 0);
+    for (int b = 0; b < BI; b++) xo[ks][b] = XOp::read(xa[b], ks);
+#pragma unroll
+    for (int b = 0; b < BJ; b++) yo[ks][b] = YOp::read(ya[b], ks);
+  }
 
-  // One stage: NS sub-steps of BI * BJ MFMAs; behind each MFMA its share of the operand reads of the next
-  // sub-step ((k, ks+1), in the last one (k+1, 0) from the next buffer) and of the copies of stage k + AHEAD,
-  // which replaces stage k - 1.
+  // One stage: NS sub-steps of BI * BJ MFMAs; behind each MFMA its share of the operand reads (of the next sub-step, in the last one from
+  // the next buffer; or of the same sub-step of the next stage) and of the copies of stage k + AHEAD, which replaces stage k - 1.
   int buf = 0;
   auto stage = [&](auto copying) __attribute__((always_inline)) {
     constexpr bool COPY = decltype(copying)::value;
@@ -255,7 +274,7 @@ gemm_kernel(const __bf16* __restrict__ X, long long ldx, const __bf16* __restric
     const uint32_t dst = base + (buf == 0 ? NST - 1 : buf - 1) * STAGE;
 #pragma unroll
     for (int ks = 0; ks < NS; ks++) {
-      if (ks == NS - 1) {
+      if (ks == (STAGE_AHEAD ? 0 : NS - 1)) {
 #pragma unroll
         for (int b = 0; b < BI; b++)
 #pragma unroll
@@ -267,14 +286,15 @@ gemm_kernel(const __bf16* __restrict__ X, long long ldx, const __bf16* __restric
       }
 #pragma unroll
       for (int m = 0; m < MM; m++) {
-        const int jb = m / BI, ib = m % BI;
-        acc[jb][ib] = mfma32(yo[ks & 1][jb], xo[ks & 1][ib], acc[jb][ib]);
+        const int jb = m / BI, ib = m % BI, set = STAGE_AHEAD ? ks : ks & 1;
+        acc[jb][ib] = mfma32(yo[set][jb], xo[set][ib], acc[jb][ib]);
         // reads go behind the first MFMAs of a sub-step, one each where there are enough of them
+        const int to = STAGE_AHEAD ? ks : (ks & 1) ^ 1, next_ks = STAGE_AHEAD ? ks : (ks + 1) % NS;
 #pragma unroll
         for (int q = 0; q < READS; q++) {
           if ((MM >= READS ? q : q * MM / READS) != m) continue;
-          if (q < BI) xo[(ks & 1) ^ 1][q] = XOp::read(xa[q], (ks + 1) % NS);
-          else yo[(ks & 1) ^ 1][q - BI] = YOp::read(ya[q - BI], (ks + 1) % NS);
+          if (q < BI) xo[to][q] = XOp::read(xa[q], next_ks);
+          else yo[to][q - BI] = YOp::read(ya[q - BI], next_ks);
         }
         if constexpr (COPY) {
 #pragma unroll
@@ -321,9 +341,26 @@ gemm_kernel(const __bf16* __restrict__ X, long long ldx, const __bf16* __restric
       put_rows<W>(out, lane, jb, acc[jb][ib], OutT());
       __builtin_amdgcn_sched_barrier(0);   // keeps the registers of one block in flight, not of all
     }
-    store_rows<W>(out, lane, C + (size_t)(i_wave + 32 * ib) * ldc + j_wave, ldc, I - i_wave - 32 * ib, J - j_wave);
+    store_rows<W>(out, lane, g.C + (size_t)part * g.part_stride + (size_t)(i_wave + 32 * ib) * g.ldc + j_wave, g.ldc,
+                  g.I - i_wave - 32 * ib, g.J - j_wave);
     __builtin_amdgcn_sched_barrier(0);
   }
+}
+
+template <typename G, bool X_ROWS_ARE_R, bool Y_ROWS_ARE_R, typename OutT>
+__global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(G::WORKGROUPS, G::WORKGROUPS)))
+gemm_kernel(Gemm<OutT> g) {
+  gemm_block<G, X_ROWS_ARE_R, Y_ROWS_ARE_R, OutT>(blockIdx.x, g);
+}
+
+// Both gradients in one launch (see launch_linear_bwd): the first `weight_blocks` workgroups take the weight gradient.
+template <typename GI, bool WT, typename GW>
+__global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(GI::WORKGROUPS, GI::WORKGROUPS)))
+linear_bwd_kernel(Gemm<__bf16> input, Gemm<float> weight, int weight_blocks) {
+  static_assert(GI::WORKGROUPS == GW::WORKGROUPS, "tiles that share a compute unit alike");
+  const int block = (int)blockIdx.x;
+  if (block < weight_blocks) gemm_block<GW, true, true, float>(block, weight);
+  else gemm_block<GI, false, WT, __bf16>(block - weight_blocks, input);
 }
 
 // dst[e] = sum over `parts` slabs of src, `n` elements each (n a multiple of 4).
@@ -339,61 +376,89 @@ __global__ void __launch_bounds__(256) sum_parts_kernel(const float* __restrict_
   *reinterpret_cast<f32x4*>(dst + (size_t)r * ld_dst + c) = acc;
 }
 
+template <typename G, typename OutT>
+static long long set_tiles(Gemm<OutT>& g) {
+  g.tiles_i = (g.I + G::TI - 1) / G::TI;
+  g.tiles_j = (g.J + G::TJ - 1) / G::TJ;
+  return (long long)g.blocks_per_part() * g.parts;
+}
 template <typename G, bool XR, bool YR, typename OutT>
-static hipError_t launch_gemm_tile(const void* X, long long ldx, const void* Y, long long ldy, void* C, long long ldc,
-                              int I, int J, int R, int parts, int r_per_part, long long part_stride, hipStream_t stream) {
-  const int tiles_i = (I + G::TI - 1) / G::TI, tiles_j = (J + G::TJ - 1) / G::TJ;
-  const unsigned grid = 8u * (unsigned)(((long long)tiles_i * tiles_j + 7) / 8);
-  const size_t lds = G::LDS;
+static hipError_t launch_gemm_tile(Gemm<OutT> g, hipStream_t stream) {
+  const unsigned grid = (unsigned)set_tiles<G>(g);
   auto kern = gemm_kernel<G, XR, YR, OutT>;
+  static unsigned long long configured = 0;   // one static per template instantiation
+  hipError_t e = allow_dynamic_lds(kern, G::LDS, configured);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * kWaves), G::LDS, stream, g);
+  return hipGetLastError();
+}
+template <typename GI, bool WT, typename GW>
+static hipError_t launch_gradients(Gemm<__bf16> input, Gemm<float> weight, hipStream_t stream) {
+  const long long weight_blocks = set_tiles<GW>(weight), input_blocks = set_tiles<GI>(input);
+  const size_t lds = GI::LDS > GW::LDS ? GI::LDS : GW::LDS;
+  auto kern = linear_bwd_kernel<GI, WT, GW>;
   static unsigned long long configured = 0;   // one static per template instantiation
   hipError_t e = allow_dynamic_lds(kern, lds, configured);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(grid, (unsigned)parts), dim3(64 * kWaves), lds, stream, (const __bf16*)X, ldx, (const __bf16*)Y, ldy,
-                     (OutT*)C, ldc, I, J, R, tiles_i, tiles_j, r_per_part, part_stride);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(weight_blocks + input_blocks)), dim3(64 * kWaves), lds, stream, input, weight, (int)weight_blocks);
   return hipGetLastError();
 }
 
-// The tile that takes the least time by a model of four figures per tile.  A round of workgroups takes between `sparse`
-// (few of them on the chip: latency of the copies and barriers) and `full` nanoseconds per contraction index, plus
-// `fixed` for first copies and stores.  The times themselves are rough (a third too low to a half too high: 8192 x 2048 x 768 on 64 tiles
-// 64 for 43 us); what counts is the choice.  Over 110 random shapes (32 to 131072 tokens, K to 5120, N to 3072) it is the fastest tile or
-// within 3 % of it for 99 forward products, 103 input and 98 weight gradients, 1.4, 0.6 and 1.1 % off on average; at worst, with a short
-// contraction or few columns, 47776 x 256 x 1024 forward 47.9 for 36.8 us, 5888 x 1920 x 1920 da + dw 118 for 108, 37024 x 896 x 512 121 for 105.
-// Measured, 256 / 128 / 64, us: forward of 64 tokens x 2048 x 768
-// 39 / 14.5 / 10.2; 2080 x 2048 x 768 45 / 18.6 / 14.7; 2080 x 4096 x 1536 82 / 38 / 60; 8192 x 2048 x 768
-// 48 / 35 / 43; 16384 x 4096 x 1536 207 / 224 / 489; 131072 x 4096 x 1536 1396 / 1862 / 3873.
-// `extra_256`: microseconds that only the large tile's path spends.
 enum class TileKind { k256, k128, k64 };
-static TileKind pick_tile(int I, int J, int R, int parts, double extra_256 = 0.) {
+static double tiles_of(int I, int J, int edge) { return (double)((I + edge - 1) / edge) * ((J + edge - 1) / edge); }
+
+// The forward's tile: the one that takes the least time by a model of four figures per tile.  A round of workgroups takes between `sparse`
+// (few of them on the chip: latency of the copies and barriers) and `full` nanoseconds per contraction index, plus
+// `fixed` for first copies and stores.  The times themselves are rough; what counts is the choice: over 390 random shapes (32 to
+// 131072 tokens, K to 5120, N to 3072) 0.8 % off the fastest tile on average; at worst, with a short
+// contraction, 128128 x 256 x 512 60.7 for 52.9 us, 47776 x 256 x 1024 46.2 for 39.4.
+// Measured, 256 / 128 / 64, us: 64 tokens x 2048 x 768 37 / 14 / 7.8; 2080 x 2048 x 768 43 / 18.2 / 14.1; 2080 x 4096 x 1536 82 / 38 / 60;
+// 8192 x 2048 x 768 48 / 35 / 43; 16384 x 4096 x 1536 207 / 224 / 489; 131072 x 4096 x 1536 1396 / 1862 / 3873.
+static TileKind pick_tile(int I, int J, int R) {
   auto microseconds = [&](int edge, int slots, double sparse, double full, double fixed) {
-    const long long n = (long long)((I + edge - 1) / edge) * ((J + edge - 1) / edge) * parts;
-    const long long rounds = n / slots, rest = n % slots;
-    const double per_index = rounds * full + (rest ? sparse + (full - sparse) * rest / slots : 0.);
-    return per_index * R * 1e-3 + (rounds + (rest ? 1 : 0)) * fixed;
+    const double n = tiles_of(I, J, edge), rounds = std::floor(n / slots), rest = n - rounds * slots;
+    const double per_index = rounds * full + (rest > 0. ? sparse + (full - sparse) * rest / slots : 0.);
+    return per_index * R * 1e-3 + (rounds + (rest > 0. ? 1. : 0.)) * fixed;
   };
-  const double t256 = microseconds(256, 256, 17., 28., 11.) + extra_256;
+  const double t256 = microseconds(256, 256, 17., 28., 11.);
   const double t128 = microseconds(128, 512, 6.5, 18.5, 4.4);
   const double t64 = microseconds(64, 512, 2.5, 9.5, 2.);
   return t256 <= t128 && t256 <= t64 ? TileKind::k256 : t128 <= t64 ? TileKind::k128 : TileKind::k64;
 }
 
-template <bool XR, bool YR, typename OutT>
-static hipError_t launch_gemm(TileKind kind, const void* X, long long ldx, const void* Y, long long ldy, void* C, long long ldc,
-                              int I, int J, int R, int parts, int r_per_part, long long part_stride, hipStream_t stream) {
-  using Small = typename std::conditional<XR, Tile64ShortStages, Tile64>::type;
-  switch (kind) {
-    case TileKind::k256:
-      if constexpr (XR || YR) return launch_gemm_tile<Tile256, XR, YR, OutT>(X, ldx, Y, ldy, C, ldc, I, J, R, parts, r_per_part, part_stride, stream);
-      return hipErrorInvalidValue;   // two contiguous operands: launch_linear_bwd_input transposes w for this tile
-    case TileKind::k128: return launch_gemm_tile<Tile128, XR, YR, OutT>(X, ldx, Y, ldy, C, ldc, I, J, R, parts, r_per_part, part_stride, stream);
-    default: return launch_gemm_tile<Small, XR, YR, OutT>(X, ldx, Y, ldy, C, ldc, I, J, R, parts, r_per_part, part_stride, stream);
+// The tiles of the two gradients, which share a launch: those with the least time of it, among the pairs that take a compute unit
+// alike.  `work` is the time in which the chip gets through all workgroups, `chain` that of the longest one with a compute unit of its own; the launch
+// takes the larger of the two, or somewhat more where they are close.  The figures are fitted to 390 random shapes as above, at which the
+// choice is 1.5 % off the best pair on average (3.0 % for each product's fastest tile by itself) and more than 8 % off at 5 % of them (short
+// contractions mostly: 47776 x 256 x 1024 103 for 82 us).  One launch each on its own fastest tile -> both in one, us,
+// forward and backward: 2080 x 2048 x 768 43.2 -> 37.2; 131072 x 4096 x 1536 4283 -> 4150.
+struct TilePair { TileKind input, weight; };
+static TilePair pick_tiles(int M, int K, int N, int parts) {
+  struct Cost { int edge; double slots, full, sparse, input_fixed, weight_fixed; };   // of a workgroup: us per contraction index, us
+  static const Cost cost[3] = {{256, 256., 0.0331, 0.0175, 0.7, 1.4}, {128, 512., 0.0186, 0.0032, 3.0, 4.7}, {64, 512., 0.0052, 0.0004, 1.15, 4.0}};
+  static const TilePair pairs[5] = {{TileKind::k256, TileKind::k256}, {TileKind::k128, TileKind::k128}, {TileKind::k128, TileKind::k64},
+                                    {TileKind::k64, TileKind::k128}, {TileKind::k64, TileKind::k64}};
+  const double R = (double)M / parts;
+  TilePair best = pairs[0];
+  double least = 0.;
+  for (const TilePair& p : pairs) {
+    const Cost &i = cost[(int)p.input], &w = cost[(int)p.weight];
+    const double work = (tiles_of(M, K, i.edge) * (N * i.full + i.input_fixed) + tiles_of(K, N, w.edge) * parts * (R * w.full + w.weight_fixed)) / i.slots;
+    const double chain = std::max(N * i.sparse + i.input_fixed, R * w.sparse + w.weight_fixed);
+    const double t = std::pow(std::pow(work, 3.5) + std::pow(chain, 3.5), 1 / 3.5) + (p.input == TileKind::k256 ? 5. : 0.);   // the transposing copy
+    if (least == 0. || t < least) { least = t; best = p; }
   }
+  return best;
 }
 
 hipError_t launch_linear_fwd(const void* a, long long lda, const void* w, long long ldw, void* out, long long ldo,
                              int M, int K, int N, hipStream_t stream) {
-  return launch_gemm<false, true, __bf16>(pick_tile(M, N, K, 1), a, lda, w, ldw, out, ldo, M, N, K, 1, K, 0, stream);
+  const Gemm<__bf16> g = {(const __bf16*)a, (const __bf16*)w, (__bf16*)out, lda, ldw, ldo, 0, M, N, K, 0, 0, 1, K};
+  switch (pick_tile(M, N, K)) {
+    case TileKind::k256: return launch_gemm_tile<Tile256, false, true>(g, stream);
+    case TileKind::k128: return launch_gemm_tile<Tile128, false, true>(g, stream);
+    default: return launch_gemm_tile<Tile64, false, true>(g, stream);
+  }
 }
 // out[c][r] = in[r][c] for a [rows][cols] bf16 matrix (both extents multiples of 64).
 __global__ void __launch_bounds__(256) transpose_kernel(const __bf16* __restrict__ in, long long ld_in,
@@ -406,21 +471,6 @@ __global__ void __launch_bounds__(256) transpose_kernel(const __bf16* __restrict
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < 16; i++) out[(c0 + ty * 16 + i) * ld_out + r0 + tx] = tile[tx][ty * 16 + i];
-}
-
-// Input gradient da = dout * w^T.  With w as stored ([K][N], contraction index n contiguous) both
-// operands would reach LDS in 64-byte row pieces, the least efficient pattern of the copy path
-// (measured 30 % slower than the forward product); a transposed copy of the small weight matrix
-// (w^T [N][K], in the workspace) turns it into the forward's operand combination.
-hipError_t launch_linear_bwd_input(const void* dout, long long ldd, const void* w, long long ldw, void* da, long long lda,
-                                   void* wt, int M, int K, int N, hipStream_t stream) {
-  const TileKind kind = pick_tile(M, K, N, 1, 6.);   // the transposing copy
-  if (kind != TileKind::k256) return launch_gemm<false, false, __bf16>(kind, dout, ldd, w, ldw, da, lda, M, K, N, 1, N, 0, stream);
-  hipLaunchKernelGGL(transpose_kernel, dim3((unsigned)(N / 64), (unsigned)(K / 64)), dim3(256), 0, stream,
-                     (const __bf16*)w, ldw, (__bf16*)wt, (long long)K);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_gemm<false, true, __bf16>(kind, dout, ldd, wt, K, da, lda, M, K, N, 1, N, 0, stream);
 }
 
 // The weight gradient has few output tiles and a long contraction (over all M tokens), so the
@@ -440,16 +490,42 @@ size_t linear_bwd_workspace_bytes(int M, int K, int N) {
   const int parts = linear_bwd_weight_parts(M, K, N);
   return linear_bwd_wt_bytes(K, N) + (parts > 1 ? (size_t)parts * K * N * sizeof(float) : 0);
 }
-hipError_t launch_linear_bwd_weight(const void* a, long long lda, const void* dout, long long ldd, float* dw, long long ldw,
-                                    float* workspace, int M, int K, int N, hipStream_t stream) {
+
+// Input gradient da = dout * w^T.  With w as stored ([K][N], contraction index n contiguous) both
+// operands would reach LDS in 64-byte row pieces, the least efficient pattern of the copy path
+// (measured 30 % slower than the forward product); on the large tile a transposed copy of the small weight matrix
+// (w^T [N][K], in the workspace) turns it into the forward's operand combination.
+// Weight gradient dw = a^T * dout, in parts.
+//
+// The two need nothing of each other, so they go in one launch, the weight gradient's longer workgroups first: the last round of one is
+// filled by the other, and a small layer pays for one start.
+hipError_t launch_linear_bwd(const void* a, long long lda, const void* w, long long ldw, const void* dout, long long ldd, void* da,
+                             long long ldda, float* dw, long long lddw, void* workspace, int M, int K, int N, hipStream_t stream) {
+  __bf16* const wt = (__bf16*)workspace;
+  float* const slabs = reinterpret_cast<float*>(static_cast<char*>(workspace) + linear_bwd_wt_bytes(K, N));
   const int parts = linear_bwd_weight_parts(M, K, N);
-  const TileKind kind = pick_tile(K, N, (M + parts - 1) / parts, parts);
-  if (parts == 1) return launch_gemm<true, true, float>(kind, a, lda, dout, ldd, dw, ldw, K, N, M, 1, M, 0, stream);
-  const int per = ((M / 32 + parts - 1) / parts) * 32;    // tokens per part, a multiple of the stage length
-  hipError_t e = launch_gemm<true, true, float>(kind, a, lda, dout, ldd, workspace, N, K, N, M, parts, per, (long long)K * N, stream);
-  if (e != hipSuccess) return e;
+  const int per = parts == 1 ? M : ((M / 32 + parts - 1) / parts) * 32;    // tokens per part, a multiple of the stage length
+  Gemm<__bf16> in = {(const __bf16*)dout, (const __bf16*)w, (__bf16*)da, ldd, ldw, ldda, 0, M, K, N, 0, 0, 1, N};
+  const Gemm<float> grad_w = {(const __bf16*)a, (const __bf16*)dout, parts == 1 ? dw : slabs, lda, ldd, parts == 1 ? lddw : N,
+                          (long long)K * N, K, N, M, 0, 0, parts, per};
+  const TilePair kind = pick_tiles(M, K, N, parts);
+  hipError_t e = hipSuccess;
+  if (kind.input == TileKind::k256) {
+    hipLaunchKernelGGL(transpose_kernel, dim3((unsigned)(N / 64), (unsigned)(K / 64)), dim3(256), 0, stream, (const __bf16*)w, ldw, wt, (long long)K);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    in.Y = wt;
+    in.ldy = K;
+    e = launch_gradients<Tile256, true, Tile256>(in, grad_w, stream);
+  } else if (kind.input == TileKind::k128) {
+    e = kind.weight == TileKind::k128 ? launch_gradients<Tile128, false, Tile128>(in, grad_w, stream)
+                                      : launch_gradients<Tile128, false, Tile64ShortStages>(in, grad_w, stream);
+  } else {
+    e = kind.weight == TileKind::k128 ? launch_gradients<Tile64, false, Tile128>(in, grad_w, stream)
+                                      : launch_gradients<Tile64, false, Tile64ShortStages>(in, grad_w, stream);
+  }
+  if (e != hipSuccess || parts == 1) return e;
   const long long quads = (long long)K * N / 4;
-  hipLaunchKernelGGL(sum_parts_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream, workspace, dw, ldw, K, N, parts);
+  hipLaunchKernelGGL(sum_parts_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream, slabs, dw, lddw, K, N, parts);
   return hipGetLastError();
 }
 
