@@ -337,7 +337,12 @@ __device__ __forceinline__ TileCoord map_block(int n, int BH, int T, bool heavy_
     }
   }
   const int vh = xcd + 8 * v;
-  const int k = r * P + (vh & (P - 1));          // rank of the tile inside its head, heaviest first
+  // The parts of a head rotate among its P XCDs from head to head, by an odd number of places close to T, and every other row of P tiles
+  // is dealt backwards: with a fixed part to an XCD the heads' short rows (T no multiple of P) and the heavier tiles of every row
+  // fall to the same XCDs (35 heads of 3 tiles: all on three of the eight).  Fixed -> rotating, forward / backward, us, head dimension 128:
+  // 35 x 300 23.2 -> 11.7 / 65 -> 31; 21 x 1216 30.9 -> 24.8 / 96 -> 72; 39 x 2100 83 -> 73 / 321 -> 256; 7 x 20000 688 -> 655 / 2226 -> 2188.
+  const int part = (xcd - v * (T | 1)) & (P - 1);
+  const int k = r * P + ((r & 1) ? P - 1 - part : part);   // rank of the tile inside its head, heaviest first
   c.bh = vh / P;
   c.tile = heavy_is_high ? (T - 1 - k) : k;
   c.valid = c.bh < BH && k < T;
