@@ -110,13 +110,13 @@ struct DeltaHead {
 // 256-row tiles (split_rows): every wave takes both halves of a tile for 32 rows of its own, one after the other, so an operand
 // copied to LDS serves twice the rows; the halves keep sums of their own, and delta has the same bits.  Whole backward of 4 x 16
 // heads x 2k tokens (512 tiles of 256 rows) with KG = 2 -> 1: 350.5 -> 336.7 us; 2 x 40 x 8000 forward + backward unchanged.
-template <int D, bool CAUSAL, int KG>
-__global__ void __launch_bounds__(512, 1)
+template <int D, bool CAUSAL, int KG, int RG>
+__global__ void __launch_bounds__(64 * KG * RG) __attribute__((amdgpu_waves_per_eu(2)))
 bwd_delta_head_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
                       const __bf16* __restrict__ dO, const float* __restrict__ lse, float* __restrict__ neg_delta_out,
                       float* __restrict__ lse2_out, BwdMaps maps, int BH, int H, int S, int T, float scale) {
   using G = DeltaHead<D>;
-  constexpr int BM = 256 / KG, BN = 64, KS = D / 16, R = 4;   // R: operands in flight
+  constexpr int BM = 32 * RG, BN = 64, KS = D / 16, R = 4;   // R: operands in flight
   constexpr int TILE = G::TILE, HALF = 32 * D * 2, STAGE = G::STAGE, NST = G::NST, AHEAD = G::AHEAD;
   extern __shared__ __align__(16) char smem[];   // tile j (K, V) in stage j % NST
 
@@ -124,7 +124,7 @@ bwd_delta_head_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k
   if (!tc.valid) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int rg = KG == 2 ? w & 3 : w, kg = KG == 2 ? w >> 2 : 0;
+  const int rg = w & (RG - 1), kg = w / RG;
   const int half = lane >> 5, n = lane & 31;
   const int q0 = tc.tile * BM;
   const int wave_qmin = q0 + 32 * rg, my_q = wave_qmin + n;
@@ -145,7 +145,7 @@ bwd_delta_head_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k
   const int n_w = wave_qmin < S ? (k_end - 32 * kg + BN - 1) / BN : 0;
   const int n_full = KG == 2 ? (k_all + 32 - 32 * kg) / BN : k_all / BN;
 
-  const TileLoader<D, BN, 8> kload(lane, w, maps.k.row), vload(lane, w, maps.v.row);
+  const TileLoader<D, BN, KG * RG> kload(lane, w, maps.k.row), vload(lane, w, maps.v.row);
   constexpr int NDMA = decltype(kload)::N + decltype(vload)::N;
   int j = 0, st = 0;   // tile and its stage (j % NST)
   auto plus = [&](int d) __attribute__((always_inline)) { return st + d >= NST ? st + d - NST : st + d; };
@@ -315,15 +315,16 @@ static hipError_t launch_delta_head_t(const void* q, const void* k, const void* 
                                       float* delta_out, float* lse2_out, const BwdMaps& maps, int B, int H, int S, int rows,
                                       float scale, hipStream_t stream) {
   const int BH = B * H;
-  const bool split = split_rows(BH, rows, CAUSAL);
-  const int T = split ? (rows + 127) / 128 : (rows + 255) / 256;   // query tiles 0..T-1 of every head
+  const Rows kind = delta_rows(D, BH, rows, CAUSAL);
+  const int T = tiles(rows, kind);   // query tiles 0..T-1 of every head
   const unsigned grid = (unsigned)grid_blocks(BH, T);
   const size_t lds = DeltaHead<D>::LDS;
-  auto kern = split ? bwd_delta_head_kernel<D, CAUSAL, 2> : bwd_delta_head_kernel<D, CAUSAL, 1>;
-  static unsigned long long configured[2] = {};   // per template instantiation and kernel
-  hipError_t e = allow_dynamic_lds(kern, lds, configured[split]);
+  auto kern = kind == Rows::k64 ? bwd_delta_head_kernel<D, CAUSAL, 2, 2>
+              : kind == Rows::k128 ? bwd_delta_head_kernel<D, CAUSAL, 2, 4> : bwd_delta_head_kernel<D, CAUSAL, 1, 8>;
+  static unsigned long long configured[3] = {};   // per template instantiation and kernel
+  hipError_t e = allow_dynamic_lds(kern, lds, configured[(int)kind]);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(512), lds, stream, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v,
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(kind == Rows::k64 ? 256 : 512), lds, stream, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v,
                      (const __bf16*)dO, lse, delta_out, lse2_out, maps, BH, H, S, T, scale);
   return hipGetLastError();
 }

@@ -67,13 +67,13 @@ __device__ __forceinline__ f32x16 join4(const f32x4 (&x)[4]) {
   return r;
 }
 
-template <int D>
+template <int D, int KW>
 struct Geometry {
   static constexpr int KS = D / 16, DB = D / 32;
   static constexpr int TILE = 64 * D * 2;            // one 64-row bf16 tile
   static constexpr int ROWS32 = 32 * D * 2;          // bytes of 32 rows
   static constexpr int STATS = 2 * TILE;             // per-wave copies of lse2[64], -delta[64] follow Q, dO
-  static constexpr int STAGE = 2 * TILE + 4 * 512;
+  static constexpr int STAGE = 2 * TILE + KW * 512;
   static constexpr int NSTAGE = 4;
 };
 
@@ -93,11 +93,11 @@ struct Pipe {
 // tile, so the block ahead starts the next tile.  On entry sp_cur = P(b) (fp32), dp_cur =
 // dP(b) (delta already subtracted), pipe.ring = first Q operands of block b+1; on exit the
 // same holds for block b+1 in sp_next / dp_next.
-template <int D, bool ODD>
+template <int D, int KW, bool ODD>
 __device__ __forceinline__ void dkdv_step(const f32x16& sp_cur, const f32x16& dp_cur, f32x16& sp_next, f32x16& dp_next,
                                           Pipe<D>& pp, const bf16x8 (&kf)[D / 16], const bf16x8 (&vf)[D / 16],
                                           f32x16 (&dkacc)[D / 32], f32x16 (&dvacc)[D / 32], int stage_step, float c) {
-  using G = Geometry<D>;
+  using G = Geometry<D, KW>;
   constexpr int KS = G::KS, DB = G::DB, NS = 4 * KS, R = kRing;
   constexpr int AHEAD_ROWS = ODD ? 0 : 32;                 // block b+1 inside its tile
   constexpr int AHEAD = AHEAD_ROWS * D * 2;
@@ -177,20 +177,20 @@ __device__ __forceinline__ void dkdv_step(const f32x16& sp_cur, const f32x16& dp
 
 // GROUPS = 2 (see two_query_groups): two groups of four waves own the same 128 keys and sweep one half of the query
 // tiles each, with stages of their own; at the end they swap partial sums through LDS and each stores one result.
-template <int D, bool CAUSAL, int GROUPS>
+template <int D, bool CAUSAL, int GROUPS, int KW>
 __device__ __forceinline__ void dkdv_keys(int block, const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
                                           const __bf16* __restrict__ dO, const float* __restrict__ lse2, const float* __restrict__ neg_delta,
                                           __bf16* __restrict__ dk, __bf16* __restrict__ dv, BwdMaps maps, int BH, int H, int S, int T,
                                           float scale) {
-  using G = Geometry<D>;
-  constexpr int BN = 128, BM = 64, KS = G::KS, DB = G::DB;
+  using G = Geometry<D, KW>;
+  constexpr int BN = 32 * KW, BM = 64, KS = G::KS, DB = G::DB;
   extern __shared__ __align__(16) char smem[];
 
   const TileCoord tc = map_block<CAUSAL, D>(block, BH, T, false);
   if (!tc.valid) return;
   const int tid = threadIdx.x, lane = tid & 63;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6) & 3;       // wave of its group
-  const int group = GROUPS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 8);
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6) & (KW - 1);   // wave of its group
+  const int group = GROUPS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid / (64 * KW));
   const int half = lane >> 5, n = lane & 31;
   const int n0 = tc.tile * BN;
   const int wave_kmin = n0 + 32 * w;
@@ -208,7 +208,7 @@ __device__ __forceinline__ void dkdv_keys(int block, const __bf16* __restrict__ 
   // K^T and V^T operand fragments of this lane's key (columns of S and dP): through stages 2 and 3, so tile 2 follows
   // when every wave has them.
   const uint32_t frag = base + 2 * G::STAGE + w * 2 * G::ROWS32;
-  static_assert(4 * 2 * G::ROWS32 <= 2 * G::STAGE, "the fragments of four waves fit two stages");
+  static_assert(KW * 2 * G::ROWS32 <= 2 * G::STAGE, "the fragments of a group fit two stages");
   issue_fragments<D>(kh, maps.k.row, wave_kmin, S, lane, 0, frag);
   issue_fragments<D>(vh, maps.v.row, wave_kmin, S, lane, 0, frag + G::ROWS32);
   f32x16 dkacc[DB], dvacc[DB];
@@ -223,13 +223,13 @@ __device__ __forceinline__ void dkdv_keys(int block, const __bf16* __restrict__ 
   const int nt = group == 0 ? nt_first : nt_all - nt_first;
   const int m_start = m_first + group * nt_first * BM;
   // Plain (masked) path: the tiles the causal diagonal crosses and a ragged last tile.
-  int t_lo = CAUSAL ? 2 - group * nt_first : 0;
+  int t_lo = CAUSAL ? BN / BM - group * nt_first : 0;
   if (t_lo < 0) t_lo = 0;
   if (t_lo > nt) t_lo = nt;
   int t_hi = (m_start + nt * BM > S) ? nt - 1 : nt;
   if (t_hi < t_lo) t_hi = t_lo;
 
-  const TileLoader<D, BM, 4> qload(lane, w, maps.q.row), gload(lane, w, maps.dO.row);
+  const TileLoader<D, BM, KW> qload(lane, w, maps.q.row), gload(lane, w, maps.dO.row);
   constexpr int kStatCopies = 2;                             // lse2 and -delta of the tile's rows, one instruction each
   constexpr int NDMA = decltype(qload)::N + decltype(gload)::N + kStatCopies;   // copy instructions per wave and tile: what copy_tile() issues
   int t = 0, st = 0;                                          // tile and its stage (t % 4)
@@ -275,7 +275,10 @@ __device__ __forceinline__ void dkdv_keys(int block, const __bf16* __restrict__ 
     const float* dlt_t = lse_t + 64;
     f32x16 sacc, pacc;
 #pragma unroll
-    for (int e = 0; e < 16; e++) { sacc[e] = 0.f; pacc[e] = 0.f; }
+    for (int e = 0; e < 16; e++) {
+      sacc[e] = 0.f;
+      pacc[e] = dlt_t[32 * blk + 8 * (e >> 2) + 4 * half + (e & 3)];   // dP starts from -delta, as in the pipelined path
+    }
 #pragma unroll
     for (int ks = 0; ks < KS; ks++) sacc = mfma32(lds_operand<D>(qt, 32 * blk + n, ks, half), kf[ks], sacc);
 #pragma unroll
@@ -283,7 +286,6 @@ __device__ __forceinline__ void dkdv_keys(int block, const __bf16* __restrict__ 
 #pragma unroll
     for (int g = 0; g < 4; g++) {
       const f32x4 l4 = *reinterpret_cast<const f32x4*>(lse_t + 32 * blk + 8 * g + 4 * half);
-      const f32x4 d4 = *reinterpret_cast<const f32x4*>(dlt_t + 32 * blk + 8 * g + 4 * half);
 #pragma unroll
       for (int e4 = 0; e4 < 4; e4++) {
         const int e = 4 * g + e4;
@@ -292,7 +294,7 @@ __device__ __forceinline__ void dkdv_keys(int block, const __bf16* __restrict__ 
         const bool ok = (!CAUSAL || my_key <= row) && row < S;
         p = ok ? p : 0.f;
         sacc[e] = p;
-        pacc[e] = p * (pacc[e] + d4[e4]);
+        pacc[e] = p * pacc[e];
       }
     }
 #pragma unroll
@@ -353,8 +355,8 @@ __device__ __forceinline__ void dkdv_keys(int block, const __bf16* __restrict__ 
     for (; t < t_hi; t++) {
       copy_ahead();
       const int stage_step = (st == 3) ? -3 * G::STAGE : G::STAGE;
-      dkdv_step<D, false>(spA, dpA, spB, dpB, pp, kf, vf, dkacc, dvacc, stage_step, c);
-      dkdv_step<D, true>(spB, dpB, spA, dpA, pp, kf, vf, dkacc, dvacc, stage_step, c);
+      dkdv_step<D, KW, false>(spA, dpA, spB, dpB, pp, kf, vf, dkacc, dvacc, stage_step, c);
+      dkdv_step<D, KW, true>(spB, dpB, spA, dpA, pp, kf, vf, dkacc, dvacc, stage_step, c);
       finish_tile();
     }
   }
@@ -363,8 +365,8 @@ __device__ __forceinline__ void dkdv_keys(int block, const __bf16* __restrict__ 
 
   if constexpr (GROUPS == 2) {
     for (; t < nt_first; t++) __syncthreads();   // the second group has one tile fewer at times; all stages are free after this
-    char* const give = smem + (group * 4 + w) * (DB * 4096);
-    char* const take = smem + ((group ^ 1) * 4 + w) * (DB * 4096);   // the results pass through it too
+    char* const give = smem + (group * KW + w) * (DB * 4096);
+    char* const take = smem + ((group ^ 1) * KW + w) * (DB * 4096);   // the results pass through it too
 #pragma unroll
     for (int db = 0; db < DB; db++) lds_put_block(give + db * 4096, lane, group == 0 ? dkacc[db] : dvacc[db]);
     __syncthreads();
@@ -394,43 +396,53 @@ __device__ __forceinline__ void dkdv_keys(int block, const __bf16* __restrict__ 
   store_rows<D>(out + G::ROWS32, lane, dv + head_offset(maps.dv, tc.bh, H) + (size_t)wave_kmin * maps.dv.row, maps.dv.row, S - wave_kmin);
 }
 
-template <int D, bool CAUSAL, int GROUPS>
-__global__ void __launch_bounds__(256 * GROUPS) __attribute__((amdgpu_waves_per_eu(2, 2)))
+template <int D, bool CAUSAL, int GROUPS, int KW>
+__global__ void __launch_bounds__(64 * KW * GROUPS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 bwd_dkdv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
                 const __bf16* __restrict__ dO, const float* __restrict__ lse2, const float* __restrict__ neg_delta,
                 __bf16* __restrict__ dk, __bf16* __restrict__ dv, BwdMaps maps, int BH, int H, int S, int T,
                 float scale) {
-  dkdv_keys<D, CAUSAL, GROUPS>(blockIdx.x, q, k, v, dO, lse2, neg_delta, dk, dv, maps, BH, H, S, T, scale);
+  dkdv_keys<D, CAUSAL, GROUPS, KW>(blockIdx.x, q, k, v, dO, lse2, neg_delta, dk, dv, maps, BH, H, S, T, scale);
 }
 
 // The dK/dV and the dQ pass in one launch (see launch_bwd_dkdv_dq): the first `key_blocks` workgroups take key tiles, the others
-// 128-row query tiles.
-template <int D, bool CAUSAL>
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+// query tiles of as many rows.
+template <int D, bool CAUSAL, int KW>
+__global__ void __launch_bounds__(128 * KW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 bwd_dkdv_dq_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
                    const __bf16* __restrict__ dO, const float* __restrict__ lse2, const float* __restrict__ neg_delta,
                    __bf16* __restrict__ dq, __bf16* __restrict__ dk, __bf16* __restrict__ dv, BwdMaps maps, int BH, int H, int S,
                    int key_tiles, int key_blocks, int query_tiles, float scale) {
   const int block = (int)blockIdx.x;
-  if (block < key_blocks) dkdv_keys<D, CAUSAL, 2>(block, q, k, v, dO, lse2, neg_delta, dk, dv, maps, BH, H, S, key_tiles, scale);
-  else dq_split_rows<D, CAUSAL>(block - key_blocks, q, k, v, dO, lse2, neg_delta, dq, maps, BH, H, S, query_tiles, scale);
+  if (block < key_blocks) dkdv_keys<D, CAUSAL, 2, KW>(block, q, k, v, dO, lse2, neg_delta, dk, dv, maps, BH, H, S, key_tiles, scale);
+  else dq_split_rows<D, CAUSAL, KW>(block - key_blocks, q, k, v, dO, lse2, neg_delta, dq, maps, BH, H, S, query_tiles, scale);
 }
 
-template <int D, bool CAUSAL, int GROUPS>
+template <int D, bool CAUSAL, int GROUPS, int KW>
 static hipError_t launch_dkdv_t(const void* q, const void* k, const void* v, const void* dO,
                                 const float* lse2, const float* neg_delta, void* dk, void* dv, const BwdMaps& maps,
                                 int B, int H, int S, float scale, hipStream_t stream) {
-  constexpr int BN = 128;
+  using G = Geometry<D, KW>;
+  constexpr int BN = 32 * KW;
   const int T = (S + BN - 1) / BN, BH = B * H;
   const unsigned grid = (unsigned)grid_blocks(BH, T);
-  const size_t lds = GROUPS * Geometry<D>::NSTAGE * Geometry<D>::STAGE;
-  auto kern = bwd_dkdv_kernel<D, CAUSAL, GROUPS>;
+  const size_t lds = GROUPS * G::NSTAGE * G::STAGE;
+  auto kern = bwd_dkdv_kernel<D, CAUSAL, GROUPS, KW>;
   static unsigned long long configured = 0;   // one static per template instantiation
   hipError_t e = allow_dynamic_lds(kern, lds, configured);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(256 * GROUPS), lds, stream, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v,
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * KW * GROUPS), lds, stream, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v,
                      (const __bf16*)dO, lse2, neg_delta, (__bf16*)dk, (__bf16*)dv, maps, BH, H, S, T, scale);
   return hipGetLastError();
+}
+
+template <bool CAUSAL>
+static hipError_t launch_dkdv_64(const void* q, const void* k, const void* v, const void* dO,
+                                 const float* lse2, const float* neg_delta, void* dk, void* dv, const BwdMaps& maps,
+                                 int B, int H, int S, float scale, hipStream_t stream) {
+  if (key_tile(B * H, S, CAUSAL) == 64) return launch_dkdv_t<64, CAUSAL, 2, 2>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B, H, S, scale, stream);
+  if (two_query_groups(B * H, S, CAUSAL)) return launch_dkdv_t<64, CAUSAL, 2, 4>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B, H, S, scale, stream);
+  return launch_dkdv_t<64, CAUSAL, 1, 4>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B, H, S, scale, stream);
 }
 
 hipError_t launch_bwd_dkdv(const void* q, const void* k, const void* v, const void* dO,
@@ -438,28 +450,33 @@ hipError_t launch_bwd_dkdv(const void* q, const void* k, const void* v, const vo
                            int B, int H, int S, int D, float scale, bool causal, hipStream_t stream) {
   // Head dimension 128 has its own kernel with two waves per SIMD; this one serves head dimension 64.
   if (D == 128) return launch_bwd_dkdv_pair(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B, H, S, scale, causal, stream);
-  if (two_query_groups(B * H, S, causal))
-    return causal ? launch_dkdv_t<64, true, 2>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B, H, S, scale, stream)
-                  : launch_dkdv_t<64, false, 2>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B, H, S, scale, stream);
-  return causal ? launch_dkdv_t<64, true, 1>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B, H, S, scale, stream)
-                : launch_dkdv_t<64, false, 1>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B, H, S, scale, stream);
+  return causal ? launch_dkdv_64<true>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B, H, S, scale, stream)
+                : launch_dkdv_64<false>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B, H, S, scale, stream);
 }
 
-template <int D, bool CAUSAL>
+template <int D, bool CAUSAL, int KW>
 static hipError_t launch_dkdv_dq_t(const void* q, const void* k, const void* v, const void* dO, const float* lse2,
                                    const float* neg_delta, void* dq, void* dk, void* dv, const BwdMaps& maps, int B, int H, int S,
                                    float scale, hipStream_t stream) {
-  const int BH = B * H, TK = (S + 127) / 128, TQ = dq_tiles(S, true);
-  const long long key_blocks = grid_blocks(BH, TK);
-  const size_t lds = std::max(2 * Geometry<D>::NSTAGE * Geometry<D>::STAGE, DqSplit<D>::LDS);
-  auto kern = bwd_dkdv_dq_kernel<D, CAUSAL>;
+  using G = Geometry<D, KW>;
+  const int BH = B * H, T = (S + 32 * KW - 1) / (32 * KW);   // key tiles and query tiles
+  const long long key_blocks = grid_blocks(BH, T);
+  const size_t lds = std::max(2 * G::NSTAGE * G::STAGE, DqSplit<D>::LDS);
+  auto kern = bwd_dkdv_dq_kernel<D, CAUSAL, KW>;
   static unsigned long long configured = 0;   // one static per template instantiation
   hipError_t e = allow_dynamic_lds(kern, lds, configured);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(key_blocks + grid_blocks(BH, TQ))), dim3(512), lds, stream, (const __bf16*)q,
+  hipLaunchKernelGGL(kern, dim3((unsigned)(2 * key_blocks)), dim3(128 * KW), lds, stream, (const __bf16*)q,
                      (const __bf16*)k, (const __bf16*)v, (const __bf16*)dO, lse2, neg_delta, (__bf16*)dq, (__bf16*)dk, (__bf16*)dv, maps,
-                     BH, H, S, TK, (int)key_blocks, TQ, scale);
+                     BH, H, S, T, (int)key_blocks, T, scale);
   return hipGetLastError();
+}
+template <bool CAUSAL>
+static hipError_t launch_dkdv_dq_64(const void* q, const void* k, const void* v, const void* dO, const float* lse2,
+                                    const float* neg_delta, void* dq, void* dk, void* dv, const BwdMaps& maps, int B, int H, int S,
+                                    float scale, hipStream_t stream) {
+  return key_tile(B * H, S, CAUSAL) == 64 ? launch_dkdv_dq_t<64, CAUSAL, 2>(q, k, v, dO, lse2, neg_delta, dq, dk, dv, maps, B, H, S, scale, stream)
+                                              : launch_dkdv_dq_t<64, CAUSAL, 4>(q, k, v, dO, lse2, neg_delta, dq, dk, dv, maps, B, H, S, scale, stream);
 }
 
 // Both passes need the row statistics and nothing of each other, and a workgroup of either fills a compute unit (LDS at head
@@ -477,9 +494,9 @@ hipError_t launch_bwd_dkdv_dq(const void* q, const void* k, const void* v, const
   const long long key_tiles = (long long)B * H * ((S + 127) / 128);
   if (D == 128 && key_tiles <= 1024)
     return launch_bwd_dkdv_dq_pair(q, k, v, dO, lse2, neg_delta, dq, dk, dv, maps, B, H, S, scale, causal, stream);
-  if (D == 64 && two_query_groups(B * H, S, causal))
-    return causal ? launch_dkdv_dq_t<64, true>(q, k, v, dO, lse2, neg_delta, dq, dk, dv, maps, B, H, S, scale, stream)
-                  : launch_dkdv_dq_t<64, false>(q, k, v, dO, lse2, neg_delta, dq, dk, dv, maps, B, H, S, scale, stream);
+  if (D == 64 && (key_tile(B * H, S, causal) == 64 || two_query_groups(B * H, S, causal)))
+    return causal ? launch_dkdv_dq_64<true>(q, k, v, dO, lse2, neg_delta, dq, dk, dv, maps, B, H, S, scale, stream)
+                  : launch_dkdv_dq_64<false>(q, k, v, dO, lse2, neg_delta, dq, dk, dv, maps, B, H, S, scale, stream);
   hipError_t e = launch_bwd_dkdv(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B, H, S, D, scale, causal, stream);
   return e != hipSuccess ? e : launch_bwd_dq(q, k, v, dO, lse2, neg_delta, dq, maps, B, H, S, D, scale, causal, stream);
 }

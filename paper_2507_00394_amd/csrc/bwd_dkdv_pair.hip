@@ -41,8 +41,10 @@ namespace helix {
 
 namespace {
 
-struct PG {
-  static constexpr int D = 128, KS = 8, DB = 4, BN = 128, RB = 32;   // head dim, contraction steps, 32-wide blocks of D, keys per workgroup, rows per block
+template <int PAIRS>
+struct PairGeometry {
+  static constexpr int D = 128, KS = 8, DB = 4, BN = 32 * PAIRS, RB = 32;   // head dim, contraction steps, 32-wide blocks of D, keys per workgroup, rows per block
+  static constexpr int WAVES = 2 * PAIRS;
   static constexpr int NSTAGE = 7;
   static constexpr int BLOCK = RB * D * 2;                // one 32-row bf16 block: 8 KB
   static constexpr int QRING = 0;                         // NSTAGE blocks of Q
@@ -50,13 +52,15 @@ struct PG {
   static constexpr int STATS = 2 * NSTAGE * BLOCK;        // ring of [lse2: 64 floats][-delta: 64 floats] per stage
   static constexpr int STAT_STAGE = 512;
   static constexpr int PBUF = STATS + NSTAGE * STAT_STAGE;   // two buffers of P: [pair][group of 4 registers][lane][4] fp32
-  static constexpr int PBYTES = 4 * 4096;
+  static constexpr int PBYTES = PAIRS * 4096;
   static constexpr int LDS = PBUF + 2 * PBYTES;
   static constexpr int AHEAD = 5;                         // a block is copied this many blocks before it becomes A's current one
-  static constexpr int NDMA = 3;                          // copy instructions per wave and block: Q piece, dO piece, one statistics row
+  static constexpr int PIECES = 8 / WAVES;                // 1 KB pieces of a Q or dO block that a wave copies
+  static constexpr int NDMA = 2 * PIECES + 1;             // copy instructions per wave and block: Q and dO pieces, one statistics row
+  static_assert(LDS <= 160 * 1024, "LDS budget of a compute unit");
+  static_assert(AHEAD + 2 <= NSTAGE && PAIRS * BLOCK <= 2 * PBYTES, "room for the fragments on their way to registers");
 };
-static_assert(PG::LDS <= 160 * 1024, "LDS budget of a compute unit");
-static_assert(PG::AHEAD + 2 <= PG::NSTAGE && 4 * PG::BLOCK <= 2 * PG::PBYTES, "room for the fragments on their way to registers");
+using PG = PairGeometry<4>;   // what does not depend on the number of pairs
 static_assert(PG::NSTAGE * PG::BLOCK <= 65536, "a whole ring is within reach of the 16-bit offset field of an LDS instruction");
 
 // LDS byte offset of stage k inside a ring.
@@ -113,23 +117,27 @@ struct Lane {
 
 // Copy state of the pipelined loop: whole blocks only, so a copy is three instructions with
 // precomputed operands.  The pointers are wave-uniform (scalar registers).
+template <int PIECES>
 struct Copier {
   const __bf16* qptr;     // first row of the next Q block to copy
   const __bf16* gptr;     // same for dO
   const float* stat;      // this role's statistics row of the head
-  uint32_t qoff, goff;    // this lane's byte offset inside a block (row * row bytes + swizzled chunk)
+  uint32_t qoff[PIECES], goff[PIECES];   // this lane's byte offsets inside a block (row * row bytes + swizzled chunk)
   uint32_t soff;          // this lane's byte offset into the statistics row
   uint32_t qstep, gstep;  // bytes between consecutive blocks
-  uint32_t dst;           // LDS address of this wave's 1 KB piece in stage 0 of the Q ring
+  uint32_t dst;           // LDS address of this wave's first 1 KB piece in stage 0 of the Q ring
   uint32_t sdst;          // LDS address of this role's half of stage 0 of the statistics ring
 };
-template <int STG>
-__device__ __forceinline__ void copy_whole_block(Copier& cp) {
+template <int STG, int PIECES>
+__device__ __forceinline__ void copy_whole_block(Copier<PIECES>& cp) {
   using G = PG;
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-               :: "v"(cp.qoff), "s"(cp.qptr), "s"(cp.dst + G::QRING + STG * G::BLOCK) : "memory");
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-               :: "v"(cp.goff), "s"(cp.gptr), "s"(cp.dst + G::GRING + STG * G::BLOCK) : "memory");
+#pragma unroll
+  for (int i = 0; i < PIECES; i++) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                 :: "v"(cp.qoff[i]), "s"(cp.qptr), "s"(cp.dst + G::QRING + STG * G::BLOCK + i * (8192 / PIECES)) : "memory");
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                 :: "v"(cp.goff[i]), "s"(cp.gptr), "s"(cp.dst + G::GRING + STG * G::BLOCK + i * (8192 / PIECES)) : "memory");
+  }
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1"
                :: "v"(cp.soff), "s"(cp.stat), "s"(cp.sdst + STG * G::STAT_STAGE) : "memory");
   cp.qptr = reinterpret_cast<const __bf16*>(reinterpret_cast<const char*>(cp.qptr) + cp.qstep);
@@ -143,9 +151,9 @@ __device__ __forceinline__ f32x4 (&l2ref(f32x4 (&st)[4]))[2] { return reinterpre
 // Block i at stage K.  On entry s_cur = S(i) with entries 0..7 already exponentiated, l2 =
 // lse2 of block i, ring = the first four Q row operands of block i+1.  On exit the same for i+1.
 // COPY: copies block i + AHEAD.  MASK: rows 8g + r of this lane's half count from first_row on (block i; 32 less for i+1).
-template <int K, bool COPY, bool MASK>
+template <int K, bool COPY, bool MASK, int PIECES>
 __device__ __forceinline__ void step_a(f32x16& s_cur, f32x16& s_next, bf16x8 (&ring)[4], f32x4 (&l2)[2], Lane& ln,
-                                       const bf16x8 (&kf)[PG::KS], f32x16 (&dvacc)[PG::DB], float c, Copier& cp, int first_row) {
+                                       const bf16x8 (&kf)[PG::KS], f32x16 (&dvacc)[PG::DB], float c, Copier<PIECES>& cp, int first_row) {
   using G = PG;
   constexpr int KS = G::KS, DB = G::DB;
   constexpr int KN = wrap(K + 1), KP = wrap(K + 2);
@@ -207,9 +215,9 @@ __device__ __forceinline__ void step_a(f32x16& s_cur, f32x16& s_next, bf16x8 (&r
 // ------------------------------------------------------------------ wave B: one pipelined iteration
 // Iteration i (A's block, stage K): finishes block j = i-1 (dS, dK) unless SKIP and computes
 // dP(i).  On entry dp_cur = dP(j), nd = -delta(i), ring = the first four dO row operands of block i.
-template <int K, bool COPY, bool SKIP>
+template <int K, bool COPY, bool SKIP, int PIECES>
 __device__ __forceinline__ void step_b(f32x16& dp_cur, f32x16& dp_next, bf16x8 (&ring)[4], f32x4 (&nd)[4], Lane& ln,
-                                       const bf16x8 (&vf)[PG::KS], f32x16 (&dkacc)[PG::DB], Copier& cp) {
+                                       const bf16x8 (&vf)[PG::KS], f32x16 (&dkacc)[PG::DB], Copier<PIECES>& cp) {
   using G = PG;
   constexpr int KS = G::KS, DB = G::DB;
   constexpr int KJ = wrap(K - 1), KN = wrap(K + 1);
@@ -266,20 +274,20 @@ __device__ __forceinline__ void step_b(f32x16& dp_cur, f32x16& dp_next, bf16x8 (
 
 // The whole sweep of one wave in its role (0: wave A, 1: wave B).  Both programs execute the same
 // sequence of workgroup barriers.
-template <bool CAUSAL, int ROLE>
+template <bool CAUSAL, int ROLE, int PAIRS>
 __device__ __forceinline__ void pair_sweep(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
                                            const __bf16* __restrict__ v, const __bf16* __restrict__ dO,
                                            const float* __restrict__ lse2, const float* __restrict__ neg_delta,
                                            __bf16* __restrict__ dk, __bf16* __restrict__ dv, const BwdMaps& maps,
                                            const TileCoord tc, int H, int S, float scale) {
-  using G = PG;
+  using G = PairGeometry<PAIRS>;
   constexpr int D = G::D, KS = G::KS, DB = G::DB, RB = G::RB, NST = G::NSTAGE;
   extern __shared__ __align__(16) char smem[];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   constexpr int role = ROLE;                                 // 0: wave A, 1: wave B
-  const int pair = w & 3;
+  const int pair = w & (PAIRS - 1);
   const int half = lane >> 5, n = lane & 31;
   const int n0 = tc.tile * G::BN;
   const int my_key = n0 + 32 * pair + n;
@@ -328,7 +336,7 @@ __device__ __forceinline__ void pair_sweep(const __bf16* __restrict__ q, const _
   constexpr int kStart = CAUSAL ? G::BN / RB : 1;
   auto stage_of = [](int i) __attribute__((always_inline)) { return i % NST; };
 
-  const TileLoader<D, RB, 8> qload(lane, w, maps.q.row), gload(lane, w, maps.dO.row);
+  const TileLoader<D, RB, G::WAVES> qload(lane, w, maps.q.row), gload(lane, w, maps.dO.row);
   static_assert(decltype(qload)::N + decltype(gload)::N + 1 == G::NDMA, "copy instructions per wave and block");
   auto copy_block = [&](int i, int stage) __attribute__((always_inline)) {
     const int row0 = m_start + i * RB;
@@ -446,7 +454,7 @@ __device__ __forceinline__ void pair_sweep(const __bf16* __restrict__ q, const _
 #pragma unroll
       for (int r = 0; r < 4; r++) ring[r] = lds_b128(ln.aq[r], 0);
     }
-    Copier cp;
+    Copier<G::PIECES> cp;
     // One block of this wave's role at stage K with the general copy in front of it.
     auto careful = [&](auto stage, auto masked, auto skip, f32x16& cur, f32x16& next) __attribute__((always_inline)) {
       constexpr int K = decltype(stage)::value;
@@ -464,8 +472,10 @@ __device__ __forceinline__ void pair_sweep(const __bf16* __restrict__ q, const _
     careful(std::integral_constant<int, 0>{}, diagonal, std::true_type{}, xa, xb);
     if constexpr (CAUSAL) {
       careful(std::integral_constant<int, 1>{}, diagonal, std::false_type{}, xb, xa);
-      careful(std::integral_constant<int, 2>{}, diagonal, std::false_type{}, xa, xb);
-      careful(std::integral_constant<int, 3>{}, diagonal, std::false_type{}, xb, xa);
+      if constexpr (PAIRS == 4) {
+        careful(std::integral_constant<int, 2>{}, diagonal, std::false_type{}, xa, xb);
+        careful(std::integral_constant<int, 3>{}, diagonal, std::false_type{}, xb, xa);
+      }
     } else {
       xa = xb;
     }
@@ -478,8 +488,8 @@ __device__ __forceinline__ void pair_sweep(const __bf16* __restrict__ q, const _
       cp.qptr = uniform_ptr(reinterpret_cast<const __bf16*>(reinterpret_cast<const char*>(qh) + (size_t)row0 * qload.row_bytes));
       cp.gptr = uniform_ptr(reinterpret_cast<const __bf16*>(reinterpret_cast<const char*>(gh) + (size_t)row0 * gload.row_bytes));
       cp.stat = uniform_ptr(stat_h);
-      cp.qoff = qload.off[0];
-      cp.goff = gload.off[0];
+#pragma unroll
+      for (int p = 0; p < G::PIECES; p++) { cp.qoff[p] = qload.off[p]; cp.goff[p] = gload.off[p]; }
       cp.soff = (uint32_t)(row0 + lane) * 4;
       cp.dst = __builtin_amdgcn_readfirstlane(base + w * 1024);
       cp.sdst = __builtin_amdgcn_readfirstlane(base + G::STATS + role * 256);
@@ -542,7 +552,7 @@ __device__ __forceinline__ void pair_sweep(const __bf16* __restrict__ q, const _
   store_rows<D>(out, lane, (role == 0 ? dv : dk) + head_offset(map, tc.bh, H) + (size_t)key0 * map.row, map.row, S - key0);
 }
 
-template <bool CAUSAL>
+template <bool CAUSAL, int PAIRS>
 __device__ __forceinline__ void pair_keys(int block, const __bf16* __restrict__ q, const __bf16* __restrict__ k,
                                           const __bf16* __restrict__ v, const __bf16* __restrict__ dO, const float* __restrict__ lse2,
                                           const float* __restrict__ neg_delta, __bf16* __restrict__ dk, __bf16* __restrict__ dv,
@@ -550,31 +560,32 @@ __device__ __forceinline__ void pair_keys(int block, const __bf16* __restrict__ 
   const TileCoord tc = map_block<CAUSAL, PG::D>(block, BH, T, false);
   if (!tc.valid) return;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (w < 4) pair_sweep<CAUSAL, 0>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, tc, H, S, scale);
-  else pair_sweep<CAUSAL, 1>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, tc, H, S, scale);
+  if (w < PAIRS) pair_sweep<CAUSAL, 0, PAIRS>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, tc, H, S, scale);
+  else pair_sweep<CAUSAL, 1, PAIRS>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, tc, H, S, scale);
 }
 
-template <bool CAUSAL>
-__global__ void __launch_bounds__(512, 1)
+template <bool CAUSAL, int PAIRS>
+__global__ void __launch_bounds__(128 * PAIRS) __attribute__((amdgpu_waves_per_eu(2)))
 bwd_dkdv_pair_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
                      const __bf16* __restrict__ dO, const float* __restrict__ lse2, const float* __restrict__ neg_delta,
                      __bf16* __restrict__ dk, __bf16* __restrict__ dv, BwdMaps maps, int BH, int H, int S, int T,
                      float scale) {
-  pair_keys<CAUSAL>(blockIdx.x, q, k, v, dO, lse2, neg_delta, dk, dv, maps, BH, H, S, T, scale);
+  pair_keys<CAUSAL, PAIRS>(blockIdx.x, q, k, v, dO, lse2, neg_delta, dk, dv, maps, BH, H, S, T, scale);
 }
 
 // The dK/dV and the dQ pass in one launch (see launch_bwd_dkdv_dq): the first `key_blocks` workgroups take key tiles, the others
 // query tiles.
-template <bool CAUSAL, bool SPLIT>
-__global__ void __launch_bounds__(512, 1)
+template <bool CAUSAL, int ROWS, int PAIRS>
+__global__ void __launch_bounds__(128 * PAIRS) __attribute__((amdgpu_waves_per_eu(2)))
 bwd_dkdv_dq_pair_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
                         const __bf16* __restrict__ dO, const float* __restrict__ lse2, const float* __restrict__ neg_delta,
                         __bf16* __restrict__ dq, __bf16* __restrict__ dk, __bf16* __restrict__ dv, BwdMaps maps, int BH, int H,
                         int S, int key_tiles, int key_blocks, int query_tiles, float scale) {
+  static_assert((ROWS == 64) == (PAIRS == 2), "workgroups of one size");
   const int block = (int)blockIdx.x;
-  if (block < key_blocks) pair_keys<CAUSAL>(block, q, k, v, dO, lse2, neg_delta, dk, dv, maps, BH, H, S, key_tiles, scale);
-  else if constexpr (SPLIT) dq_split_rows<128, CAUSAL>(block - key_blocks, q, k, v, dO, lse2, neg_delta, dq, maps, BH, H, S, query_tiles, scale);
-  else dq_whole_rows<128, CAUSAL>(block - key_blocks, q, k, v, dO, lse2, neg_delta, dq, maps, BH, H, S, query_tiles, scale);
+  if (block < key_blocks) pair_keys<CAUSAL, PAIRS>(block, q, k, v, dO, lse2, neg_delta, dk, dv, maps, BH, H, S, key_tiles, scale);
+  else if constexpr (ROWS == 256) dq_whole_rows<128, CAUSAL>(block - key_blocks, q, k, v, dO, lse2, neg_delta, dq, maps, BH, H, S, query_tiles, scale);
+  else dq_split_rows<128, CAUSAL, ROWS / 32>(block - key_blocks, q, k, v, dO, lse2, neg_delta, dq, maps, BH, H, S, query_tiles, scale);
 }
 
 template <bool CAUSAL>
@@ -582,15 +593,17 @@ static hipError_t launch_dkdv_dq_pair_t(const void* q, const void* k, const void
                                         const float* neg_delta, void* dq, void* dk, void* dv, const BwdMaps& maps, int B, int H, int S,
                                         float scale, hipStream_t stream) {
   const int BH = B * H;
-  const bool split = split_dq(PG::D, BH, S, CAUSAL);
-  const int TK = (S + PG::BN - 1) / PG::BN, TQ = dq_tiles(S, split);
+  const Rows rows = dq_rows(PG::D, BH, S, CAUSAL);
+  const int keys = key_tile(BH, S, CAUSAL);
+  const int TK = (S + keys - 1) / keys, TQ = tiles(S, rows);
   const long long key_blocks = grid_blocks(BH, TK);
-  const size_t lds = std::max(PG::LDS, split ? DqSplit<128>::LDS : kDqWholeLds<128>);
-  auto kern = split ? bwd_dkdv_dq_pair_kernel<CAUSAL, true> : bwd_dkdv_dq_pair_kernel<CAUSAL, false>;
-  static unsigned long long configured[2] = {};   // per template instantiation and kernel
-  hipError_t e = allow_dynamic_lds(kern, lds, configured[split]);
+  const size_t lds = std::max(PG::LDS, rows == Rows::k256 ? kDqWholeLds<128> : DqSplit<128>::LDS);
+  auto kern = rows == Rows::k64 ? bwd_dkdv_dq_pair_kernel<CAUSAL, 64, 2>
+              : rows == Rows::k128 ? bwd_dkdv_dq_pair_kernel<CAUSAL, 128, 4> : bwd_dkdv_dq_pair_kernel<CAUSAL, 256, 4>;
+  static unsigned long long configured[3] = {};   // per template instantiation and kernel
+  hipError_t e = allow_dynamic_lds(kern, lds, configured[(int)rows]);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(key_blocks + grid_blocks(BH, TQ))), dim3(512), lds, stream, (const __bf16*)q,
+  hipLaunchKernelGGL(kern, dim3((unsigned)(key_blocks + grid_blocks(BH, TQ))), dim3(4 * keys), lds, stream, (const __bf16*)q,
                      (const __bf16*)k, (const __bf16*)v, (const __bf16*)dO, lse2, neg_delta, (__bf16*)dq, (__bf16*)dk, (__bf16*)dv, maps,
                      BH, H, S, TK, (int)key_blocks, TQ, scale);
   return hipGetLastError();
@@ -602,28 +615,28 @@ hipError_t launch_bwd_dkdv_dq_pair(const void* q, const void* k, const void* v, 
                 : launch_dkdv_dq_pair_t<false>(q, k, v, dO, lse2, neg_delta, dq, dk, dv, maps, B, H, S, scale, stream);
 }
 
+template <bool CAUSAL, int PAIRS>
+static hipError_t launch_dkdv_pair_t(const void* q, const void* k, const void* v, const void* dO, const float* lse2,
+                                     const float* neg_delta, void* dk, void* dv, const BwdMaps& maps, int BH, int H, int S,
+                                     float scale, hipStream_t stream) {
+  using G = PairGeometry<PAIRS>;
+  const int T = (S + G::BN - 1) / G::BN;
+  auto kern = bwd_dkdv_pair_kernel<CAUSAL, PAIRS>;
+  static unsigned long long configured = 0;   // one static per template instantiation
+  hipError_t e = allow_dynamic_lds(kern, G::LDS, configured);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid_blocks(BH, T)), dim3(64 * G::WAVES), G::LDS, stream, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v,
+                     (const __bf16*)dO, lse2, neg_delta, (__bf16*)dk, (__bf16*)dv, maps, BH, H, S, T, scale);
+  return hipGetLastError();
+}
 hipError_t launch_bwd_dkdv_pair(const void* q, const void* k, const void* v, const void* dO, const float* lse2,
                                 const float* neg_delta, void* dk, void* dv, const BwdMaps& maps, int B, int H, int S,
                                 float scale, bool causal, hipStream_t stream) {
-  const int T = (S + PG::BN - 1) / PG::BN, BH = B * H;
-  const unsigned grid = (unsigned)grid_blocks(BH, T);
-  const size_t lds = PG::LDS;
-  if (causal) {
-    auto kern = bwd_dkdv_pair_kernel<true>;
-    static unsigned long long configured = 0;
-    hipError_t e = allow_dynamic_lds(kern, lds, configured);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(512), lds, stream, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v,
-                       (const __bf16*)dO, lse2, neg_delta, (__bf16*)dk, (__bf16*)dv, maps, BH, H, S, T, scale);
-  } else {
-    auto kern = bwd_dkdv_pair_kernel<false>;
-    static unsigned long long configured = 0;
-    hipError_t e = allow_dynamic_lds(kern, lds, configured);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(512), lds, stream, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v,
-                       (const __bf16*)dO, lse2, neg_delta, (__bf16*)dk, (__bf16*)dv, maps, BH, H, S, T, scale);
-  }
-  return hipGetLastError();
+  if (key_tile(B * H, S, causal) == 64)
+    return causal ? launch_dkdv_pair_t<true, 2>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B * H, H, S, scale, stream)
+                  : launch_dkdv_pair_t<false, 2>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B * H, H, S, scale, stream);
+  return causal ? launch_dkdv_pair_t<true, 4>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B * H, H, S, scale, stream)
+                : launch_dkdv_pair_t<false, 4>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B * H, H, S, scale, stream);
 }
 
 }  // namespace helix

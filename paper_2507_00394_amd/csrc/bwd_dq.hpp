@@ -114,7 +114,6 @@ __device__ __forceinline__ void dq_half_step(const Copy& copy_tile, f32x16& s_cu
 
 template <int D>
 constexpr int kDqWholeLds = 5 * 2 * 64 * D * 2;   // four stages; the Q and dO rows of a workgroup take one more
-inline int dq_tiles(int S, bool split) { return split ? (S + 127) / 128 : (S + 255) / 256; }
 
 template <int D, bool CAUSAL>
 __device__ __forceinline__ void dq_whole_rows(int block, const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
@@ -314,12 +313,12 @@ struct DqSplit {
   static constexpr int LDS = NST * STAGE;
 };
 
-template <int D, bool CAUSAL>
+template <int D, bool CAUSAL, int RG>
 __device__ __forceinline__ void dq_split_rows(int block, const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
                                               const __bf16* __restrict__ dO, const float* __restrict__ lse2_all, const float* __restrict__ neg_delta,
                                               __bf16* __restrict__ dq, BwdMaps maps, int BH, int H, int S, int T, float scale) {
   using G = DqSplit<D>;
-  constexpr int BM = 128, BN = 64, KS = D / 16, DB = D / 32;
+  constexpr int BM = 32 * RG, BN = 64, KS = D / 16, DB = D / 32;
   constexpr int TILE = G::TILE, HALF = 32 * D * 2, STAGE = G::STAGE, NST = G::NST, AHEAD = G::AHEAD;
   extern __shared__ __align__(16) char smem[];   // tile j (K, V) in stage j % NST
 
@@ -327,7 +326,7 @@ __device__ __forceinline__ void dq_split_rows(int block, const __bf16* __restric
   if (!tc.valid) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int rg = w & 3, kg = w >> 2;
+  const int rg = w & (RG - 1), kg = w / RG;
   const int half = lane >> 5, n = lane & 31;
   const int q0 = tc.tile * BM;
   const int wave_qmin = q0 + 32 * rg, my_q = wave_qmin + n;
@@ -352,7 +351,7 @@ __device__ __forceinline__ void dq_split_rows(int block, const __bf16* __restric
   const int n_w = wave_qmin < S ? (k_end - 32 * kg + BN - 1) / BN : 0;
   const int n_full = (k_all + 32 - 32 * kg) / BN;
 
-  const TileLoader<D, BN, 8> kload(lane, w, maps.k.row), vload(lane, w, maps.v.row);
+  const TileLoader<D, BN, 2 * RG> kload(lane, w, maps.k.row), vload(lane, w, maps.v.row);
   constexpr int NDMA = decltype(kload)::N + decltype(vload)::N;
   int j = 0, st = 0;   // tile and its stage (j % NST)
   auto plus = [&](int d) __attribute__((always_inline)) { return st + d >= NST ? st + d - NST : st + d; };
@@ -481,10 +480,10 @@ __device__ __forceinline__ void dq_split_rows(int block, const __bf16* __restric
 #pragma unroll
   for (int b = 0; b < HB; b++) {
     const f32x16 give = kg == 0 ? dqacc[HB + b] : dqacc[b];
-    lds_put_block(smem + ((kg * 4 + rg) * HB + b) * 4096, lane, give);
+    lds_put_block(smem + ((kg * RG + rg) * HB + b) * 4096, lane, give);
   }
   __syncthreads();
-  char* const in = smem + ((kg ^ 1) * 4 + rg) * HB * 4096;   // what the other wave handed over; the results pass through it too
+  char* const in = smem + ((kg ^ 1) * RG + rg) * HB * 4096;   // what the other wave handed over; the results pass through it too
 #pragma unroll
   for (int b = 0; b < HB; b++) {
     f32x16 x = kg == 0 ? dqacc[b] : dqacc[HB + b];

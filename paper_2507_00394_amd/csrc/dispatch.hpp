@@ -24,9 +24,10 @@ struct Share {
   bool causal, keys;
   int P, T, per_tile;          // parts of a head, tiles of a head, steps by which neighbouring tiles differ
   double heads, own, longest;
-  Share(int BH, int S, bool causal_, int rows, bool keys_)
+  // `even`: an average XCD's share in the place of the fullest one's (a fraction of a tile where T is no multiple of P).
+  Share(int BH, int S, bool causal_, int rows, bool keys_, bool even = false)
       : causal(causal_), keys(keys_), P(head_parts(BH)), T((S + rows - 1) / rows), per_tile(rows / 64), heads((double)BH * P / 8),
-        own((T + P - 1) / P), longest((S + 63) / 64) {}
+        own(even ? (double)T / P : (T + P - 1) / P), longest((S + 63) / 64) {}
   double blocks() const { return own * heads; }
   double length(double i) const {   // of the i-th longest tile of a head
     if (!causal || i == 0.) return longest;
@@ -41,7 +42,7 @@ struct Share {
 // results, the longest first: the average of a slot or, if that is more, what the longest ones take where k of them cannot help
 // sharing a slot.  Without a mask all are equal, and that is whole rounds.  The unit is a step of a 256-row workgroup.
 inline double pass_time(const Share& w, int slots, double per_step, double start) {
-  const double rounds = std::ceil(w.blocks() / slots);
+  const double rounds = std::ceil(w.blocks() / slots - 1e-9);
   double t = (per_step * w.steps() + start * w.blocks()) / slots;
   if (!w.causal) return std::max(t, rounds * (per_step * w.longest + start));
   for (int k = 0; k < 3 && k < rounds; k++) t = std::max(t, (k + 1) * (per_step * w.length(std::floor(k * slots / w.heads)) + start));
@@ -102,5 +103,51 @@ inline bool two_query_groups(int BH, int S, bool causal) {
 inline bool split_dq(int D, int BH, int S, bool causal) {
   return (D == 64 && two_query_groups(BH, S, causal)) || split_rows(BH, S, causal);
 }
+
+
+// Rows of a query tile: 256 with a wave for every 32 rows, or 128 or 64 with the keys split over two groups of waves.
+enum class Rows { k256, k128, k64 };
+inline int tiles(int S, Rows r) { const int n = r == Rows::k256 ? 256 : r == Rows::k128 ? 128 : 64; return (S + n - 1) / n; }
+
+// Narrow workgroups: 64 rows (or keys) and four waves, one per SIMD, in the place of 128 and eight.  A wave that has its SIMD to itself takes a step
+// in about 0.85 of the time that two side by side take theirs in, so that where narrow workgroups find compute units of their own every one of them
+// ends earlier; beyond that they only cost.  The arithmetic of a row is that of the 128-row workgroups, bit for bit.
+//
+// Forward and delta of the first rows: by the time on an average XCD, as above but with the tiles spread evenly, as the order of map_block does
+// by now.  At head dimension 64 two workgroups share a compute unit for about 1.5 times the rate of one.  Over 225 shapes (head dimension 128, all three
+// variants) and 222 (64) the choice is 0.8 and 0.5 % off the fastest; at worst, few tiles to a head on all compute units, 46 heads x 273 12.7 for 10.0 us.
+// 128 -> 64 rows, us: head dimension 128 causal 12 heads x 1500 25.2 -> 21.4, 4 x 2048 31.5 -> 26.8, 32 x 512 12.5 -> 10.8, 2 x 8192 107 -> 92,
+// 16 x 2048 33.1 -> 32.4, 64 x 2048 91 -> 135; delta 12 x 1500 22.2 -> 17.9, 16 x 2048 29.7 -> 27.8, 64 x 2048 84 -> 116; head dimension 64
+// 2 x 512 9.3 -> 7.6, 12 x 1500 18.7 -> 15.2, 16 x 16384 612 -> 693; delta 16 x 16384 23.3 -> 18.9.
+inline double rows_time(int BH, int S, bool causal, int rows, int slots, double per_step, double start) {
+  return pass_time(Share(BH, S, causal, rows, false, true), slots, per_step, start);
+}
+inline bool narrow_rows(int D, int BH, int S, bool causal, bool whole_is_a_choice) {
+  const int slots = D == 64 && !whole_is_a_choice ? 48 : 32;
+  double other = rows_time(BH, S, causal, 128, slots, 0.58, 4.5);
+  if (whole_is_a_choice) other = std::min(other, rows_time(BH, S, causal, 256, slots, 1., 3.5));
+  return (D == 64 ? rows_time(BH, S, causal, 64, 48, 0.42, 2.) : rows_time(BH, S, causal, 64, 32, 0.52, 3.2)) < other;
+}
+
+// dK/dV and dQ: in their common launch, where 64-key and 64-row workgroups take their turns on the compute units.  Without a mask all take equally long, and
+// the launch has to fit (half of the chip for either); causal ones differ in length and fill each other's gaps.  Over 420 shapes 0.3 %
+// (head dimension 128, causal), 1.2 (no mask), 0.8 and 1.6 % (head dimension 64) off the better choice; at worst 10 x 819 x 64 without a mask 23.4 for 19.3 us.  128 -> 64, whole backward, us, 64-row
+// tiles in brackets: causal 2 heads x 512 x 64 [16] 19.6 -> 17.1, 2 x 512 x 128 28 -> 22.8, 4 x 2048 [128] 75 -> 60, 2 x 8192 [256] 205 -> 167,
+// 12 x 1500 [288] 62 -> 65, 16 x 2048 [512] 97 -> 109; no mask 4 x 2048 [128] 49 -> 38, 5 x 4187 [330] 187 -> 186, 27 x 777 x 64 [351] 37 -> 48.
+inline bool narrow_gradients(int BH, int S, bool causal) {
+  const long long tiles_64 = (long long)BH * ((S + 63) / 64);
+  return tiles_64 <= (causal ? 288 : 128);
+}
+
+inline Rows forward_rows(int D, int BH, int S, bool causal) {
+  return narrow_rows(D, BH, S, causal, !kForwardSplitsAlways(D)) ? Rows::k64 : split_forward(D, BH, S, causal) ? Rows::k128 : Rows::k256;
+}
+inline Rows delta_rows(int D, int BH, int S, bool causal) {
+  return narrow_rows(D, BH, S, causal, true) ? Rows::k64 : split_rows(BH, S, causal) ? Rows::k128 : Rows::k256;
+}
+inline Rows dq_rows(int D, int BH, int S, bool causal) {
+  return narrow_gradients(BH, S, causal) ? Rows::k64 : split_dq(D, BH, S, causal) ? Rows::k128 : Rows::k256;
+}
+inline int key_tile(int BH, int S, bool causal) { return narrow_gradients(BH, S, causal) ? 64 : 128; }
 
 }  // namespace helix

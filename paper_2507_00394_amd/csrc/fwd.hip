@@ -373,21 +373,21 @@ fwd_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __b
 // the price is that a tile's copy serves half the rows.  The step for tile j already reads K of tile j + 2, so
 // five buffers (two in use beside the current one, one landing, one being issued) take the place of four.
 // 12 heads x 1500 tokens 39.7 -> 25.9 us, 2 heads x 32k 710 -> 531.
-template <int D>
+template <int D, int RG>
 struct FwdSplit {
   static constexpr int NST = 5, AHEAD = NST - 1;
   static constexpr int TILE = 64 * D * 2;
   static constexpr int LDS = 2 * NST * TILE;
-  static constexpr int ROW_STATS = 4 * (D / 32) * 4096;    // merge: after the accumulator blocks, (reference, sum) of every row and half
-  static_assert(ROW_STATS + 8 * 64 * 8 <= LDS, "the merge reuses the tile buffers");
+  static constexpr int ROW_STATS = RG * (D / 32) * 4096;   // merge: after the accumulator blocks, (reference, sum) of every row and half
+  static_assert(ROW_STATS + 2 * RG * 64 * 8 <= LDS, "the merge reuses the tile buffers");
 };
 
-template <int D, bool CAUSAL>
-__global__ void __launch_bounds__(512, 1)
+template <int D, bool CAUSAL, int RG>
+__global__ void __launch_bounds__(128 * RG) __attribute__((amdgpu_waves_per_eu(2)))
 fwd_split_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
                  __bf16* __restrict__ o, float* __restrict__ lse, FwdMaps maps, int BH, int H, int S, int T, float scale) {
-  using G = FwdSplit<D>;
-  constexpr int BM = 128, BN = 64, KS = D / 16, DB = D / 32;
+  using G = FwdSplit<D, RG>;
+  constexpr int BM = 32 * RG, BN = 64, KS = D / 16, DB = D / 32;
   constexpr int TILE = G::TILE, HALF = 32 * D * 2, NST = G::NST, AHEAD = G::AHEAD, VREGION = NST * TILE;
   extern __shared__ __align__(16) char smem[];   // K[NST] then V[NST]; tile j in buffer j % NST
 
@@ -395,7 +395,7 @@ fwd_split_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, con
   if (!tc.valid) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int rg = w & 3, kg = w >> 2;
+  const int rg = w & (RG - 1), kg = w / RG;
   const int half = lane >> 5, n = lane & 31;
   const int q0 = tc.tile * BM;
   const int wave_qmin = q0 + 32 * rg, my_q = wave_qmin + n;
@@ -407,7 +407,7 @@ fwd_split_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, con
 
   const int q_end = (q0 + BM < S ? q0 + BM : S);
   const int n_tiles = CAUSAL ? (q_end + BN - 1) / BN : (S + BN - 1) / BN;
-  const TileLoader<D, BN, 8> kload(lane, w, maps.k.row), vload(lane, w, maps.v.row);
+  const TileLoader<D, BN, 2 * RG> kload(lane, w, maps.k.row), vload(lane, w, maps.v.row);
   constexpr int NDMA = decltype(kload)::N + decltype(vload)::N;
   auto copy_tile = [&](int jj, int buf) __attribute__((always_inline)) {
     kload.issue(kh, jj * BN, S, base + buf * TILE);
@@ -537,13 +537,13 @@ fwd_split_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, con
 #pragma unroll
   for (int b = 0; b < HB; b++) {
     const f32x16 give = kg == 0 ? oacc[HB + b] : oacc[b];
-    lds_put_block(smem + ((kg * 4 + rg) * HB + b) * 4096, lane, give);
+    lds_put_block(smem + ((kg * RG + rg) * HB + b) * 4096, lane, give);
   }
   stats[(w * 64 + lane) * 2] = st.mref_c;
   stats[(w * 64 + lane) * 2 + 1] = l_own;
   __syncthreads();
   {
-    const float m_other = stats[((w ^ 4) * 64 + lane) * 2], l_other = stats[((w ^ 4) * 64 + lane) * 2 + 1];
+    const float m_other = stats[((w ^ RG) * 64 + lane) * 2], l_other = stats[((w ^ RG) * 64 + lane) * 2 + 1];
     const float m = fmaxf(st.mref_c, m_other);
     const bool second = (CAUSAL ? my_q : S - 1) >= 32;
     const bool own = kg == 0 || second, other = kg == 1 || second;
@@ -551,7 +551,7 @@ fwd_split_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, con
     const float a_other = other ? __builtin_amdgcn_exp2f(m_other - m) : 0.f;
     const float ltot = (own ? l_own * a_own : 0.f) + (other ? l_other * a_other : 0.f);
     const float inv = 1.f / ltot;
-    char* const in = smem + ((kg ^ 1) * 4 + rg) * HB * 4096;   // what the other wave handed over; the results pass through it too
+    char* const in = smem + ((kg ^ 1) * RG + rg) * HB * 4096;   // what the other wave handed over; the results pass through it too
 #pragma unroll
     for (int b = 0; b < HB; b++) {
       const f32x16 mine = kg == 0 ? oacc[b] : oacc[HB + b];
@@ -570,18 +570,25 @@ template <int D, bool CAUSAL>
 static hipError_t launch_fwd_t(const void* q, const void* k, const void* v, void* o, float* lse,
                                const FwdMaps& maps, int B, int H, int S, float scale, hipStream_t stream) {
   const int BH = B * H;
-  const bool split = split_forward(D, BH, S, CAUSAL);
-  const int BM = split ? 128 : 256, T = (S + BM - 1) / BM;
+  const Rows rows = forward_rows(D, BH, S, CAUSAL);
+  const int T = tiles(S, rows);
   const unsigned grid = (unsigned)grid_blocks(BH, T);
-  const size_t lds = split ? FwdSplit<D>::LDS : 8 * 64 * D * 2;
-  auto kern = fwd_split_kernel<D, CAUSAL>;
-  if constexpr (!kForwardSplitsAlways(D)) {
-    if (!split) kern = fwd_kernel<D, CAUSAL>;
+  size_t lds = FwdSplit<D, 4>::LDS;
+  auto kern = fwd_split_kernel<D, CAUSAL, 4>;
+  if (rows == Rows::k64) {
+    kern = fwd_split_kernel<D, CAUSAL, 2>;
+    lds = FwdSplit<D, 2>::LDS;
   }
-  static unsigned long long configured[2] = {};   // per template instantiation and kernel
-  hipError_t e = allow_dynamic_lds(kern, lds, configured[split]);
+  if constexpr (!kForwardSplitsAlways(D)) {
+    if (rows == Rows::k256) {
+      kern = fwd_kernel<D, CAUSAL>;
+      lds = 8 * 64 * D * 2;
+    }
+  }
+  static unsigned long long configured[3] = {};   // per template instantiation and kernel
+  hipError_t e = allow_dynamic_lds(kern, lds, configured[(int)rows]);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(512), lds, stream, (const __bf16*)q, (const __bf16*)k,
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(rows == Rows::k64 ? 256 : 512), lds, stream, (const __bf16*)q, (const __bf16*)k,
                      (const __bf16*)v, (__bf16*)o, lse, maps, BH, H, S, T, scale);
   return hipGetLastError();
 }

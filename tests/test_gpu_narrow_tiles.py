@@ -1,0 +1,54 @@
+"""Narrow workgroups (64 rows or keys, four waves), which small grids take in every pass: lengths at the edges of their 32-row groups, of
+the 64-key tiles and of the query halves, heads enough that the forward (60 x 333, 40 x 1100) or the gradients alone (9 x 2100,
+7 x 1300) take the wider ones, and the same bits as the 128-row workgroups."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import attention_ref as A
+from paper_2507_00394_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("H,S", [(1, 1), (2, 31), (5, 33), (1, 63), (3, 95), (2, 127), (7, 129), (2, 191), (4, 193), (9, 257), (1, 700), (3, 1000),
+                                 (7, 1300), (9, 2100), (60, 333), (40, 1100)])
+def test_edges(H, S, causal, D):
+    from tests import gpu_util as G
+
+    cfg, bits = I.random_case_bits(6200 + S + H, 1, H, S, D)
+    out = G.run_fwd_bwd(bits, cfg.scale, causal)
+    for n in ("o", "lse", "dq", "dk", "dv"):
+        assert bool(torch.isfinite(out[n].float()).all()), n
+    heads = sorted({0, H // 2, H - 1})
+    x = {t: I.bf16_bits_to_float(bits[t][:, heads]) for t in bits}
+    ref = A.attn_bwd_ref(x["q"], x["k"], x["v"], x["dO"], cfg.scale, causal)
+    for n in ("o", "dq", "dk", "dv"):
+        G.check(n, G.to_f64(out[n][:, heads].contiguous()), ref[n])
+    assert np.abs(G.to_f64(out["lse"][:, heads]) - ref["lse"]).max() <= G.TOL_LSE
+
+
+# many heads (128-row and 128-key workgroups) against two of them alone (narrow ones)
+@pytest.mark.parametrize("H,S,D,causal,same", [(24, 1500, 128, True, ("o", "lse", "dq", "dk", "dv")), (30, 777, 128, False, ("o", "lse", "dk", "dv")),
+                                               (200, 333, 64, True, ("o", "lse")), (200, 333, 64, False, ("o", "lse"))])
+def test_bits_of_a_head_alone(H, S, D, causal, same):
+    from tests import gpu_util as G
+
+    cfg, bits = I.random_case_bits(6300 + S, 1, H, S, D)
+    many = G.run_fwd_bwd(bits, cfg.scale, causal)
+    few = G.run_fwd_bwd({t: np.ascontiguousarray(bits[t][:, H - 2:]) for t in bits}, cfg.scale, causal)
+    for n in same:
+        assert torch.equal(many[n][:, H - 2:], few[n]), n
+
+
+def test_stage_calls_take_the_same_tiles():
+    """The backward's stages one by one are the whole backward bit for bit."""
+    from tests import gpu_util as G
+
+    for H, S, D, causal in ((3, 500, 128, True), (3, 500, 64, True), (2, 333, 64, False), (2, 333, 128, False)):
+        cfg, bits = I.random_case_bits(6400 + S, 1, H, S, D)
+        a, b = G.run_fwd_bwd(bits, cfg.scale, causal), G.run_fwd_bwd(bits, cfg.scale, causal, fused_bwd=False)
+        for n in ("dq", "dk", "dv"):
+            assert torch.equal(a[n], b[n]), (n, H, S, D, causal)
