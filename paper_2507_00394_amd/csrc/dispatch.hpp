@@ -105,19 +105,18 @@ inline bool split_dq(int D, int BH, int S, bool causal) {
 }
 
 
-// Rows of a query tile: 256 with a wave for every 32 rows, or 128 or 64 with the keys split over two groups of waves.
-enum class Rows { k256, k128, k64 };
+// Rows of a query tile: 256 with a wave for every 32 rows, or 128 or 64 with the keys split over two groups of waves, or 64 over four.
+enum class Rows { k256, k128, k64, k64Quad };
 inline int tiles(int S, Rows r) { const int n = r == Rows::k256 ? 256 : r == Rows::k128 ? 128 : 64; return (S + n - 1) / n; }
 
 // Narrow workgroups: 64 rows (or keys) and four waves, one per SIMD, in the place of 128 and eight.  A wave that has its SIMD to itself takes a step
 // in about 0.85 of the time that two side by side take theirs in, so that where narrow workgroups find compute units of their own every one of them
 // ends earlier; beyond that they only cost.  The arithmetic of a row is that of the 128-row workgroups, bit for bit.
 //
-// Forward and delta of the first rows: by the time on an average XCD, as above but with the tiles spread evenly, as the order of map_block does
-// by now.  At head dimension 64 two workgroups share a compute unit for about 1.5 times the rate of one.  Over 225 shapes (head dimension 128, all three
-// variants) and 222 (64) the choice is 0.8 and 0.5 % off the fastest; at worst, few tiles to a head on all compute units, 46 heads x 273 12.7 for 10.0 us.
-// 128 -> 64 rows, us: head dimension 128 causal 12 heads x 1500 25.2 -> 21.4, 4 x 2048 31.5 -> 26.8, 32 x 512 12.5 -> 10.8, 2 x 8192 107 -> 92,
-// 16 x 2048 33.1 -> 32.4, 64 x 2048 91 -> 135; delta 12 x 1500 22.2 -> 17.9, 16 x 2048 29.7 -> 27.8, 64 x 2048 84 -> 116; head dimension 64
+// Delta of the first rows, and the forward at head dimension 64: by the time on an average XCD, as above but with the tiles spread evenly, as the order of map_block does
+// by now.  At head dimension 64 two workgroups share a compute unit for about 1.5 times the rate of one.  Over 222 shapes
+// of the forward and 145 and 149 of delta (head dimension 128 and 64) the choice is 0.5, 0.4 and 0.1 % off the fastest; at worst 71 heads x 1177 without a mask 63 for 50 us.
+// 128 -> 64 rows, us: delta, head dimension 128 12 heads x 1500 22.2 -> 17.9, 16 x 2048 29.7 -> 27.8, 64 x 2048 84 -> 116; head dimension 64
 // 2 x 512 9.3 -> 7.6, 12 x 1500 18.7 -> 15.2, 16 x 16384 612 -> 693; delta 16 x 16384 23.3 -> 18.9.
 inline double rows_time(int BH, int S, bool causal, int rows, int slots, double per_step, double start) {
   return pass_time(Share(BH, S, causal, rows, false, true), slots, per_step, start);
@@ -139,8 +138,16 @@ inline bool narrow_gradients(int BH, int S, bool causal) {
   return tiles_64 <= (causal ? 288 : 128);
 }
 
+// The forward at head dimension 128 has both, narrow workgroups with two key groups, which start and end sooner, and eight waves in four, which have half the
+// steps.  Over 300 shapes the choice among all four is 1.5 % off the fastest (5.1 % without the last); at worst short sequences of many heads, 155 x 203
+// 31 for 24 us, and 11 x 1399 without a mask, whose tiles just fill the chip, 34 for 26.  256 / 128 / 64 / 64 in four groups, us: causal
+// 4 heads x 1124 25.5 / 19.9 / 17.3 / 14.9, 12 x 1500 39 / 25.2 / 21.4 / 19.4, 2 x 8192 - / 107 / 91 / 70, 3 x 300 - / - / 8.25 / 8.6, 52 x 543 18.0 / 19.4 / 19.4 / 21.1.
 inline Rows forward_rows(int D, int BH, int S, bool causal) {
-  return narrow_rows(D, BH, S, causal, !kForwardSplitsAlways(D)) ? Rows::k64 : split_forward(D, BH, S, causal) ? Rows::k128 : Rows::k256;
+  if (kForwardSplitsAlways(D)) return narrow_rows(D, BH, S, causal, false) ? Rows::k64 : Rows::k128;
+  const double wide = std::min(rows_time(BH, S, causal, 256, 32, 1., 3.5), rows_time(BH, S, causal, 128, 32, 0.58, 4.5));
+  const double narrow = rows_time(BH, S, causal, 64, 32, 0.52, 3.2), quad = rows_time(BH, S, causal, 64, 32, 0.38, 4.5);
+  if (std::min(narrow, quad) < wide) return quad < narrow ? Rows::k64Quad : Rows::k64;
+  return split_forward(D, BH, S, causal) ? Rows::k128 : Rows::k256;
 }
 inline Rows delta_rows(int D, int BH, int S, bool causal) {
   return narrow_rows(D, BH, S, causal, true) ? Rows::k64 : split_rows(BH, S, causal) ? Rows::k128 : Rows::k256;

@@ -566,6 +566,248 @@ fwd_split_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, con
   }
 }
 
+// The forward at head dimension 128 for small grids: a workgroup owns 64 query rows and its four pairs of waves share the keys, wave
+// (rg, kg) on 32 rows and key block kg of every 128-key tile.  A quarter of the steps of a 256-row workgroup at two waves per SIMD; a
+// tile's copy serves 64 rows.  A tile of K and V takes 64 KB, so LDS holds three of K and two of V, and a step reads nothing ahead of its own
+// tiles: K(j+1), which it scores, and V(j).  K runs two tiles ahead, V(j+1) has the length of step j to land, which it does not always keep: a step
+// takes 1.0 us where the split kernel's takes 0.79.  64 rows in two groups -> in four, us: 12 heads x 1500 22.3 -> 19.6, 4 x 2048 26.5 -> 22.1,
+// 2 x 8192 91 -> 70, 3 x 300 8.25 -> 8.6 (the merge of four).
+template <int D>
+struct FwdQuad {
+  static constexpr int KG = 4, RG = 2, NK = 3, NV = 2;
+  static constexpr int TILE = 32 * KG * D * 2;
+  static constexpr int LDS = (NK + NV) * TILE;
+  static constexpr int STATS = 8 * (D / 32) * 4096;          // merge: after the accumulator blocks, (reference, sum) of every row and group
+  static_assert(STATS + 8 * 64 * 8 <= LDS && D / 32 == KG, "the merge reuses the tile buffers; a wave finishes one block of the head dimension");
+};
+
+// One step: S of the next tile while P of this one is formed and multiplied, in 16 slots like half_step.
+template <int D, typename Copy>
+__device__ __forceinline__ float quad_step(const Copy& copy_tiles, const f32x16& s_cur, f32x16& s_next, const bf16x8 (&qf)[D / 16],
+                                           const int (&kaddr)[D / 16], const int (&vaddr)[D / 32][2], uint32_t kbuf, uint32_t vbuf,
+                                           f32x16 (&oacc)[D / 32], float c, SoftmaxState& st) {
+  constexpr int KS = D / 16, DB = D / 32, RING = KS / 2;
+  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  bf16x8 kop[RING], vop[RING];
+  float ev[16];
+  uint32_t pw[8];
+  auto element = [&](int x) {
+    ev[x] = __builtin_amdgcn_exp2f(fmaf(s_cur[x], c, -st.mref_c));
+    st.lsum[x & 1] += ev[x];
+    if (x & 1) pw[x / 2] = pack_bf16_pair(ev[x - 1], ev[x]);
+  };
+#pragma unroll
+  for (int i = 0; i < RING; i++) kop[i] = lds_b128(kbuf + kaddr[i]);
+#pragma unroll
+  for (int i = 0; i < KS; i++) {
+    s_next = mfma32(kop[i % RING], qf[i], i == 0 ? zero : s_next);
+    if (i < RING) kop[i] = lds_b128(kbuf + kaddr[i + RING]);
+    else vop[i - RING] = lds_tr_pair(vbuf + vaddr[i - RING][0], vbuf + vaddr[i - RING][1], 0);
+    if (i == 1) copy_tiles();
+#pragma unroll
+    for (int x = 0; x < kExpInScoreSlots; x++)
+      if (x * KS / kExpInScoreSlots == i) element(x);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  float m0 = 0.f, m1 = 0.f, m2 = 0.f, m3 = 0.f, m4 = 0.f;
+#pragma unroll
+  for (int i = 0; i < KS; i++) {
+    const u32x4 pk = {pw[4 * (i / DB)], pw[4 * (i / DB) + 1], pw[4 * (i / DB) + 2], pw[4 * (i / DB) + 3]};
+    oacc[i % DB] = mfma32(vop[i % RING], __builtin_bit_cast(bf16x8, pk), oacc[i % DB]);
+    if (i < RING) {
+      vop[i] = lds_tr_pair(vbuf + vaddr[i][0], vbuf + vaddr[i][1], 16 * D * 2);
+#pragma unroll
+      for (int x = kExpInScoreSlots; x < 16; x++)
+        if ((x - kExpInScoreSlots) * RING / (16 - kExpInScoreSlots) == i) element(x);
+    }
+    if (i == KS - 4) { m0 = fmaxf(fmaxf(s_next[0], s_next[1]), s_next[2]); m1 = fmaxf(fmaxf(s_next[3], s_next[4]), s_next[5]); pin(m0); pin(m1); }
+    if (i == KS - 3) { m2 = fmaxf(fmaxf(s_next[6], s_next[7]), s_next[8]); m3 = fmaxf(fmaxf(s_next[9], s_next[10]), s_next[11]); pin(m2); pin(m3); }
+    if (i == KS - 2) { m4 = fmaxf(fmaxf(s_next[12], s_next[13]), s_next[14]); m0 = fmaxf(fmaxf(m0, m1), s_next[15]); pin(m4); pin(m0); }
+    if (i == KS - 1) { m2 = fmaxf(fmaxf(m2, m3), m4); m0 = fmaxf(m0, m2); pin(m0); }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  return m0;
+}
+
+template <int D, bool CAUSAL>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
+fwd_quad_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
+                __bf16* __restrict__ o, float* __restrict__ lse, FwdMaps maps, int BH, int H, int S, int T, float scale) {
+  using G = FwdQuad<D>;
+  constexpr int RG = G::RG, KG = G::KG, BM = 32 * RG, BN = 32 * KG, KS = D / 16, DB = D / 32;
+  constexpr int TILE = G::TILE, HALF = 32 * D * 2, VREGION = G::NK * TILE;
+  extern __shared__ __align__(16) char smem[];   // K[3] then V[2]; tile j in buffers j % 3 and j % 2
+
+  const TileCoord tc = map_block<CAUSAL, D>(blockIdx.x, BH, T, true);
+  if (!tc.valid) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rg = w & (RG - 1), kg = w / RG;
+  const int half = lane >> 5, n = lane & 31;
+  const int q0 = tc.tile * BM;
+  const int wave_qmin = q0 + 32 * rg, my_q = wave_qmin + n;
+  const __bf16* qh = q + head_offset(maps.q, tc.bh, H);
+  const __bf16* kh = k + head_offset(maps.k, tc.bh, H);
+  const __bf16* vh = v + head_offset(maps.v, tc.bh, H);
+  const float c = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, scale * kLog2e)));
+  const uint32_t base = lds_base(smem);
+
+  const int q_end = (q0 + BM < S ? q0 + BM : S);
+  const int n_tiles = CAUSAL ? (q_end + BN - 1) / BN : (S + BN - 1) / BN;
+  const TileLoader<D, BN, 8> kload(lane, w, maps.k.row), vload(lane, w, maps.v.row);
+  constexpr int NDMA = decltype(kload)::N;   // copy instructions per wave and tile of K or V
+
+  // the Q rows pass through the second V buffer; the four waves of a row group copy a quarter each
+  const uint32_t frag = base + VREGION + TILE + rg * HALF;
+  issue_fragments<D, KG>(qh, maps.q.row, wave_qmin, S, lane, kg, frag);
+  kload.issue(kh, 0, S, base);
+  vload.issue(vh, 0, S, base + VREGION);
+  if (n_tiles > 1) kload.issue(kh, BN, S, base + TILE);
+  if (n_tiles > 2) kload.issue(kh, 2 * BN, S, base + 2 * TILE);
+  f32x16 oacc[DB];
+#pragma unroll
+  for (int db = 0; db < DB; db++)
+#pragma unroll
+    for (int e = 0; e < 16; e++) oacc[db][e] = 0.f;
+  SoftmaxState st;
+  if (kg > 0) st.mref_c = -FLT_MAX;   // as in fwd_split_kernel
+
+  // Key blocks (block kg of tiles 0, 1, ...) this wave works on and how many of them need no mask (n_full >= n_w - 1).
+  const int k_end = CAUSAL ? (wave_qmin + 32 < S ? wave_qmin + 32 : S) : S;
+  const int k_all = CAUSAL ? wave_qmin + 1 : S;
+  const int n_w = wave_qmin < S && k_end > 32 * kg ? (k_end - 32 * kg + BN - 1) / BN : 0;
+  const int n_full = (k_all + BN - 32 - 32 * kg) / BN;
+
+  if (n_tiles > 2) wait_tile_loads_except<4 * NDMA>();
+  else wait_tile_loads();
+  __syncthreads();
+  bf16x8 qf[KS];
+  read_fragments<D>(frag, lane, qf);
+  if (n_tiles > 2) wait_tile_loads_except<NDMA>();   // K(0), V(0), K(1)
+  else wait_tile_loads();
+  __syncthreads();
+
+  const FwdLaneAddr<D> la(lane);
+  const uint32_t kbase = base + kg * HALF, vbase = kbase + VREGION;
+  f32x16 sa, sb;
+  if (n_w > 0) {
+    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    sa = zero;
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) sa = mfma32(lds_b128(kbase + la.k[ks]), qf[ks], sa);
+    if (n_w > 1) check_reference<DB>(max16(sa), c, st, oacc);
+  }
+  __syncthreads();   // the first step copies K(3) over K(0)
+
+  int j = 0, kb = 0;   // tile, j % 3
+  auto next3 = [&](int b) __attribute__((always_inline)) { return b == 2 ? 0 : b + 1; };
+  auto copy_ahead = [&]() __attribute__((always_inline)) {
+    // V(j+1) replaces V(j-1), K(j+3) replaces K(j), scored in the step before this one
+    if (j + 1 < n_tiles) vload.issue(vh, (j + 1) * BN, S, base + VREGION + ((j + 1) & 1) * TILE);
+    if (j + 3 < n_tiles) kload.issue(kh, (j + 3) * BN, S, base + kb * TILE);
+  };
+  auto finish_tile = [&]() __attribute__((always_inline)) {
+    if (j + 3 < n_tiles) wait_tile_loads_except<NDMA>();   // K(j+3) may fly; K(j+2) and V(j+1) have landed
+    else wait_tile_loads();
+    __syncthreads();
+    kb = next3(kb);
+  };
+  auto step = [&](const f32x16& s_cur, f32x16& s_next) __attribute__((always_inline)) {
+    const bool whole = j + 3 < n_tiles && (j + 4) * BN <= S;
+    if (!whole) copy_ahead();
+    const __bf16* kt = kload.tile_ptr(kh, (j + 3) * BN);
+    const __bf16* vt = vload.tile_ptr(vh, (j + 1) * BN);
+    const uint32_t vdst = base + VREGION + ((j + 1) & 1) * TILE, kdst = base + kb * TILE;
+    const auto copy_whole = [&]() __attribute__((always_inline)) {
+      if (whole) {
+        vload.issue_whole(vt, vdst);
+        kload.issue_whole(kt, kdst);
+      }
+    };
+    const float m = quad_step<D>(copy_whole, s_cur, s_next, qf, la.k, la.v, kbase + next3(kb) * TILE, vbase + (j & 1) * TILE, oacc, c, st);
+    if (j + 1 < n_w - 1) check_reference<DB>(m, c, st, oacc);   // the plain path masks first
+    finish_tile();
+    j++;
+  };
+  while (j + 1 < n_w - 1) {
+    step(sa, sb);
+    step(sb, sa);
+  }
+  if (j < n_w - 1) {
+    step(sa, sb);
+    sa = sb;
+  }
+  for (; j < n_tiles; j++) {
+    copy_ahead();
+    if (j == n_w - 1) {
+      if (j >= n_full) {
+#pragma unroll
+        for (int e = 0; e < 16; e++) {
+          const int key = j * BN + 32 * kg + 8 * (e >> 2) + 4 * half + (e & 3);
+          sa[e] = (CAUSAL ? (key <= my_q) : (key < S)) ? sa[e] : -INFINITY;
+        }
+      }
+      bf16x8 p[2];
+      uint32_t vaddr[DB][2];
+#pragma unroll
+      for (int db = 0; db < DB; db++) {
+        vaddr[db][0] = vbase + (j & 1) * TILE + la.v[db][0];
+        vaddr[db][1] = vbase + (j & 1) * TILE + la.v[db][1];
+      }
+      check_reference<DB>(max16(sa), c, st, oacc);
+      exp_pack(sa, c, st, p);
+      pv_block<D>(vaddr, 0, p, oacc);
+    }
+    finish_tile();
+  }
+
+  // merge: O = sum over the groups of 2^(own reference - common reference) O_g; wave kg finishes block kg of the head dimension.  A
+  // group counts for the rows that see its first key, 32 * kg.
+  const float l_own = half_sum(st.lsum[0] + st.lsum[1]);
+  float2* const stats = reinterpret_cast<float2*>(smem + G::STATS);
+#pragma unroll
+  for (int db = 0; db < DB; db++)
+    if (db != kg) lds_put_block(smem + (w * DB + db) * 4096, lane, oacc[db]);
+  stats[w * 64 + lane] = make_float2(st.mref_c, l_own);
+  __syncthreads();
+  const int seen = CAUSAL ? my_q : S - 1;
+  float a[KG], m = -INFINITY, ltot = 0.f;
+  float2 ml[KG];
+#pragma unroll
+  for (int g = 0; g < KG; g++) {
+    ml[g] = stats[(rg + RG * g) * 64 + lane];
+    if (seen >= 32 * g) m = fmaxf(m, ml[g].x);
+  }
+#pragma unroll
+  for (int g = 0; g < KG; g++) {
+    a[g] = seen >= 32 * g ? __builtin_amdgcn_exp2f(ml[g].x - m) : 0.f;
+    ltot += seen >= 32 * g ? ml[g].y * a[g] : 0.f;
+  }
+  const float inv = 1.f / ltot;
+  f32x16 x;
+#pragma unroll
+  for (int e = 0; e < 16; e++) x[e] = 0.f;
+#pragma unroll
+  for (int g = 0; g < KG; g++) {
+    f32x16 part;
+    if (g == kg) {
+#pragma unroll
+      for (int db = 0; db < DB; db++)
+        if (db == g) part = oacc[db];
+    } else {
+      part = lds_get_block(smem + ((rg + RG * g) * DB + kg) * 4096, lane);
+    }
+#pragma unroll
+    for (int e = 0; e < 16; e++) x[e] += seen >= 32 * g ? part[e] * a[g] : 0.f;
+  }
+#pragma unroll
+  for (int e = 0; e < 16; e++) x[e] *= inv;
+  char* const out = smem + (w * DB + kg) * 4096;   // this wave's own block, which nobody put anything in
+  put_rows<32>(out, lane, 0, x);
+  if (half == 0 && kg == 0 && my_q < S) lse[(size_t)tc.bh * S + my_q] = m * kLn2 + __logf(ltot);
+  store_rows<32>(out, lane, o + head_offset(maps.o, tc.bh, H) + (size_t)wave_qmin * maps.o.row + 32 * kg, maps.o.row, S - wave_qmin);
+}
+
 template <int D, bool CAUSAL>
 static hipError_t launch_fwd_t(const void* q, const void* k, const void* v, void* o, float* lse,
                                const FwdMaps& maps, int B, int H, int S, float scale, hipStream_t stream) {
@@ -580,12 +822,15 @@ static hipError_t launch_fwd_t(const void* q, const void* k, const void* v, void
     lds = FwdSplit<D, 2>::LDS;
   }
   if constexpr (!kForwardSplitsAlways(D)) {
-    if (rows == Rows::k256) {
+    if (rows == Rows::k64Quad) {
+      kern = fwd_quad_kernel<D, CAUSAL>;
+      lds = FwdQuad<D>::LDS;
+    } else if (rows == Rows::k256) {
       kern = fwd_kernel<D, CAUSAL>;
       lds = 8 * 64 * D * 2;
     }
   }
-  static unsigned long long configured[3] = {};   // per template instantiation and kernel
+  static unsigned long long configured[4] = {};   // per template instantiation and kernel
   hipError_t e = allow_dynamic_lds(kern, lds, configured[(int)rows]);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(rows == Rows::k64 ? 256 : 512), lds, stream, (const __bf16*)q, (const __bf16*)k,

@@ -30,15 +30,31 @@ def test_edges(H, S, causal, D):
     assert np.abs(G.to_f64(out["lse"][:, heads]) - ref["lse"]).max() <= G.TOL_LSE
 
 
-# many heads (128-row and 128-key workgroups) against two of them alone (narrow ones)
-@pytest.mark.parametrize("H,S,D,causal,same", [(24, 1500, 128, True, ("o", "lse", "dq", "dk", "dv")), (30, 777, 128, False, ("o", "lse", "dk", "dv")),
+# Keys in four groups (head dimension 128, few heads, no short sequence): tokens at the edges of the 32-key blocks of a 128-key tile and of the
+# 64-row tiles, rows that see one, two, three and all of the groups of their last tile
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("H,S", [(2, 640), (1, 641), (3, 671), (2, 672), (1, 673), (2, 703), (1, 736), (3, 737), (2, 767), (1, 769), (5, 1500), (2, 2113)])
+def test_four_key_groups(H, S, causal):
+    test_edges(H, S, causal, 128)
+
+
+# many heads (128-row and 128-key workgroups) against two of them alone (narrow ones): the forward at head dimension 64, and the gradients from
+# the same O and LSE
+@pytest.mark.parametrize("H,S,D,causal,same", [(24, 1500, 128, True, ("dq", "dk", "dv")), (30, 777, 128, False, ("dk", "dv")),
                                                (200, 333, 64, True, ("o", "lse")), (200, 333, 64, False, ("o", "lse"))])
 def test_bits_of_a_head_alone(H, S, D, causal, same):
+    from paper_2507_00394_amd import binding as hx
     from tests import gpu_util as G
 
     cfg, bits = I.random_case_bits(6300 + S, 1, H, S, D)
     many = G.run_fwd_bwd(bits, cfg.scale, causal)
-    few = G.run_fwd_bwd({t: np.ascontiguousarray(bits[t][:, H - 2:]) for t in bits}, cfg.scale, causal)
+    few = {n: many[n][:, H - 2:].contiguous() for n in ("q", "k", "v", "dO")}
+    few.update({n: torch.full_like(few["q"], float("nan")) for n in ("o", "dq", "dk", "dv")}, lse=torch.full((1, 2, S), float("nan"), device="cuda"))
+    hx.helix_attn_fwd(few["q"], few["k"], few["v"], few["o"], few["lse"], cfg.scale, causal)
+    ws = torch.empty(hx.helix_attn_bwd_workspace_bytes(1, 2, S, D), dtype=torch.uint8, device="cuda")
+    o, lse = many["o"][:, H - 2:].contiguous(), many["lse"][:, H - 2:].contiguous()
+    hx.helix_attn_bwd(few["q"], few["k"], few["v"], o, lse, few["dO"], few["dq"], few["dk"], few["dv"], ws, cfg.scale, causal)
+    torch.cuda.synchronize()
     for n in same:
         assert torch.equal(many[n][:, H - 2:], few[n]), n
 
