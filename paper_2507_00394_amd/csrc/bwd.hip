@@ -46,10 +46,12 @@ bwd_preprocess_kernel(const __bf16* __restrict__ o, const __bf16* __restrict__ d
   const __bf16* oh = o + head_offset(mo, bh, H);
   const __bf16* gh = dO + head_offset(mdo, bh, H);
   bf16x8 a[PASSES], b[PASSES];
+  float l[PASSES];   // requested with the rows: behind their sums it is one more round trip (27 heads x 777 x 64 3.48 -> 3.26 us)
 #pragma unroll
   for (int p = 0; p < PASSES; p++) {
     const int r = row0 + p * RPB;
     if (r < S) {
+      if (sub == 0) l[p] = lse[(size_t)bh * S + r];
       a[p] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8*>(oh + (size_t)r * mo.row + sub * 8));
       b[p] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8*>(gh + (size_t)r * mdo.row + sub * 8));
     }
@@ -66,7 +68,7 @@ bwd_preprocess_kernel(const __bf16* __restrict__ o, const __bf16* __restrict__ d
     for (int off = LPR / 2; off >= 1; off >>= 1) s += __shfl_xor(s, off);
     if (sub == 0 && r < S) {
       neg_delta[(size_t)bh * S + r] = -s;
-      lse2[(size_t)bh * S + r] = lse[(size_t)bh * S + r] * kLog2e;
+      lse2[(size_t)bh * S + r] = l[p] * kLog2e;
     }
   }
 }
