@@ -194,6 +194,22 @@ __device__ __forceinline__ uint32_t pack_bf16_pair(float a, float b) {
 template <typename T>
 __device__ __forceinline__ void pin(T& x) { asm volatile("" : "+v"(x)); }
 
+// One 32 x 32 accumulator block as bf16: the lane owns a row, its registers 4g..4g+3 are the columns 8g + 4*half .. +3
+// (half = lane / 32).  The two lanes of a row exchange halves of two groups, so that each holds 16 consecutive bytes:
+// put(chunk, x) takes the 8 columns from 8*chunk on.
+template <typename Put>
+__device__ __forceinline__ void for_each_chunk(int half, const f32x16& acc, Put&& put) {
+#pragma unroll
+  for (int g = 0; g < 4; g += 2) {
+    const auto lo = __builtin_amdgcn_permlane32_swap(pack_bf16_pair(acc[4 * g], acc[4 * g + 1]),
+                                                     pack_bf16_pair(acc[4 * g + 4], acc[4 * g + 5]), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(pack_bf16_pair(acc[4 * g + 2], acc[4 * g + 3]),
+                                                     pack_bf16_pair(acc[4 * g + 6], acc[4 * g + 7]), false, false);
+    const u32x4 x = {lo[0], hi[0], lo[1], hi[1]};
+    put(g + half, x);
+  }
+}
+
 // What a wave loads before its sweep and stores after it are 32 rows of a tensor with a lane to a row: read or written from
 // the lanes directly, an instruction touches 32 or 64 rows with 16 or 8 bytes each, and the address unit takes a cycle for each of
 // them - 64 to 128 of them a workgroup, 2 to 6 us in which the compute unit does nothing else.  Both go through LDS instead,
@@ -205,17 +221,9 @@ __device__ __forceinline__ void pin(T& x) { asm volatile("" : "+v"(x)); }
 template <int W>
 __device__ __forceinline__ void put_rows(char* tile, int lane, int block, const f32x16& acc) {
   pin(lane);
-  // the lane's registers 4g..4g+3 are the columns 8g + 4*(lane/32) .. +3 of its row: the two lanes of a row exchange halves of two
-  // groups, so that each holds 16 consecutive bytes
-#pragma unroll
-  for (int g = 0; g < 4; g += 2) {
-    const auto lo = __builtin_amdgcn_permlane32_swap(pack_bf16_pair(acc[4 * g], acc[4 * g + 1]),
-                                                     pack_bf16_pair(acc[4 * g + 4], acc[4 * g + 5]), false, false);
-    const auto hi = __builtin_amdgcn_permlane32_swap(pack_bf16_pair(acc[4 * g + 2], acc[4 * g + 3]),
-                                                     pack_bf16_pair(acc[4 * g + 6], acc[4 * g + 7]), false, false);
-    const u32x4 x = {lo[0], hi[0], lo[1], hi[1]};
-    *reinterpret_cast<u32x4*>(tile + lds_chunk_off<W>(lane & 31, 4 * block + g + (lane >> 5))) = x;
-  }
+  for_each_chunk(lane >> 5, acc, [&](int chunk, const u32x4& x) __attribute__((always_inline)) {
+    *reinterpret_cast<u32x4*>(tile + lds_chunk_off<W>(lane & 31, 4 * block + chunk)) = x;
+  });
 }
 template <int W>
 __device__ __forceinline__ void store_rows(const char* tile, int lane, __bf16* row0, int row_stride, int rows) {

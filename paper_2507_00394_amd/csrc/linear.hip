@@ -148,6 +148,17 @@ __device__ __forceinline__ void put_rows(char* tile, int lane, int block, const 
 }
 template <int W>
 __device__ __forceinline__ void put_rows(char* tile, int lane, int block, const f32x16& acc, __bf16) { helix::put_rows<W>(tile, lane, block, acc); }
+// One 32 x 32 block from the lanes, 16 bytes at a time.
+__device__ __forceinline__ void store_block(float* row, int half, const f32x16& acc) {
+#pragma unroll
+  for (int g = 0; g < 4; g++) {
+    const f32x4 x = {acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]};
+    *reinterpret_cast<f32x4*>(row + 8 * g + 4 * half) = x;
+  }
+}
+__device__ __forceinline__ void store_block(__bf16* row, int half, const f32x16& acc) {
+  for_each_chunk(half, acc, [&](int chunk, const u32x4& x) __attribute__((always_inline)) { *reinterpret_cast<u32x4*>(row + 8 * chunk) = x; });
+}
 // Stores the tile; `rows` of its rows and `cols` of its columns (a multiple of 32) exist.
 template <int W, typename T>
 __device__ __forceinline__ void store_rows(const char* tile, int lane, T* row0, long long row_stride, int rows, int cols) {
@@ -322,7 +333,7 @@ __device__ __forceinline__ void gemm_block(int block, const Gemm<OutT>& g) {
     stage_barrier<0>();
   }
 
-  // A lane owns row i of C: 32 rows at a time go through LDS (free since the last barrier), this wave's part of it, and leave as whole
+  // A lane owns row i of C: on the larger tiles 32 rows at a time go through LDS (free since the last barrier), this wave's part of it, and leave as whole
   // rows.  Stored from the lanes, 16 bytes of 32 or 64 rows an instruction, a 256 x 256 tile takes 4 to 5 us (fp32 7) in which the
   // compute unit has nothing else to do, of 21 us for a contraction of 768.
   if constexpr (BI * BJ == 16) {   // 256 sums stay in accumulator registers: moved to the others all at once, they push the lane's index out to memory
@@ -332,8 +343,13 @@ __device__ __forceinline__ void gemm_block(int block, const Gemm<OutT>& g) {
       for (int ib = 0; ib < BI; ib++) asm volatile("" : "+a"(acc[jb][ib]));
   }
   constexpr int W = 32 * BJ;
-  char* const out = smem + w * (32 * W * (int)sizeof(OutT));
   const int i_wave = i0 + 32 * BI * wi, j_wave = j0 + W * wj;
+  if constexpr (BI * BJ == 1) {   // one block to a wave: straight from the lanes is the shorter way (0.28 against 0.45 us at the end of a short call)
+    const int half = lane >> 5, i = i_wave + (lane & 31);
+    if (i < g.I && j_wave < g.J) store_block(g.C + (size_t)part * g.part_stride + (size_t)i * g.ldc + j_wave, half, acc[0][0]);
+    return;
+  }
+  char* const out = smem + w * (32 * W * (int)sizeof(OutT));
 #pragma unroll
   for (int ib = 0; ib < BI; ib++) {
 #pragma unroll
@@ -426,28 +442,36 @@ static TileKind pick_tile(int I, int J, int R) {
   return t256 <= t128 && t256 <= t64 ? TileKind::k256 : t128 <= t64 ? TileKind::k128 : TileKind::k64;
 }
 
-// The tiles of the two gradients, which share a launch: those with the least time of it, among the pairs that take a compute unit
-// alike.  `work` is the time in which the chip gets through all workgroups, `chain` that of the longest one with a compute unit of its own; the launch
-// takes the larger of the two, or somewhat more where they are close.  The figures are fitted to 390 random shapes as above, at which the
-// choice is 1.5 % off the best pair on average (3.0 % for each product's fastest tile by itself) and more than 8 % off at 5 % of them (short
-// contractions mostly: 47776 x 256 x 1024 103 for 82 us).  One launch each on its own fastest tile -> both in one, us,
-// forward and backward: 2080 x 2048 x 768 43.2 -> 37.2; 131072 x 4096 x 1536 4283 -> 4150.
+// The tiles of the two gradients: the pair that takes the least time.  `work` is the time in which the chip gets through a product's workgroups,
+// `chain` that of one of them with a compute unit of its own; a launch takes the larger of the two, or somewhat more where they are
+// close.  Tiles that take a compute unit alike share a launch, the large one and a small one take one each.  The figures are fitted to 1000
+// random shapes (32 to 131072 tokens, K to 5120, N to 3072, short contractions among them), at which the choice is 1.4 % off the best pair on
+// average and more than 8 % off at 5 % of them (47776 x 256 x 1024 103 for 82 us).  Few columns and many tokens lose a little against a launch each (61440 x
+// 1152 x 256 154 for 143).  One launch each on its own fastest tile -> this, forward and
+// backward, us: 2080 x 2048 x 768 43.2 -> 36.5; 131072 x 4096 x 1536 4283 -> 4150.
 struct TilePair { TileKind input, weight; };
 static TilePair pick_tiles(int M, int K, int N, int parts) {
   struct Cost { int edge; double slots, full, sparse, input_fixed, weight_fixed; };   // of a workgroup: us per contraction index, us
-  static const Cost cost[3] = {{256, 256., 0.0331, 0.0175, 0.7, 1.4}, {128, 512., 0.0186, 0.0032, 3.0, 4.7}, {64, 512., 0.0052, 0.0004, 1.15, 4.0}};
-  static const TilePair pairs[5] = {{TileKind::k256, TileKind::k256}, {TileKind::k128, TileKind::k128}, {TileKind::k128, TileKind::k64},
-                                    {TileKind::k64, TileKind::k128}, {TileKind::k64, TileKind::k64}};
+  static const Cost cost[3] = {{256, 256., 0.0296, 0.0119, 4.8, 3.5}, {128, 512., 0.0187, 0.0028, 1.7, 3.15}, {64, 512., 0.0050, 0.0004, 0.8, 3.15}};
+  constexpr double kSharp = 2.66, kLaunch = 4., kTranspose = 5.6;
   const double R = (double)M / parts;
-  TilePair best = pairs[0];
+  auto launch_time = [&](double work, double chain) { return std::pow(std::pow(work, kSharp) + std::pow(chain, kSharp), 1. / kSharp); };
+  TilePair best = {TileKind::k256, TileKind::k256};
   double least = 0.;
-  for (const TilePair& p : pairs) {
-    const Cost &i = cost[(int)p.input], &w = cost[(int)p.weight];
-    const double work = (tiles_of(M, K, i.edge) * (N * i.full + i.input_fixed) + tiles_of(K, N, w.edge) * parts * (R * w.full + w.weight_fixed)) / i.slots;
-    const double chain = std::max(N * i.sparse + i.input_fixed, R * w.sparse + w.weight_fixed);
-    const double t = std::pow(std::pow(work, 3.5) + std::pow(chain, 3.5), 1 / 3.5) + (p.input == TileKind::k256 ? 5. : 0.);   // the transposing copy
-    if (least == 0. || t < least) { least = t; best = p; }
-  }
+  for (int ki = 0; ki < 3; ki++)
+    for (int kw = 0; kw < 3; kw++) {
+      if (ki == 0 && kw == 2) continue;   // nowhere the fastest
+      // With two column tiles or fewer the large tile's panels are read for little work, in either product (127232 x 1024 x 256, both 256 / both 128,
+      // 286 / 262 us; 88448 x 1024 x 256 204 / 171); it pays again where K is large (97152 x 3456 x 256 536 / 566).
+      if ((ki == 0 || kw == 0) && N <= 256 && K < 3072) continue;
+      const Cost &i = cost[ki], &w = cost[kw];
+      const double work_i = tiles_of(M, K, i.edge) * (N * i.full + i.input_fixed) / i.slots, chain_i = N * i.sparse + i.input_fixed;
+      const double work_w = tiles_of(K, N, w.edge) * parts * (R * w.full + w.weight_fixed) / w.slots, chain_w = R * w.sparse + w.weight_fixed;
+      const double t = (i.slots == w.slots ? launch_time(work_i + work_w, std::max(chain_i, chain_w))
+                                           : launch_time(work_i, chain_i) + launch_time(work_w, chain_w) + kLaunch) +
+                       (ki == 0 ? kTranspose : 0.);
+      if (least == 0. || t < least) { least = t; best = {(TileKind)ki, (TileKind)kw}; }
+    }
   return best;
 }
 
@@ -497,8 +521,8 @@ size_t linear_bwd_workspace_bytes(int M, int K, int N) {
 // (w^T [N][K], in the workspace) turns it into the forward's operand combination.
 // Weight gradient dw = a^T * dout, in parts.
 //
-// The two need nothing of each other, so they go in one launch, the weight gradient's longer workgroups first: the last round of one is
-// filled by the other, and a small layer pays for one start.
+// The two need nothing of each other, so they go in one launch where their tiles share a compute unit alike, the weight gradient's longer
+// workgroups first: the last round of one is filled by the other, and a small layer pays for one start.
 hipError_t launch_linear_bwd(const void* a, long long lda, const void* w, long long ldw, const void* dout, long long ldd, void* da,
                              long long ldda, float* dw, long long lddw, void* workspace, int M, int K, int N, hipStream_t stream) {
   __bf16* const wt = (__bf16*)workspace;
@@ -515,7 +539,14 @@ hipError_t launch_linear_bwd(const void* a, long long lda, const void* w, long l
     if ((e = hipGetLastError()) != hipSuccess) return e;
     in.Y = wt;
     in.ldy = K;
+  }
+  if (kind.input == TileKind::k256 && kind.weight == TileKind::k256) {
     e = launch_gradients<Tile256, true, Tile256>(in, grad_w, stream);
+  } else if (kind.input == TileKind::k256 || kind.weight == TileKind::k256) {   // tiles that do not share a compute unit alike: a launch each
+    e = kind.weight == TileKind::k256 ? launch_gemm_tile<Tile256, true, true>(grad_w, stream) : launch_gemm_tile<Tile128, true, true>(grad_w, stream);
+    if (e != hipSuccess) return e;
+    e = kind.input == TileKind::k256 ? launch_gemm_tile<Tile256, false, true>(in, stream)
+        : kind.input == TileKind::k128 ? launch_gemm_tile<Tile128, false, false>(in, stream) : launch_gemm_tile<Tile64, false, false>(in, stream);
   } else if (kind.input == TileKind::k128) {
     e = kind.weight == TileKind::k128 ? launch_gradients<Tile128, false, Tile128>(in, grad_w, stream)
                                       : launch_gradients<Tile128, false, Tile64ShortStages>(in, grad_w, stream);

@@ -1,5 +1,5 @@
-"""The linear layer's two gradients in their common launch: one shape for every pair of tiles it is built with, with workgroup
-counts that are no multiple of the XCDs, ragged token tiles and, in the last two, a weight gradient in parts."""
+"""The linear layer's two gradients, in their common launch or one each: shapes for the pairs of tiles, with workgroup
+counts that are no multiple of the XCDs, ragged token tiles and, in the last ones, a weight gradient in parts."""
 import pytest
 import torch
 
@@ -10,8 +10,9 @@ from tests.test_gpu_parity_linear import _check_bf16, _check_f32
 pytestmark = pytest.mark.gpu
 
 
-# input / weight tiles: 64 / 64, 128 / 64, 64 / 128, 128 / 128, 128 / 64 in parts, 256 / 256 in parts
-@pytest.mark.parametrize("M,K,N", [(32, 384, 128), (224, 384, 128), (224, 1280, 1280), (608, 1152, 1152), (6176, 256, 384), (16416, 1280, 512)])
+# input / weight tiles: 64 / 64, 128 / 64, 64 / 128, 128 / 128, 128 / 64 in parts, 256 / 256 in parts; one launch each: 64 / 256, 128 / 256, 256 / 128 in parts
+@pytest.mark.parametrize("M,K,N", [(32, 384, 128), (224, 384, 128), (224, 1280, 1280), (608, 1152, 1152), (6176, 256, 384), (6176, 1280, 1536),
+                                   (32, 12544, 2048), (224, 12032, 1792), (201024, 256, 640)])
 def test_gradients_in_one_launch(M, K, N):
     from paper_2507_00394_amd import binding as hx
     from tests import gpu_util as G
