@@ -118,8 +118,11 @@ inline int tiles(int S, Rows r) { const int n = r == Rows::k256 ? 256 : r == Row
 // of the forward and 145 and 149 of delta (head dimension 128 and 64) the choice is 0.5, 0.4 and 0.1 % off the fastest; at worst 71 heads x 1177 without a mask 63 for 50 us.
 // 128 -> 64 rows, us: delta, head dimension 128 12 heads x 1500 22.2 -> 17.9, 16 x 2048 29.7 -> 27.8, 64 x 2048 84 -> 116; head dimension 64
 // 2 x 512 9.3 -> 7.6, 12 x 1500 18.7 -> 15.2, 16 x 16384 612 -> 693; delta 16 x 16384 23.3 -> 18.9.
+// Narrow tiles that just fit the compute units at once do not where T is no multiple of P: workgroups without a tile are dealt out between
+// the others, some compute units get two in their place, and without a mask that is a second round (11 heads x 1399 34 us for the 18 of one).
 inline double rows_time(int BH, int S, bool causal, int rows, int slots, double per_step, double start) {
-  return pass_time(Share(BH, S, causal, rows, false, true), slots, per_step, start);
+  const Share even(BH, S, causal, rows, false, true), fullest(BH, S, causal, rows, false);
+  return pass_time(!causal && rows == 64 && slots == 32 && even.blocks() <= slots && fullest.blocks() > slots ? fullest : even, slots, per_step, start);
 }
 inline bool narrow_rows(int D, int BH, int S, bool causal, bool whole_is_a_choice) {
   const int slots = D == 64 && !whole_is_a_choice ? 48 : 32;
