@@ -109,7 +109,7 @@ struct DeltaHead {
 };
 
 // KG = 2: 128 rows per workgroup, key halves in two groups of waves, as above.  KG = 1, for the grids that fill the chip with
-// 256-row tiles (split_rows): every wave takes both halves of a tile for 32 rows of its own, one after the other, so an operand
+// 256-row tiles (delta_rows): every wave takes both halves of a tile for 32 rows of its own, one after the other, so an operand
 // copied to LDS serves twice the rows; the halves keep sums of their own, and delta has the same bits.  Whole backward of 4 x 16
 // heads x 2k tokens (512 tiles of 256 rows) with KG = 2 -> 1: 350.5 -> 336.7 us; 2 x 40 x 8000 forward + backward unchanged.
 template <int D, bool CAUSAL, int KG, int RG>

@@ -303,8 +303,8 @@ __device__ __forceinline__ void dq_whole_rows(int block, const __bf16* __restric
   store_rows<D>(out, lane, dq + head_offset(maps.dq, tc.bh, H) + (size_t)wave_qmin * maps.dq.row, maps.dq.row, S - wave_qmin);
 }
 
-// The dQ pass for grids that 256-row tiles cannot fill (split_rows in dispatch.hpp): 128 query rows per
-// workgroup, wave (rg, kg) on 32 rows and half kg of every 64-key tile, the two partial sums of a row added in LDS at
+// The dQ pass for grids that 256-row tiles cannot fill (dq_rows in dispatch.hpp): 32 RG = 128 query rows per
+// workgroup, or 64 on the smallest grids, wave (rg, kg) on 32 rows and half kg of every 64-key tile, the two partial sums of a row added in LDS at
 // the end (see fwd_split_kernel).  12 heads x 1500 tokens 49.1 -> 31.5 us, 2 heads x 32k 904 -> 693.
 template <int D>
 struct DqSplit {

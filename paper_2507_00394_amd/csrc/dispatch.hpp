@@ -142,8 +142,8 @@ inline bool narrow_gradients(int BH, int S, bool causal) {
 }
 
 // The forward at head dimension 128 has both, narrow workgroups with two key groups, which start and end sooner, and eight waves in four, which have half the
-// steps.  Over 300 shapes the choice among all four is 1.5 % off the fastest (5.1 % without the last); at worst short sequences of many heads, 155 x 203
-// 31 for 24 us, and 11 x 1399 without a mask, whose tiles just fill the chip, 34 for 26.  256 / 128 / 64 / 64 in four groups, us: causal
+// steps.  Over 519 shapes the choice among all four is 1.1 % (causal) and 1.9 % (no mask) off the fastest; at worst short sequences of many heads, 155 x 203
+// 31 for 24 us, and full grids that miss a round by little, 101 x 851 without a mask 81 for 59.  256 / 128 / 64 / 64 in four groups, us: causal
 // 4 heads x 1124 25.5 / 19.9 / 17.3 / 14.9, 12 x 1500 39 / 25.2 / 21.4 / 19.4, 2 x 8192 - / 107 / 91 / 70, 3 x 300 - / - / 8.25 / 8.6, 52 x 543 18.0 / 19.4 / 19.4 / 21.1.
 inline Rows forward_rows(int D, int BH, int S, bool causal) {
   if (kForwardSplitsAlways(D)) return narrow_rows(D, BH, S, causal, false) ? Rows::k64 : Rows::k128;

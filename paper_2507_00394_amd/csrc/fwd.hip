@@ -1,8 +1,8 @@
 // Forward attention for gfx950: O = softmax(scale * Q K^T + causal mask) V and the
 // log-sum-exp of every score row (Table 1, Attention column, "Forward").
 //
-// Work split (fwd_kernel; fwd_split_kernel, which serves small grids and head dimension 64, differs as its comment
-// says): one workgroup of 8 waves owns 256 consecutive query rows of one (batch, head)
+// Work split (fwd_kernel; fwd_split_kernel, which serves small grids and head dimension 64, and fwd_quad_kernel, for
+// smaller grids still, differ as their comments say): one workgroup of 8 waves owns 256 consecutive query rows of one (batch, head)
 // slice, 32 rows per wave, and sweeps the key tiles (64 keys) that the causal mask leaves
 // visible.  Each wave computes the TRANSPOSED score block S^T = K Q^T with the 32x32x16 bf16
 // MFMA, so that a lane owns ONE query (column l%32) and 16 keys per 32-key block: the
