@@ -113,22 +113,27 @@ inline int tiles(int S, Rows r) { const int n = r == Rows::k256 ? 256 : r == Row
 // in about 0.85 of the time that two side by side take theirs in, so that where narrow workgroups find compute units of their own every one of them
 // ends earlier; beyond that they only cost.  The arithmetic of a row is that of the 128-row workgroups, bit for bit.
 //
-// Delta of the first rows, and the forward at head dimension 64: by the time on an average XCD, as above but with the tiles spread evenly, as the order of map_block does
-// by now.  At head dimension 64 two workgroups share a compute unit for about 1.5 times the rate of one.  Over 222 shapes
-// of the forward and 145 and 149 of delta (head dimension 128 and 64) the choice is 0.5, 0.4 and 0.1 % off the fastest; at worst 71 heads x 1177 without a mask 63 for 50 us.
-// 128 -> 64 rows, us: delta, head dimension 128 12 heads x 1500 22.2 -> 17.9, 16 x 2048 29.7 -> 27.8, 64 x 2048 84 -> 116; head dimension 64
-// 2 x 512 9.3 -> 7.6, 12 x 1500 18.7 -> 15.2, 16 x 16384 612 -> 693; delta 16 x 16384 23.3 -> 18.9.
+// Delta of the first rows: by the time on an average XCD, as above but with the tiles spread evenly, as the order of map_block does by now.  Over 145
+// and 149 shapes (head dimension 128 and 64) the choice is 0.4 and 0.1 % off the fastest.  128 -> 64 rows, us: head dimension 128 12 heads x 1500
+// 22.2 -> 17.9, 16 x 2048 29.7 -> 27.8, 64 x 2048 84 -> 116; head dimension 64 16 x 16384 23.3 -> 18.9.
 // Narrow tiles that just fit the compute units at once do not where T is no multiple of P: workgroups without a tile are dealt out between
 // the others, some compute units get two in their place, and without a mask that is a second round (11 heads x 1399 34 us for the 18 of one).
 inline double rows_time(int BH, int S, bool causal, int rows, int slots, double per_step, double start) {
   const Share even(BH, S, causal, rows, false, true), fullest(BH, S, causal, rows, false);
   return pass_time(!causal && rows == 64 && slots == 32 && even.blocks() <= slots && fullest.blocks() > slots ? fullest : even, slots, per_step, start);
 }
-inline bool narrow_rows(int D, int BH, int S, bool causal, bool whole_is_a_choice) {
-  const int slots = D == 64 && !whole_is_a_choice ? 48 : 32;
-  double other = rows_time(BH, S, causal, 128, slots, 0.58, 4.5);
-  if (whole_is_a_choice) other = std::min(other, rows_time(BH, S, causal, 256, slots, 1., 3.5));
-  return (D == 64 ? rows_time(BH, S, causal, 64, 48, 0.42, 2.) : rows_time(BH, S, causal, 64, 32, 0.52, 3.2)) < other;
+inline bool narrow_delta(int D, int BH, int S, bool causal) {
+  const double wide = std::min(rows_time(BH, S, causal, 128, 32, 0.58, 4.5), rows_time(BH, S, causal, 256, 32, 1., 3.5));
+  return (D == 64 ? rows_time(BH, S, causal, 64, 48, 0.42, 2.) : rows_time(BH, S, causal, 64, 32, 0.52, 3.2)) < wide;
+}
+// The forward at head dimension 64 shares a compute unit between two wide or more narrow workgroups, at a rate that grows with every one but less than
+// in step, hence slots that are more than the compute units and no whole number of them.  Fitted to 441 shapes (1 to 200 heads, 65 to 6600 tokens, up to 4000 tiles of 64 rows), a
+// wrong narrow choice counted three times: 1.4 (no mask) and 0.5 % (causal) off the faster one.  Narrow is at worst 1.11 times the wide one's time where it is taken (148 heads x 143 without a mask 8.8 / 9.8 us, causal 54 x 563 11.2 / 11.6), and
+// where it is not, 0.72 (6 x 5164 79.8 / 57.7).  128 -> 64 rows, us, taken: 2 x 512 9.3 -> 7.6, 12 x 1500 18.7 -> 15.2; not: 120 x 1181 without a
+// mask 64.5 -> 73.9, 60 x 896 15.8 -> 18.1, 16 x 16384 612 -> 693.
+inline bool narrow_forward_64(int BH, int S, bool causal) {
+  return causal ? rows_time(BH, S, true, 64, 64, 0.52, 3.8) < rows_time(BH, S, true, 128, 88, 0.58, 4.5)
+                : rows_time(BH, S, false, 64, 48, 0.39, 2.1) < rows_time(BH, S, false, 128, 88, 0.58, 4.9);
 }
 
 // dK/dV and dQ: in their common launch, where 64-key and 64-row workgroups take their turns on the compute units.  Without a mask all take equally long, and
@@ -146,14 +151,14 @@ inline bool narrow_gradients(int BH, int S, bool causal) {
 // 31 for 24 us, and full grids that miss a round by little, 101 x 851 without a mask 81 for 59.  256 / 128 / 64 / 64 in four groups, us: causal
 // 4 heads x 1124 25.5 / 19.9 / 17.3 / 14.9, 12 x 1500 39 / 25.2 / 21.4 / 19.4, 2 x 8192 - / 107 / 91 / 70, 3 x 300 - / - / 8.25 / 8.6, 52 x 543 18.0 / 19.4 / 19.4 / 21.1.
 inline Rows forward_rows(int D, int BH, int S, bool causal) {
-  if (kForwardSplitsAlways(D)) return narrow_rows(D, BH, S, causal, false) ? Rows::k64 : Rows::k128;
+  if (kForwardSplitsAlways(D)) return narrow_forward_64(BH, S, causal) ? Rows::k64 : Rows::k128;
   const double wide = std::min(rows_time(BH, S, causal, 256, 32, 1., 3.5), rows_time(BH, S, causal, 128, 32, 0.58, 4.5));
   const double narrow = rows_time(BH, S, causal, 64, 32, 0.52, 3.2), quad = rows_time(BH, S, causal, 64, 32, 0.38, 4.5);
   if (std::min(narrow, quad) < wide) return quad < narrow ? Rows::k64Quad : Rows::k64;
   return split_forward(D, BH, S, causal) ? Rows::k128 : Rows::k256;
 }
 inline Rows delta_rows(int D, int BH, int S, bool causal) {
-  return narrow_rows(D, BH, S, causal, true) ? Rows::k64 : split_rows(BH, S, causal) ? Rows::k128 : Rows::k256;
+  return narrow_delta(D, BH, S, causal) ? Rows::k64 : split_rows(BH, S, causal) ? Rows::k128 : Rows::k256;
 }
 inline Rows dq_rows(int D, int BH, int S, bool causal) {
   return narrow_gradients(BH, S, causal) ? Rows::k64 : split_dq(D, BH, S, causal) ? Rows::k128 : Rows::k256;
