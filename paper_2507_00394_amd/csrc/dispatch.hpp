@@ -1,20 +1,63 @@
-// Which variant of a pass a launch takes, as a function of the shape alone.  Plain host arithmetic (head_parts and grid_blocks are
-// constexpr so that the device code that maps workgroup ids to tiles shares them), free of HIP, so that a test without a GPU can
-// compile it and hold every rule against the times it was read from.
+// Which tile a workgroup takes, and which variant of a pass a launch takes, as functions of the shape alone.  Plain host arithmetic (what the device
+// code shares is constexpr), free of HIP, so that a test without a GPU can compile it, count the tiles and hold every rule against the times it was
+// read from.
 #pragma once
 #include <algorithm>
 #include <cmath>
 
 namespace helix {
 
-// Heads are dealt to the 8 XCDs as "virtual heads", P interleaved parts each (see map_block in helix_common.hpp): the smallest power
-// of two that makes BH * P a multiple of 8.
-constexpr int head_parts(int BH) { return (BH & 1) ? 8 : (BH & 2) ? 4 : (BH & 4) ? 2 : 1; }
-// Number of workgroups to launch for BH slices of T tiles.  An eighth of them is the share of the fullest XCD, which has one
-// tile more where T is not a multiple of P.
-constexpr long long grid_blocks(int BH, int T) {
-  const int P = head_parts(BH);
-  return (long long)BH * P * ((T + P - 1) / P);
+// A launch's tiles are dealt to the 8 XCDs (workgroup id mod 8) in groups of P XCDs, P the smallest power of two that makes BH * P a multiple
+// of 8: a group has BH * P / 8 heads of its own, so that no XCD idles whatever the number of heads - with 32 heads a group is an XCD, with the 4
+// or 5 heads of one GPU's share of a tensor-parallel layer (Section 2.2) it is 2 or all 8 of them.
+constexpr int head_parts_log2(int BH) { return (BH & 1) ? 3 : (BH & 2) ? 2 : (BH & 4) ? 1 : 0; }
+constexpr int head_parts(int BH) { return 1 << head_parts_log2(BH); }
+// Number of workgroups to launch for BH slices of T tiles: one for a tile, rounded up to the same number on every XCD.
+constexpr long long grid_blocks(int BH, int T) { return ((long long)BH * T + 7) / 8 * 8; }
+
+// The tile of workgroup n: slice `head`, the `rank`-th heaviest of its T tiles.
+//
+// A group's tiles form one running sequence, head after head, heaviest tiles first.  Its P XCDs take the sequence P tiles at a time, every
+// other time backwards, so that none of them gets the heavier tile each time.  Only the last few workgroups of the grid are without a tile.
+// (With a head's T tiles padded to a multiple of P the empty workgroups stand between the others and the tiles that they push into a compute unit's second round
+// cost up to a third.  Padded, parts fixed / padded, parts rotating / one sequence, us, head dimension 128 unless said: forward 11 heads x 1399 no mask 34 /
+// 18 / 17.9; 33 x 1984 no mask 104 / 108 / 89.5; 42 x 384 causal 12.9 / 14.5 / 9.8; 76 x 180 causal 8.5 / 10.0 / 7.4; 22 x 3840 x 64 no mask 105.5 / 110.8 / 105.6; 68 x
+// 1080 x 64 no mask 36.1 / 37.9 / 34.8; backward 9 x 888 x 64 no mask 23.0 / 24.5 / 16.2.  Over 784 random shapes with BH no multiple of 8, time against
+// rotating parts: forward 0.92, backward 0.90.)
+//
+// Causal tiles differ in length, so an XCD that takes its heads one after the other starts
+// the longest tiles of the last one when hardly anything is left to fill the other compute units.
+// The last heads therefore go side by side, all of their heaviest tiles first: as many as
+// hold about four rounds of workgroups for the 32 compute units of an XCD, two at least.  More of
+// them only cost L2 hits (4 instead of 2 at 32 heads x 32k tokens: dK/dV 4 % slower), fewer leave the
+// imbalance.  One head after the other -> this rule, forward / dQ, us: 4 x 16 heads x 2k tokens 99 -> 77 /
+// 132 -> 101; 5 x 32k 1472 -> 1249 / 1997 -> 1733; 24 x 4k 131 -> 108 / 174 -> 147; 32 x 32k 7552 -> 7441 /
+// 10272 -> 10128.  Without a mask all tiles are equal and heads stay one after the other.
+//
+// Head dimension 128 with three or five tiles of a head to an XCD: only as many heads as hold about one and a half rounds.  Two or four tiles pair up,
+// a long one of one head with a short one of another, and fill whole rounds; of an odd number one is left without a partner, so more heads
+// side by side even nothing out and cost L2 hits.  One head after the other / four rounds / one and a half, forward, us: 272 heads x
+// 570 59 / 73 / 55; 344 x 700 82 / 101 / 81; 360 x 520 72 / 74 / 65; 248 x 620 54 / 65 / 52; whole backward 272 x 570 225 / 247 / 208.  Over 43
+// shapes with such heads the forward takes 0.93 of the time of four rounds, the backward 0.97.  At head dimension 64, where two workgroups
+// share a compute unit, four rounds are the better choice there too (532 x 640 forward 69.6 / 65.4, backward 330 / 285).
+struct TilePlace { int head, rank; bool valid; };
+constexpr TilePlace tile_place(int n, int BH, int T, bool causal, int D) {
+  const int l = head_parts_log2(BH), P = 1 << l;
+  const int xcd = n & 7, s = n >> 3, part = xcd & (P - 1);
+  const int m = (s << l) + ((s & 1) ? P - 1 - part : part);   // place in the group's sequence
+  const int heads = (int)(((long long)BH << l) >> 3);         // of the group: xcd / P, and every 8 / P-th one after it
+  int v = m / T, rank = m - v * T;
+  if (causal) {
+    const int per_xcd = (T + P - 1) >> l;                     // tiles of a head on an XCD
+    const int blocks = D == 128 && (per_xcd == 3 || per_xcd == 5) ? 48 : 128;
+    const int wanted = per_xcd >= 64 ? 2 : blocks / per_xcd;
+    const int side = heads < wanted ? heads : wanted, m2 = m - (heads - side) * T;
+    if (m2 >= 0) {
+      rank = m2 / side;
+      v = heads - side + m2 - rank * side;
+    }
+  }
+  return TilePlace{(v << (3 - l)) + (xcd >> l), rank, m < heads * T};
 }
 
 // The workgroups of a launch on the fullest XCD (32 compute units): `heads` virtual heads with `own` tiles each, the longest of every

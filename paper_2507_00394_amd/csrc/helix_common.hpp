@@ -305,56 +305,13 @@ __device__ __forceinline__ bf16x8 pack_half(const f32x16& acc, int t) {
   return __builtin_convertvector(x, bf16x8);
 }
 
-// Map a linear workgroup id to (batch*head slice, tile).  Workgroup id mod 8 selects the XCD, and
-// each XCD sweeps "virtual heads", heaviest tiles first (`heavy_is_high`: the heaviest
-// tiles are those with the highest index (forward, dQ), else the lowest (dK/dV)).  A virtual
-// head is one of P interleaved parts of a head (tiles congruent mod P), with P the smallest
-// power of two that makes BH * P a multiple of 8: with 32 heads a virtual head is a head, with
-// the 4 or 5 heads of one GPU's share of a tensor-parallel layer (Section 2.2) a head is
-// spread over 2 or 8 XCDs so that none of them idles.
-//
-// Causal tiles differ in length, so an XCD that takes its virtual heads one after the other starts
-// the longest tiles of the last one when hardly anything is left to fill the other compute units.
-// The last virtual heads therefore go side by side, all of their heaviest tiles first: as many as
-// hold about four rounds of workgroups for the 32 compute units of an XCD, two at least.  More of
-// them only cost L2 hits (4 instead of 2 at 32 heads x 32k tokens: dK/dV 4 % slower), fewer leave the
-// imbalance.  One head after the other -> this rule, forward / dQ, us: 4 x 16 heads x 2k tokens 99 -> 77 /
-// 132 -> 101; 5 x 32k 1472 -> 1249 / 1997 -> 1733; 24 x 4k 131 -> 108 / 174 -> 147; 32 x 32k 7552 -> 7441 /
-// 10272 -> 10128.  Without a mask all tiles are equal and heads stay one after the other.
-//
-// Head dimension 128 with three or five tiles to a virtual head: only as many as hold about one and a half rounds.  Two or four tiles pair up,
-// a long one of one head with a short one of another, and fill whole rounds; of an odd number one is left without a partner, so more heads
-// side by side even nothing out and cost L2 hits.  One head after the other / four rounds / one and a half, forward, us: 272 heads x
-// 570 59 / 73 / 55; 344 x 700 82 / 101 / 81; 360 x 520 72 / 74 / 65; 248 x 620 54 / 65 / 52; whole backward 272 x 570 225 / 247 / 208.  Over 43
-// shapes with such heads the forward takes 0.93 of the time of four rounds, the backward 0.97.  At head dimension 64, where two workgroups
-// share a compute unit, four rounds are the better choice there too (532 x 640 forward 69.6 / 65.4, backward 330 / 285).
+// The (batch*head slice, tile) of a workgroup (tile_place in dispatch.hpp).  `heavy_is_high`: the heaviest tiles of a causal head are those with the
+// highest index (forward, dQ), else the lowest (dK/dV).
 struct TileCoord { int bh; int tile; bool valid; };
 template <bool CAUSAL, int D>
 __device__ __forceinline__ TileCoord map_block(int n, int BH, int T, bool heavy_is_high) {
-  TileCoord c;
-  const int P = head_parts(BH), TP = (T + P - 1) / P;
-  const int xcd = n & 7, s = n >> 3;
-  int v = s / TP, r = s - v * TP;                // virtual head of this XCD and position among its tiles
-  if (CAUSAL) {
-    const int blocks = D == 128 && (TP == 3 || TP == 5) ? 48 : 128;
-    const int V = (int)((long long)BH * P / 8), wanted = TP >= 64 ? 2 : blocks / TP;
-    const int side = V < wanted ? V : wanted, s2 = s - (V - side) * TP;
-    if (s2 >= 0) {
-      r = s2 / side;
-      v = V - side + s2 - r * side;
-    }
-  }
-  const int vh = xcd + 8 * v;
-  // The parts of a head rotate among its P XCDs from head to head, by an odd number of places close to T, and every other row of P tiles
-  // is dealt backwards: with a fixed part to an XCD the heads' short rows (T no multiple of P) and the heavier tiles of every row
-  // fall to the same XCDs (35 heads of 3 tiles: all on three of the eight).  Fixed -> rotating, forward / backward, us, head dimension 128:
-  // 35 x 300 23.2 -> 11.7 / 65 -> 31; 21 x 1216 30.9 -> 24.8 / 96 -> 72; 39 x 2100 83 -> 73 / 321 -> 256; 7 x 20000 688 -> 655 / 2226 -> 2188.
-  const int part = (xcd - v * (T | 1)) & (P - 1);
-  const int k = r * P + ((r & 1) ? P - 1 - part : part);   // rank of the tile inside its head, heaviest first
-  c.bh = vh / P;
-  c.tile = heavy_is_high ? (T - 1 - k) : k;
-  c.valid = c.bh < BH && k < T;
-  return c;
+  const TilePlace p = tile_place(n, BH, T, CAUSAL, D);
+  return TileCoord{p.head, heavy_is_high ? T - 1 - p.rank : p.rank, p.valid};
 }
 
 // Element offset of row 0 of slice bh = b * H + h.

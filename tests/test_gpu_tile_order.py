@@ -1,4 +1,4 @@
-"""The order in which workgroups take the tiles of causal attention: an XCD sweeps its first virtual heads
+"""The order in which workgroups take the tiles of causal attention: an XCD sweeps its first heads
 one after the other and the last ones side by side.  With outputs prefilled with NaN a tile done by nobody
 fails the finiteness check, one done under a wrong head the comparison with the oracle."""
 import numpy as np
@@ -11,8 +11,8 @@ from paper_2507_00394_amd import inputs as I
 pytestmark = pytest.mark.gpu
 
 
-# (heads, S): 10 virtual heads per XCD of which 4 (1 tile each) to 10 go first; heads split in 2, 4 and 8 parts; at head dimension 128
-# three and five tiles to a virtual head, of which all but one, all and some go side by side
+# (heads, S): 10 heads per XCD of which 4 (1 tile each) to 10 go first; heads shared by 2, 4 and 8 XCDs; at head dimension 128
+# three and five tiles of a head to an XCD, of which all but one, all and some go side by side
 @pytest.mark.parametrize("BH,S,D", [(80, 2600, 64), (80, 8193, 64), (44, 2600, 64), (42, 1500, 64), (13, 3000, 64), (136, 570, 128), (80, 1100, 128),
                                     (40, 640, 128), (264, 300, 128), (36, 1300, 128)])
 def test_every_tile_once(BH, S, D):
