@@ -60,6 +60,94 @@ constexpr TilePlace tile_place(int n, int BH, int T, bool causal, int D) {
   return TilePlace{(v << (3 - l)) + (xcd >> l), rank, m < heads * T};
 }
 
+// ---------------------------------------------------------------- which variant a pass takes
+//
+// Every variant has a time model of a few figures, fitted to its own times over 4700 random shapes (1 to 160, now and then 1000, heads, 48 to 131072
+// tokens), and a launch takes the variant with the least.  With tile_place every XCD gets the same tiles, so an XCD's share is known.
+
+// The workgroups of a pass on one XCD: `heads` heads (a fraction where XCDs share them) of T tiles each, the longest of every head, the second longest
+// of every head, ...  `keys`: tiles of the dK/dV pass, which sweep the query rows from their first key on; else of query rows, which sweep the keys up
+// to their last row.  Lengths in steps of 64 rows or keys.
+struct XcdShare {
+  bool causal, keys;
+  int T, per_tile;             // tiles of a head, steps by which neighbouring tiles differ
+  long long count;             // workgroups
+  double heads, longest, mb;   // mb: what the pass reads and writes, MB: two tensors once, two by every XCD that a head's tiles are spread over
+  XcdShare(int D, int BH, int S, bool causal_, int rows, bool keys_)
+      : causal(causal_), keys(keys_), T((S + rows - 1) / rows), per_tile(rows / 64), count(grid_blocks(BH, T) / 8), heads(BH / 8.), longest((S + 63) / 64),
+        mb((double)BH * S * D * 2 * (2 + 2 * std::min(head_parts(BH), T)) * 1e-6) {}
+  double tiles() const { return heads * T; }
+  double steps() const {
+    if (!causal) return tiles() * longest;
+    const double less = (double)per_tile * T * (T - 1) / 2;
+    return heads * (keys ? T * longest - less : longest + less);
+  }
+  double length(double i) const {   // of the i-th longest tile of a head
+    i = std::min(std::floor(i), T - 1.);
+    return !causal || i == 0. ? longest : keys ? longest - per_tile * i : per_tile * (T - i);
+  }
+};
+// us of a workgroup: per step with the chip full and with a compute unit (almost) to itself, and for its start and end; `tail`: the share of an average tile
+// that causal tiles of unequal lengths leave idle at the end; us for a MB of XcdShare::mb.
+struct Cost { double step, alone, fixed, tail, mb; };
+
+// A pass whose workgroups have a compute unit each (32 on an XCD).  Without a mask all take equally long: whole rounds, the last one quicker the emptier it
+// is.  Causal ones go longest first: the average of a compute unit or, if that is more, what the longest take where k of them have to share one.
+inline double pass_time(const XcdShare& w, const Cost& c) {
+  const double mb = c.mb * w.mb;
+  if (!w.causal) {
+    const double rounds = (double)((w.count - 1) / 32), rest = w.count - 32 * rounds;
+    return rounds * (c.step * w.longest + c.fixed) + (c.alone + (c.step - c.alone) * rest / 32) * w.longest + c.fixed + mb;
+  }
+  const double step = c.alone + (c.step - c.alone) * std::min(1., w.count / 32.), work = step * w.steps() + c.fixed * w.tiles();
+  double t = work / 32 + c.tail * work / w.tiles();
+  for (int k = 0; k < 3 && 32 * k < w.count; k++) t = std::max(t, (k + 1) * (step * w.length(32 * k / w.heads) + c.fixed));
+  return t + mb;
+}
+// A pass whose workgroups share a compute unit in pairs: up to 32 of them on an XCD have one alone.
+inline double paired_time(const XcdShare& w, const Cost& c) {
+  const double mb = c.mb * w.mb;
+  if (!w.causal) {
+    const double rounds = (double)((w.count - 1) / 64), rest = w.count - 64 * rounds;
+    return rounds * (c.step * w.longest + c.fixed) + (rest <= 32 ? c.alone : c.step) * w.longest + c.fixed + mb;
+  }
+  const double pairs = std::min(1., std::max(0., (w.count - 32) / 32.)), step = c.alone + (c.step - c.alone) * pairs;
+  const double work = step * w.steps() + c.fixed * w.tiles();
+  double t = work / (32 + 32 * pairs) + c.tail * work / w.tiles();
+  for (int k = 0; k < 3 && 64 * k < w.count; k++) t = std::max(t, (k + 1) * ((k == 0 ? c.alone : step) * w.length(64 * k / w.heads) + c.fixed));
+  return t + mb;
+}
+
+// Rows of a query tile: 256 with a wave for every 32 rows, or 128 or 64 with the keys split over two groups of waves, or 64 over four.
+enum class Rows { k256, k128, k64, k64Quad };
+inline int tiles(int S, Rows r) { const int n = r == Rows::k256 ? 256 : r == Rows::k128 ? 128 : 64; return (S + n - 1) / n; }
+
+// The forward.  A 128-row workgroup needs a little more than half of a 256-row one's time for a step and more for its start and end, and there are twice as
+// many: it pays where 256-row ones leave compute units idle or fill a round badly.  Narrow workgroups of 64 rows and four waves, one to a SIMD, start and end
+// sooner still; with the keys over four groups (eight waves, a merge of four) they have half the steps.  The arithmetic of a row is the same with 128 and
+// with 64 rows, bit for bit; 256 rows and four groups have reference maxima of their own.
+// Head dimension 128, 256 / 128 / 64 / 64 in four groups, us:
+//   causal: 3 x 300 - / - / 8.25 / 8.6; 12 x 1500 36 / 24.9 / 21.4 / 18.7; 42 x 384 10.8 / 10.8 / 9.4 / 9.4; 38 x 949 26.4 / 22.1 / 27.4 / 27.8; 34 x 960 25.7 / 20.3 /
+//     21.7 / 21.3; 155 x 203 11.6 / 14.8 / 17.5 / 19.5; 128 x 512 19.8 / 23.4 / 30.5 / 31.4; 2 x 32k 733 / 538 / 797 / 618; 16 x 16k 960 / 1063 / 1483 / 1244.
+//   no mask: 7 x 1104 28.7 / 20.1 / 17.4 / 15.4; 12 x 1500 36.8 / 25.6 / 41 / 35; 11 x 2246 54 / 38.8 / 58 / 49; 101 x 851 60 / 61 / 87 / 80; 33 x 1984 110 / 103 / 99.7 / 91.2;
+//     36 x 4096 329 / 326 / 441 / 362; 512 x 1024 284 / 358 / 501 / 487.
+// Head dimension 64 never takes 256 rows: two 128-row workgroups share a compute unit (80 KB of LDS each, as the 64-row ones), where a 256-row one takes it
+// alone.  128 / 64 rows, us: causal 2 x 512 8.8 / 7.2; 54 x 563 10.3 / 9.1; 60 x 896 15.1 / 16.4; 16 x 16k 600 / 690; no mask 6 x 5164 55.7 / 58.6; 10 x 819 12.0 / 9.9;
+// 27 x 777 13.1 / 14.2; 148 x 143 8.4 / 6.5; 120 x 1181 60.9 / 67.1.
+// Over all shapes the choice is 0.15 (head dimension 128, causal) and less than 0.1 % (no mask; 64) off the fastest variant.
+inline Rows forward_rows(int D, int BH, int S, bool causal) {
+  static constexpr Cost at128[2][4] = {{{1.6, 1.46, 3.97, 0, .0213}, {.932, .7, 5.63, 0, .0246}, {.706, .653, 4.2, 0, .0216}, {.549, .464, 5.49, 0, .0228}},
+                                       {{1.52, 1.4, 4.49, .29, 0}, {.917, .629, 5.74, .15, .0115}, {.734, .592, 4.38, .183, .0257}, {.571, .372, 5.83, .219, .0158}}};
+  static constexpr Cost at64[2][2] = {{{1.05, .565, 3.97, 0, .0249}, {.647, .418, 3.65, 0, .0401}}, {{1.09, .65, 4.09, .181, .0204}, {.652, .464, 3.68, .0707, .0238}}};
+  const XcdShare wide(D, BH, S, causal, 128, false), narrow(D, BH, S, causal, 64, false);
+  if (D == 64) return paired_time(narrow, at64[causal][1]) < paired_time(wide, at64[causal][0]) ? Rows::k64 : Rows::k128;
+  const Cost* const c = at128[causal];
+  const double t[4] = {pass_time(XcdShare(D, BH, S, causal, 256, false), c[0]), pass_time(wide, c[1]), pass_time(narrow, c[2]), pass_time(narrow, c[3])};
+  return (Rows)(std::min_element(t, t + 4) - t);
+}
+
+// ---- the backward
+
 // The workgroups of a launch on the fullest XCD (32 compute units): `heads` virtual heads with `own` tiles each, the longest of every
 // head, the second longest of every head, ...  `keys`: tiles of the dK/dV pass, which sweep the query rows from their first key on;
 // else of query rows, which sweep the keys up to their last row.  Lengths in steps of 64 rows or keys.
@@ -110,14 +198,6 @@ inline bool split_rows(int BH, int S, bool causal) {
   return split_rows_time(BH, S, causal) < whole_rows_time(BH, S, causal);
 }
 
-// The forward at head dimension 64 always splits: two split workgroups fit a compute unit (LDS and registers), where a whole one takes it
-// alone, so the split is the faster one on full grids too.  Whole -> split, us: causal 267 heads x 209 75 -> 35, 962 x 40 48 -> 37, 512 x 1024
-// 144 -> 116, 256 x 2048 204 -> 184, 64 x 8192 626 -> 609, 2 x 512 13.3 -> 10.0; no mask 2048 x 256 82 -> 68, 512 x 1024 175 -> 169, 16 x 32k
-// 4614 -> 4547; at worst, where whole tiles just fill the chip, 128 x 300 11.4 -> 12.6, 32 x 2048 41.7 -> 42.6.  So at this head dimension O and
-// LSE of a head depend on nothing but the head.
-constexpr bool kForwardSplitsAlways(int D) { return D == 64; }
-inline bool split_forward(int D, int BH, int S, bool causal) { return kForwardSplitsAlways(D) || split_rows(BH, S, causal); }
-
 // Head dimension 64: whether two groups of waves share the query tiles of a key tile in the dK/dV pass, and that pass its launch with
 // the dQ pass on split tiles (a launch of its own is what the stage calls make of it).  With one group a SIMD has one wave, which
 // is bound by instruction issue, unless a second workgroup finds room beside it; two groups halve the sweep, and the common launch fills
@@ -148,10 +228,6 @@ inline bool split_dq(int D, int BH, int S, bool causal) {
 }
 
 
-// Rows of a query tile: 256 with a wave for every 32 rows, or 128 or 64 with the keys split over two groups of waves, or 64 over four.
-enum class Rows { k256, k128, k64, k64Quad };
-inline int tiles(int S, Rows r) { const int n = r == Rows::k256 ? 256 : r == Rows::k128 ? 128 : 64; return (S + n - 1) / n; }
-
 // Narrow workgroups: 64 rows (or keys) and four waves, one per SIMD, in the place of 128 and eight.  A wave that has its SIMD to itself takes a step
 // in about 0.85 of the time that two side by side take theirs in, so that where narrow workgroups find compute units of their own every one of them
 // ends earlier; beyond that they only cost.  The arithmetic of a row is that of the 128-row workgroups, bit for bit.
@@ -169,16 +245,6 @@ inline bool narrow_delta(int D, int BH, int S, bool causal) {
   const double wide = std::min(rows_time(BH, S, causal, 128, 32, 0.58, 4.5), rows_time(BH, S, causal, 256, 32, 1., 3.5));
   return (D == 64 ? rows_time(BH, S, causal, 64, 48, 0.42, 2.) : rows_time(BH, S, causal, 64, 32, 0.52, 3.2)) < wide;
 }
-// The forward at head dimension 64 shares a compute unit between two wide or more narrow workgroups, at a rate that grows with every one but less than
-// in step, hence slots that are more than the compute units and no whole number of them.  Fitted to 441 shapes (1 to 200 heads, 65 to 6600 tokens, up to 4000 tiles of 64 rows), a
-// wrong narrow choice counted three times: 1.4 (no mask) and 0.5 % (causal) off the faster one.  Narrow is at worst 1.11 times the wide one's time where it is taken (148 heads x 143 without a mask 8.8 / 9.8 us, causal 54 x 563 11.2 / 11.6), and
-// where it is not, 0.72 (6 x 5164 79.8 / 57.7).  128 -> 64 rows, us, taken: 2 x 512 9.3 -> 7.6, 12 x 1500 18.7 -> 15.2; not: 120 x 1181 without a
-// mask 64.5 -> 73.9, 60 x 896 15.8 -> 18.1, 16 x 16384 612 -> 693.
-inline bool narrow_forward_64(int BH, int S, bool causal) {
-  return causal ? rows_time(BH, S, true, 64, 64, 0.52, 3.8) < rows_time(BH, S, true, 128, 88, 0.58, 4.5)
-                : rows_time(BH, S, false, 64, 48, 0.39, 2.1) < rows_time(BH, S, false, 128, 88, 0.58, 4.9);
-}
-
 // dK/dV and dQ: in their common launch, where 64-key and 64-row workgroups take their turns on the compute units.  Without a mask all take equally long, and
 // the launch has to fit (half of the chip for either); causal ones differ in length and fill each other's gaps.  Over 420 shapes 0.3 %
 // (head dimension 128, causal), 1.2 (no mask), 0.8 and 1.6 % (head dimension 64) off the better choice; at worst 10 x 819 x 64 without a mask 23.4 for 19.3 us.  128 -> 64, whole backward, us, 64-row
@@ -189,17 +255,6 @@ inline bool narrow_gradients(int BH, int S, bool causal) {
   return tiles_64 <= (causal ? 288 : 128);
 }
 
-// The forward at head dimension 128 has both, narrow workgroups with two key groups, which start and end sooner, and eight waves in four, which have half the
-// steps.  Over 519 shapes the choice among all four is 1.1 % (causal) and 1.9 % (no mask) off the fastest; at worst short sequences of many heads, 155 x 203
-// 31 for 24 us, and full grids that miss a round by little, 101 x 851 without a mask 81 for 59.  256 / 128 / 64 / 64 in four groups, us: causal
-// 4 heads x 1124 25.5 / 19.9 / 17.3 / 14.9, 12 x 1500 39 / 25.2 / 21.4 / 19.4, 2 x 8192 - / 107 / 91 / 70, 3 x 300 - / - / 8.25 / 8.6, 52 x 543 18.0 / 19.4 / 19.4 / 21.1.
-inline Rows forward_rows(int D, int BH, int S, bool causal) {
-  if (kForwardSplitsAlways(D)) return narrow_forward_64(BH, S, causal) ? Rows::k64 : Rows::k128;
-  const double wide = std::min(rows_time(BH, S, causal, 256, 32, 1., 3.5), rows_time(BH, S, causal, 128, 32, 0.58, 4.5));
-  const double narrow = rows_time(BH, S, causal, 64, 32, 0.52, 3.2), quad = rows_time(BH, S, causal, 64, 32, 0.38, 4.5);
-  if (std::min(narrow, quad) < wide) return quad < narrow ? Rows::k64Quad : Rows::k64;
-  return split_forward(D, BH, S, causal) ? Rows::k128 : Rows::k256;
-}
 inline Rows delta_rows(int D, int BH, int S, bool causal) {
   return narrow_delta(D, BH, S, causal) ? Rows::k64 : split_rows(BH, S, causal) ? Rows::k128 : Rows::k256;
 }

@@ -366,7 +366,7 @@ fwd_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __b
   store_rows<D>(out, lane, o + head_offset(maps.o, tc.bh, H) + (size_t)wave_qmin * maps.o.row, maps.o.row, S - wave_qmin);
 }
 
-// The forward for grids that 256-row tiles cannot fill (split_forward in dispatch.hpp says which): a workgroup owns
+// The forward for grids that 256-row tiles cannot fill (forward_rows in dispatch.hpp says which): a workgroup owns
 // 128 query rows and its two groups of four waves share the keys.  Wave (rg, kg) works on 32 query rows and on
 // half kg of every 64-key tile, through the same half steps as above, one per tile; at the end the two partial
 // results of a row are merged in LDS.  Twice the workgroups, each of half the length, at two waves per SIMD;
@@ -566,7 +566,7 @@ fwd_split_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, con
   }
 }
 
-// The forward at head dimension 128 for small grids: a workgroup owns 64 query rows and its four pairs of waves share the keys, wave
+// The forward at head dimension 128 for small grids (forward_rows): a workgroup owns 64 query rows and its four pairs of waves share the keys, wave
 // (rg, kg) on 32 rows and key block kg of every 128-key tile.  A quarter of the steps of a 256-row workgroup at two waves per SIMD; a
 // tile's copy serves 64 rows.  A tile of K and V takes 64 KB, so LDS holds three of K and two of V, and a step reads nothing ahead of its own
 // tiles: K(j+1), which it scores, and V(j).  K runs two tiles ahead, V(j+1) has the length of step j to land, which it does not always keep: a step
@@ -821,7 +821,7 @@ static hipError_t launch_fwd_t(const void* q, const void* k, const void* v, void
     kern = fwd_split_kernel<D, CAUSAL, 2>;
     lds = FwdSplit<D, 2>::LDS;
   }
-  if constexpr (!kForwardSplitsAlways(D)) {
+  if constexpr (D == 128) {   // at head dimension 64 forward_rows knows the two above only
     if (rows == Rows::k64Quad) {
       kern = fwd_quad_kernel<D, CAUSAL>;
       lds = FwdQuad<D>::LDS;

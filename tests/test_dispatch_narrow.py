@@ -11,7 +11,7 @@ PROGRAM = """
 int main() {
   int D, BH, S, causal;
   while (scanf("%d %d %d %d", &D, &BH, &S, &causal) == 4)
-    printf("%d %d %d %d\\n", (int)helix::forward_rows(D, BH, S, causal), (int)helix::delta_rows(D, BH, S < 2048 ? S : 2048, causal),
+    printf("%d %d %d\\n", (int)helix::delta_rows(D, BH, S < 2048 ? S : 2048, causal),
            helix::narrow_gradients(BH, S, causal), (int)helix::dq_rows(D, BH, S, causal));
 }
 """
@@ -31,7 +31,7 @@ def rules(tmp_path_factory):
     return ask
 
 
-# head dimension, causal, heads, tokens; us of the forward on 256-, 128- and 64-row tiles (used at head dimension 64, which has no 256), of the causal delta of the
+# head dimension, causal, heads, tokens; us of the forward on 256-, 128- and 64-row tiles (not used), of the causal delta of the
 # first rows likewise, and of the backward on wide and narrow gradient workgroups
 MEASURED = """
 64 N 31 190 | - 6.4 5.5 | - - - | 11.5 12.6
@@ -96,70 +96,6 @@ MEASURED = """
 128 C 8 11372 | 282.2 279.2 364.6 | 45.0 28.2 23.1 | 813.7 944.0"""
 
 
-# the forward at head dimension 128: mask, heads, tokens; us on 256-, 128- and 64-row tiles and on 64-row tiles with four key groups
-FORWARD_128 = """
-N 3 177 9.1 8.0 6.7 7.4
-N 4 411 14.6 11.0 9.3 9.3
-N 1 2781 63.3 40.4 33.8 27.3
-N 3 937 24.9 17.7 15.0 13.4
-N 5 739 21.1 15.2 12.6 11.7
-N 49 114 7.5 7.8 6.5 7.6
-N 37 172 9.7 8.6 7.1 8.1
-N 11 890 24.6 18.2 15.9 14.5
-N 2 19718 424.5 551.7 623.0 511.8
-N 36 1334 39.6 47.2 72.3 64.9
-N 248 199 16.3 21.2 28.5 30.3
-N 96 1143 70.4 86.1 111.1 99.5
-N 36 5920 629.8 643.3 903.1 778.0
-C 1 56 5.9 6.5 5.4 6.5
-C 1 180 8.7 7.9 6.6 7.4
-C 1 196 10.1 8.6 7.0 7.7
-C 2 247 10.5 8.9 7.4 7.8
-C 5 98 7.0 7.3 6.1 6.8
-C 6 83 7.0 7.2 6.1 6.8
-C 9 103 7.0 7.4 6.2 6.9
-C 11 87 7.0 7.2 6.2 7.0
-C 2 822 20.6 15.8 13.4 12.4
-C 3 627 15.5 13.8 11.5 10.7
-C 10 159 9.0 7.9 6.9 7.7
-C 15 155 8.8 7.9 7.0 7.8
-C 25 176 9.0 8.2 6.9 7.7
-C 6 900 24.1 17.2 14.5 13.3
-C 54 99 7.4 7.7 6.5 7.2
-C 19 377 10.8 10.9 9.2 9.0
-C 5 1950 45.5 30.1 26.0 21.8
-C 9 1548 36.4 25.6 22.4 19.7
-C 36 411 14.6 11.6 10.4 12.3
-C 8 2092 47.2 31.7 27.7 23.1
-C 41 421 15.2 12.6 18.2 19.8
-C 19 1048 28.1 21.8 22.0 20.9
-C 9 2328 52.2 36.0 30.4 26.2
-C 1 21257 433.2 264.0 227.0 178.1
-C 185 83 22.7 23.6 18.8 22.2
-C 2 12000 250.3 151.4 130.6 104.0
-C 132 161 17.3 16.1 16.4 19.0
-C 20 1281 31.8 23.2 23.1 22.0
-C 14 2042 48.0 33.7 32.4 28.8
-C 116 384 16.4 21.9 23.6 24.5
-C 40 1140 28.7 24.4 33.0 30.7
-C 43 1077 38.4 36.9 39.8 39.6
-C 246 229 41.2 36.6 35.2 37.6
-C 75 840 45.0 45.7 53.5 54.6
-C 66 979 58.2 48.8 59.1 61.3
-C 10 7240 178.8 157.3 256.2 241.3
-C 47 1917 73.9 76.1 116.6 110.3
-C 263 329 51.3 54.4 60.3 62.6
-C 12 10596 332.6 348.7 486.1 412.0
-C 7 18308 566.2 639.9 849.9 721.2
-C 18 7871 291.4 319.4 470.7 411.4
-C 17 8889 346.6 394.1 587.9 508.6
-C 183 815 72.1 84.0 118.3 116.0
-C 4 44334 1829.7 1928.5 2644.3 2224.2
-C 270 656 100.0 102.5 106.3 108.4
-C 22 9372 477.7 548.0 712.4 605.2
-C 4 58165 3008.8 3291.3 4473.3 3795.3"""
-
-
 def _rows():
     for line in MEASURED.split("\n"):
         if line.strip():
@@ -170,10 +106,8 @@ def _rows():
 
 def test_choices_against_measured_times(rules):
     table = list(_rows())
-    regret = {"forward": [], "delta": [], "gradients": []}
-    for (D, c, bh, s, (f, d, g)), (rf, rd, rg, _) in zip(table, rules([r[:1] + r[2:4] + r[1:2] for r in table])):
-        if D == 64:
-            regret["forward"].append(f[rf] / min(f))
+    regret = {"delta": [], "gradients": []}
+    for (D, c, bh, s, (_, d, g)), (rd, rg, _) in zip(table, rules([r[:1] + r[2:4] + r[1:2] for r in table])):
         if c:
             regret["delta"].append(d[rd] / min(d))
         regret["gradients"].append(g[rg] / min(g))
@@ -181,15 +115,9 @@ def test_choices_against_measured_times(rules):
         assert max(r) <= 1.3 and sum(r) / len(r) <= 1.02, (name, max(r), sum(r) / len(r))
 
 
-def test_forward_at_head_dimension_128(rules):
-    table = [(line.split()[0] == "C", *map(int, line.split()[1:3]), [float(x) for x in line.split()[3:]]) for line in FORWARD_128.split("\n") if line]
-    regret = [us[r[0]] / min(us) for (_, _, _, us), r in zip(table, rules([(128, bh, s, c) for c, bh, s, _ in table]))]
-    assert max(regret) <= 1.36 and sum(regret) / len(regret) <= 1.03, (max(regret), sum(regret) / len(regret))
-
-
 def test_narrow_gradients_go_together(rules):
     """Narrow key tiles share their launch with narrow query tiles only, and never beyond the grids they were measured at."""
-    for (D, bh, s, c), (_, _, narrow, dq) in zip(SHAPES, rules(SHAPES)):
+    for (D, bh, s, c), (_, narrow, dq) in zip(SHAPES, rules(SHAPES)):
         assert (dq == 2) == bool(narrow)
         assert not narrow or bh * ((s + 63) // 64) <= 288
 
