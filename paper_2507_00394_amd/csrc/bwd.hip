@@ -321,8 +321,10 @@ static hipError_t launch_delta_head_t(const void* q, const void* k, const void* 
   const int T = tiles(rows, kind);   // query tiles 0..T-1 of every head
   const unsigned grid = (unsigned)grid_blocks(BH, T);
   const size_t lds = DeltaHead<D>::LDS;
-  auto kern = kind == Rows::k64 ? bwd_delta_head_kernel<D, CAUSAL, 2, 2>
-              : kind == Rows::k128 ? bwd_delta_head_kernel<D, CAUSAL, 2, 4> : bwd_delta_head_kernel<D, CAUSAL, 1, 8>;
+  auto kern = kind == Rows::k64 ? bwd_delta_head_kernel<D, CAUSAL, 2, 2> : bwd_delta_head_kernel<D, CAUSAL, 1, 8>;
+  if constexpr (D == 128) {   // at head dimension 64 delta_rows knows the other two only
+    if (kind == Rows::k128) kern = bwd_delta_head_kernel<D, CAUSAL, 2, 4>;
+  }
   static unsigned long long configured[3] = {};   // per template instantiation and kernel
   hipError_t e = allow_dynamic_lds(kern, lds, configured[(int)kind]);
   if (e != hipSuccess) return e;

@@ -146,7 +146,21 @@ inline Rows forward_rows(int D, int BH, int S, bool causal) {
   return (Rows)(std::min_element(t, t + 4) - t);
 }
 
-// ---- the backward
+// Delta of the first rows, likewise (S: the rows it is wanted for).  Its causal times serve full attention too, for which the backward does not ask for it.  The same bits
+// with every one.  256 / 128 / 64 rows, us, head dimension 128: 2 x 512 14.5 / 9.8 / 8.1; 16 x 2048 45 / 28.4 / 26.8; 38 x 949 26 / 18.8 / 22.7; 64 x 2048 69 / 76 / 107;
+// 128 x 512 19.9 / 19.5 / 24.8.  Head dimension 64, where two 64-row workgroups share a compute unit and 128 rows are not built (the fastest at 28 of 803 shapes, by 8 % at
+// most): 2 x 512 10.6 / 8.0 / 6.1; 16 x 2048 32 / 21.8 / 16.6; 60 x 896 15.9 / 14.9 / 14.2; 256 x 256 8.0 / 9.8 / 8.7; 64 x 2048 43 / 51 / 47.
+// 0.2 % off the fastest, at worst 1.25 times its time (99 x 404 x 64 12.3 for 9.8).
+inline Rows delta_rows(int D, int BH, int S, bool causal) {
+  static constexpr Cost at128[3] = {{1.46, 1.21, 3.53, .216, .0155}, {.827, .666, 3.94, .118, .027}, {.6, .598, 3.03, .201, .0372}};
+  static constexpr Cost at64[2] = {{1.01, .799, 3.42, .177, .0084}, {.526, .444, 2.61, .19, .0218}};
+  const XcdShare wide(D, BH, S, causal, 256, false), narrow(D, BH, S, causal, 64, false);
+  if (D == 64) return paired_time(narrow, at64[1]) < pass_time(wide, at64[0]) ? Rows::k64 : Rows::k256;
+  const double t[3] = {pass_time(wide, at128[0]), pass_time(XcdShare(D, BH, S, causal, 128, false), at128[1]), pass_time(narrow, at128[2])};
+  return (Rows)(std::min_element(t, t + 3) - t);
+}
+
+// ---- the gradients
 
 // The workgroups of a launch on the fullest XCD (32 compute units): `heads` virtual heads with `own` tiles each, the longest of every
 // head, the second longest of every head, ...  `keys`: tiles of the dK/dV pass, which sweep the query rows from their first key on;
@@ -232,19 +246,6 @@ inline bool split_dq(int D, int BH, int S, bool causal) {
 // in about 0.85 of the time that two side by side take theirs in, so that where narrow workgroups find compute units of their own every one of them
 // ends earlier; beyond that they only cost.  The arithmetic of a row is that of the 128-row workgroups, bit for bit.
 //
-// Delta of the first rows: by the time on an average XCD, as above but with the tiles spread evenly, as the order of map_block does by now.  Over 145
-// and 149 shapes (head dimension 128 and 64) the choice is 0.4 and 0.1 % off the fastest.  128 -> 64 rows, us: head dimension 128 12 heads x 1500
-// 22.2 -> 17.9, 16 x 2048 29.7 -> 27.8, 64 x 2048 84 -> 116; head dimension 64 16 x 16384 23.3 -> 18.9.
-// Narrow tiles that just fit the compute units at once do not where T is no multiple of P: workgroups without a tile are dealt out between
-// the others, some compute units get two in their place, and without a mask that is a second round (11 heads x 1399 34 us for the 18 of one).
-inline double rows_time(int BH, int S, bool causal, int rows, int slots, double per_step, double start) {
-  const Share even(BH, S, causal, rows, false, true), fullest(BH, S, causal, rows, false);
-  return pass_time(!causal && rows == 64 && slots == 32 && even.blocks() <= slots && fullest.blocks() > slots ? fullest : even, slots, per_step, start);
-}
-inline bool narrow_delta(int D, int BH, int S, bool causal) {
-  const double wide = std::min(rows_time(BH, S, causal, 128, 32, 0.58, 4.5), rows_time(BH, S, causal, 256, 32, 1., 3.5));
-  return (D == 64 ? rows_time(BH, S, causal, 64, 48, 0.42, 2.) : rows_time(BH, S, causal, 64, 32, 0.52, 3.2)) < wide;
-}
 // dK/dV and dQ: in their common launch, where 64-key and 64-row workgroups take their turns on the compute units.  Without a mask all take equally long, and
 // the launch has to fit (half of the chip for either); causal ones differ in length and fill each other's gaps.  Over 420 shapes 0.3 %
 // (head dimension 128, causal), 1.2 (no mask), 0.8 and 1.6 % (head dimension 64) off the better choice; at worst 10 x 819 x 64 without a mask 23.4 for 19.3 us.  128 -> 64, whole backward, us, 64-row
@@ -255,9 +256,6 @@ inline bool narrow_gradients(int BH, int S, bool causal) {
   return tiles_64 <= (causal ? 288 : 128);
 }
 
-inline Rows delta_rows(int D, int BH, int S, bool causal) {
-  return narrow_delta(D, BH, S, causal) ? Rows::k64 : split_rows(BH, S, causal) ? Rows::k128 : Rows::k256;
-}
 inline Rows dq_rows(int D, int BH, int S, bool causal) {
   return narrow_gradients(BH, S, causal) ? Rows::k64 : split_dq(D, BH, S, causal) ? Rows::k128 : Rows::k256;
 }

@@ -11,8 +11,7 @@ PROGRAM = """
 int main() {
   int D, BH, S, causal;
   while (scanf("%d %d %d %d", &D, &BH, &S, &causal) == 4)
-    printf("%d %d %d\\n", (int)helix::delta_rows(D, BH, S < 2048 ? S : 2048, causal),
-           helix::narrow_gradients(BH, S, causal), (int)helix::dq_rows(D, BH, S, causal));
+    printf("%d %d\\n", helix::narrow_gradients(BH, S, causal), (int)helix::dq_rows(D, BH, S, causal));
 }
 """
 
@@ -32,7 +31,7 @@ def rules(tmp_path_factory):
 
 
 # head dimension, causal, heads, tokens; us of the forward on 256-, 128- and 64-row tiles (not used), of the causal delta of the
-# first rows likewise, and of the backward on wide and narrow gradient workgroups
+# first rows likewise (not used), and of the backward on wide and narrow gradient workgroups
 MEASURED = """
 64 N 31 190 | - 6.4 5.5 | - - - | 11.5 12.6
 64 N 13 494 | - 9.2 7.5 | - - - | 15.0 14.0
@@ -106,10 +105,8 @@ def _rows():
 
 def test_choices_against_measured_times(rules):
     table = list(_rows())
-    regret = {"delta": [], "gradients": []}
-    for (D, c, bh, s, (_, d, g)), (rd, rg, _) in zip(table, rules([r[:1] + r[2:4] + r[1:2] for r in table])):
-        if c:
-            regret["delta"].append(d[rd] / min(d))
+    regret = {"gradients": []}
+    for (D, c, bh, s, (_, _, g)), (rg, _) in zip(table, rules([r[:1] + r[2:4] + r[1:2] for r in table])):
         regret["gradients"].append(g[rg] / min(g))
     for name, r in regret.items():
         assert max(r) <= 1.3 and sum(r) / len(r) <= 1.02, (name, max(r), sum(r) / len(r))
@@ -117,7 +114,7 @@ def test_choices_against_measured_times(rules):
 
 def test_narrow_gradients_go_together(rules):
     """Narrow key tiles share their launch with narrow query tiles only, and never beyond the grids they were measured at."""
-    for (D, bh, s, c), (_, narrow, dq) in zip(SHAPES, rules(SHAPES)):
+    for (D, bh, s, c), (narrow, dq) in zip(SHAPES, rules(SHAPES)):
         assert (dq == 2) == bool(narrow)
         assert not narrow or bh * ((s + 63) // 64) <= 288
 
