@@ -11,7 +11,7 @@
 //                dK^T += Q^T dS
 //   dq         : (bwd_dq.hpp) a workgroup owns 256 or 128 queries and sweeps the visible key tiles:
 //                S^T = K Q^T, dP^T = V dO^T, dS^T = P^T o (dP^T - delta), dQ^T += K^T dS^T
-// dkdv and dq share a launch on all but the largest grids (launch_bwd_dkdv_dq).  Between the kernels the row statistics travel as neg_delta = -delta and lse2 = LSE * log2(e).
+// dkdv and dq share a launch on all but the largest grids (gradient_tiles in dispatch.hpp).  Between the kernels the row statistics travel as neg_delta = -delta and lse2 = LSE * log2(e).
 //
 // Every output element is produced by exactly one lane, so there are no atomics and the
 // result is bit-reproducible.

@@ -175,7 +175,7 @@ __device__ __forceinline__ void dkdv_step(const f32x16& sp_cur, const f32x16& dp
 
 }  // namespace
 
-// GROUPS = 2 (see two_query_groups): two groups of four waves own the same 128 keys and sweep one half of the query
+// GROUPS = 2 (see gradient_tiles): two groups of KW waves own the same 32 KW keys and sweep one half of the query
 // tiles each, with stages of their own; at the end they swap partial sums through LDS and each stores one result.
 template <int D, bool CAUSAL, int GROUPS, int KW>
 __device__ __forceinline__ void dkdv_keys(int block, const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
@@ -405,7 +405,7 @@ bwd_dkdv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, cons
   dkdv_keys<D, CAUSAL, GROUPS, KW>(blockIdx.x, q, k, v, dO, lse2, neg_delta, dk, dv, maps, BH, H, S, T, scale);
 }
 
-// The dK/dV and the dQ pass in one launch (see launch_bwd_dkdv_dq): the first `key_blocks` workgroups take key tiles, the others
+// The dK/dV and the dQ pass in one launch (see gradient_tiles in dispatch.hpp): the first `key_blocks` workgroups take key tiles, the others
 // query tiles of as many rows.
 template <int D, bool CAUSAL, int KW>
 __global__ void __launch_bounds__(128 * KW) __attribute__((amdgpu_waves_per_eu(2, 2)))
@@ -440,8 +440,9 @@ template <bool CAUSAL>
 static hipError_t launch_dkdv_64(const void* q, const void* k, const void* v, const void* dO,
                                  const float* lse2, const float* neg_delta, void* dk, void* dv, const BwdMaps& maps,
                                  int B, int H, int S, float scale, hipStream_t stream) {
-  if (key_tile(B * H, S, CAUSAL) == 64) return launch_dkdv_t<64, CAUSAL, 2, 2>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B, H, S, scale, stream);
-  if (two_query_groups(B * H, S, CAUSAL)) return launch_dkdv_t<64, CAUSAL, 2, 4>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B, H, S, scale, stream);
+  const Gradients kind = gradient_tiles(64, B * H, S, CAUSAL);
+  if (kind == Gradients::kNarrow) return launch_dkdv_t<64, CAUSAL, 2, 2>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B, H, S, scale, stream);
+  if (one_launch(kind)) return launch_dkdv_t<64, CAUSAL, 2, 4>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B, H, S, scale, stream);
   return launch_dkdv_t<64, CAUSAL, 1, 4>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B, H, S, scale, stream);
 }
 
@@ -474,29 +475,20 @@ static hipError_t launch_dkdv_dq_t(const void* q, const void* k, const void* v, 
 template <bool CAUSAL>
 static hipError_t launch_dkdv_dq_64(const void* q, const void* k, const void* v, const void* dO, const float* lse2,
                                     const float* neg_delta, void* dq, void* dk, void* dv, const BwdMaps& maps, int B, int H, int S,
-                                    float scale, hipStream_t stream) {
-  return key_tile(B * H, S, CAUSAL) == 64 ? launch_dkdv_dq_t<64, CAUSAL, 2>(q, k, v, dO, lse2, neg_delta, dq, dk, dv, maps, B, H, S, scale, stream)
-                                              : launch_dkdv_dq_t<64, CAUSAL, 4>(q, k, v, dO, lse2, neg_delta, dq, dk, dv, maps, B, H, S, scale, stream);
+                                    float scale, Gradients kind, hipStream_t stream) {
+  return kind == Gradients::kNarrow ? launch_dkdv_dq_t<64, CAUSAL, 2>(q, k, v, dO, lse2, neg_delta, dq, dk, dv, maps, B, H, S, scale, stream)
+                                    : launch_dkdv_dq_t<64, CAUSAL, 4>(q, k, v, dO, lse2, neg_delta, dq, dk, dv, maps, B, H, S, scale, stream);
 }
 
-// Both passes need the row statistics and nothing of each other, and a workgroup of either fills a compute unit (LDS at head
-// dimension 128, registers at 64), so one launch with the key tiles first fills the compute units that a small grid or its
-// last, uneven round leaves idle, and pays for one start instead of two.  The work of a workgroup is that of the separate passes, bit for bit.
-// Head dimension 128, two launches -> one, backward, us, key tiles in brackets: causal 2 heads x 512 [8] 51 -> 34; 12 x 1500 [144] 94 -> 65;
-// 16 x 2048 [256] 124 -> 99; 5 x 8192 383 -> 336; 16 x 8192 [1024] 848 -> 841; 36 x 4096 [1152] 568 -> 548; 80 x 2048 [1280] 411 -> 405;
-// with more rounds there is little left to fill and the change from one pass to the other costs L2 hits: 5 x 32k [1280] 4190 -> 4276,
-// 16 x 16k [2048] 3164 -> 3159, 80 x 8000 [5040] 4139 -> 4165.  No mask: 2 x 512 39 -> 23; 16 x 7168 [896] 1259 -> 1288; 16 x 8192 [1024]
-// 1548 -> 1536; 36 x 4096 [1152] 995 -> 943; 5 x 30000 [1175] 6871 -> 6998.  The line at 1024 gives away up to 4 % between 1024 and 1280.
-// Head dimension 64: two_query_groups in dispatch.hpp.
 hipError_t launch_bwd_dkdv_dq(const void* q, const void* k, const void* v, const void* dO, const float* lse2, const float* neg_delta,
                               void* dq, void* dk, void* dv, const BwdMaps& maps, int B, int H, int S, int D, float scale, bool causal,
                               hipStream_t stream) {
-  const long long key_tiles = (long long)B * H * ((S + 127) / 128);
-  if (D == 128 && key_tiles <= 1024)
-    return launch_bwd_dkdv_dq_pair(q, k, v, dO, lse2, neg_delta, dq, dk, dv, maps, B, H, S, scale, causal, stream);
-  if (D == 64 && (key_tile(B * H, S, causal) == 64 || two_query_groups(B * H, S, causal)))
-    return causal ? launch_dkdv_dq_64<true>(q, k, v, dO, lse2, neg_delta, dq, dk, dv, maps, B, H, S, scale, stream)
-                  : launch_dkdv_dq_64<false>(q, k, v, dO, lse2, neg_delta, dq, dk, dv, maps, B, H, S, scale, stream);
+  const Gradients kind = gradient_tiles(D, B * H, S, causal);
+  if (one_launch(kind)) {
+    if (D == 128) return launch_bwd_dkdv_dq_pair(q, k, v, dO, lse2, neg_delta, dq, dk, dv, maps, B, H, S, scale, causal, kind, stream);
+    return causal ? launch_dkdv_dq_64<true>(q, k, v, dO, lse2, neg_delta, dq, dk, dv, maps, B, H, S, scale, kind, stream)
+                  : launch_dkdv_dq_64<false>(q, k, v, dO, lse2, neg_delta, dq, dk, dv, maps, B, H, S, scale, kind, stream);
+  }
   hipError_t e = launch_bwd_dkdv(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B, H, S, D, scale, causal, stream);
   return e != hipSuccess ? e : launch_bwd_dq(q, k, v, dO, lse2, neg_delta, dq, maps, B, H, S, D, scale, causal, stream);
 }

@@ -573,7 +573,7 @@ bwd_dkdv_pair_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
   pair_keys<CAUSAL, PAIRS>(blockIdx.x, q, k, v, dO, lse2, neg_delta, dk, dv, maps, BH, H, S, T, scale);
 }
 
-// The dK/dV and the dQ pass in one launch (see launch_bwd_dkdv_dq): the first `key_blocks` workgroups take key tiles, the others
+// The dK/dV and the dQ pass in one launch (see gradient_tiles in dispatch.hpp): the first `key_blocks` workgroups take key tiles, the others
 // query tiles.
 template <bool CAUSAL, int ROWS, int PAIRS>
 __global__ void __launch_bounds__(128 * PAIRS) __attribute__((amdgpu_waves_per_eu(2)))
@@ -591,10 +591,10 @@ bwd_dkdv_dq_pair_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__
 template <bool CAUSAL>
 static hipError_t launch_dkdv_dq_pair_t(const void* q, const void* k, const void* v, const void* dO, const float* lse2,
                                         const float* neg_delta, void* dq, void* dk, void* dv, const BwdMaps& maps, int B, int H, int S,
-                                        float scale, hipStream_t stream) {
+                                        float scale, Gradients kind, hipStream_t stream) {
   const int BH = B * H;
-  const Rows rows = dq_rows(PG::D, BH, S, CAUSAL);
-  const int keys = key_tile(BH, S, CAUSAL);
+  const Rows rows = dq_rows(kind);
+  const int keys = key_tile(kind);
   const int TK = (S + keys - 1) / keys, TQ = tiles(S, rows);
   const long long key_blocks = grid_blocks(BH, TK);
   const size_t lds = std::max(PG::LDS, rows == Rows::k256 ? kDqWholeLds<128> : DqSplit<128>::LDS);
@@ -610,9 +610,9 @@ static hipError_t launch_dkdv_dq_pair_t(const void* q, const void* k, const void
 }
 hipError_t launch_bwd_dkdv_dq_pair(const void* q, const void* k, const void* v, const void* dO, const float* lse2,
                                    const float* neg_delta, void* dq, void* dk, void* dv, const BwdMaps& maps, int B, int H, int S,
-                                   float scale, bool causal, hipStream_t stream) {
-  return causal ? launch_dkdv_dq_pair_t<true>(q, k, v, dO, lse2, neg_delta, dq, dk, dv, maps, B, H, S, scale, stream)
-                : launch_dkdv_dq_pair_t<false>(q, k, v, dO, lse2, neg_delta, dq, dk, dv, maps, B, H, S, scale, stream);
+                                   float scale, bool causal, Gradients kind, hipStream_t stream) {
+  return causal ? launch_dkdv_dq_pair_t<true>(q, k, v, dO, lse2, neg_delta, dq, dk, dv, maps, B, H, S, scale, kind, stream)
+                : launch_dkdv_dq_pair_t<false>(q, k, v, dO, lse2, neg_delta, dq, dk, dv, maps, B, H, S, scale, kind, stream);
 }
 
 template <bool CAUSAL, int PAIRS>
@@ -632,7 +632,7 @@ static hipError_t launch_dkdv_pair_t(const void* q, const void* k, const void* v
 hipError_t launch_bwd_dkdv_pair(const void* q, const void* k, const void* v, const void* dO, const float* lse2,
                                 const float* neg_delta, void* dk, void* dv, const BwdMaps& maps, int B, int H, int S,
                                 float scale, bool causal, hipStream_t stream) {
-  if (key_tile(B * H, S, causal) == 64)
+  if (key_tile(gradient_tiles(PG::D, B * H, S, causal)) == 64)
     return causal ? launch_dkdv_pair_t<true, 2>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B * H, H, S, scale, stream)
                   : launch_dkdv_pair_t<false, 2>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B * H, H, S, scale, stream);
   return causal ? launch_dkdv_pair_t<true, 4>(q, k, v, dO, lse2, neg_delta, dk, dv, maps, B * H, H, S, scale, stream)

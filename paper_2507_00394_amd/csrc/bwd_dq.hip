@@ -17,7 +17,7 @@ static hipError_t launch_dq_pipe_t(const void* q, const void* k, const void* v, 
                                    const float* lse2, const float* neg_delta, void* dq, const BwdMaps& maps,
                                    int B, int H, int S, float scale, hipStream_t stream) {
   const int BH = B * H;
-  const Rows rows = dq_rows(D, BH, S, CAUSAL);
+  const Rows rows = dq_rows(gradient_tiles(D, BH, S, CAUSAL));
   const int T = tiles(S, rows);
   const unsigned grid = (unsigned)grid_blocks(BH, T);
   const size_t lds = rows == Rows::k256 ? kDqWholeLds<D> : DqSplit<D>::LDS;

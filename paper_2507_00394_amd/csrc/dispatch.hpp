@@ -117,6 +117,31 @@ inline double paired_time(const XcdShare& w, const Cost& c) {
   for (int k = 0; k < 3 && 64 * k < w.count; k++) t = std::max(t, (k + 1) * ((k == 0 ? c.alone : step) * w.length(64 * k / w.heads) + c.fixed));
   return t + mb;
 }
+// The dK/dV and the dQ pass in one launch: key tiles first, then query tiles, a compute unit each.  `sparse`: a step's time with the chip nearly empty
+// over that with it full.
+struct CommonCost { double key_step, key_fixed, query_step, query_fixed, tail, sparse, mb; };
+inline double common_time(const XcdShare& k, const XcdShare& q, const CommonCost& c) {
+  const double f = c.sparse + (1 - c.sparse) * std::min(1., (k.tiles() + q.tiles()) / 32), ks = c.key_step * f, qs = c.query_step * f;
+  const double key = ks * k.longest + c.key_fixed, query = qs * q.longest + c.query_fixed, mb = c.mb * (k.mb + q.mb);
+  if (!k.causal) {
+    // Tile by tile: `late` compute units end their last key tile a key tile after the other ones, and every one takes query tiles as soon as it is free.
+    // The end is that of the n-th query tile of one kind of compute unit or the other.
+    const double rounds = (double)(k.count / 32), late = k.count - 32 * rounds, early = rounds * key, then = early + key;
+    const auto done = [&](double t) { return late * std::max(0., std::floor((t - then) / query + 1e-9)) + (32 - late) * std::floor((t - early) / query + 1e-9); };
+    double n = std::max(1., std::ceil((q.count + late * key / query) / 32) - 2), t = 1e30;
+    while (done(early + n * query) < q.count) n++;
+    t = early + n * query;
+    if (late > 0) {
+      n = std::max(0., std::ceil((q.count - (32 - late) * std::floor(key / query)) / 32) - 1);
+      while (done(then + n * query) < q.count) n++;
+      t = std::max(std::min(t, then + n * query), then);
+    }
+    return t + mb;
+  }
+  double t = (ks * k.steps() + c.key_fixed * k.tiles() + qs * q.steps() + c.query_fixed * q.tiles()) / 32 + c.tail * (qs * q.steps() / q.tiles() + c.query_fixed);
+  for (int i = 0; i < 2 && 32 * i < k.count; i++) t = std::max(t, (i + 1) * (ks * k.length(32 * i / k.heads) + c.key_fixed));
+  return t + mb;
+}
 
 // Rows of a query tile: 256 with a wave for every 32 rows, or 128 or 64 with the keys split over two groups of waves, or 64 over four.
 enum class Rows { k256, k128, k64, k64Quad };
@@ -160,105 +185,51 @@ inline Rows delta_rows(int D, int BH, int S, bool causal) {
   return (Rows)(std::min_element(t, t + 3) - t);
 }
 
-// ---- the gradients
-
-// The workgroups of a launch on the fullest XCD (32 compute units): `heads` virtual heads with `own` tiles each, the longest of every
-// head, the second longest of every head, ...  `keys`: tiles of the dK/dV pass, which sweep the query rows from their first key on;
-// else of query rows, which sweep the keys up to their last row.  Lengths in steps of 64 rows or keys.
-struct Share {
-  bool causal, keys;
-  int P, T, per_tile;          // parts of a head, tiles of a head, steps by which neighbouring tiles differ
-  double heads, own, longest;
-  // `even`: an average XCD's share in the place of the fullest one's (a fraction of a tile where T is no multiple of P).
-  Share(int BH, int S, bool causal_, int rows, bool keys_, bool even = false)
-      : causal(causal_), keys(keys_), P(head_parts(BH)), T((S + rows - 1) / rows), per_tile(rows / 64), heads((double)BH * P / 8),
-        own(even ? (double)T / P : (T + P - 1) / P), longest((S + 63) / 64) {}
-  double blocks() const { return own * heads; }
-  double length(double i) const {   // of the i-th longest tile of a head
-    if (!causal || i == 0.) return longest;
-    return keys ? longest - per_tile * P * i : per_tile * (T - P * i);
+// dK/dV and dQ: in a launch each, with 256 or 128 query rows to a dQ workgroup and 128 keys to a dK/dV one; in one launch likewise; or in one launch on narrow workgroups of 64 of
+// either, which end sooner where the chip has room for all of them.  Head dimension 64: a launch each goes with one group of waves to a key tile, two workgroups of
+// which share a compute unit; in one launch two groups share the query tiles of a key tile and end in half the time, which pays where the chip is not full.
+// Both passes need the row statistics and nothing of each other, and a workgroup of either fills a compute unit in the common launch (LDS at head
+// dimension 128, registers at 64), so one launch with the key tiles first fills the compute units that a small grid or its
+// last, uneven round leaves idle, and pays for one start instead of two.  The work of a workgroup is that of the separate passes, bit for bit.
+// A launch each 256 / 128 - together 256 / 128 / narrow, whole backward, us, head dimension 128:
+//   causal: 2 x 512 44 / 39 - 28 / 26 / 20.5; 12 x 1500 98 / 82 - 66 / 57.3 / 58.8; 4 x 2048 123 / 102 - 81 / 69 / 54; 42 x 384 37 / 36 - 25.8 / 25.9 / 26.9; 16 x 2048 135 / 116 - 107 / 95 /
+//     103; 128 x 512 75 / 77 - 74 / 75 / 91; 64 x 2048 309 / 318 - 304 / 313 / 368; 16 x 16k 3171 / 3272 - 3171 / 3270 / 3861; 5 x 32k 4109 / 4161 - 4100 / 4202 / -;
+//     80 x 8000 3956 / 4075 - 3946 / 4062 / -; 256 x 2048 1350 / 1365 - 1320 / 1359 / -; 32 x 32k 24619 / 25399 - 24663 / 25438 / -.
+//   no mask: 7 x 1104 69 / 57 - 42 / 36 / 28.7; 11 x 1399 81 / 67 - 52 / 49 / 53; 17 x 1438 93 / 81 - 95 / 80 / 99; 5 x 4187 211 / 169 - 150 / 188 / 184; 36 x 4096 1006 / 993 - 929 / 947 / 1089;
+//     512 x 1024 946 / 1010 - 942 / 1015 / -; 12 x 8192 1231 / 1216 - 1246 / 1213 / 1409.
+// Head dimension 64, a launch each 256 / 128 - together 128 / narrow:
+//   causal: 2 x 512 31 / 27 - 17 / 15; 131 x 146 23 / 24 - 21 / 22; 54 x 563 39 / 36 - 29.5 / 36; 256 x 256 32 / 34 - 37 / 48; 4 x 16k 614 / 534 - 483 / 582; 16 x 16k 1718 / 1780 - 1834 / 2211.
+//   no mask: 9 x 888 39 / 34 - 19.7 / 17.0; 10 x 819 37 / 31 - 18.9 / 22.9; 27 x 777 40 / 35 - 32 / 37; 22 x 3840 324 / 310 - 314 / 366; 120 x 1181 185 / 184 - 190 / 234.
+// The choice is 0.3 (head dimension 128, causal) and 0.1 to 0.2 % (no mask; 64) off the fastest, at worst 1.19 times its time (81 x 135 causal 21.4 for 17.9).  At
+// head dimension 128 a launch each is left to causal grids of more than 1024 key tiles, where one launch costs L2 hits in the change from one pass to the other: it takes
+// 0.98 (up to 1500 key tiles) to 1.00 (beyond 5000) of the time on average, and up to 1.03 of it at single shapes.
+enum class Gradients { kSeparate256, kSeparate128, kTogether256, kTogether128, kNarrow };
+inline Gradients gradient_tiles(int D, int BH, int S, bool causal) {
+  static constexpr CommonCost at128[2][3] = {{{1.65, 4.07, 2.01, 5.01, 0, .844, .0297}, {1.54, 4.97, 1.3, 4.48, 0, .861, .026}, {1.01, 4.26, .765, 4., 0, .955, .0428}},
+                                             {{1.47, 6.08, 1.73, 3.01, .948, 1.02, .0166}, {1.4, 5.42, 1.43, 6.35, .0866, 1.15, .0269}, {1., 4.91, .789, 4.49, .34, .898, .0136}}};
+  static constexpr CommonCost at64[2][2] = {{{.847, 4.19, .752, 2.93, 0, 1.04, .0263}, {.561, 3.62, .474, 2.73, 0, 1.12, .0355}},
+                                            {{.882, 5.21, .776, 3.99, .242, 1.07, .0048}, {.608, 4.57, .422, 2.74, .597, 1.08, .0112}}};
+  static constexpr Cost one_group[2] = {{1.4, .839, 4.32, 0, .0329}, {1.64, .863, 5.58, .392, .0099}}, query_256[2] = {{1.42, 1.38, 2.97, 0, .0329}, {1.24, 1.06, 4.01, 0, .0099}},
+                        query_128[2] = {{.855, .699, 3.29, 0, .0329}, {.786, .824, 3.19, .503, .0099}};
+  const XcdShare k128(D, BH, S, causal, 128, true), k64(D, BH, S, causal, 64, true), q256(D, BH, S, causal, 256, false), q128(D, BH, S, causal, 128, false),
+      q64(D, BH, S, causal, 64, false);
+  double t[5] = {1e30, 1e30, 1e30, 1e30, 1e30};
+  if (D == 128) {
+    if (causal && (long long)BH * k128.T > 1024) return Gradients::kSeparate256;
+    t[2] = common_time(k128, q256, at128[causal][0]);
+    t[3] = common_time(k128, q128, at128[causal][1]);
+    t[4] = common_time(k64, q64, at128[causal][2]);
+  } else {
+    const double keys = paired_time(k128, one_group[causal]);
+    t[0] = keys + pass_time(q256, query_256[causal]);
+    t[1] = keys + pass_time(q128, query_128[causal]);
+    t[3] = common_time(k128, q128, at64[causal][0]);
+    t[4] = common_time(k64, q64, at64[causal][1]);
   }
-  double steps() const {
-    if (!causal) return blocks() * longest;
-    return heads * (keys ? own * longest - per_tile * P * own * (own - 1) / 2 : longest + per_tile * ((own - 1) * T - P * own * (own - 1) / 2));
-  }
-};
-// Time of a pass whose workgroups go `slots` at a time, `per_step` for a step and `start` for a workgroup's first loads, its last tile and its
-// results, the longest first: the average of a slot or, if that is more, what the longest ones take where k of them cannot help
-// sharing a slot.  Without a mask all are equal, and that is whole rounds.  The unit is a step of a 256-row workgroup.
-inline double pass_time(const Share& w, int slots, double per_step, double start) {
-  const double rounds = std::ceil(w.blocks() / slots - 1e-9);
-  double t = (per_step * w.steps() + start * w.blocks()) / slots;
-  if (!w.causal) return std::max(t, rounds * (per_step * w.longest + start));
-  for (int k = 0; k < 3 && k < rounds; k++) t = std::max(t, (k + 1) * (per_step * w.length(std::floor(k * slots / w.heads)) + start));
-  return t;
+  return (Gradients)(std::min_element(t, t + 5) - t);
 }
-inline double whole_rows_time(int BH, int S, bool causal) { return pass_time(Share(BH, S, causal, 256, false), 32, 1., 3.5); }
-inline double split_rows_time(int BH, int S, bool causal) { return pass_time(Share(BH, S, causal, 128, false), 32, 0.58, 4.5); }
-
-// Whether a pass takes 128-row tiles with the keys split over two groups of waves instead of 256-row tiles.  A split workgroup needs little
-// more than half of a whole one's time per key tile, a little more for its start and end, and there are twice as many: it pays where
-// whole tiles leave compute units idle, or where they fill a round or an XCD badly.  Over 467 shapes (1 to 2048 heads, 65 to 32k tokens; forward
-// at head dimension 128, dQ at both) the rule costs 0.4 and 0.2 % against the faster variant of each, more than 10 % at four forward ones:
-// 416 x 304 without a mask 64 for 52 us; causal 472 x 381 67 for 60, 252 x 761 95 for 86, 66 x 2521 166 for 151.
-// Whole -> split, us, forward / dQ (or the whole backward, b) at head dimension 128:
-//   causal: 12 heads x 1500 39.0 -> 24.9 / 49 -> 31.5; 2 x 32k 708 -> 527 / 904 -> 693; 64 x 1024 32.4 -> 29.7; 500 x 200 59 -> 41 / b 182 -> 157;
-//     78 x 589 39.9 -> 32.7; 66 x 768 53 -> 41;
-//     128 x 512 21.9 -> 24.0; 256 x 256 19.4 -> 23.4 / b 77.7 -> 81.0; 16 x 8192 255 -> 282 / 339 -> 364; 256 x 2048 316 -> 367 / b 1353 -> 1394.
-//   no mask: 32 x 1024 30.3 -> 22.3; 7 x 9000 446 -> 286 / b 1079 -> 875; 36 x 1700 94 -> 64; 12 x 8192 412 -> 399 / 533 -> 522;
-//     275 x 987 341 -> 229 / b 824 -> 658;
-//     32 x 1500 43.9 -> 53.8; 21 x 1216 38.5 -> 45.9; 120 x 3637 775 -> 848; 512 x 1024 301 -> 342; 36 x 16568 4585 -> 5196 / b 15128 -> 15659.
-inline bool split_rows(int BH, int S, bool causal) {
-  return split_rows_time(BH, S, causal) < whole_rows_time(BH, S, causal);
-}
-
-// Head dimension 64: whether two groups of waves share the query tiles of a key tile in the dK/dV pass, and that pass its launch with
-// the dQ pass on split tiles (a launch of its own is what the stage calls make of it).  With one group a SIMD has one wave, which
-// is bound by instruction issue, unless a second workgroup finds room beside it; two groups halve the sweep, and the common launch fills
-// the compute units that a small grid or its last round leaves idle and saves a start.  Where the chip is full both only cost: the swap of
-// partial sums, and one workgroup in the place of two.  The times of both ways, fitted to the whole backward at 465 shapes (1 to 2048
-// heads, 20 to 32k tokens): the rule costs 0.3 % against the best of all variants, 10 % at worst.
-// Separate passes (the faster way) -> one launch, us, key tiles in brackets:
-//   causal: 2 heads x 512 [8] 33.7 -> 23.1; 12 x 1500 [144] 64 -> 44; 32 x 1024 [256] 51 -> 41; 32 x 1500 [384] 72.5 -> 70.5; 4 x 16k [512]
-//     486 -> 484 (533 with one group); 60 x 900 [480] 69 -> 73; 128 x 512 [512] 51 -> 55; 256 x 256 [512] 43 -> 48; 256 x 2048 [4096] 730 -> 811.
-//   no mask: 2 x 512 [8] 26.7 -> 16.2; 27 x 777 [189] 40.5 -> 39; 2 x 16k [256] 446 -> 443; 24 x 1500 [288] 80.5 -> 74; 40 x 1500 [480]
-//     94 -> 102; 64 x 1024 [512] 72 -> 79; 24 x 3000 [576] 248 -> 214; 10 x 8192 [640] 626 -> 563; 11 x 8192 [704] 634 -> 649; 190 x 400 [760]
-//     74 -> 81; 8 x 17920 [1120] 2244 -> 2128; 160 x 1024 [1280] 173 -> 187; 512 x 300 [1536] 102 -> 120; 80 x 6528 [4080] 2756 -> 2841.
-inline bool two_query_groups(int BH, int S, bool causal) {
-  const Share k(BH, S, causal, 128, true), q(BH, S, causal, 128, false);
-  // one group: two workgroups beside one another on a compute unit, 1.6 a step; one alone takes 0.7 of that
-  const double beside = 1.6 * k.longest + 7., alone = 0.7 * 1.6 * k.longest + 7., rest = std::fmod(k.blocks(), 64.);
-  const double one = causal ? std::max((1.6 * k.steps() + 7. * k.blocks()) / 64, alone)
-                            : std::floor(k.blocks() / 64) * beside + (rest == 0. ? 0. : rest <= 32. ? alone : beside);
-  const double separate = one + std::min(split_rows_time(BH, S, causal), whole_rows_time(BH, S, causal)) + 7.;   // a second launch
-  // together: key tiles, 0.8 a step, then query tiles, 0.55; no mask: rounded up to a whole query tile
-  const double query = 0.55 * q.longest + 5.2;
-  const double work = (0.8 * k.steps() + 10. * k.blocks() + 0.55 * q.steps() + 5.2 * q.blocks()) / 32;
-  const double together = causal ? std::max(work, pass_time(k, 32, 0.8, 10.)) : query * std::ceil(work / query);
-  return together < separate;
-}
-inline bool split_dq(int D, int BH, int S, bool causal) {
-  return (D == 64 && two_query_groups(BH, S, causal)) || split_rows(BH, S, causal);
-}
-
-
-// Narrow workgroups: 64 rows (or keys) and four waves, one per SIMD, in the place of 128 and eight.  A wave that has its SIMD to itself takes a step
-// in about 0.85 of the time that two side by side take theirs in, so that where narrow workgroups find compute units of their own every one of them
-// ends earlier; beyond that they only cost.  The arithmetic of a row is that of the 128-row workgroups, bit for bit.
-//
-// dK/dV and dQ: in their common launch, where 64-key and 64-row workgroups take their turns on the compute units.  Without a mask all take equally long, and
-// the launch has to fit (half of the chip for either); causal ones differ in length and fill each other's gaps.  Over 420 shapes 0.3 %
-// (head dimension 128, causal), 1.2 (no mask), 0.8 and 1.6 % (head dimension 64) off the better choice; at worst 10 x 819 x 64 without a mask 23.4 for 19.3 us.  128 -> 64, whole backward, us, 64-row
-// tiles in brackets: causal 2 heads x 512 x 64 [16] 19.6 -> 17.1, 2 x 512 x 128 28 -> 22.8, 4 x 2048 [128] 75 -> 60, 2 x 8192 [256] 205 -> 167,
-// 12 x 1500 [288] 62 -> 65, 16 x 2048 [512] 97 -> 109; no mask 4 x 2048 [128] 49 -> 38, 5 x 4187 [330] 187 -> 186, 27 x 777 x 64 [351] 37 -> 48.
-inline bool narrow_gradients(int BH, int S, bool causal) {
-  const long long tiles_64 = (long long)BH * ((S + 63) / 64);
-  return tiles_64 <= (causal ? 288 : 128);
-}
-
-inline Rows dq_rows(int D, int BH, int S, bool causal) {
-  return narrow_gradients(BH, S, causal) ? Rows::k64 : split_dq(D, BH, S, causal) ? Rows::k128 : Rows::k256;
-}
-inline int key_tile(int BH, int S, bool causal) { return narrow_gradients(BH, S, causal) ? 64 : 128; }
+inline Rows dq_rows(Gradients g) { return g == Gradients::kNarrow ? Rows::k64 : g == Gradients::kSeparate256 || g == Gradients::kTogether256 ? Rows::k256 : Rows::k128; }
+inline int key_tile(Gradients g) { return g == Gradients::kNarrow ? 64 : 128; }
+inline bool one_launch(Gradients g) { return g >= Gradients::kTogether256; }
 
 }  // namespace helix

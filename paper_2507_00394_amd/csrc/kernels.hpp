@@ -5,6 +5,8 @@
 
 namespace helix {
 
+enum class Gradients;   // dispatch.hpp
+
 // Where a [B, H, S, D] tensor lives: element strides of batch, head and row; the D elements
 // of a row are contiguous.
 struct TensorMap {
@@ -59,7 +61,7 @@ hipError_t launch_bwd_dkdv_dq(const void* q, const void* k, const void* v, const
                               hipStream_t stream);
 hipError_t launch_bwd_dkdv_dq_pair(const void* q, const void* k, const void* v, const void* dO, const float* lse2,
                                    const float* neg_delta, void* dq, void* dk, void* dv, const BwdMaps& maps, int B, int H, int S,
-                                   float scale, bool causal, hipStream_t stream);   // head dimension 128, one launch
+                                   float scale, bool causal, Gradients tiles, hipStream_t stream);   // head dimension 128, one launch
 
 // Linear layer next to attention: out[M][N] = a[M][K] w[K][N] (bf16, fp32 accumulation) and its
 // backward products da[M][K] = dout[M][N] w[K][N]^T (bf16) and dw[K][N] = a[M][K]^T dout[M][N] (fp32).
