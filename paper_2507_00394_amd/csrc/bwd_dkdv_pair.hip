@@ -1,8 +1,6 @@
 // dK / dV pass of the attention backward, head dimension 128, TWO waves per SIMD (Table 1,
-// Attention column, "Backward B").  The arithmetic is that of bwd_dkdv.hip (dV comes out bit
-// for bit the same; dK differs in the last bit of some elements because here -delta is the
-// initial accumulator of the dP product in every code path); what differs is the division of
-// labour.
+// Attention column, "Backward B").  The arithmetic is that of bwd_dkdv.hip; what differs is the
+// division of labour.
 //
 // The one-wave-per-SIMD kernel keeps S, dP, dK^T and dV^T of 32 keys in one wave (364
 // registers at this head dimension) and is bound by instruction issue: a single wave issues
@@ -13,7 +11,7 @@
 //     wave B (waves 4..7):  dP = dO V^T - delta,  dS = P o dP,  dK^T += Q^T bf16(dS)
 // A hands P (fp32, register for register: both accumulators have the same lane layout)
 // to B through LDS; B works one 32-row block behind A, and one workgroup barrier per block
-// orders the hand-over.  Each wave needs 212 registers (240-242 in the launch shared with dQ), so two fit on a SIMD and the
+// orders the hand-over.  Each wave needs 220-222 registers (239-255 in the launch shared with dQ), so two fit on a SIMD and the
 // instructions of one issue under the MFMAs of the other; per MFMA a wave issues about two
 // vector-ALU and two LDS instructions.
 //
@@ -115,8 +113,8 @@ struct Lane {
   int pstep;
 };
 
-// Copy state of the pipelined loop: whole blocks only, so a copy is three instructions with
-// precomputed operands.  The pointers are wave-uniform (scalar registers).
+// Copy state of the pipelined loop: whole blocks only, so a copy is a few instructions (three with four
+// pairs, five with two) with precomputed operands.  The pointers are wave-uniform (scalar registers).
 template <int PIECES>
 struct Copier {
   const __bf16* qptr;     // first row of the next Q block to copy
