@@ -1,5 +1,5 @@
 """NaN and infinity in the inputs of the forward.  A NaN score reaches O and LSE of every row that sees it, wherever in the row it
-stands: also where it is all that one of the two key halves of a split workgroup holds for that row (a maximum does not see it).
+stands: also where it is all that one of the two or four key groups of a workgroup holds for that row (a maximum does not see it).
 A score of -inf takes its key out.  Rows that see neither are as without them.  Few heads and many, both masks."""
 import numpy as np
 import pytest
@@ -7,6 +7,7 @@ import torch
 
 from oracle import attention_ref as A
 from paper_2507_00394_amd import inputs as I
+from tests.dispatch_host import ask
 
 pytestmark = pytest.mark.gpu
 
@@ -73,4 +74,48 @@ def test_score_of_minus_infinity_takes_its_key_out(S, D, H):
     m = s.max(1, keepdims=True)
     p = np.exp(s - m)
     G.check("o", o, p / p.sum(1, keepdims=True) @ x["v"][keep])
+    assert np.abs(lse - (m[:, 0] + np.log(p.sum(1)))).max() <= G.TOL_LSE
+
+
+def _four_groups(S, causal):
+    """Two heads of S tokens at head dimension 128 take the kernel with four key groups: group g has keys 32 g .. 32 g + 31 of every 128."""
+    assert ask([(128, 2, S, causal)], "forward_rows(D, BH, S, causal)") == [(3,)]
+
+
+# the first key of a group, all that a row has of it; a whole block; one block of a later tile, and the last, ragged one
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("S,bad", [(673, (32, 33)), (673, (64, 65)), (673, (96, 97)), (673, (64, 96)), (673, (96, 128)), (673, (0, 1)), (673, (544, 545)), (673, (672, 673)),
+                                   (1500, (32, 64)), (1500, (1376, 1377)), (1500, (1472, 1500))])
+def test_nan_keys_in_four_groups(S, bad, causal):
+    _four_groups(S, causal)
+    test_nan_keys_reach_every_row_that_sees_them(S, bad, causal, 128, 2)
+
+
+def test_nan_query_row_in_four_groups():
+    _four_groups(673, True)
+    test_nan_query_row(673, 128, True, 2)
+
+
+# every key of a group goes; of the first group, as in the kernels without groups, all but the first block
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("group", [0, 1, 2, 3])
+def test_scores_of_minus_infinity_in_one_of_four_groups(group, causal):
+    from tests import gpu_util as G
+
+    S, D = 673, 128
+    _four_groups(S, causal)
+    x = _inputs(S, D)
+    x["q"][:, 0] = 1.0
+    gone = (np.arange(S) // 32) % 4 == group
+    if group == 0:
+        gone[:32] = False
+    x["k"][gone, 0] = -np.inf
+    o, lse = _forward(x, causal, D ** -0.5, 2)
+    s = x["q"] @ np.where(gone[:, None], 0.0, x["k"]).T * D ** -0.5
+    s[:, gone] = -np.inf
+    if causal:
+        s[np.triu_indices(S, 1)] = -np.inf
+    m = s.max(1, keepdims=True)
+    p = np.exp(s - m)
+    G.check("o", o, p / p.sum(1, keepdims=True) @ x["v"])
     assert np.abs(lse - (m[:, 0] + np.log(p.sum(1)))).max() <= G.TOL_LSE
