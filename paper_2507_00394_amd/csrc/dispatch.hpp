@@ -232,4 +232,105 @@ inline Rows dq_rows(Gradients g) { return g == Gradients::kNarrow ? Rows::k64 : 
 inline int key_tile(Gradients g) { return g == Gradients::kNarrow ? 64 : 128; }
 inline bool one_launch(Gradients g) { return g >= Gradients::kTogether256; }
 
+// ---------------------------------------------------------------- the linear layer's tiles
+//
+// Square tiles of C.  As above every variant has a time model fitted to its own times, here over 3300 shapes (32 to 131072 tokens, K to 5120, N to 3072).
+enum class TileKind { k256, k128, k64 };
+inline int tile_edge(TileKind k) { return k == TileKind::k256 ? 256 : k == TileKind::k128 ? 128 : 64; }
+inline int tile_slots(TileKind k) { return k == TileKind::k256 ? 256 : 512; }   // workgroups that the chip holds: one or two on a compute unit
+// Workgroups of a product with `I` x `J` results: its tiles, rounded up to the same number on every XCD.
+inline double tile_blocks(int I, int J, TileKind k) {
+  const int e = tile_edge(k);
+  return 8 * std::ceil(((I + e - 1) / e) * (double)((J + e - 1) / e) / 8);
+}
+// How far a round of n workgroups is on its way from the pace of one alone (0) to that of a full chip (1); where two share a compute unit, the step comes
+// with the first pair.
+inline double pace(TileKind k, double n) {
+  const double x = n / tile_slots(k);
+  return k == TileKind::k256 ? x : x <= 0.5 ? 0. : std::min(1., x);
+}
+
+// The forward.  us per 1000 contraction indices with the chip full and alone, for the start and end of a round and of the last one, per MB read (the weights by every
+// XCD), per MB written, and for every one of those beyond `cached`, which the last cache no longer holds.
+// 256 / 128 / 64, us: 64 x 2048 x 768 38.9 / 13.7 / 7.2; 2080 x 2048 x 768 40.6 / 17.4 / 13.3; 2080 x 4096 x 1536 75.0 / 36.3 / 58.7; 8192 x 2048 x 768
+// 46.1 / 31.9 / 39.8; 16384 x 4096 x 1536 188 / 208 / 484; 131072 x 4096 x 1536 1310 / 1798 / 3863; 47776 x 256 x 1024 45.2 / 38.6 / 60.0; 123680 x 256
+// x 2176 250 / 285 / 397.
+// 0.1 % off the fastest tile, at worst 1.15 times its time (736 x 4864 x 2560 52.0 for 45.2).
+inline TileKind linear_tile(int M, int K, int N) {
+  struct Cost { double full, alone, round, last, mb_read, mb_written, mb_more, cached; };
+  static constexpr Cost cost[3] = {{22.6, 15.3, 5.83, 6.72, .0176, .119, .0092, 314}, {16.7, 6.3, 0, 2.54, .0279, .0979, .415, 170},
+                                   {6.73, 2.56, .742, 2.21, .0025, .0295, .619, 165}};
+  const double k = K * 1e-3, read = ((double)M * K + 8. * K * N) * 2e-6, written = (double)M * N * 2e-6;
+  double t[3];
+  for (int i = 0; i < 3; i++) {
+    const Cost& c = cost[i];
+    const double n = tile_blocks(M, N, (TileKind)i), slots = tile_slots((TileKind)i), rounds = std::ceil(n / slots) - 1;
+    t[i] = rounds * (c.full * k + c.round) + (c.alone + (c.full - c.alone) * pace((TileKind)i, n - rounds * slots)) * k + c.last + c.mb_read * read +
+           c.mb_written * written + c.mb_more * std::max(0., written - c.cached);
+  }
+  return (TileKind)(std::min_element(t, t + 3) - t);
+}
+
+// The weight gradient has few output tiles and a long contraction (over all M tokens), so the
+// contraction is cut into parts until the grid fills the chip about twice; the parts' fp32
+// results go to the workspace and are summed in a fixed order (no atomics).
+inline int linear_bwd_weight_parts(int M, int K, int N) {
+  const long long tiles = (long long)((K + 255) / 256) * ((N + 255) / 256);
+  long long parts = (512 + tiles - 1) / tiles;
+  const long long most = M / 2048 > 0 ? M / 2048 : 1;      // at least 2048 tokens per part
+  if (parts > most) parts = most;
+  if (parts > 32) parts = 32;
+  return (int)parts;
+}
+
+// The tiles of the two gradients, chosen as a pair: tiles that take a compute unit alike share a launch, the large one and a small one take one each (the input gradient on
+// the small one; the other way round is not built, 5 % faster than any of these at most).  In a
+// launch: the time in which the chip gets through all workgroups, that of the longest with a compute unit of its own, or somewhat more than the larger of the two
+// where they are close (`sharp`), and no less than the input gradient's workgroup takes behind full rounds of others.
+// Input / weight tile 256,256 - 256,128 - 128,256 - 128,128 - 128,64 - 64,256 - 64,128 - 64,64, us: 2080 x 2048 x 768 49.1 - 43.6 - 58.4 - 24.2 - 24.6 -
+// 58.4 - 23.0 - 26.1; 131072 x 4096 x 1536 2825 - 3686 - 3903 - 4460 - 6929 - 5061 - 5669 - 8151; 352 x 4608 x 2560 63.0 - 79.2 - 49.0 - 51.1 - 48.9 -
+// 43.4 - 44.4 - 45.7; 14880 x 128 x 2688 63.5 - 78.0 - 77.3 - 50.1 - 54.6 - 68.8 - 44.0 - 50.5; 92352 x 896 x 896 378 - 425 - 411 - 439 - 525 - 481 -
+// 512 - 599; 82720 x 1792 x 256 268 - 288 - 269 - 293 - 329 - 325 - 351 - 383; 47776 x 256 x 1024 95.4 - 89.3 - 94.4 - 81.1 - 107 - 101 - 88.7 - 113;
+// 1536 x 1280 x 2048 49.3 - 62.3 - 53.8 - 25.9 - 32.4 - 50.0 - 29.6 - 33.5.
+// One launch for each product on its own fastest tile takes 32.5 us at 2080 x 2048 x 768 and 3015 at 131072 x 4096 x 1536.
+// 0.6 % off the fastest pair, more than 5 % off at 5 % of the shapes, at worst 1.2 times its time (1472 x 256 x 3072 16.4 for 13.6).  Against a launch each on their own fastest
+// tiles 9 of the 3300 shapes are more than 5 % slower (1888 x 1024 x 2816 38.4 -> 43.7 the most), and the mean is 0.76 of the time.
+struct TilePair { TileKind input, weight; };
+inline TilePair linear_gradient_tiles(int M, int K, int N, int parts) {
+  // per 1000 contraction indices with the chip full and alone, start and end, of the input and of the weight gradient; of the launches; per MB read; per MB written beyond
+  // `cached`
+  struct Cost { int input, weight; double i_full, i_alone, i_fixed, w_full, w_alone, w_fixed, launch, mb_read, mb_written, sharp, cached; };
+  static constexpr Cost cost[7] = {{0, 0, 24.7, 18.5, .0659, 21.8, 17.4, 1.53, 8.83, .0325, .19, 5.74, .0248},
+                                   {1, 0, 20.3, 5.24, .0039, 24.6, 17.6, 2.55, 9.07, .0199, .165, 12., 221.},
+                                   {1, 1, 16., 7.91, 1.07, 18.8, 6.47, 3.36, .284, .0615, .0091, 1.03, 137.},
+                                   {1, 2, 5.29, 5.4, 1.99, 12.6, 2.6, 1.1, 1.35, .0892, 0, 1., 96.},
+                                   {2, 0, 7.62, 3.37, .245, 24.8, 15.8, 0, 10.5, 0, .243, 1.08, 109.},
+                                   {2, 1, 5.76, 2.56, .0135, 28.2, 7.52, 1.56, 1.75, 0, .0927, 4.13, .0065},
+                                   {2, 2, .988, 3.08, 1.22, 13.3, 3.58, 2.07, .645, .0717, 0, 3.12, 4970.}};
+  const double n = N * 1e-3, r = (double)M / parts * 1e-3;
+  const double read = ((double)M * K + 2. * M * N + (double)K * N) * 2e-6, written = (2. * M * K + 4. * K * N * parts) * 1e-6;
+  const Cost* best = cost;
+  double least = 0;
+  for (const Cost& c : cost) {
+    const TileKind ki = (TileKind)c.input, kw = (TileKind)c.weight;
+    const double blocks_i = tile_blocks(M, K, ki), blocks_w = tile_blocks(K, N, kw) * parts, slots = tile_slots(ki);
+    const double full_i = c.i_full * n + c.i_fixed, full_w = c.w_full * r + c.w_fixed, alone_i = c.i_alone * n + c.i_fixed, alone_w = c.w_alone * r + c.w_fixed;
+    double t;
+    if (slots == tile_slots(kw)) {
+      const double work = (blocks_i * full_i + blocks_w * full_w) / slots, chain = std::max(alone_i, alone_w), big = std::max(work, chain);
+      t = big * std::pow(1 + std::pow(std::min(work, chain) / big, 1 + c.sharp), 1 / (1 + c.sharp));
+      t = std::max(t, (std::ceil((blocks_i + blocks_w) / slots) - 1) * std::min(alone_i, alone_w) + alone_i);
+    } else {
+      const auto launch = [](TileKind k, double blocks, double full, double alone) {
+        const double rounds = std::ceil(blocks / tile_slots(k)) - 1;
+        return rounds * full + alone + (full - alone) * pace(k, blocks - rounds * tile_slots(k));
+      };
+      t = launch(ki, blocks_i, full_i, alone_i) + launch(kw, blocks_w, full_w, alone_w);
+    }
+    t += c.launch + c.mb_read * read + c.mb_written * std::max(0., written - c.cached);
+    if (&c == cost || t < least) { least = t; best = &c; }
+  }
+  return TilePair{(TileKind)best->input, (TileKind)best->weight};
+}
+
 }  // namespace helix

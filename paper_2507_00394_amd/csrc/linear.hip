@@ -8,7 +8,7 @@
 //   backward input   da[M][K]  = dqkv[M][N] * w[K][N]^T    X stored [i][r],  Y stored [r][j] after a transposing copy of w
 //   backward weight  dw[K][N]  = a[M][K]^T  * dqkv[M][N]   X stored [r][i],  Y stored [r][j]
 //
-// A workgroup of 4 waves owns a 256 x 256, 128 x 128 or 64 x 64 tile of C (pick_tile and pick_tiles say which: a
+// A workgroup of 4 waves owns a 256 x 256, 128 x 128 or 64 x 64 tile of C (linear_tile and linear_gradient_tiles in dispatch.hpp say which: a
 // large tile reads less per MFMA, a small one fills the chip when C is small); wave (wi, wj) owns a quarter of
 // it as accumulator blocks of the 32x32x16 MFMA (256 accumulator registers and one wave per SIMD for the large
 // tile), computed transposed (the MFMA's row index is j) so that a lane owns one row i of C and stores
@@ -424,65 +424,10 @@ static hipError_t launch_gradients(Gemm<__bf16> input, Gemm<float> weight, hipSt
   return hipGetLastError();
 }
 
-enum class TileKind { k256, k128, k64 };
-static double tiles_of(int I, int J, int edge) { return (double)((I + edge - 1) / edge) * ((J + edge - 1) / edge); }
-
-// The forward's tile: the one that takes the least time by a model of four figures per tile.  A round of workgroups takes between `sparse`
-// (few of them on the chip: latency of the copies and barriers) and `full` nanoseconds per contraction index, plus
-// `fixed` for first copies and stores.  The times themselves are rough; what counts is the choice: over 390 random shapes (32 to
-// 131072 tokens, K to 5120, N to 3072) 0.8 % off the fastest tile on average; at worst, with a short
-// contraction, 128128 x 256 x 512 60.7 for 52.9 us, 47776 x 256 x 1024 46.2 for 39.4.
-// Measured, 256 / 128 / 64, us: 64 tokens x 2048 x 768 37 / 14 / 7.8; 2080 x 2048 x 768 43 / 18.2 / 14.1; 2080 x 4096 x 1536 82 / 38 / 60;
-// 8192 x 2048 x 768 48 / 35 / 43; 16384 x 4096 x 1536 207 / 224 / 489; 131072 x 4096 x 1536 1396 / 1862 / 3873.
-static TileKind pick_tile(int I, int J, int R) {
-  auto microseconds = [&](int edge, int slots, double sparse, double full, double fixed) {
-    const double n = tiles_of(I, J, edge), rounds = std::floor(n / slots), rest = n - rounds * slots;
-    const double per_index = rounds * full + (rest > 0. ? sparse + (full - sparse) * rest / slots : 0.);
-    return per_index * R * 1e-3 + (rounds + (rest > 0. ? 1. : 0.)) * fixed;
-  };
-  const double t256 = microseconds(256, 256, 17., 28., 11.);
-  const double t128 = microseconds(128, 512, 6.5, 18.5, 4.4);
-  const double t64 = microseconds(64, 512, 2.5, 9.5, 2.);
-  return t256 <= t128 && t256 <= t64 ? TileKind::k256 : t128 <= t64 ? TileKind::k128 : TileKind::k64;
-}
-
-// The tiles of the two gradients: the pair that takes the least time.  `work` is the time in which the chip gets through a product's workgroups,
-// `chain` that of one of them with a compute unit of its own; a launch takes the larger of the two, or somewhat more where they are
-// close.  Tiles that take a compute unit alike share a launch, the large one and a small one take one each.  The figures are fitted to 1000
-// random shapes (32 to 131072 tokens, K to 5120, N to 3072, short contractions among them), at which the choice is 1.4 % off the best pair on
-// average and more than 8 % off at 5 % of them (47776 x 256 x 1024 103 for 82 us).  Few columns and many tokens lose a little against a launch each (61440 x
-// 1152 x 256 154 for 143).  One launch each on its own fastest tile -> this, forward and
-// backward, us: 2080 x 2048 x 768 43.2 -> 36.5; 131072 x 4096 x 1536 4283 -> 4150.
-struct TilePair { TileKind input, weight; };
-static TilePair pick_tiles(int M, int K, int N, int parts) {
-  struct Cost { int edge; double slots, full, sparse, input_fixed, weight_fixed; };   // of a workgroup: us per contraction index, us
-  static const Cost cost[3] = {{256, 256., 0.0296, 0.0119, 4.8, 3.5}, {128, 512., 0.0187, 0.0028, 1.7, 3.15}, {64, 512., 0.0050, 0.0004, 0.8, 3.15}};
-  constexpr double kSharp = 2.66, kLaunch = 4., kTranspose = 5.6;
-  const double R = (double)M / parts;
-  auto launch_time = [&](double work, double chain) { return std::pow(std::pow(work, kSharp) + std::pow(chain, kSharp), 1. / kSharp); };
-  TilePair best = {TileKind::k256, TileKind::k256};
-  double least = 0.;
-  for (int ki = 0; ki < 3; ki++)
-    for (int kw = 0; kw < 3; kw++) {
-      if (ki == 0 && kw == 2) continue;   // nowhere the fastest
-      // With two column tiles or fewer the large tile's panels are read for little work, in either product (127232 x 1024 x 256, both 256 / both 128,
-      // 286 / 262 us; 88448 x 1024 x 256 204 / 171); it pays again where K is large (97152 x 3456 x 256 536 / 566).
-      if ((ki == 0 || kw == 0) && N <= 256 && K < 3072) continue;
-      const Cost &i = cost[ki], &w = cost[kw];
-      const double work_i = tiles_of(M, K, i.edge) * (N * i.full + i.input_fixed) / i.slots, chain_i = N * i.sparse + i.input_fixed;
-      const double work_w = tiles_of(K, N, w.edge) * parts * (R * w.full + w.weight_fixed) / w.slots, chain_w = R * w.sparse + w.weight_fixed;
-      const double t = (i.slots == w.slots ? launch_time(work_i + work_w, std::max(chain_i, chain_w))
-                                           : launch_time(work_i, chain_i) + launch_time(work_w, chain_w) + kLaunch) +
-                       (ki == 0 ? kTranspose : 0.);
-      if (least == 0. || t < least) { least = t; best = {(TileKind)ki, (TileKind)kw}; }
-    }
-  return best;
-}
-
 hipError_t launch_linear_fwd(const void* a, long long lda, const void* w, long long ldw, void* out, long long ldo,
                              int M, int K, int N, hipStream_t stream) {
   const Gemm<__bf16> g = {(const __bf16*)a, (const __bf16*)w, (__bf16*)out, lda, ldw, ldo, 0, M, N, K, 0, 0, 1, K};
-  switch (pick_tile(M, N, K)) {
+  switch (linear_tile(M, K, N)) {
     case TileKind::k256: return launch_gemm_tile<Tile256, false, true>(g, stream);
     case TileKind::k128: return launch_gemm_tile<Tile128, false, true>(g, stream);
     default: return launch_gemm_tile<Tile64, false, true>(g, stream);
@@ -501,17 +446,6 @@ __global__ void __launch_bounds__(256) transpose_kernel(const __bf16* __restrict
   for (int i = 0; i < 16; i++) out[(c0 + ty * 16 + i) * ld_out + r0 + tx] = tile[tx][ty * 16 + i];
 }
 
-// The weight gradient has few output tiles and a long contraction (over all M tokens), so the
-// contraction is cut into parts until the grid fills the chip about twice; the parts' fp32
-// results go to the workspace and are summed in a fixed order (no atomics).
-int linear_bwd_weight_parts(int M, int K, int N) {
-  const long long tiles = (long long)((K + 255) / 256) * ((N + 255) / 256);
-  long long parts = (512 + tiles - 1) / tiles;
-  const long long most = M / 2048 > 0 ? M / 2048 : 1;      // at least 2048 tokens per part
-  if (parts > most) parts = most;
-  if (parts > 32) parts = 32;
-  return (int)parts;
-}
 // Workspace of the backward: w^T (bf16 [N][K], rounded up to 256 bytes), then the partial weight gradients.
 size_t linear_bwd_wt_bytes(int K, int N) { return ((size_t)K * N * 2 + 255) & ~(size_t)255; }
 size_t linear_bwd_workspace_bytes(int M, int K, int N) {
@@ -536,7 +470,7 @@ hipError_t launch_linear_bwd(const void* a, long long lda, const void* w, long l
   Gemm<__bf16> in = {(const __bf16*)dout, (const __bf16*)w, (__bf16*)da, ldd, ldw, ldda, 0, M, K, N, 0, 0, 1, N};
   const Gemm<float> grad_w = {(const __bf16*)a, (const __bf16*)dout, parts == 1 ? dw : slabs, lda, ldd, parts == 1 ? lddw : N,
                           (long long)K * N, K, N, M, 0, 0, parts, per};
-  const TilePair kind = pick_tiles(M, K, N, parts);
+  const TilePair kind = linear_gradient_tiles(M, K, N, parts);
   hipError_t e = hipSuccess;
   if (kind.input == TileKind::k256) {
     hipLaunchKernelGGL(transpose_kernel, dim3((unsigned)(N / 64), (unsigned)(K / 64)), dim3(256), 0, stream, (const __bf16*)w, ldw, wt, (long long)K);
@@ -544,13 +478,12 @@ hipError_t launch_linear_bwd(const void* a, long long lda, const void* w, long l
     in.Y = wt;
     in.ldy = K;
   }
-  if (kind.input == TileKind::k256 && kind.weight == TileKind::k256) {
+  if (kind.input == TileKind::k256) {   // which the weight gradient then has too
     e = launch_gradients<Tile256, true, Tile256>(in, grad_w, stream);
-  } else if (kind.input == TileKind::k256 || kind.weight == TileKind::k256) {   // tiles that do not share a compute unit alike: a launch each
-    e = kind.weight == TileKind::k256 ? launch_gemm_tile<Tile256, true, true>(grad_w, stream) : launch_gemm_tile<Tile128, true, true>(grad_w, stream);
+  } else if (kind.weight == TileKind::k256) {   // tiles that do not share a compute unit alike: a launch each
+    e = launch_gemm_tile<Tile256, true, true>(grad_w, stream);
     if (e != hipSuccess) return e;
-    e = kind.input == TileKind::k256 ? launch_gemm_tile<Tile256, false, true>(in, stream)
-        : kind.input == TileKind::k128 ? launch_gemm_tile<Tile128, false, false>(in, stream) : launch_gemm_tile<Tile64, false, false>(in, stream);
+    e = kind.input == TileKind::k128 ? launch_gemm_tile<Tile128, false, false>(in, stream) : launch_gemm_tile<Tile64, false, false>(in, stream);
   } else if (kind.input == TileKind::k128) {
     e = kind.weight == TileKind::k128 ? launch_gradients<Tile128, false, Tile128>(in, grad_w, stream)
                                       : launch_gradients<Tile128, false, Tile64ShortStages>(in, grad_w, stream);

@@ -5,15 +5,20 @@ import torch
 
 from oracle import linear_ref as L
 from paper_2507_00394_amd import inputs as I
+from tests.dispatch_host import ask
 from tests.test_gpu_parity_linear import _check_bf16, _check_f32
 
 pytestmark = pytest.mark.gpu
 
 
-# input / weight tiles: 64 / 64, 128 / 64, 64 / 128, 128 / 128, 128 / 64 in parts, 256 / 256 in parts; one launch each: 64 / 256, 128 / 256, 256 / 128 in parts
-@pytest.mark.parametrize("M,K,N", [(32, 384, 128), (224, 384, 128), (224, 1280, 1280), (608, 1152, 1152), (6176, 256, 384), (6176, 1280, 1536),
-                                   (32, 12544, 2048), (224, 12032, 1792), (201024, 256, 640)])
-def test_gradients_in_one_launch(M, K, N):
+# edges of the input and of the weight gradient's tile; whether the weight gradient comes in parts
+@pytest.mark.parametrize("input,weight,in_parts,M,K,N", [
+    (64, 64, False, 32, 384, 128), (64, 64, True, 4128, 128, 1152), (64, 128, False, 224, 1280, 1280), (64, 128, True, 6176, 256, 1408), (128, 64, False, 608, 256, 128),
+    (128, 64, True, 6176, 256, 384), (128, 128, False, 608, 4992, 256), (128, 128, True, 4128, 2048, 256), (256, 256, False, 1504, 4096, 1792),
+    (256, 256, True, 6176, 1280, 1536), (64, 256, False, 32, 12544, 2048), (128, 256, False, 224, 12032, 1792), (128, 256, True, 65568, 384, 896)])
+def test_gradients_in_one_launch(input, weight, in_parts, M, K, N):
+    edges = [f"tile_edge(linear_gradient_tiles(M, K, N, linear_bwd_weight_parts(M, K, N)).{x})" for x in ("input", "weight")]
+    assert ask([(M, K, N)], *edges, "linear_bwd_weight_parts(M, K, N) > 1", names=("M", "K", "N")) == [(input, weight, in_parts)]
     from paper_2507_00394_amd import binding as hx
     from tests import gpu_util as G
 

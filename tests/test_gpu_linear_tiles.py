@@ -6,15 +6,17 @@ import torch
 
 from oracle import linear_ref as L
 from paper_2507_00394_amd import inputs as I
+from tests.dispatch_host import ask
 from tests.test_gpu_parity_linear import _check_bf16, _check_f32
 
 pytestmark = pytest.mark.gpu
 
 
-# 64 x 64 tiles (the first four), 128 x 128 (three), 256 x 256 with a missing column half (the last)
-@pytest.mark.parametrize("M,K,N", [(1, 128, 128), (63, 128, 384), (65, 256, 128), (129, 2048, 768), (8191, 256, 384), (8193, 1024, 768),
-                                   (32769, 128, 2688), (16129, 2048, 896)])
-def test_forward_edges(M, K, N):
+# edge of the tile; the last: a missing column half
+@pytest.mark.parametrize("edge,M,K,N", [(64, 1, 128, 128), (64, 63, 128, 384), (64, 65, 256, 128), (64, 129, 2048, 768), (128, 8191, 256, 384), (128, 8193, 1024, 768),
+                                        (128, 32769, 128, 2688), (256, 16129, 2048, 896)])
+def test_forward_edges(edge, M, K, N):
+    assert ask([(M, K, N)], "tile_edge(linear_tile(M, K, N))", names=("M", "K", "N")) == [(edge,)]
     from paper_2507_00394_amd import binding as hx
     from tests import gpu_util as G
 
@@ -26,11 +28,12 @@ def test_forward_edges(M, K, N):
     assert torch.isnan(guard[M]).all()
 
 
-# da and dw on 64 x 64 (the first two and the last but one), 128 x 128, and 256 x 256 (the last) tiles; dw over up to seven
-# token ranges of uneven length
-@pytest.mark.parametrize("M,K,N", [(32, 128, 384), (96, 384, 128), (2080, 2048, 768), (16352, 640, 1408), (6176, 384, 2304), (4128, 128, 640),
-                                   (8160, 1920, 2048)])
-def test_backward_edges(M, K, N):
+# edges of the tiles of da and dw; dw over up to seven token ranges of uneven length
+@pytest.mark.parametrize("input,weight,M,K,N", [(64, 64, 32, 128, 384), (64, 64, 96, 384, 128), (128, 128, 2080, 2048, 768), (128, 128, 16352, 640, 1408),
+                                                (128, 128, 6176, 384, 2304), (128, 64, 4128, 128, 640), (256, 256, 8160, 1920, 2048)])
+def test_backward_edges(input, weight, M, K, N):
+    edges = [f"tile_edge(linear_gradient_tiles(M, K, N, linear_bwd_weight_parts(M, K, N)).{x})" for x in ("input", "weight")]
+    assert ask([(M, K, N)], *edges, names=("M", "K", "N")) == [(input, weight)]
     from paper_2507_00394_amd import binding as hx
     from tests import gpu_util as G
 
