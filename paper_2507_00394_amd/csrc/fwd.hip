@@ -114,6 +114,46 @@ __device__ __forceinline__ void pv_block(const uint32_t (&vaddr)[D / 32][2], int
       oacc[db] = mfma32(lds_tr_pair(vaddr[db][0] + row_off, vaddr[db][1] + row_off, 16 * t * D * 2), p[t], oacc[db]);
 }
 
+// The vector work of a step on 32 keys, shared out over its 2 KS slots of one MFMA each.  P of the current block: elements
+// 0..9 in the score slots, 10..15 in the first half of the P V slots (the second half of the P V MFMAs consume them).
+constexpr int kExpInScoreSlots = 10;
+template <int KS>
+struct StepWeights {
+  float ev[16];     // exp2 values, each alive until its pair is packed
+  uint32_t pw[8];   // bf16 pairs of P
+  __device__ __forceinline__ void element(int x, const f32x16& s, float c, SoftmaxState& st) {
+    ev[x] = __builtin_amdgcn_exp2f(fmaf(s[x], c, -st.mref_c));
+    st.lsum[x & 1] += ev[x];
+    if (x & 1) pw[x / 2] = pack_bf16_pair(ev[x - 1], ev[x]);
+  }
+  __device__ __forceinline__ void in_score_slot(int i, const f32x16& s, float c, SoftmaxState& st) {
+#pragma unroll
+    for (int x = 0; x < kExpInScoreSlots; x++)
+      if (x * KS / kExpInScoreSlots == i) element(x, s, c, st);
+  }
+  __device__ __forceinline__ void in_output_slot(int i, const f32x16& s, float c, SoftmaxState& st) {
+#pragma unroll
+    for (int x = kExpInScoreSlots; x < 16; x++)
+      if ((x - kExpInScoreSlots) * (KS / 2) / (16 - kExpInScoreSlots) == i) element(x, s, c, st);
+  }
+  __device__ __forceinline__ bf16x8 packed(int half) const {
+    const u32x4 pk = {pw[4 * half], pw[4 * half + 1], pw[4 * half + 2], pw[4 * half + 3]};
+    return __builtin_bit_cast(bf16x8, pk);
+  }
+};
+
+// This lane's maximum of the next block's 16 scores, in the last P V slots (the score MFMAs have drained by then).
+template <int KS>
+struct StepMaximum {
+  float m0 = 0.f, m1 = 0.f, m2 = 0.f, m3 = 0.f, m4 = 0.f;
+  __device__ __forceinline__ void in_output_slot(int i, const f32x16& s) {
+    if (i == KS - 4) { m0 = fmaxf(fmaxf(s[0], s[1]), s[2]); m1 = fmaxf(fmaxf(s[3], s[4]), s[5]); pin(m0); pin(m1); }
+    if (i == KS - 3) { m2 = fmaxf(fmaxf(s[6], s[7]), s[8]); m3 = fmaxf(fmaxf(s[9], s[10]), s[11]); pin(m2); pin(m3); }
+    if (i == KS - 2) { m4 = fmaxf(fmaxf(s[12], s[13]), s[14]); m0 = fmaxf(fmaxf(m0, m1), s[15]); pin(m4); pin(m0); }
+    if (i == KS - 1) { m2 = fmaxf(fmaxf(m2, m3), m4); m0 = fmaxf(m0, m2); pin(m0); }
+  }
+};
+
 // One pipelined half step (see the header comment).  On entry s_cur is complete, kop holds
 // the first KS/2 K operands of the block to be scored now and vop the first KS/2 V operands
 // of this step; on exit s_next is complete, this lane's maximum over its 16 entries of
@@ -123,13 +163,10 @@ __device__ __forceinline__ void pv_block(const uint32_t (&vaddr)[D / 32][2], int
 //   P V slots 0..KS/2-1     read V operand i + KS/2 of this step    (vaddr + V_IMM + 16 rows)
 //   P V slots KS/2..KS-1    read K operand i - KS/2 of the next block (klo + K_NEXT) and
 //                           V operand i - KS/2 of the next step
-// The vector-ALU work is spread evenly: the 16 elements of P(h) (fma, exp2, row sum, bf16
-// pack) go to the score slots (elements 0..9) and to the first half of the P V slots
-// (elements 10..15, which the second half of the P V MFMAs consume); the row maximum of
-// S(h+1) fills the last P V slots.
+// The vector-ALU work is spread evenly: P(h) (fma, exp2, row sum, bf16 pack) by StepWeights, the
+// row maximum of S(h+1) by StepMaximum.
 // When LAST_OF_TILE the next step works on the next V tile: vaddr moves on by v_step once this
 // tile's reads are issued.
-constexpr int kExpInScoreSlots = 10;
 template <int D, int K_CUR, int K_NEXT, int V_IMM, bool LAST_OF_TILE, typename Copy>
 __device__ __forceinline__ float half_step(const Copy& copy_tile, const f32x16& s_cur, f32x16& s_next,
                                            bf16x8 (&kop)[D / 32], bf16x8 (&vop)[D / 32], const bf16x8 (&qf)[D / 16],
@@ -140,46 +177,31 @@ __device__ __forceinline__ float half_step(const Copy& copy_tile, const f32x16& 
   constexpr int RING = KS / 2;                              // operands in flight (== DB)
   constexpr int HALF = 32 * D * 2;
   const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  float ev[16];     // exp2 values, each alive until its pair is packed
-  uint32_t pw[8];   // bf16 pairs of P
-  auto element = [&](int x) {
-    ev[x] = __builtin_amdgcn_exp2f(fmaf(s_cur[x], c, -st.mref_c));
-    st.lsum[x & 1] += ev[x];
-    if (x & 1) pw[x / 2] = pack_bf16_pair(ev[x - 1], ev[x]);
-  };
+  StepWeights<KS> w;
 #pragma unroll
   for (int i = 0; i < KS; i++) {
     s_next = mfma32(kop[i % RING], qf[i], i == 0 ? zero : s_next);
     if (i < RING) kop[i] = lds_b128(khi[i], K_CUR);
     if (i == 1) copy_tile();   // tile copies are issued under the first MFMAs, not in front of them
-#pragma unroll
-    for (int x = 0; x < kExpInScoreSlots; x++)
-      if (x * KS / kExpInScoreSlots == i) element(x);
+    w.in_score_slot(i, s_cur, c, st);
     __builtin_amdgcn_sched_barrier(0);
   }
-  float m0 = 0.f, m1 = 0.f, m2 = 0.f, m3 = 0.f, m4 = 0.f;
+  StepMaximum<KS> m;
 #pragma unroll
   for (int i = 0; i < KS; i++) {
-    const u32x4 pk = {pw[4 * (i / DB)], pw[4 * (i / DB) + 1], pw[4 * (i / DB) + 2], pw[4 * (i / DB) + 3]};
-    oacc[i % DB] = mfma32(vop[i % RING], __builtin_bit_cast(bf16x8, pk), oacc[i % DB]);
+    oacc[i % DB] = mfma32(vop[i % RING], w.packed(i / DB), oacc[i % DB]);
     if (i < RING) {
       vop[i] = lds_tr_pair(vaddr[i][0], vaddr[i][1], V_IMM + 16 * D * 2);
-#pragma unroll
-      for (int x = kExpInScoreSlots; x < 16; x++)
-        if ((x - kExpInScoreSlots) * RING / (16 - kExpInScoreSlots) == i) element(x);
+      w.in_output_slot(i, s_cur, c, st);
     } else {
       if (LAST_OF_TILE) { vaddr[i - RING][0] += v_step; vaddr[i - RING][1] += v_step; }
       vop[i - RING] = lds_tr_pair(vaddr[i - RING][0], vaddr[i - RING][1], LAST_OF_TILE ? 0 : V_IMM + HALF);
       kop[i - RING] = lds_b128(klo[i - RING], K_NEXT);
     }
-    // row maximum of s_next in the last slots (the score MFMAs have drained by then)
-    if (i == KS - 4) { m0 = fmaxf(fmaxf(s_next[0], s_next[1]), s_next[2]); m1 = fmaxf(fmaxf(s_next[3], s_next[4]), s_next[5]); pin(m0); pin(m1); }
-    if (i == KS - 3) { m2 = fmaxf(fmaxf(s_next[6], s_next[7]), s_next[8]); m3 = fmaxf(fmaxf(s_next[9], s_next[10]), s_next[11]); pin(m2); pin(m3); }
-    if (i == KS - 2) { m4 = fmaxf(fmaxf(s_next[12], s_next[13]), s_next[14]); m0 = fmaxf(fmaxf(m0, m1), s_next[15]); pin(m4); pin(m0); }
-    if (i == KS - 1) { m2 = fmaxf(fmaxf(m2, m3), m4); m0 = fmaxf(m0, m2); pin(m0); }
+    m.in_output_slot(i, s_next);
     __builtin_amdgcn_sched_barrier(0);
   }
-  return m0;
+  return m.m0;
 }
 
 template <int D, bool CAUSAL>
@@ -581,7 +603,8 @@ struct FwdQuad {
   static_assert(STATS + 8 * 64 * 8 <= LDS && D / 32 == KG, "the merge reuses the tile buffers; a wave finishes one block of the head dimension");
 };
 
-// One step: S of the next tile while P of this one is formed and multiplied, in 16 slots like half_step.
+// One step: S of the next tile while P of this one is formed and multiplied, in 16 slots like half_step,
+// with the same vector work in them; the operands come from the tile alone.
 template <int D, typename Copy>
 __device__ __forceinline__ float quad_step(const Copy& copy_tiles, const f32x16& s_cur, f32x16& s_next, const bf16x8 (&qf)[D / 16],
                                            const int (&kaddr)[D / 16], const int (&vaddr)[D / 32][2], uint32_t kbuf, uint32_t vbuf,
@@ -589,13 +612,7 @@ __device__ __forceinline__ float quad_step(const Copy& copy_tiles, const f32x16&
   constexpr int KS = D / 16, DB = D / 32, RING = KS / 2;
   const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   bf16x8 kop[RING], vop[RING];
-  float ev[16];
-  uint32_t pw[8];
-  auto element = [&](int x) {
-    ev[x] = __builtin_amdgcn_exp2f(fmaf(s_cur[x], c, -st.mref_c));
-    st.lsum[x & 1] += ev[x];
-    if (x & 1) pw[x / 2] = pack_bf16_pair(ev[x - 1], ev[x]);
-  };
+  StepWeights<KS> w;
 #pragma unroll
   for (int i = 0; i < RING; i++) kop[i] = lds_b128(kbuf + kaddr[i]);
 #pragma unroll
@@ -604,29 +621,21 @@ __device__ __forceinline__ float quad_step(const Copy& copy_tiles, const f32x16&
     if (i < RING) kop[i] = lds_b128(kbuf + kaddr[i + RING]);
     else vop[i - RING] = lds_tr_pair(vbuf + vaddr[i - RING][0], vbuf + vaddr[i - RING][1], 0);
     if (i == 1) copy_tiles();
-#pragma unroll
-    for (int x = 0; x < kExpInScoreSlots; x++)
-      if (x * KS / kExpInScoreSlots == i) element(x);
+    w.in_score_slot(i, s_cur, c, st);
     __builtin_amdgcn_sched_barrier(0);
   }
-  float m0 = 0.f, m1 = 0.f, m2 = 0.f, m3 = 0.f, m4 = 0.f;
+  StepMaximum<KS> m;
 #pragma unroll
   for (int i = 0; i < KS; i++) {
-    const u32x4 pk = {pw[4 * (i / DB)], pw[4 * (i / DB) + 1], pw[4 * (i / DB) + 2], pw[4 * (i / DB) + 3]};
-    oacc[i % DB] = mfma32(vop[i % RING], __builtin_bit_cast(bf16x8, pk), oacc[i % DB]);
+    oacc[i % DB] = mfma32(vop[i % RING], w.packed(i / DB), oacc[i % DB]);
     if (i < RING) {
       vop[i] = lds_tr_pair(vbuf + vaddr[i][0], vbuf + vaddr[i][1], 16 * D * 2);
-#pragma unroll
-      for (int x = kExpInScoreSlots; x < 16; x++)
-        if ((x - kExpInScoreSlots) * RING / (16 - kExpInScoreSlots) == i) element(x);
+      w.in_output_slot(i, s_cur, c, st);
     }
-    if (i == KS - 4) { m0 = fmaxf(fmaxf(s_next[0], s_next[1]), s_next[2]); m1 = fmaxf(fmaxf(s_next[3], s_next[4]), s_next[5]); pin(m0); pin(m1); }
-    if (i == KS - 3) { m2 = fmaxf(fmaxf(s_next[6], s_next[7]), s_next[8]); m3 = fmaxf(fmaxf(s_next[9], s_next[10]), s_next[11]); pin(m2); pin(m3); }
-    if (i == KS - 2) { m4 = fmaxf(fmaxf(s_next[12], s_next[13]), s_next[14]); m0 = fmaxf(fmaxf(m0, m1), s_next[15]); pin(m4); pin(m0); }
-    if (i == KS - 1) { m2 = fmaxf(fmaxf(m2, m3), m4); m0 = fmaxf(m0, m2); pin(m0); }
+    m.in_output_slot(i, s_next);
     __builtin_amdgcn_sched_barrier(0);
   }
-  return m0;
+  return m.m0;
 }
 
 template <int D, bool CAUSAL>
