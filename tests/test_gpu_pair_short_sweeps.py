@@ -1,6 +1,7 @@
 """Shortest sweeps of the head-dimension-128 dK/dV pass: no, one and few complete 32-row blocks with and without a ragged
 last one, around the first step (no mask) and around the four blocks of the diagonal (causal), up to the first
-trip of seven blocks whose copies need no check."""
+trip of seven blocks whose copies need no check.  Three heads take key tiles of 64 keys; those of 128 have their shortest sweeps in
+test_gpu_parity_dkdv_pair.py."""
 import pytest
 
 from oracle import attention_ref as A
