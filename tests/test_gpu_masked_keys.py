@@ -1,15 +1,21 @@
 """Delta of the first rows: a key block that lies wholly above the causal diagonal of a wave's rows is not touched, whatever V holds
-there, on grids of 128-row and of 256-row tiles."""
+there, on grids of 64-row, 128-row and 256-row tiles."""
 import pytest
 import torch
 
 from paper_2507_00394_amd import inputs as I
+from tests.dispatch_host import ask
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("H,S,D", [(3, 64, 64), (3, 200, 128), (300, 64, 64), (300, 64, 128), (300, 200, 128), (192, 200, 128)])
-def test_delta_of_rows_that_do_not_see_an_infinite_value(H, S, D):
+K256, K128, K64 = 0, 1, 2
+
+
+@pytest.mark.parametrize("kind,H,S,D", [(K64, 3, 64, 64), (K64, 3, 200, 128), (K64, 300, 64, 64), (K64, 300, 64, 128), (K128, 300, 200, 128), (K256, 192, 200, 128),
+                                        (K256, 203, 191, 64)])
+def test_delta_of_rows_that_do_not_see_an_infinite_value(kind, H, S, D):
+    assert ask([(D, H, S, True)], "delta_rows(D, BH, S, causal)") == [(kind,)]
     from paper_2507_00394_amd import binding as hx
     from tests import gpu_util as G
 

@@ -1,28 +1,30 @@
-"""Forward and dQ on both sides of the rule that splits the keys of small grids over two groups of waves: lengths at
-the edges of the 32-key halves, of the 64-key tiles and of the 128- and 256-row workgroup tiles; few heads (split, but for
-head dimension 128 up to 128 tokens) and heads enough for whole tiles (forward and dQ at head dimension 128, dQ at 64: 65
-tokens and, from 192 x 129 on, both masks; the heads between are on either side)."""
+"""Forward and dQ on grids of few and of many heads: lengths at the edges of the 32-key halves, of the 64-key tiles and of the
+64-, 128- and 256-row workgroup tiles.  Three heads take 64-row tiles in both passes (the forward at head dimension 128 with four key groups where they
+are long), the others 128 or 256 rows, but for one forward."""
 import numpy as np
 import pytest
 import torch
 
 from oracle import attention_ref as A
 from paper_2507_00394_amd import inputs as I
+from tests.dispatch_host import ask
 
 pytestmark = pytest.mark.gpu
 
-SPLIT = [(3, S) for S in (1, 31, 32, 33, 64, 65, 96, 97, 128, 129, 255, 257, 321, 449, 640)]
-WHOLE = [(260, 65), (258, 255), (130, 257), (90, 641), (192, 129), (192, 255), (128, 257), (96, 515), (80, 641), (64, 1025)]
+FEW = [(3, S) for S in (1, 31, 32, 33, 64, 65, 96, 97, 128, 129, 255, 257, 321, 449, 640)]
+MANY = [(260, 65), (258, 255), (130, 257), (90, 641), (192, 129), (192, 255), (128, 257), (96, 515), (80, 641), (64, 1025)]
 # (96 x 513 has, with its seed, a dV of 5.52 in row 0: the rounding of results in [4, 8) takes up to 2^-6 of the tolerance of 0.02, and that of P and
 # dS to bf16, 2^-8 of a sum of such terms, the rest; all versions of the kernels return 5.5 there)
 
 
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("causal", [True, False])
-@pytest.mark.parametrize("H,S", SPLIT + WHOLE)
+@pytest.mark.parametrize("H,S", FEW + MANY)
 def test_both_sides(H, S, causal, D):
     from tests import gpu_util as G
 
+    rows, = ask([(D, H, S, causal)], "forward_rows(D, BH, S, causal)", "dq_rows(gradient_tiles(D, BH, S, causal))")
+    assert all((r >= 2) == (H == 3) for r in rows) or (H, S, causal, D) == (90, 641, False, 64)   # 64 rows
     cfg, bits = I.random_case_bits(4100 + S + H, 1, H, S, D)
     out = G.run_fwd_bwd(bits, cfg.scale, causal)
     for n in ("o", "lse", "dq"):

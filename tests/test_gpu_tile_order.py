@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 # (heads, S): 10 heads per XCD of which 4 (1 tile each) to 10 go first; heads shared by 2, 4 and 8 XCDs; at head dimension 128
 # three and five tiles of a head to an XCD, of which all but one, all and some go side by side
 @pytest.mark.parametrize("BH,S,D", [(80, 2600, 64), (80, 8193, 64), (44, 2600, 64), (42, 1500, 64), (13, 3000, 64), (136, 570, 128), (80, 1100, 128),
-                                    (40, 640, 128), (264, 300, 128), (36, 1300, 128)])
+                                    (40, 640, 128), (264, 300, 128), (36, 1300, 128), (36, 1200, 128)])
 def test_every_tile_once(BH, S, D):
     from tests import gpu_util as G
 
